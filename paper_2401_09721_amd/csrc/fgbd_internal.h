@@ -369,7 +369,7 @@ constexpr int kSortPasses = 4;                        // 8-bit digits of 32-bit 
 // codes of at most 32 bits: one pass on the top kMsdBits bits, then local sorts
 constexpr int kMsdBits = 10;
 constexpr int kMsdBins = 1 << kMsdBits;
-constexpr int kLocalWin = kSortTile;  // sorted positions per local-sort window
+constexpr int kLocalWin = kSortTile;  // sorted positions per local-sort window (windows are numbered like the tiles)
 // a range this large sorted by one block makes later eager calls on the
 // context sort by LSD passes for kSortLsdCalls calls
 constexpr int kBigRange = 32768;
@@ -414,7 +414,7 @@ struct Bufs {
   uint32_t *hist;               // [L][ntiles_cap + 1][256]
   uint32_t *rank;               // [L][stride]
   uint8_t *digits;              // [L][stride]: the next radix pass's digit of each sorted item
-  int32_t *win;                 // [L][windows]: the first bucket start in each local-sort window
+  int4 *win;                    // [L][ntiles_cap]: each local-sort window's range and its first and last top digit
   int32_t *col, *dist2;         // [n_cap][K]
   float *p;                     // [n_cap][K] weights the fused path's first sweep stores
   double *spread;               // [n_cap]

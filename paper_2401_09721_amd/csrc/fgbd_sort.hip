@@ -48,8 +48,8 @@ struct SortArgs {
   int32_t passes;     // passes of the sort (4, or more for codes above 32 bits)
   int32_t fold;       // pass 0 only: the first blocks also do the call's setup
   SetupArgs su;
-  int32_t *win;       // top-digit pass: the first bucket start of each local-sort window
-  int32_t nwin;       // windows per direction
+  int4 *win;          // top-digit pass: the range of each local-sort window (see k_msd_downsweep)
+  int32_t nwin;       // windows per direction (the tiles' own numbering)
 };
 
 // The tile's cloud and point range; false for a tile beyond the last one.
@@ -60,9 +60,9 @@ struct TileInfo {
   int next_first;  // first tile of the next cloud (= tile count after the last)
   int seg_start;   // first point of the cloud
 };
-__device__ __forceinline__ bool tile_info(const SortArgs &a, int tile, TileInfo &ti) {
-  if (a.sa.n_fixed >= 0) {
-    const int n = a.sa.n_fixed;
+__device__ __forceinline__ bool tile_info(const SegArgs &sa, int tile, TileInfo &ti) {
+  if (sa.n_fixed >= 0) {
+    const int n = sa.n_fixed;
     if (tile * kSortTile >= n) return false;
     ti.s = 0;
     ti.first = 0;
@@ -72,9 +72,9 @@ __device__ __forceinline__ bool tile_info(const SortArgs &a, int tile, TileInfo 
     ti.end = min(ti.begin + kSortTile, n);
     return true;
   }
-  const Segs *sg = a.sa.segs;
+  const Segs *sg = sa.segs;
   if (tile >= sg->ntiles) return false;
-  const int s = seg_lookup(sg->tile_first, a.sa.B, tile);
+  const int s = seg_lookup(sg->tile_first, sa.B, tile);
   ti.s = s;
   ti.first = sg->tile_first[s];
   ti.next_first = sg->tile_first[s + 1];
@@ -123,6 +123,7 @@ __device__ __forceinline__ int num_tiles(const SortArgs &a) {
 // reload from the argument segment would wait on the LDS atomics too.
 struct CodeGen {
   int ia, ih, im, uh, um, wm, bits;
+  int sa, sh, sm;  // where the axes a, h, m sit in packed coordinates
   uint32_t oh, om;
 };
 __device__ __forceinline__ CodeGen code_gen(const DirTable &dt, int d) {
@@ -138,6 +139,9 @@ __device__ __forceinline__ CodeGen code_gen(const DirTable &dt, int d) {
   c.om = di.um > 0 ? (uint32_t)di.um * top : 0u;
   c.wm = dt.bits + di.wm_extra;
   c.bits = dt.bits;
+  c.sa = di.a * dt.bits;
+  c.sh = di.h * dt.bits;
+  c.sm = di.m * dt.bits;
   return c;
 }
 __device__ __forceinline__ uint32_t gen_code(const CodeGen &c, int gx, int gy, int gz) {
@@ -167,10 +171,7 @@ __device__ __forceinline__ uint32_t decode_packed(const CodeGen &c, uint32_t cod
   const int eh = (int)(code >> (c.bits + c.wm));
   const int gm = em + c.um * ga - (int)c.om;
   const int gh = eh + c.uh * ga - (int)c.oh;
-  const int gx = c.ia == 0 ? ga : (c.ih == 0 ? gh : gm);
-  const int gy = c.ia == 1 ? ga : (c.ih == 1 ? gh : gm);
-  const int gz = c.ia == 2 ? ga : (c.ih == 2 ? gh : gm);
-  return (uint32_t)gx | ((uint32_t)gy << c.bits) | ((uint32_t)gz << (2 * c.bits));
+  return ((uint32_t)ga << c.sa) | ((uint32_t)gh << c.sh) | ((uint32_t)gm << c.sm);
 }
 
 __device__ __forceinline__ uint64_t load_item(const SortArgs &a, const CodeGen &cg, const int32_t *__restrict__ xyz,
@@ -274,7 +275,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_upsweep(SortArgs a, const
   int d, tile;
   xcd_tile(d, tile);
   TileInfo ti;
-  if (!tile_info(a, tile, ti)) return;  // uniform over the block
+  if (!tile_info(a.sa, tile, ti)) return;  // uniform over the block
   const int t = threadIdx.x;
   for (int i = t; i < kSub * kSubStride; i += kSortThreads) s_hs[i] = 0;
   __syncthreads();
@@ -475,7 +476,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_downsweep(SortArgs a, con
   else
     xcd_tile(d, tile);
   TileInfo ti;
-  if (!tile_info(a, tile, ti)) return;  // uniform over the block
+  if (!tile_info(a.sa, tile, ti)) return;  // uniform over the block
   const int t = threadIdx.x;
   const int wave = t / kWave;
   const int lane = (int)lane_id();
@@ -625,21 +626,35 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_downsweep(SortArgs a, con
 // (upsweep, scan and downsweep as above, with 2^kMsdBits digits, the codes
 // made from the coordinates) splits every cloud's points, stably, into
 // buckets of equal top digit; the downsweep also records, from its counts,
-// the first bucket start inside every window of kLocalWin sorted positions.
+// which buckets start in every window of kLocalWin of a cloud's sorted
+// positions.
 // k_local_sort then gives each window of a direction one block, which sorts
-// the buckets that start in its window (the range from its recorded start
-// to the next window's), stably, by their codes less the smallest top
-// digit's base, with 8-bit LSD passes in LDS (three for the usual ranges).
+// the buckets that start in its window (up to the first bucket of the next
+// window), stably, by their codes less the smallest top digit's base.
 // Buckets are ordered by their top digits already, so sorting a range by the
 // whole code sorts each bucket and keeps the buckets in place; ties keep the
-// MSD pass's order, which is the input's.  The final pass writes the sorted
-// items in their final form and rank, as the last LSD pass does.  A range of
-// more than kLocalCap items, of two clouds, or of keys wider than 26 bits is
-// sorted by its block alone through the two item buffers: correct for any
-// input, slow for a very large range (points crowded into few top digits,
-// such as a plane normal to a scan axis), which the block then reports
-// through a host-mapped flag so that the caller's context can choose the LSD
-// passes for its next calls.
+// MSD pass's order, which is the input's.  The block writes the sorted items
+// in their final form and rank, as the last LSD pass does.  A range of more
+// than kLocalCap items, or with more than kMaxBin items in one bin, is sorted
+// by its block through the two item buffers: correct for any input, slow for
+// a very large range (points crowded into few top digits, such as a plane
+// normal to a scan axis), which the block then reports through a host-mapped
+// flag so that the caller's context can choose the LSD passes for its next
+// calls.
+//
+// In LDS a range of R items is sorted by counting: the codes, less the base,
+// are split by their top 13 bits into bins (one LDS atomic per item gives its
+// place in its bin, in no particular order), and each item's rank in its bin
+// is the number of its bin's keys below its own, a key being the code's low
+// bits and then the position in the range.  The bins are short (on the frames
+// measured an item shares its bin with 5 to 12 others on average, at most
+// about 230), lanes with neighbouring slots read the same keys, and nothing
+// has to be matched across lanes: 19 M vector instructions per launch on the
+// 1M frame against 32 M for three 8-bit LSD passes in LDS whose stable ranks
+// came from 8 ballots per item and pass; 90 -> 61 us there, 410 -> 250 us on
+// 8 clouds of 4.4M points, 81 -> 51 us on 421k points in 16 directions.
+// Items stay in registers; 65 KB of LDS and 1024 threads let two blocks (all
+// 32 waves) share a CU.
 
 __device__ __forceinline__ int code_width(const DirTable &dt, int d) {
   const DirInfo di = dt.d[d];
@@ -668,12 +683,8 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_upsweep(SortArgs a, const 
   }
   int d, tile;
   xcd_tile(d, tile);
-  // every (direction, window) entry of the window table starts empty; the
-  // downsweep then writes each window's first bucket start (blocks and
-  // windows pair up one to one: the grid has at least one tile per window)
-  if (threadIdx.x == 0 && tile < a.nwin) a.win[(size_t)d * a.nwin + tile] = 0x7fffffff;
   TileInfo ti;
-  if (!tile_info(a, tile, ti)) return;  // uniform over the block
+  if (!tile_info(a.sa, tile, ti)) return;  // uniform over the block
   const int t = threadIdx.x;
   for (int i = t; i < kSub * kSubStride; i += kSortThreads) s_hs[i] = 0;
   __syncthreads();
@@ -733,11 +744,12 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
   int d, tile;
   xcd_tile(d, tile);
   TileInfo ti;
-  if (!tile_info(a, tile, ti)) return;  // uniform over the block
+  if (!tile_info(a.sa, tile, ti)) return;  // uniform over the block
   const int t = threadIdx.x;
   const int wave = t / kWave;
   const int lane = (int)lane_id();
   const int valid = ti.end - ti.begin;
+  const int seg_end = a.sa.n_fixed >= 0 ? a.sa.n_fixed : a.sa.segs->start[ti.s + 1];
   for (int i = t; i < 4 * kMsdBins; i += kSortThreads) (&s_wh[0][0])[i] = 0;
   // scanned counts of the thread's digits: the cloud's count and this tile's
   // offset inside the cloud
@@ -818,17 +830,6 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
       s_wh[3][kPer * t + q] = e + c[0][q] + c[1][q] + c[2][q];
       s_off[kPer * t + q] = (uint32_t)ti.seg_start + run_below + ex_below[q] + off_q[q] - e;
     }
-    // the cloud's first tile records where its buckets start: each window's
-    // entry keeps the first start inside it
-    if (tile == ti.first) {
-#pragma unroll
-      for (int q = 0; q < kPer; ++q) {
-        if (below_q[q] > 0) {
-          const int st = ti.seg_start + (int)(run_below + ex_below[q]);
-          atomicMin(&a.win[(size_t)d * a.nwin + st / kLocalWin], st);
-        }
-      }
-    }
   }
   __syncthreads();
 #pragma unroll
@@ -851,21 +852,59 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
 #pragma unroll
   for (int j = 0; j < kSortItems; ++j)
     if (t + j * kSortThreads < valid && gp[j] < (uint32_t)a.stride) out[gp[j]] = st[j];
+  // The cloud's first tile records the range of each of the cloud's windows,
+  // the buckets that start in it: the range's first position, the digit of the
+  // items there, the first digit whose bucket starts at or after the window's
+  // base, and (in the cloud's last window) the digit after the cloud's last.  A binary search over the bucket starts (here a bucket starts
+  // at s_off + s_wh[0], the first tile's offset inside every bucket being 0)
+  // finds the first digit whose bucket starts at or after a position; an
+  // empty bucket shares the start of the next one that is not.  One store per
+  // window; an atomic minimum per bucket took 45 us instead of 26 on 64
+  // clouds of 4k points, whose every tile is a first one.
+  if (tile == ti.first) {  // (uniform)
+    __syncthreads();       // the staged tile has been read
+    uint32_t *s_start = s_wh[1];
+    for (int c = t; c < kMsdBins; c += kSortThreads) s_start[c] = s_off[c] + s_wh[0][c];
+    __syncthreads();
+    auto first_at = [&](uint32_t pos) {
+      int l = 0, h = kMsdBins;
+      while (l < h) {
+        const int m = (l + h) >> 1;
+        if (s_start[m] >= pos)
+          h = m;
+        else
+          l = m + 1;
+      }
+      return l;
+    };
+    for (int w = t; w < ti.next_first - tile; w += kSortThreads) {
+      const int l = first_at((uint32_t)(ti.seg_start + w * kLocalWin));
+      const uint32_t lo = l < kMsdBins ? s_start[l] : (uint32_t)seg_end;
+      // when bucket l is empty, the items at lo are of a later digit
+      const int held = l + 1 < kMsdBins && s_start[l + 1] == lo ? first_at(lo + 1u) - 1 : l;
+      const int end_digit = tile + w + 1 == ti.next_first ? first_at((uint32_t)seg_end) : 0;
+      a.win[(size_t)d * a.nwin + tile + w] = make_int4((int)lo, held, l, end_digit);
+    }
+  }
 }
 
-constexpr int kLocalThreads = 512;
+constexpr int kLocalThreads = 1024;
 constexpr int kLocalWaves = kLocalThreads / kWave;
-constexpr int kLocalItems = 16;                         // per thread, in-LDS ranges
+constexpr int kLocalItems = 8;                          // per thread, in-LDS ranges
 constexpr int kLocalCap = kLocalThreads * kLocalItems;  // 8192 items
-constexpr int kLocalKeyBits = 26;                       // wider relative keys take the slow path
-constexpr int kSlowItems = 8;                           // per thread and chunk, slow path
-static_assert(2 * kLocalThreads == kMsdBins, "two top digits per thread when the range is found");
+constexpr int kPosBits = 13;                            // a position in an in-LDS range
+constexpr int kBinBits = 13;
+constexpr int kBins = 1 << kBinBits;
+constexpr uint32_t kMaxBin = 512;                       // a larger bin sends its window to the slow path
+constexpr int kLenBits = 32 - kPosBits + 16 - kPosBits; // a bin's length less 1 has kLenBits - shift bits
+constexpr int kSlowItems = 4;                           // per thread and chunk, slow path
+static_assert(kLocalCap == 1 << kPosBits, "positions of the largest in-LDS range");
 
 struct LocalArgs {
   DirTable dt;
   SegArgs sa;
   int64_t stride;
-  const int32_t *win;  // [L][nwin]: each window's first bucket start (0x7fffffff: none)
+  const int4 *win;     // [L][nwin]: where each window's range starts (see k_msd_downsweep)
   int32_t nwin;
   int32_t *big;        // host-mapped flag set for a range of more than kBigRange items (NULL: none)
 };
@@ -915,39 +954,31 @@ __device__ __forceinline__ uint32_t exclusive_scan_block(uint32_t v, uint32_t *s
   return b + x - v;
 }
 
-// The cloud holding position x: the last cloud whose start is at most x.
-__device__ __forceinline__ int cloud_at(const int32_t *starts, int B, int x) {
-  int l = 0, h = B;  // starts[l] <= x; h == B or starts[h] > x
-  while (h - l > 1) {
-    const int m = (l + h) >> 1;
-    if (starts[m] <= x)
-      l = m;
-    else
-      h = m;
-  }
-  return l;
-}
-
-// One block per (direction, window of kLocalWin sorted positions).
-__global__ __launch_bounds__(kLocalThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_local_sort(
+// One block per (direction, window).  A window is kLocalWin sorted positions
+// of one cloud, numbered like the radix tiles, so no window holds points of
+// two clouds: with windows laid over the whole batch, every window of a batch
+// of small clouds straddled some and took the slow path below (64 clouds of
+// 4k points: 144 us; 29 us with windows of their own).
+__global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
     LocalArgs a, uint64_t *__restrict__ src, uint64_t *__restrict__ dst, uint32_t *__restrict__ rank) {
-  __shared__ uint64_t s_it[kLocalCap];
-  __shared__ uint32_t s_cnt[kLocalWaves][256];
-  __shared__ uint32_t s_base[256];
+  // in-LDS path: the bins' counts, then starts (two 16-bit values a word),
+  // then each position's rank; a slot's key and its bin's start
+  __shared__ uint32_t s_key[kLocalCap + 4];
+  __shared__ uint32_t s_two[kLocalCap + 2];  // [kBins / 2 + 2] bins, then [kLocalCap] 16-bit bin starts
+  uint32_t *const s_bin = s_two;
+  uint16_t *const s_b0 = reinterpret_cast<uint16_t *>(s_two + kBins / 2 + 2);
   __shared__ uint32_t s_w[16];
-  __shared__ int32_t s_starts[kMaxSeg + 1];
-  __shared__ int32_t s_multi;
-  __shared__ unsigned long long s_max;
+  __shared__ uint32_t s_max;
+  // slow path
+  uint32_t(*const s_cnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s_key);  // [kLocalWaves][256]
+  uint32_t *const s_base = s_bin;                                          // [256]
 
-  // each XCD takes one contiguous range of the direction-major sequence
-  int d, win;
-  xcd_tile_last(d, win);
-  const bool segmented = a.sa.n_fixed < 0;
-  const int B = segmented ? a.sa.segs->B : 1;
-  const int n_tot = segmented ? a.sa.segs->n : a.sa.n_fixed;
-  const int w0 = win * kLocalWin;
-  if (w0 >= n_tot) return;  // uniform over the block
-  const int w1 = min(w0 + kLocalWin, n_tot);
+  // Consecutive windows of a direction go to the XCDs in turn.  Windows differ
+  // in cost by direction and by part of the cloud: with one direction per XCD
+  // the slowest one set the time (96 us on the 1M frame against 68 then).
+  const int d = (int)blockIdx.y, win = (int)blockIdx.x;
+  TileInfo ti;
+  if (!tile_info(a.sa, win, ti)) return;  // uniform over the block
   const int t = threadIdx.x;
   const int wave = t / kWave;
   const int lane = (int)lane_id();
@@ -955,139 +986,173 @@ __global__ __launch_bounds__(kLocalThreads) __attribute__((amdgpu_waves_per_eu(4
   const uint64_t *items = src + dbase;
   const int sh = msd_shift(a.dt, d);
 
-  // The range: buckets start at the cloud starts and, inside a cloud, where
-  // the top digit changes.  The top-digit pass recorded each window's first
-  // bucket start (from its counts, never from the items, which a
-  // neighbouring block may be reordering): lo = this window's, hi = the
-  // next one recorded after it (or the end).
-  const int32_t *wrow = a.win + (size_t)d * a.nwin;
-  const int lo = wrow[win];
-  if (lo >= w1) return;  // no bucket starts in the window (uniform)
-  int hi = n_tot;
-  for (int k = win + 1; k < a.nwin; ++k) {  // uniform; nearly always one step
-    const int v = wrow[k];
-    if (v < n_tot) {
-      hi = v;
-      break;
-    }
-  }
-  if (t == 0) {
-    s_multi = 0;
-    s_max = 0ull;
-  }
-  for (int i = t; i <= B; i += kLocalThreads) s_starts[i] = segmented ? a.sa.segs->start[i] : (i == 0 ? 0 : n_tot);
-  for (int i = t; i < kLocalWaves * 256; i += kLocalThreads) (&s_cnt[0][0])[i] = 0u;  // the first pass's counts
-  __syncthreads();
-  for (int i = t; i <= B; i += kLocalThreads)
-    if (s_starts[i] > lo && s_starts[i] < hi) s_multi = 1;
-  __syncthreads();
-  const bool multi = s_multi != 0;
+  // The range as the top-digit pass recorded it from its counts (never taken
+  // from the items, which a neighbouring block may be reordering): it ends
+  // where the cloud's next window's starts.  The digit before the next
+  // window's first one that starts at or after its base is never empty.
+  const int4 *wrow = a.win + (size_t)d * a.nwin;
+  const int4 here = wrow[win], next = wrow[min(win + 1, a.nwin - 1)];
+  const bool last_win = win + 1 == ti.next_first;
+  const int seg_end = a.sa.n_fixed >= 0 ? a.sa.n_fixed : (int)a.sa.segs->start[ti.s + 1];
+  const int lo = here.x, hi = last_win ? seg_end : next.x;
+  if (lo >= hi) return;  // no bucket starts in the window (uniform)
+  const uint32_t df = (uint32_t)here.y, dl = (uint32_t)(last_win ? here.w : next.z) - 1u;
   const int R = hi - lo;
-  const uint32_t cf = (uint32_t)(items[lo] >> 32), cl = (uint32_t)(items[hi - 1] >> 32);
-  const uint32_t df = msd_digit(cf, sh), dl = msd_digit(cl, sh);
   const uint32_t base = df << sh;
   const int bits = sh + (dl > df ? 32 - __clz(dl - df) : 0);
   const CodeGen cg = code_gen(a.dt, d);
   uint64_t *out = dst + dbase;
 
-  if (!multi && R <= kLocalCap && bits <= kLocalKeyBits) {
-    // ---- in LDS.  Slots: wave w holds range positions (w J + j) 64 + lane,
-    // j < J, so the visiting order (wave, round, lane) is the range order.
-    // The items move from pass to pass through s_it carrying the code less
-    // the range's base (rel << 32 | index), so a pass's digit is one byte of
-    // rel; slots past the range hold all ones, take the largest digit in
-    // every pass and stay after every real item.
-    const int passes = bits > 0 ? (bits + 7) / 8 : 1;  // (one pass of digit 0 copies)
+  if (R <= kLocalCap) {
+    // ---- in LDS.  Items stay with their thread (position j kLocalThreads + t
+    // of the range); their codes less the range's base are counted into
+    // 2^kBinBits bins by the top bits, the key of each item (the low bits,
+    // then the position) goes to a slot of its bin, and the rank of a slot's
+    // key among its bin's keys is counted.
     const int J = (R + kLocalThreads - 1) / kLocalThreads;  // <= kLocalItems
-    uint64_t it[kLocalItems];
+    // (bits <= 32, so kPosBits + shift <= 32 and a key fits its word)
+    const int shift = bits > kBinBits ? bits - kBinBits : 0;
+    uint32_t code[kLocalItems], id[kLocalItems], place[kLocalItems];
 #pragma unroll
     for (int j = 0; j < kLocalItems; ++j) {
-      const int s = (wave * J + j) * kWave + lane;
-      const uint64_t v = items[lo + min(s, R - 1)];  // clamped: every load unconditional
-      it[j] = (j < J && s < R) ? v - ((uint64_t)base << 32) : ~0ull;
+      if (j >= J) break;  // uniform
+      const uint64_t v = items[lo + min(j * kLocalThreads + t, R - 1)];
+      code[j] = (uint32_t)(v >> 32) - base;
+      id[j] = (uint32_t)v;
     }
-    for (int pass = 0; pass < passes; ++pass) {
-      const bool last = pass == passes - 1;
-      const uint32_t sft = 8u * (uint32_t)pass;
-      auto digit = [&](uint64_t v) { return __builtin_amdgcn_ubfe((uint32_t)(v >> 32), sft, 8u); };
-      uint32_t rk[kLocalItems], bf[kLocalItems];
+    for (int i = t; i < kBins / 2 + 2; i += kLocalThreads) s_bin[i] = 0u;
+    if (t == 0) s_max = 0u;
+    __syncthreads();
+    // (codes of coordinates outside the grid can exceed the range's bits: the
+    // minimum keeps their bins inside the table)
+    auto bin_of = [&](uint32_t c) { return min(c >> shift, (uint32_t)kBins - 1u); };
 #pragma unroll
-      for (int j = 0; j < kLocalItems; ++j)
-        if (j < J) rk[j] = wave_rank8(digit(it[j]), s_cnt[wave], bf[j]);  // (j < J is uniform)
-#pragma unroll
-      for (int j = 0; j < kLocalItems; ++j)
-        if (j < J) rk[j] += bf[j];
-      __syncthreads();
-      // per digit t: the exclusive prefix over digits, then each wave's start
-      // (column t is read twice rather than held in registers)
-      uint32_t tot = 0;
-      if (t < 256) {
-#pragma unroll
-        for (int w = 0; w < kLocalWaves; ++w) tot += s_cnt[w][t];
+    for (int j = 0; j < kLocalItems; ++j) {
+      if (j >= J) break;
+      if (j * kLocalThreads + t < R) {
+        const uint32_t b = bin_of(code[j]), sh16 = 16u * (b & 1u);
+        place[j] = (atomicAdd(&s_bin[b >> 1], 1u << sh16) >> sh16) & 0xffffu;
       }
-      const uint32_t ex = exclusive_scan_block(tot, s_w);
-      if (t < 256) {
-        uint32_t run = ex;
+    }
+    __syncthreads();
+    {  // exclusive prefix over the bins, and the largest bin
+      constexpr int kPerT = kBins / 2 / kLocalThreads;
+      uint32_t w[kPerT], sum = 0, big = 0;
 #pragma unroll
-        for (int w = 0; w < kLocalWaves; ++w) {
-          const uint32_t c = s_cnt[w][t];
-          s_cnt[w][t] = run;
-          run += c;
+      for (int q = 0; q < kPerT; ++q) {
+        w[q] = s_bin[t * kPerT + q];
+        const uint32_t a0 = w[q] & 0xffffu, a1 = w[q] >> 16;
+        big = max(big, max(a0, a1));
+        sum += a0 + a1;
+      }
+      if (big > min(kMaxBin, 1u << (kLenBits - shift))) s_max = 1u;
+      uint32_t run = exclusive_scan_block(sum, s_w);
+#pragma unroll
+      for (int q = 0; q < kPerT; ++q) {
+        const uint32_t a0 = w[q] & 0xffffu, a1 = w[q] >> 16;
+        s_bin[t * kPerT + q] = run | (run + a0) << 16;
+        run += a0 + a1;
+      }
+      if (t == kLocalThreads - 1) s_bin[kBins / 2] = run;
+    }
+    __syncthreads();
+    if (s_max == 0u) {  // uniform
+      const uint16_t *start = reinterpret_cast<const uint16_t *>(s_bin);
+      const uint32_t low = (1u << shift) - 1u;
+#pragma unroll
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        const int pos = j * kLocalThreads + t;
+        if (pos < R) {
+          const uint32_t b = bin_of(code[j]);
+          const uint32_t b0 = start[b], len = start[b + 1] - b0;
+          const uint32_t s = b0 + place[j];
+          s_key[s] = ((len - 1u) << shift | (code[j] & low)) << kPosBits | (uint32_t)pos;
+          s_b0[s] = (uint16_t)(b0 | (len - 1u) >> (32 - kPosBits - shift) << kPosBits);
+        }
+      }
+      __syncthreads();
+      uint16_t *s_rank = reinterpret_cast<uint16_t *>(s_bin);  // (the starts have been read)
+#pragma unroll
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        const int s = j * kLocalThreads + t;
+        if (s < R) {
+          const uint32_t key = s_key[s], b = s_b0[s];
+          const uint32_t b0 = b & (kLocalCap - 1);
+          // (two shifts: kPosBits + shift can be 32)
+          const uint32_t len = (key >> kPosBits >> shift | b >> kPosBits << (32 - kPosBits - shift)) + 1u;
+          uint32_t r = b0;
+          const uint32_t *bin = s_key + b0;
+          uint32_t k = 0;
+          for (; k + 8 <= len; k += 8) {
+            uint32_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = bin[k + u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) r += v[u] < key ? 1u : 0u;
+          }
+          for (; k < len; k += 4) {
+            uint32_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = bin[k + u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) r += (k + u < len && v[u] < key) ? 1u : 0u;
+          }
+          s_rank[key & (kLocalCap - 1)] = (uint16_t)r;
         }
       }
       __syncthreads();
 #pragma unroll
-      for (int j = 0; j < kLocalItems; ++j)
-        if (j < J) s_it[s_cnt[wave][digit(it[j])] + rk[j]] = it[j];
-      __syncthreads();
-      if (!last) {
-#pragma unroll
-        for (int j = 0; j < kLocalItems; ++j)
-          if (j < J) it[j] = s_it[(wave * J + j) * kWave + lane];
-        for (int i = t; i < kLocalWaves * 256; i += kLocalThreads) (&s_cnt[0][0])[i] = 0u;
-        __syncthreads();
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        const int pos = j * kLocalThreads + t;
+        if (pos < R) place[j] = s_rank[pos];
       }
-    }
-    // write-out in sorted order, straight from LDS
-    for (int i0 = 0; i0 * kLocalThreads < R; i0 += 4) {  // uniform
-      uint64_t v[4];
+      __syncthreads();
+      // rank is written in the order of the range (near the input's inside a
+      // bucket), the items in sorted order through LDS
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = s_it[min(t + (i0 + u) * kLocalThreads, R - 1)];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int s = t + (i0 + u) * kLocalThreads;
-        const uint32_t idx = (uint32_t)v[u];
-        if (s < R && idx < (uint32_t)a.stride) {  // (idx is a point of the range; the bound is a guard)
-          out[lo + s] = ((uint64_t)decode_packed(cg, (uint32_t)(v[u] >> 32) + base) << 32) | idx;
-          rank[dbase + idx] = (uint32_t)(lo + s);
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        const int pos = j * kLocalThreads + t;
+        if (pos < R) {
+          s_key[place[j]] = id[j];
+          s_two[place[j]] = decode_packed(cg, code[j] + base);
+          if (id[j] < (uint32_t)a.stride)  // (the id is a point of the range; the bound is a guard)
+            rank[dbase + id[j]] = (uint32_t)lo + place[j];
         }
       }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        const int s = j * kLocalThreads + t;
+        if (s < R) out[lo + s] = (uint64_t)s_two[s] << 32 | s_key[s];
+      }
+      return;
     }
-    return;
+    __syncthreads();
   }
 
   // ---- slow path: the block sorts its range alone, LSD over 8-bit digits of
-  // the 64-bit key ((cloud - first cloud) << 32 | code) - base, in chunks of
-  // kSlowItems * kLocalThreads items per round, through the two item buffers
-  // (its own range of each).  An odd number of passes (a first pass of digit
-  // 0, a plain stable copy, when needed) ends in dst, in the final form.
+  // the code less the range's base, in chunks of kSlowItems * kLocalThreads
+  // items per round, through the two item buffers (its own range of each).
+  // An odd number of passes (a first pass of digit 0, a plain stable copy,
+  // when needed) ends in dst, in the final form.
   if (a.big && R > kBigRange && t == 0) *a.big = 1;  // (only ever set to 1)
-  const int c_first = cloud_at(s_starts, B, lo);
-  const uint64_t base64 = (uint64_t)base;
+  if (t == 0) s_max = 0u;
+  __syncthreads();
+  auto rel = [&](uint64_t v) { return (uint32_t)(v >> 32) - base; };
   // the widest key of the range, for the pass count
   {
-    unsigned long long mx = 0ull;
-    for (int s = t; s < R; s += kLocalThreads) {
-      const uint64_t it = items[lo + s];
-      const int cr = multi ? cloud_at(s_starts, B, (int)(uint32_t)it) - c_first : 0;
-      const uint64_t k64 = ((((uint64_t)cr) << 32) | (it >> 32)) - base64;
-      mx = k64 > mx ? k64 : mx;
-    }
+    uint32_t mx = 0u;
+    for (int s = t; s < R; s += kLocalThreads) mx = max(mx, rel(items[lo + s]));
     atomicMax(&s_max, mx);
   }
   __syncthreads();
-  const unsigned long long kmax = s_max;
-  int P = kmax ? (64 - __clzll(kmax) + 7) / 8 : 0;
+  const uint32_t kmax = s_max;
+  int P = kmax ? (32 - __clz(kmax) + 7) / 8 : 0;
   const int extra = (P % 2 == 0) ? 1 : 0;
   P += extra;
   for (int q = 0; q < P; ++q) {
@@ -1098,10 +1163,7 @@ __global__ __launch_bounds__(kLocalThreads) __attribute__((amdgpu_waves_per_eu(4
     if (t < 256) s_base[t] = 0u;
     __syncthreads();
     for (int s = t; s < R; s += kLocalThreads) {
-      const uint64_t it = rd[lo + s];
-      const int cr = multi ? cloud_at(s_starts, B, (int)(uint32_t)it) - c_first : 0;
-      const uint64_t k64 = ((((uint64_t)cr) << 32) | (it >> 32)) - base64;
-      const uint32_t digit = q < extra ? 0u : (uint32_t)((k64 >> shift) & 255u);
+      const uint32_t digit = q < extra ? 0u : (rel(rd[lo + s]) >> shift) & 255u;
       atomicAdd(&s_base[digit], 1u);
     }
     __syncthreads();
@@ -1122,9 +1184,7 @@ __global__ __launch_bounds__(kLocalThreads) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
       for (int j = 0; j < kSlowItems; ++j) {
         const int s = c0 + (wave * kSlowItems + j) * kWave + lane;
-        const int cr = multi ? cloud_at(s_starts, B, (int)(uint32_t)it[j]) - c_first : 0;
-        const uint64_t k64 = ((((uint64_t)cr) << 32) | (it[j] >> 32)) - base64;
-        dg[j] = s >= R ? 255u : (q < extra ? 0u : (uint32_t)((k64 >> shift) & 255u));
+        dg[j] = s >= R ? 255u : (q < extra ? 0u : (rel(it[j]) >> shift) & 255u);
       }
 #pragma unroll
       for (int j = 0; j < kSlowItems; ++j) rk[j] = wave_rank8(dg[j], s_cnt[wave], bf[j]);
@@ -1210,9 +1270,7 @@ hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, const
   const dim3 grid(ntiles > 0 ? ntiles : 1, r.dt.num_dirs);
   if (r.dt.passes == kSortPasses && !r.sort_lsd) {
     // codes of at most 32 bits: the MSD pass, then the windows' local sorts
-    const int64_t npos = r.sa.n_fixed >= 0 ? r.sa.n_fixed : r.pl.n_cap;
-    a.nwin = (int)((npos + kLocalWin - 1) / kLocalWin);
-    if (a.nwin < 1) a.nwin = 1;
+    a.nwin = (int)grid.x;  // windows are numbered like the tiles
     a.win = r.b.win;
     a.pass = 0;
     a.passes = 1;
