@@ -293,14 +293,16 @@ fgbd_status fgbd_denoise_batched_fixed_q(fgbd_ctx ctx, const int32_t *xyz, const
  * (noise_blocks) the patch statistics and (sweep_blocks) the filter sweeps
  * and finalise; and (sweep_launches) how many of the up to q_max filter
  * sweeps of eq. 6 are enqueued as launches of their own.  The sweeps after
- * those run in one launch whose blocks wait for each other between sweeps
- * (the grid is sized to be resident on the device at once), which returns at
- * once when every cloud's selection has already finished (a launch that
+ * those run in one launch in which the blocks of a cloud wait for each other
+ * between sweeps (the grid is sized to be resident on the device at once); a
+ * cloud whose selection has already finished skips them (a launch that
  * finds the selection finished still costs about two microseconds; waiting
  * for all blocks costs far more than a launch boundary, so the count should
  * cover the sweeps a workload usually needs).  When the sweep grid cannot be
  * resident on the device at once, every sweep is a launch of its own.
- * Defaults 4096, 1024, 512 and 8.  A schedule changes no result beyond the
+ * Defaults 4096, 1024, 512 and 8; an eager call on a context whose schedule
+ * was neither set nor tuned enqueues more separate sweeps than 8 when its
+ * recent calls needed them.  A schedule changes no result beyond the
  * rounding order of FP64 sums (block partials); it is a property of the
  * context and applies to every later call on it.  Valid ranges:
  * merge_blocks and sweep_blocks 64..4096, noise_blocks 64..1024,

@@ -61,6 +61,7 @@ struct fgbd_ctx_s {
   size_t user_bytes = 0;
   bool profile = false;
   Tune tune = kDefaultTune;
+  bool tune_set = false;  // fgbd_set_schedule or fgbd_autotune chose the schedule
   std::vector<hipEvent_t> pool;
   std::vector<Record> pending;
   double ms[FGBD_NUM_KERNELS] = {0};
@@ -719,7 +720,11 @@ fgbd_status fgbd_filter(fgbd_ctx ctx, const fgbd_graph *g, const float *rgb_in, 
 // the most sweeps any of the last eight read-back calls needed when those
 // counts agree (the finalising launch then applies the last sweep's sums
 // itself and finds the selection stopped), else to one more (a launch that
-// finds it stopped, so the in-launch loop after it returns at once).
+// finds it stopped, so the in-launch loop after it returns at once).  A
+// context whose schedule nobody set goes above the default count the same
+// way when recent calls needed more sweeps: a separate sweep of 64 clouds of
+// 4k points takes 8.5 us, one in the loop many times that (the batch of 64:
+// 1513 us with 8 separate sweeps, 439 with as many as it needs).
 // Captured calls keep the schedule's count.  *hint receives where this call's finalising launch
 // should store its sweep counts (NULL: no read-back requested).
 static int adaptive_sweep_launches(fgbd_ctx ctx, hipStream_t s, int32_t **hint) {
@@ -762,7 +767,8 @@ static int adaptive_sweep_launches(fgbd_ctx ctx, hipStream_t s, int32_t **hint) 
     lo = ctx->hint_recent[i] < lo ? ctx->hint_recent[i] : lo;
   }
   const int want = (k >= 2 && lo == m) ? m : m + 1;  // steady counts: no spare launch
-  return want < 1 ? 1 : (want < cap ? want : cap);
+  const int most = ctx->tune_set ? cap : kMaxAdaptiveSweeps;
+  return want < 1 ? 1 : (want < most ? want : most);
 }
 
 // After the launches of an eager call that asked for a read-back: mark it.
@@ -952,6 +958,7 @@ fgbd_status fgbd_set_schedule(fgbd_ctx ctx, const fgbd_schedule *s) {
   ctx->tune.cap[kGridNoise] = s->noise_blocks;
   ctx->tune.cap[kGridSweep] = s->sweep_blocks;
   ctx->tune.sweep_launches = s->sweep_launches;
+  ctx->tune_set = true;
   return ok();
 }
 
@@ -1038,6 +1045,7 @@ fgbd_status fgbd_autotune(fgbd_ctx ctx, const int32_t *xyz, const float *rgb_in,
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   ctx->tune = best;
+  ctx->tune_set = true;
   ctx->profile = was_profiling;
   if (st != FGBD_OK) return st;
   HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");

@@ -38,12 +38,11 @@
 // microseconds, and q_max of them are enqueued.  So only the first few sweeps
 // (the schedule's sweep_launches) are launches of their own; the rest, if the
 // selection has not finished by then, run in one launch that loops over the
-// remaining sweeps, its blocks waiting for each other between sweeps (a
-// counter in device memory; the grid is sized to be resident at once).  That
-// launch first reads the done flags the last separate launch stored and skips
-// the loop when every cloud is done, which is the usual case; either way it
-// then does the finalising work (so no separate launch follows it).  The
-// wait between sweeps costs far more than a kernel boundary on this GPU (it
+// remaining sweeps, the blocks of a cloud waiting for each other between
+// sweeps (a counter per cloud in device memory; the grid is sized to be
+// resident at once).  A cloud that is done, the usual case, skips the loop;
+// either way the launch then does the finalising work (so no separate launch
+// follows it).  The wait between sweeps costs far more than a kernel boundary on this GPU (it
 // writes back and invalidates the L2 of every XCD), so the loop is the
 // fallback, not the main path.  A plain launch is used because a cooperative
 // launch measured about 40 us of overhead even when it returned at once.
@@ -212,20 +211,6 @@ __device__ __forceinline__ void load_state(SweepCtrl &c, const SweepCtrl *__rest
   __syncthreads();  // s_tot is written again by the next call (the in-launch sweep loop)
   advance_loaded(c, f, u, n);
 }
-// The same advance by one wave alone (no block barrier).
-__device__ __forceinline__ void wave_advance(SweepCtrl &c, const SweepCtrl *__restrict__ prev,
-                                             const unsigned long long *__restrict__ sums_prev,
-                                             const unsigned long long *__restrict__ sums_first, int n) {
-  c = *prev;
-  unsigned long long f[kSweepParts], u[kSweepParts];
-  load_slots(sums_first, f);
-  load_slots(sums_prev, u);
-  if (c.done) return;
-  if (c.first_pending) wave_sum(f);
-  wave_sum(u);
-  advance_loaded(c, f, u, n);
-}
-
 // Block-sum of per-thread integer sums, then one atomic per value per block
 // into slot `slot` of the cloud's sums.
 __device__ __forceinline__ void add_sums(unsigned long long (&v)[kSweepParts], unsigned long long *__restrict__ out,
@@ -483,16 +468,16 @@ __global__ __launch_bounds__(kBlock) void k_sweep(SweepArgs a, int q, const int3
   sweep_step<KT, FIRST, D2, PRE, MERGED>(a, sb, sweep_io(a, q), col, p, y, xbuf, spread, noise, lds);
 }
 
-// Waits until every block of the grid has arrived `epoch` times at this
-// barrier (count starts at 0 for the launch), with this block's writes
-// released before its arrival and the others' acquired after.  The wait is
-// bounded by `limit` ticks of the constant-rate clock; false when it gave up.
-__device__ bool grid_barrier(uint32_t *count, uint32_t epoch, long long limit, int *s_flag) {
+// Waits until the cloud's `blocks` blocks have arrived `epoch` times at its
+// counter (0 at the call's setup), with this block's writes released before
+// its arrival and the others' acquired after.  The wait is bounded by `limit`
+// ticks of the constant-rate clock; false when it gave up.
+__device__ bool cloud_barrier(uint32_t *count, uint32_t epoch, int blocks, long long limit, int *s_flag) {
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();
     __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t target = epoch * gridDim.x;
+    const uint32_t target = epoch * (uint32_t)blocks;
     const long long t0 = wall_clock64();
     int ok = 1;
     while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
@@ -509,19 +494,6 @@ __device__ bool grid_barrier(uint32_t *count, uint32_t epoch, long long limit, i
   return *s_flag != 0;
 }
 
-// True when the selection of every cloud is done in states[0..B).  Each wave
-// reads the B flags (one per lane) and votes, so the answer is uniform.
-__device__ __forceinline__ bool all_clouds_done(const SweepCtrl *states, int B) {
-  const int l = (int)lane_id();
-  const bool open = l < B && !states[l].done;
-  return __builtin_amdgcn_ballot_w64(open) == 0;
-}
-
-// Sweeps q0..q_last in one launch (same grid and block-to-cloud map as the
-// separate launches; all blocks resident), every block waiting for all
-// others after each sweep.  States are left where the finalising launch looks
-// for them: in the buffer of q_last.  If a wait gives up, every block's cloud
-// is flagged FGBD_ST_SWEEP_STALL and the loop ends.
 // The finalising work of one block, from the cloud's final state c: the
 // chosen iterate (or the input for q = 0) out, and block 0 of the cloud
 // writes its results (and its sweep count to hint when given).
@@ -590,8 +562,15 @@ __global__ __launch_bounds__(kBlock) void k_finalize(SegArgs sa, int64_t buf_str
                  relabel && relabel[sb.s] ? rank0 : nullptr);
 }
 
+// Sweeps q0..q_last in one launch (same grid and block-to-cloud map as the
+// separate launches; all blocks resident), then the finalising work.  Clouds
+// are independent, so the blocks of a cloud wait only for each other after
+// each sweep, and a cloud whose selection has stopped is finalised and its
+// blocks leave: with one barrier for the whole grid, a batch of 64 clouds of
+// 4k points of which a few need 9 to 20 sweeps spent 1217 us here.  If a wait
+// gives up, the cloud is flagged FGBD_ST_SWEEP_STALL and the loop ends.
 template <int KT>
-__global__ __launch_bounds__(kBlock) void k_sweep_tail(SweepArgs a, int q0, int q_last, uint32_t *barrier,
+__global__ __launch_bounds__(kBlock) void k_sweep_tail(SweepArgs a, int q0, int q_last, uint32_t *barriers,
                                                        long long wait_limit, const int32_t *__restrict__ col,
                                                        const float *__restrict__ p, const float *__restrict__ rgb_in,
                                                        float4 *__restrict__ xbuf, const double *__restrict__ spread,
@@ -600,43 +579,20 @@ __global__ __launch_bounds__(kBlock) void k_sweep_tail(SweepArgs a, int q0, int 
   __shared__ SweepLds<false> lds;
   __shared__ int s_flag;
   const SegBlock sb = seg_block(a.sa, kGridSweep);
-  if (a.relabel && a.relabel[sb.s]) col = a.col_w;  // a renumbered cloud's graph
-  const int B = a.sa.B;
-  // state at the start of the last separate sweep, written by that launch
-  const SweepCtrl *last = a.ctrl + ((q0 - 1) & 1) * B;
-  {
-    // Those states advanced by that sweep's sums, one wave per cloud: when
-    // every cloud is then done (the usual case once the schedule launches as
-    // many separate sweeps as the selection needs), finalise at once, with no
-    // loop and no wait for the other blocks.
-    __shared__ int s_open;
-    __shared__ SweepCtrl s_mine;  // this block's cloud, as the wave that advanced it left it
-    if (threadIdx.x == 0) s_open = 0;
-    __syncthreads();
-    const size_t S = (size_t)B * kSlotVals;
-    const unsigned long long *sums_sep = a.sums3 + (size_t)((q0 - 1) % 3) * S;
-    const unsigned long long *sums_first = a.sums3 + 3 * S;
-    for (int s2 = (int)threadIdx.x / kWave; s2 < B; s2 += kBlock / kWave) {
-      const int n2 = a.sa.n_fixed >= 0 ? a.sa.n_fixed : a.sa.segs->start[s2 + 1] - a.sa.segs->start[s2];
-      SweepCtrl cs;
-      wave_advance(cs, last + s2, sums_sep + (size_t)s2 * kSlotVals, sums_first + (size_t)s2 * kSlotVals, n2);
-      if (!cs.done && lane_id() == 0) s_open = 1;
-      if (s2 == sb.s && lane_id() == 0) s_mine = cs;
-    }
-    __syncthreads();
-    if (s_open == 0) {  // uniform over the grid: every block read the same states and sums
-      const SweepCtrl c = s_mine;
-      finalize_block(sb, c, a.buf_stride, rgb_in, xbuf, noise, rgb_out, a.res, hint,
-                     a.relabel && a.relabel[sb.s] ? a.rank0 : nullptr);
-      return;
-    }
-  }
-  int q = q0;
-  bool done = all_clouds_done(last, B);
-  uint32_t epoch = 0;
-  while (!done && q <= q_last) {
-    sweep_step<KT, false, false>(a, sb, sweep_io(a, q), col, p, rgb_in, xbuf, spread, noise, lds);
-    if (!grid_barrier(barrier, ++epoch, wait_limit, &s_flag)) {
+  const int n = (int)(sb.end - sb.begin);
+  const bool renumbered = a.relabel && a.relabel[sb.s];
+  if (renumbered) col = a.col_w;  // a renumbered cloud's graph
+  uint32_t *barrier = barriers + (size_t)sb.s * kBarrierStride;
+  SweepCtrl c;
+  for (int q = q0;; ++q) {
+    // the state after sweep q - 1: the one stored at its start, advanced by
+    // its sums (the same integers for every block of the cloud)
+    const SweepIO io = sweep_io(a, q);
+    load_state(c, io.ctrl_prev + sb.s, io.sums_prev + (size_t)sb.s * kSlotVals,
+               io.sums_first + (size_t)sb.s * kSlotVals, n);
+    if (c.done || q > q_last) break;
+    sweep_step<KT, false, false>(a, sb, io, col, p, rgb_in, xbuf, spread, noise, lds);
+    if (!cloud_barrier(barrier, (uint32_t)(q - q0 + 1), sb.nb, wait_limit, &s_flag)) {
       // The selection cannot be completed: flag the cloud and leave every
       // point of this block's share defined (its input colour).
       if (threadIdx.x == 0) atomicOr(&a.res[sb.s].status, FGBD_ST_SWEEP_STALL);
@@ -650,23 +606,8 @@ __global__ __launch_bounds__(kBlock) void k_sweep_tail(SweepArgs a, int q0, int 
       }
       return;
     }
-    last = a.ctrl + (q & 1) * B;
-    done = all_clouds_done(last, B);
-    ++q;
   }
-  // Finalise.  Every sweep this launch computed ended at a grid barrier, and
-  // the earlier ones were launches of their own.  Stopped early: the last
-  // states read are final; else the states of q_last with its sums applied.
-  SweepCtrl c;
-  if (done) {
-    c = last[sb.s];
-  } else {
-    const unsigned long long *sums_last = a.sums3 + (size_t)(q_last % 3) * B * kSlotVals;
-    load_state(c, a.ctrl + (q_last & 1) * B + sb.s, sums_last + (size_t)sb.s * kSlotVals,
-               a.sums3 + (size_t)3 * B * kSlotVals + (size_t)sb.s * kSlotVals, (int)(sb.end - sb.begin));
-  }
-  finalize_block(sb, c, a.buf_stride, rgb_in, xbuf, noise, rgb_out, a.res, hint,
-                 a.relabel && a.relabel[sb.s] ? a.rank0 : nullptr);
+  finalize_block(sb, c, a.buf_stride, rgb_in, xbuf, noise, rgb_out, a.res, hint, renumbered ? a.rank0 : nullptr);
 }
 
 SweepArgs sweep_args(const Run &r, const int32_t *dist2, float *p_out, fgbd_result *res, int select, int q_limit) {
@@ -788,7 +729,7 @@ hipError_t launch_sweep_tail(const Run &r, const int32_t *col, const float *p, c
                             const int32_t *, const float *, const float *, float4 *, const double *,
                             const fgbd_result *, float *, int32_t *);
   static const Fn table[2] = {tail_kernel<0>, tail_kernel<8>};
-  return table[a.k == 8](nb, r.stream, a, q0, q_last, &r.b.segs->sweep_barrier, wait_ticks(r.wait_us), col, p,
+  return table[a.k == 8](nb, r.stream, a, q0, q_last, &r.b.segs->sweep_barrier[0][0], wait_ticks(r.wait_us), col, p,
                          rgb_in, r.b.xbuf, spread, noise, rgb_out, r.hint);
 }
 

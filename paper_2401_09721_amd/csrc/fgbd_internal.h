@@ -148,14 +148,14 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *s
 // blk_first[g][s] .. blk_first[g][s+1]-1 (at least one, the rest in proportion
 // to its size), and radix tiles never straddle two clouds.
 constexpr int kMaxSeg = 64;
+constexpr int kBarrierStride = 32;  // words: a line of its own for each cloud's arrival counter
 enum GridKind { kGridMerge = 0, kGridNoise = 1, kGridSweep = 2, kNumGrids = 3 };
 struct Segs {
   int32_t B;
   int32_t n;       // start[B]
   int32_t ntiles;  // radix tiles in use
   int32_t status;  // FGBD_ST_BAD_OFFSETS when the offsets had to be clamped
-  uint32_t sweep_barrier;  // arrival counter of the in-launch sweep loop (0 at setup)
-  uint32_t pad_[3];
+  uint32_t pad_[4];
   int32_t start[kMaxSeg + 1];
   int32_t tile_first[kMaxSeg + 1];
   int32_t blk_first[kNumGrids][kMaxSeg + 1];
@@ -163,6 +163,9 @@ struct Segs {
   // kept edges are far (the merge's counts in the edge-length sums); 0 at
   // setup.
   int32_t relabel[kMaxSeg];
+  // Per cloud, one cache line each: arrival counter of the in-launch sweep
+  // loop (0 at setup).
+  uint32_t sweep_barrier[kMaxSeg][kBarrierStride];
 };
 // An edge is far when its points are more than a sixteenth of the cloud, and
 // more than 4096 points, apart in the input numbering (a raster order keeps
@@ -401,6 +404,9 @@ struct Tune {
 };
 constexpr int kDefaultSweepLaunches = 8;
 constexpr int kMaxSweepLaunches = 1024;
+// An eager call on a context whose schedule nobody set enqueues up to this
+// many separate sweeps when recent calls needed them.
+constexpr int kMaxAdaptiveSweeps = 64;
 constexpr int kDefaultMergeGrid = 4096;  // the merge gains from more blocks than the other kernels
 constexpr int kDefaultSweepGrid = 512;  // fewer, longer-running sweep blocks: less block start and sum traffic
 constexpr Tune kDefaultTune = {{kDefaultMergeGrid, kMaxGrid, kDefaultSweepGrid}, kDefaultSweepLaunches};
@@ -556,9 +562,9 @@ bool sweep_tail_fits(const Run &r);
 
 // Sweeps q0..q_last in one launch whose blocks wait for each other between
 // sweeps, after separate launches of sweeps 1..q0-1 (same arguments as
-// launch_sweep), then the work of launch_finalize; skips the sweeps when
-// every cloud's selection was done at the start of sweep q0-1.  Uses the
-// segment table's barrier counter (zeroed by the setup launch of the call).
+// launch_sweep), then the work of launch_finalize; a cloud whose selection is
+// done after sweep q0-1 skips the sweeps.  Uses the segment table's arrival
+// counters (zeroed by the setup launch of the call).
 hipError_t launch_sweep_tail(const Run &r, const int32_t *col, const float *p, const float *rgb_in,
                              const double *spread, const fgbd_result *noise, fgbd_result *res, int select,
                              int q_limit, int q0, int q_last, float *rgb_out);

@@ -203,7 +203,10 @@ __device__ __forceinline__ void setup_work(const SetupArgs &a, int block) {
   for (int i = block * blockDim.x + t; i < a.noise_count; i += stride) a.noise_acc[i] = 0ull;
   for (int i = block * blockDim.x + t; i < a.edge_count; i += stride) a.edge_acc[i] = 0ull;
   if (block != 0) return;  // uniform over the block
-  if (t < kMaxSeg) sg->relabel[t] = 0;
+  if (t < kMaxSeg) {
+    sg->relabel[t] = 0;
+    sg->sweep_barrier[t][0] = 0u;
+  }
   const int B = a.B;
   if (t <= B) s_raw[t] = a.offsets ? a.offsets[t] : (t == 0 ? 0 : a.n_host);
   __syncthreads();
@@ -228,7 +231,6 @@ __device__ __forceinline__ void setup_work(const SetupArgs &a, int block) {
     sg->n = s_start[B];
     sg->ntiles = tiles;
     sg->status = bad ? FGBD_ST_BAD_OFFSETS : 0;
-    sg->sweep_barrier = 0u;
   }
   __syncthreads();
   if (t <= B) {
