@@ -57,6 +57,7 @@ namespace {
 struct SweepArgs {
   SegArgs sa;
   int32_t k;
+  int32_t vec;  // elements per load of a row of other than 6, 8 or 16 slots
   int32_t select, q_limit;
   double kappa;
   int64_t buf_stride;  // float4 elements per buffer
@@ -260,7 +261,7 @@ __device__ __forceinline__ void sweep_step(const SweepArgs &a, const SegBlock &s
                                            const double *__restrict__ spread, const fgbd_result *__restrict__ noise,
                                            SweepLds<D2> &lds) {
   const int K = KT > 0 ? KT : a.k;
-  constexpr int KB = KT > 0 ? KT : kMaxK;  // slots per row held in registers
+  constexpr int KB = row_cap(KT);  // slots per row held in registers
   const unsigned long long *sums_prev = io.sums_prev + (size_t)sb.s * kSlotVals;
   unsigned long long *sums_out = io.sums_out + (size_t)sb.s * kSlotVals;
   unsigned long long *sums_clear = io.sums_clear + (size_t)sb.s * kSlotVals;
@@ -358,50 +359,16 @@ __device__ __forceinline__ void sweep_step(const SweepArgs &a, const SegBlock &s
       v[4] += member != 0.0f ? 1ull : 0ull;
       continue;
     }
-    int cc[KT > 0 ? KT : kMaxK];
-    float ww[KT > 0 ? KT : kMaxK];
+    int cc[KB];
+    float ww[KB];
+    load_row<KT>(col, i, K, a.vec, -1, cc);
     if (D2) {
       int dv[KB];
-      if (KT == 8) {
-        const int4 *cr = reinterpret_cast<const int4 *>(col + i * 8);
-        const int4 *dr = reinterpret_cast<const int4 *>(a.dist2 + i * 8);
-        const int4 c0 = cr[0], c1 = cr[1], e0 = dr[0], e1 = dr[1];
-        cc[0] = c0.x; cc[1] = c0.y; cc[2] = c0.z; cc[3] = c0.w;
-        cc[4] = c1.x; cc[5] = c1.y; cc[6] = c1.z; cc[7] = c1.w;
-        dv[0] = e0.x; dv[1] = e0.y; dv[2] = e0.z; dv[3] = e0.w;
-        dv[4] = e1.x; dv[5] = e1.y; dv[6] = e1.z; dv[7] = e1.w;
-      } else {
-#pragma unroll
-        for (int k = 0; k < (KT > 0 ? KT : kMaxK); ++k) {
-          cc[k] = k < K ? col[i * K + k] : -1;
-          dv[k] = k < K ? a.dist2[i * K + k] : 0;
-        }
-      }
+      load_row<KT>(a.dist2, i, K, a.vec, 0, dv);
       row_weights<KB>(cc, dv, c.sigma_g, lds.exp, ww);
-      if (KT == 8) {
-        float4 *pr = reinterpret_cast<float4 *>(a.p_out + i * 8);
-        pr[0] = make_float4(ww[0], ww[1], ww[2], ww[3]);
-        pr[1] = make_float4(ww[4], ww[5], ww[6], ww[7]);
-      } else {
-#pragma unroll
-        for (int k = 0; k < KB; ++k)
-          if (k < K) a.p_out[i * K + k] = ww[k];
-      }
-    } else if (KT == 8) {
-      const int4 *cr = reinterpret_cast<const int4 *>(col + i * 8);
-      const float4 *pr = reinterpret_cast<const float4 *>(p + i * 8);
-      const int4 c0 = cr[0], c1 = cr[1];
-      const float4 p0 = pr[0], p1 = pr[1];
-      cc[0] = c0.x; cc[1] = c0.y; cc[2] = c0.z; cc[3] = c0.w;
-      cc[4] = c1.x; cc[5] = c1.y; cc[6] = c1.z; cc[7] = c1.w;
-      ww[0] = p0.x; ww[1] = p0.y; ww[2] = p0.z; ww[3] = p0.w;
-      ww[4] = p1.x; ww[5] = p1.y; ww[6] = p1.z; ww[7] = p1.w;
+      store_row<KT>(a.p_out, i, K, ww);
     } else {
-#pragma unroll
-      for (int k = 0; k < (KT > 0 ? KT : kMaxK); ++k) {
-        cc[k] = k < K ? col[i * K + k] : -1;
-        ww[k] = k < K ? p[i * K + k] : 0.0f;
-      }
+      load_row<KT>(p, i, K, a.vec, 0.0f, ww);
     }
     // Branch-free gathers: an empty slot (col = -1, weight 0) reads the point
     // itself.  All neighbour loads are issued before any is consumed.
@@ -614,6 +581,7 @@ SweepArgs sweep_args(const Run &r, const int32_t *dist2, float *p_out, fgbd_resu
   SweepArgs a;
   a.sa = r.sa;
   a.k = r.prm.k;
+  a.vec = 1;
   a.select = select;
   a.q_limit = q_limit;
   a.kappa = r.prm.fslr_kappa;
@@ -704,33 +672,41 @@ hipError_t launch_sweep(const Run &r, const int32_t *col, const float *p, const 
     return hipGetLastError();
   }
   // the first sweep of the fused path stores the weights it derives into p
-  const SweepArgs a = sweep_args(r, dist2, d2 ? const_cast<float *>(p) : nullptr, res, select, q_limit);
+  SweepArgs a = sweep_args(r, dist2, d2 ? const_cast<float *>(p) : nullptr, res, select, q_limit);
   const int nb = r.pl.grid[kGridSweep];
+  const size_t align = common_align(col, p, dist2);
+  a.vec = row_vec(a.k, align);
   using Fn = void (*)(int, hipStream_t, const SweepArgs &, int, const int32_t *, const float *, const float *,
                       float4 *, const double *, const fgbd_result *);
-  // [k == 8][later sweep, first sweep, first sweep deriving the weights]
-  static const Fn table[2][3] = {
-      {sweep_kernel<0, false, false>, sweep_kernel<0, true, false>, sweep_kernel<0, true, true>},
-      {sweep_kernel<8, false, false>, sweep_kernel<8, true, false>, sweep_kernel<8, true, true>}};
-  table[a.k == 8][first ? (d2 ? 2 : 1) : 0](nb, r.stream, a, q, col, p, rgb_in, r.b.xbuf, spread, noise);
+  // [row kind][later sweep, first sweep, first sweep deriving the weights]
+#define FGBD_SWEEPS(KT) {sweep_kernel<KT, false, false>, sweep_kernel<KT, true, false>, sweep_kernel<KT, true, true>}
+  static const Fn table[kNumRowKinds][3] = {FGBD_SWEEPS(8),  FGBD_SWEEPS(6),   FGBD_SWEEPS(16),
+                                            FGBD_SWEEPS(-8), FGBD_SWEEPS(-16), FGBD_SWEEPS(-32)};
+#undef FGBD_SWEEPS
+  table[row_kind(a.k, align)][first ? (d2 ? 2 : 1) : 0](nb, r.stream, a, q, col, p, rgb_in, r.b.xbuf, spread, noise);
   return hipGetLastError();
 }
 
 bool sweep_tail_fits(const Run &r) {
-  return (r.prm.k == 8 ? tail_capacity<8>() : tail_capacity<0>()) >= r.pl.grid[kGridSweep];
+  // (the exact kinds hold no more registers than the bounded ones)
+  const int k = r.prm.k;
+  const int cap = k == 8 ? tail_capacity<8>() : (k <= 8 ? tail_capacity<-8>() : (k <= 16 ? tail_capacity<-16>() : tail_capacity<-32>()));
+  return cap >= r.pl.grid[kGridSweep];
 }
 
 hipError_t launch_sweep_tail(const Run &r, const int32_t *col, const float *p, const float *rgb_in,
                              const double *spread, const fgbd_result *noise, fgbd_result *res, int select,
                              int q_limit, int q0, int q_last, float *rgb_out) {
-  const SweepArgs a = sweep_args(r, nullptr, nullptr, res, select, q_limit);
+  SweepArgs a = sweep_args(r, nullptr, nullptr, res, select, q_limit);
   const int nb = r.pl.grid[kGridSweep];
+  a.vec = row_vec(a.k, common_align(col, p));
   using Fn = hipError_t (*)(int, hipStream_t, const SweepArgs &, int, int, uint32_t *, long long,
                             const int32_t *, const float *, const float *, float4 *, const double *,
                             const fgbd_result *, float *, int32_t *);
-  static const Fn table[2] = {tail_kernel<0>, tail_kernel<8>};
-  return table[a.k == 8](nb, r.stream, a, q0, q_last, &r.b.segs->sweep_barrier[0][0], wait_ticks(r.wait_us), col, p,
-                         rgb_in, r.b.xbuf, spread, noise, rgb_out, r.hint);
+  // the loop is a fallback: bounded rows serve every K but 8
+  const Fn fn = a.k == 8 ? tail_kernel<8> : (a.k <= 8 ? tail_kernel<-8> : (a.k <= 16 ? tail_kernel<-16> : tail_kernel<-32>));
+  return fn(nb, r.stream, a, q0, q_last, &r.b.segs->sweep_barrier[0][0], wait_ticks(r.wait_us), col, p,
+            rgb_in, r.b.xbuf, spread, noise, rgb_out, r.hint);
 }
 
 hipError_t launch_finalize(const Run &r, const float *rgb_in, int q_launches, const fgbd_result *noise,

@@ -503,7 +503,8 @@ __global__ __launch_bounds__(kBlock) void k_relabel(SegArgs sa, int32_t k_rt, Se
 
 // Runs on the merge grid: block b belongs to the same cloud as merge block b.
 template <int KT>
-__global__ __launch_bounds__(kBlock) void k_weights(SegArgs sa, int32_t k_rt, const int32_t *__restrict__ col,
+__global__ __launch_bounds__(kBlock) void k_weights(SegArgs sa, int32_t k_rt, int32_t vec,
+                                                    const int32_t *__restrict__ col,
                                                     const int32_t *__restrict__ dist2,
                                                     const unsigned long long *__restrict__ edge_acc,
                                                     double sigma_g_fixed,
@@ -517,38 +518,17 @@ __global__ __launch_bounds__(kBlock) void k_weights(SegArgs sa, int32_t k_rt, co
   if (sb.lb == 0 && threadIdx.x == 0) res[sb.s].sigma_g = sg;
   fill_exp_table(sg, s_exp);
   __syncthreads();
-  constexpr int KB = KT > 0 ? KT : kMaxK;
+  constexpr int KB = row_cap(KT);
   const Share sh = seg_share(sb, kBlock);
   for (int64_t base = sh.first; base < sh.end; base += sh.step) {
     const int64_t i = base + threadIdx.x;
     if (i >= sh.end) continue;
     int cv[KB], dv[KB];
-    if (KT == 8) {
-      const int4 *cr = reinterpret_cast<const int4 *>(col + i * 8);
-      const int4 *dr = reinterpret_cast<const int4 *>(dist2 + i * 8);
-      const int4 c0 = cr[0], c1 = cr[1], e0 = dr[0], e1 = dr[1];
-      cv[0] = c0.x; cv[1] = c0.y; cv[2] = c0.z; cv[3] = c0.w;
-      cv[4] = c1.x; cv[5] = c1.y; cv[6] = c1.z; cv[7] = c1.w;
-      dv[0] = e0.x; dv[1] = e0.y; dv[2] = e0.z; dv[3] = e0.w;
-      dv[4] = e1.x; dv[5] = e1.y; dv[6] = e1.z; dv[7] = e1.w;
-    } else {
-#pragma unroll
-      for (int k = 0; k < KB; ++k) {
-        cv[k] = k < K ? col[i * K + k] : -1;
-        dv[k] = k < K ? dist2[i * K + k] : 0;
-      }
-    }
+    load_row<KT>(col, i, K, vec, -1, cv);
+    load_row<KT>(dist2, i, K, vec, 0, dv);
     float pw[KB];
     row_weights<KB>(cv, dv, sg, s_exp, pw);
-    if (KT == 8) {
-      float4 *pr = reinterpret_cast<float4 *>(p + i * 8);
-      pr[0] = make_float4(pw[0], pw[1], pw[2], pw[3]);
-      pr[1] = make_float4(pw[4], pw[5], pw[6], pw[7]);
-    } else {
-#pragma unroll
-      for (int k = 0; k < KB; ++k)
-        if (k < K) p[i * K + k] = pw[k];
-    }
+    store_row<KT>(p, i, K, pw);
   }
 }
 
@@ -610,10 +590,13 @@ hipError_t launch_relabel(const Run &r, const uint64_t *sorted, const int32_t *c
 
 hipError_t launch_weights(const Run &r, const int32_t *col, const int32_t *dist2, fgbd_result *res, float *p) {
   const int nb = r.pl.grid[kGridMerge];
-  if (r.prm.k == 8)
-    k_weights<8><<<nb, kBlock, 0, r.stream>>>(r.sa, 8, col, dist2, r.b.edge_acc, r.prm.sigma_g, res, p);
-  else
-    k_weights<0><<<nb, kBlock, 0, r.stream>>>(r.sa, r.prm.k, col, dist2, r.b.edge_acc, r.prm.sigma_g, res, p);
+  const size_t align = common_align(col, dist2, p);
+  const int k = r.prm.k, vec = row_vec(k, align);
+  using Fn = void (*)(SegArgs, int32_t, int32_t, const int32_t *, const int32_t *, const unsigned long long *, double,
+                      fgbd_result *, float *);
+  static const Fn table[kNumRowKinds] = {k_weights<8>, k_weights<6>, k_weights<16>, k_weights<-8>, k_weights<-16>,
+                                         k_weights<-32>};
+  table[row_kind(k, align)]<<<nb, kBlock, 0, r.stream>>>(r.sa, k, vec, col, dist2, r.b.edge_acc, r.prm.sigma_g, res, p);
   return hipGetLastError();
 }
 

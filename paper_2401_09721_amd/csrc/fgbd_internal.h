@@ -244,6 +244,86 @@ __device__ __forceinline__ Share seg_share(const SegBlock &sb, int chunk) {
   return s;
 }
 
+// ------------------------------------------------------------ graph rows
+// Kernels that hold a point's row in registers are instantiated for a row
+// kind KT: KT > 0 is K = KT exactly, its loads as wide as KT allows (16 bytes
+// for multiples of 4, 8 for other even K); KT < 0 any K <= -KT, loads `vec`
+// elements wide and clamped into the row (so all are issued without a branch;
+// slots past K are then filled).  The sweeps, weights and patches of other K
+// than 8 all ran 32-slot rows before: 21 us for a sweep of 180k points with
+// K = 16 against 10.5 now, 17 against 10 for 300k points with K = 6.
+constexpr int row_cap(int KT) { return KT > 0 ? KT : -KT; }
+template <typename T, int N>
+struct alignas(sizeof(T) * N) RowVec {
+  T v[N];
+};
+template <int KT, typename T>
+__device__ __forceinline__ void load_row(const T *__restrict__ base, int64_t i, int K, int vec, T fill,
+                                         T (&v)[row_cap(KT)]) {
+  constexpr int KB = row_cap(KT);
+  if constexpr (KT > 0) {
+    constexpr int N = KT % 4 == 0 ? 4 : (KT % 2 == 0 ? 2 : 1);
+    const RowVec<T, N> *r = reinterpret_cast<const RowVec<T, N> *>(base + i * KT);
+#pragma unroll
+    for (int q = 0; q < KT / N; ++q) {
+      const RowVec<T, N> x = r[q];
+#pragma unroll
+      for (int u = 0; u < N; ++u) v[N * q + u] = x.v[u];
+    }
+  } else {
+    const T *r = base + i * K;
+    if (vec == 4) {  // uniform over the launch
+#pragma unroll
+      for (int q = 0; q < KB / 4; ++q) {
+        const RowVec<T, 4> x = *reinterpret_cast<const RowVec<T, 4> *>(r + min(4 * q, K - 4));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[4 * q + u] = x.v[u];
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < KB; ++k) v[k] = r[min(k, K - 1)];
+    }
+#pragma unroll
+    for (int k = 0; k < KB; ++k)
+      if (k >= K) v[k] = fill;
+  }
+}
+template <int KT, typename T>
+__device__ __forceinline__ void store_row(T *__restrict__ base, int64_t i, int K, const T (&v)[row_cap(KT)]) {
+  if constexpr (KT > 0) {
+    constexpr int N = KT % 4 == 0 ? 4 : (KT % 2 == 0 ? 2 : 1);
+    RowVec<T, N> *r = reinterpret_cast<RowVec<T, N> *>(base + i * KT);
+#pragma unroll
+    for (int q = 0; q < KT / N; ++q) {
+      RowVec<T, N> x;
+#pragma unroll
+      for (int u = 0; u < N; ++u) x.v[u] = v[N * q + u];
+      r[q] = x;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < row_cap(KT); ++k)
+      if (k < K) base[i * K + k] = v[k];
+  }
+}
+// The row kind of a launch over rows of K slots in arrays all aligned to
+// `align` bytes: rows of 6 (the paper's graph), 8 and 16 have kernels of
+// their own, which need their loads' alignment; any other K, or a less
+// aligned array, takes the smallest bound that holds it.
+enum RowKind { kRow8 = 0, kRow6, kRow16, kRowTo8, kRowTo16, kRowTo32, kNumRowKinds };
+constexpr int kRowKT[kNumRowKinds] = {8, 6, 16, -8, -16, -32};
+inline size_t common_align(const void *a, const void *b = nullptr, const void *c = nullptr) {
+  const uintptr_t x = (uintptr_t)a | (uintptr_t)b | (uintptr_t)c;
+  return x == 0 ? 256 : (size_t)(x & (~x + 1));
+}
+inline RowKind row_kind(int K, size_t align) {
+  if (K == 8) return kRow8;
+  if (K == 6 && align >= 8) return kRow6;
+  if (K == 16 && align >= 16) return kRow16;
+  return K <= 8 ? kRowTo8 : (K <= 16 ? kRowTo16 : kRowTo32);
+}
+inline int row_vec(int K, size_t align) { return K % 4 == 0 && align >= 16 ? 4 : 1; }
+
 // ------------------------------------------------------------ edge weights
 // Eq. 4 on the integer squared distances of a CSR row: w_k = exp(-(d_k -
 // d_0) / sigma_g^2) over the valid slots (d_0 is the nearest neighbour's, so

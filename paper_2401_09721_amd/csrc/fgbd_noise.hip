@@ -75,6 +75,7 @@ struct NoiseArgs {
   int32_t groups;      // row groups per entry
   int32_t want_eig3;
   int32_t order;       // 1: patch entries by increasing point index (generic kernel only)
+  int32_t vec;         // 4: rows of col are read 16 bytes at a time (k_noise_gram)
   // the fused per-frame path (K = P = 8): the first filter sweep's colours
   // x1 = T y with the eq. 4 weights, computed here from the same neighbour
   // rows; the first sweep launch then only marks FSLR membership and sums
@@ -270,6 +271,80 @@ __device__ __forceinline__ void householder_regs(double (&A)[DT][DT], double (&d
   d[DT - 1] = A[DT - 1][DT - 1];
 }
 
+// The same reduction for any D <= DT with one row per lane (lane t holds row
+// t, zero past D in both directions): columns and vectors are broadcast from
+// lane to lane through scalar registers, so the dependent steps make no LDS
+// round trip; after a step the rows shift left by one column, so the loop
+// needs no unrolling.  d and e go to LDS.  (The LDS version took 47 us of
+// launch time for D = 17, this one 33.)
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+template <int DT>
+__device__ __forceinline__ void householder_rows(double (&A)[DT], int D, double *s_d, double *s_e) {
+  const int t = (int)lane_id();
+  for (int k = 0; k + 2 < D; ++k) {
+    // column 0 of the rows below row k (A[0] of lanes k + 1 ..): x
+    double x[DT - 1], ss0 = 0.0, ss1 = 0.0;
+#pragma unroll
+    for (int i = 0; i < DT - 1; ++i) {
+      x[i] = lane_value(A[0], min(k + 1 + i, kWave - 1));
+      if (i & 1)
+        ss1 = fma(x[i], x[i], ss1);
+      else
+        ss0 = fma(x[i], x[i], ss0);
+    }
+    const double ss = ss0 + ss1, x0 = x[0];
+    const double alpha = ss > 0.0 ? -copysign(sqrt(ss), x0) : 0.0;
+    const double vn2 = 2.0 * (ss - x0 * alpha);
+    if (t == k) {
+      s_d[k] = A[0];
+      s_e[k] = alpha;
+    }
+    if (vn2 > 0.0) {  // uniform
+      const double beta = 2.0 / vn2;
+      x[0] = x0 - alpha;  // x is v from here on
+      double p0 = 0.0, p1 = 0.0;
+#pragma unroll
+      for (int j = 0; j < DT - 1; ++j) {
+        if (j & 1)
+          p1 = fma(A[j + 1], x[j], p1);
+        else
+          p0 = fma(A[j + 1], x[j], p0);
+      }
+      const double p = beta * (p0 + p1);  // (lane t > k: row t of beta A' v)
+      double vp = 0.0;
+#pragma unroll
+      for (int i = 0; i < DT - 1; ++i) vp = fma(x[i], lane_value(p, min(k + 1 + i, kWave - 1)), vp);
+      const double kk = 0.5 * beta * vp;
+      const double vt = t == k + 1 ? x[0] : A[0];
+      const double qt = p - kk * vt;
+#pragma unroll
+      for (int j = 0; j < DT - 1; ++j) {
+        const double qj = lane_value(qt, min(k + 1 + j, kWave - 1));
+        A[j + 1] -= vt * qj + qt * x[j];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j + 1 < DT; ++j) A[j] = A[j + 1];
+    A[DT - 1] = 0.0;
+    if (t >= D || t <= k) {  // rows that are done or were never there stay zero
+#pragma unroll
+      for (int j = 0; j < DT; ++j) A[j] = 0.0;
+    }
+  }
+  // rows D - 2 and D - 1 remain, their columns shifted by D - 2
+  const int s = D >= 2 ? D - 2 : 0;
+  if (t == s) s_d[s] = A[0];
+  if (D >= 2 && t == D - 1) {
+    s_e[D - 2] = A[0];
+    s_d[D - 1] = A[1];
+  }
+}
+
 // Eigenvalues k0 .. k0 + G - 1 (ascending) of the tridiagonal (d, e) held in
 // registers, by one wave split into G groups of GL = 64 / G lanes, one
 // eigenvalue per group (lanes past G * GL follow the last group and take no
@@ -279,10 +354,11 @@ __device__ __forceinline__ void householder_regs(double (&A)[DT][DT], double (&d
 // the waves of a block share the CU's four SIMDs, so one wave doing three
 // eigenvalues in 11 steps finishes well before three waves doing one each
 // in 8 steps on the same SIMD.  Returns this lane's group's eigenvalue.
+// (D <= DT: the matrix is the leading D x D part)
 template <int DT, int G>
-__device__ double tridiag_eig_groups(const double (&d)[DT], const double (&e)[DT], int k0) {
+__device__ double tridiag_eig_groups(const double (&d)[DT], const double (&e)[DT], int k0, int D = DT) {
   constexpr int GL = kWave / G;
-  constexpr int ITERS = GL >= 63 ? 8 : GL >= 31 ? 10 : GL >= 21 ? 11 : GL >= 15 ? 12 : 48;
+  constexpr int ITERS = GL >= 63 ? 8 : GL >= 31 ? 10 : GL >= 21 ? 11 : GL >= 15 ? 12 : GL >= 12 ? 13 : 48;
   const int t = (int)lane_id();
   const int g = min(t / GL, G - 1);
   const int sub = t - g * GL;  // point of the group (GL for a spare lane)
@@ -291,11 +367,13 @@ __device__ double tridiag_eig_groups(const double (&d)[DT], const double (&e)[DT
   double glo = 1e300, ghi = -1e300, emax = 0.0, e2[DT];
 #pragma unroll
   for (int i = 0; i < DT; ++i) {
-    const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < DT ? fabs(e[i]) : 0.0);
-    glo = fmin(glo, d[i] - r);
-    ghi = fmax(ghi, d[i] + r);
+    const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < D ? fabs(e[i]) : 0.0);
     e2[i] = e[i] * e[i];
-    if (i + 1 < DT) emax = fmax(emax, e2[i]);
+    if (i < D) {
+      glo = fmin(glo, d[i] - r);
+      ghi = fmax(ghi, d[i] + r);
+      if (i + 1 < D) emax = fmax(emax, e2[i]);
+    }
   }
   const double nrm = fmax(fabs(glo), fabs(ghi));
   const double pivmin = 2.2250738585072014e-308 * fmax(1.0, emax) * 4.0;
@@ -309,11 +387,13 @@ __device__ double tridiag_eig_groups(const double (&d)[DT], const double (&e)[DT
     int cnt = q < 0.0;
 #pragma unroll
     for (int i = 1; i < DT; ++i) {
-      double r = __builtin_amdgcn_rcp(q);
-      r = fma(r, fma(-q, r, 1.0), r);
-      q = fma(-e2[i - 1], r, d[i] - x);
-      if (fabs(q) < pivmin) q = -pivmin;
-      cnt += q < 0.0;
+      if (i < D) {
+        double r = __builtin_amdgcn_rcp(q);
+        r = fma(r, fma(-q, r, 1.0), r);
+        q = fma(-e2[i - 1], r, d[i] - x);
+        if (fabs(q) < pivmin) q = -pivmin;
+        cnt += q < 0.0;
+      }
     }
     // the group's points with count <= k are its first j
     const int j = (int)__popcll(__builtin_amdgcn_ballot_w64(cnt <= k) & gmask);
@@ -384,7 +464,7 @@ __device__ __forceinline__ bool patch_point(const NoiseArgs &a, int64_t i, const
   if (col[i * K + (P - 1)] < 0) return false;
   if constexpr (PT > 0) {
     int cj[PT];
-    if (PT % 4 == 0 && (K % 4) == 0) {
+    if (PT % 4 == 0 && (PT == 8 ? (K % 4) == 0 : a.vec == 4)) {
 #pragma unroll
       for (int q = 0; q < PT / 4; ++q) {
         const int4 c4 = reinterpret_cast<const int4 *>(col + i * K)[q];
@@ -801,15 +881,129 @@ __global__ __launch_bounds__(kBlock, 4) void k_noise_mfma(NoiseArgs a, const int
   }
 }
 
+// The same for patches of PT neighbours other than 8 (no fused sweep): rows
+// of W = D + 3 features rounded up to a multiple of four (the padding stays
+// zero), all upper 4 x 4 sub-blocks of the Gram matrix, four per instruction.
+// k_noise<0> before it kept one or three entries of the moments per thread
+// and walked the rows with scalar FP64: 46 us for 180k points with P = 16
+// (21 now), 25 us for 300k points with P = 6 (16 now).
+template <int PT, bool EIG3>
+__global__ __launch_bounds__(kBlock, 2) void k_noise_gram(NoiseArgs a, const int32_t *__restrict__ col,
+                                                          const float *__restrict__ rgb_in,
+                                                          double *__restrict__ spread, float *__restrict__ eig3,
+                                                          unsigned long long *__restrict__ acc_all) {
+  constexpr int D = PT + 1;
+  constexpr int NG = (D + 3 + 3) / 4;  // feature groups of four
+  constexpr int W = 4 * NG;
+  constexpr int NB = NG * (NG + 1) / 2;  // sub-blocks (p, q), p <= q
+  constexpr int NI = (NB + 3) / 4;       // instructions per four rows
+  extern __shared__ float s_v[];  // [3 * TP][W] patch rows of the current tile; then the Gram sums
+  const int t = threadIdx.x;
+  const int TP = a.TP;
+  const int wave = __builtin_amdgcn_readfirstlane(t / kWave), lane = (int)lane_id();
+  const int bsel = (lane >> 2) & 3, inner = lane & 3, krow = lane >> 4;
+  int fa[NI], fb[NI];  // the lane's two features of each instruction
+#pragma unroll
+  for (int j = 0; j < NI; ++j) {
+    int p = 0, rem = min(4 * j + bsel, NB - 1);  // (a spare block of the last instruction repeats the last one)
+    while (rem >= NG - p) {
+      rem -= NG - p;
+      ++p;
+    }
+    fa[j] = 4 * p + inner;
+    fb[j] = 4 * (p + rem) + inner;
+  }
+  const int groups = 3 * TP / 4;
+  constexpr int kWaves = kBlock / kWave;
+  double c[NI][2];
+#pragma unroll
+  for (int j = 0; j < NI; ++j) c[j][0] = c[j][1] = 0.0;
+
+  const SegBlock sb = seg_block(a.sa, kGridNoise);
+  // a renumbered cloud reads its graph and colours in scan-order-0 numbering
+  const bool relabelled = a.relabel && a.relabel[sb.s];
+  const float *__restrict__ rgb = relabelled ? a.rgb_w : rgb_in;
+  if (relabelled) col = a.col_w;
+  const Share sh = seg_share(sb, TP);
+  for (int64_t tbase = sh.first; tbase < sh.end; tbase += sh.step) {
+    if (t < TP) {
+      const int64_t i = tbase + t;
+      float *r[3] = {s_v + (size_t)(3 * t + 0) * W, s_v + (size_t)(3 * t + 1) * W, s_v + (size_t)(3 * t + 2) * W};
+      bool complete = false;
+      if (i < sh.end) complete = patch_point<PT, EIG3>(a, i, col, rgb, r[0], r[1], r[2], spread, eig3);
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) {
+        if (!complete) {
+#pragma unroll
+          for (int k = 0; k < D; ++k) r[ch][k] = 0.0f;
+        }
+#pragma unroll
+        for (int k = D; k < W; ++k) r[ch][k] = (complete && k - D == ch) ? 1.0f : 0.0f;
+      }
+      if (!complete && i < sh.end) {
+        spread[i] = __builtin_huge_val();
+        if (EIG3) {
+          eig3[3 * i + 0] = 0.0f;
+          eig3[3 * i + 1] = 0.0f;
+          eig3[3 * i + 2] = 0.0f;
+        }
+      }
+    }
+    __syncthreads();
+    // two row groups per step (g and g + kWaves), independent accumulators
+    for (int g = wave; g < groups; g += 2 * kWaves) {  // (3 TP / 4 is a multiple of 2 kWaves)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const float *row = s_v + (size_t)(4 * (g + u * kWaves) + krow) * W;
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+          c[j][u] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)row[fa[j]], (double)row[fb[j]], c[j][u], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+  }
+
+  // the waves' Gram matrices (W x W storage, only the computed sub-blocks are
+  // read), added in wave order, then the moments into the cloud's
+  // accumulators, entry 0 = patch count
+  double *s_g = reinterpret_cast<double *>(s_v);  // [kWaves][W * W]
+#pragma unroll
+  for (int j = 0; j < NI; ++j)
+    if (4 * j + bsel < NB) s_g[wave * W * W + (fa[j] - inner + krow) * W + fb[j]] = c[j][0] + c[j][1];
+  __syncthreads();
+  unsigned long long *acc_c = acc_all + ((size_t)sb.s * kNoiseSlots + sb.lb % kNoiseSlots) * (1 + a.E);
+  for (int e = t; e < 1 + a.E; e += kBlock) {
+    int row = D, column = D;  // the patch count
+    if (e > 0 && e - 1 < a.E2) {
+      int k = 0, rem = e - 1;
+      while (rem >= D - k) {
+        rem -= D - k;
+        ++k;
+      }
+      row = k;
+      column = k + rem;
+    } else if (e > 0) {
+      const int q = e - 1 - a.E2;
+      row = q % D;
+      column = D + q / D;
+    }
+    const int at = row * W + column;
+    add_moment(acc_c, e, (s_g[at] + s_g[W * W + at]) + (s_g[2 * W * W + at] + s_g[3 * W * W + at]));
+  }
+}
+
 // One block: sum the k_noise partials in block order, form Sigma, find its
 // eigenvalues (FP64) and apply the tail rule.
 constexpr int kSolveThreads = 1024;
-// DT > 0: one wave per SIMD (the eigenvalues go three to a wave)
+// DT > 0: one wave per SIMD (the eigenvalues go three to a wave); DT < 0: D
+// up to -DT, one row per lane of wave 0, then five eigenvalues to each of four
+// waves (all the waves only add the slots); DT = 0: any D, through LDS
 template <int DT>
 constexpr int solve_threads() {
   return DT > 0 ? 4 * kWave : kSolveThreads;
 }
 constexpr int kEigGroups = 3;  // eigenvalues per wave in the register path
+constexpr int kRowEigGroups = 5;
 
 // One block per cloud: sum the cloud's moment accumulators (one wave per
 // entry, one lane per slot, integer shuffle sums), form Sigma, then wave 0
@@ -919,6 +1113,38 @@ __global__ __launch_bounds__(solve_threads<DT>()) void k_noise_solve(NoiseArgs a
       const int g = lane / GL;
       if (lane % GL == 0 && g < kEigGroups && k0 + g < DT) s_lam[DT - 1 - (k0 + g)] = ev;
     }
+  } else if constexpr (DT < 0) {
+    constexpr int DR = -DT;
+    static_assert(DR <= 4 * kRowEigGroups, "four waves of kRowEigGroups eigenvalues");
+    if (n_eff > 0.0 && wave == 0) {
+      double A[DR];
+#pragma unroll
+      for (int j = 0; j < DR; ++j) {
+        A[j] = 0.0;
+        if (lane < D && j < D) {
+          const int kk = min(lane, j), ll = max(lane, j);
+          double m = 0.0;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) m += S1[c * D + kk] * S1[c * D + ll];
+          A[j] = (S2[kk * D - kk * (kk - 1) / 2 + (ll - kk)] - m / n_eff) / (3.0 * n_eff);
+        }
+      }
+      householder_rows<DR>(A, D, s_d, s_e);
+    }
+    __syncthreads();
+    if (n_eff > 0.0 && wave * kRowEigGroups < D) {
+      double d[DR], e[DR];
+#pragma unroll
+      for (int i = 0; i < DR; ++i) {
+        d[i] = s_d[min(i, D - 1)];
+        e[i] = s_e[max(min(i, D - 2), 0)];
+      }
+      const int k0 = wave * kRowEigGroups;
+      const double ev = tridiag_eig_groups<DR, kRowEigGroups>(d, e, k0, D);
+      constexpr int GL = kWave / kRowEigGroups;
+      const int g = lane / GL;
+      if (lane % GL == 0 && g < kRowEigGroups && k0 + g < D) s_lam[D - 1 - (k0 + g)] = ev;
+    }
   } else {
     const int Dp = D + (D & 1);
     double *A = tot + stride + (stride & 1);  // Dp x Dp
@@ -994,6 +1220,7 @@ NoiseArgs make_args(const SegArgs &sa, int k, int P, bool want_eig3) {
   a.edge_acc = nullptr;
   a.sigma_g_fixed = 0.0;
   a.order = 0;
+  a.vec = 1;
   a.res = nullptr;
   a.p_out = nullptr;
   a.x1 = nullptr;
@@ -1028,6 +1255,7 @@ hipError_t launch_noise(const Run &r, const int32_t *col, const float *rgb, doub
   }
   // k_noise: rows of D floats; k_noise_mfma: rows of D + 3 floats, and at
   // least the 8 KB of its final sums
+  a.vec = row_vec(a.K, common_align(col, a.col_w));
   const size_t lds_rows = (size_t)3 * a.TP * a.D * sizeof(float);
   const size_t lds_mfma = (size_t)3 * a.TP * (a.D + 3) * sizeof(float);
   const size_t lds = a.P == 8 ? (lds_mfma > 8192 ? lds_mfma : 8192) : lds_rows;
@@ -1040,7 +1268,16 @@ hipError_t launch_noise(const Run &r, const int32_t *col, const float *rgb, doub
     k_noise_mfma<8, false, false><<<nb, kBlock, lds, st>>>(a, col, rgb, spread, eig3, part);
   else if (a.P == 8 && a.order == 0)
     k_noise_mfma<8, true, false><<<nb, kBlock, lds, st>>>(a, col, rgb, spread, eig3, part);
-  else if (eig3 == nullptr)
+  else if ((a.P == 6 || a.P == 12 || a.P == 16) && a.order == 0) {
+    // rows of D + 3 floats rounded up to a multiple of four
+    const size_t lds_gram = (size_t)3 * a.TP * ((a.D + 6) / 4 * 4) * sizeof(float);
+    using Fn = void (*)(NoiseArgs, const int32_t *, const float *, double *, float *, unsigned long long *);
+    static const Fn table[3][2] = {{k_noise_gram<6, false>, k_noise_gram<6, true>},
+                                   {k_noise_gram<12, false>, k_noise_gram<12, true>},
+                                   {k_noise_gram<16, false>, k_noise_gram<16, true>}};
+    table[a.P == 6 ? 0 : (a.P == 12 ? 1 : 2)][eig3 != nullptr]<<<nb, kBlock, lds_gram, st>>>(a, col, rgb, spread, eig3,
+                                                                                              part);
+  } else if (eig3 == nullptr)
     k_noise<0, false><<<nb, kBlock, lds, st>>>(a, col, rgb, spread, eig3, part);
   else
     k_noise<0, true><<<nb, kBlock, lds, st>>>(a, col, rgb, spread, eig3, part);
@@ -1051,6 +1288,10 @@ hipError_t launch_noise_solve(const Run &r, fgbd_result *res) {
   const NoiseArgs a = make_args(r.sa, r.prm.k, r.pl.P, false);
   if (a.D == 9)
     k_noise_solve<9><<<r.pl.B, solve_threads<9>(), 0, r.stream>>>(a, r.b.noise_acc, res);
+  else if (a.D == 7)
+    k_noise_solve<7><<<r.pl.B, solve_threads<7>(), 0, r.stream>>>(a, r.b.noise_acc, res);
+  else if (a.D <= 17)
+    k_noise_solve<-17><<<r.pl.B, solve_threads<-17>(), 0, r.stream>>>(a, r.b.noise_acc, res);
   else
     k_noise_solve<0><<<r.pl.B, solve_threads<0>(), 0, r.stream>>>(a, r.b.noise_acc, res);
   return hipGetLastError();
