@@ -138,7 +138,7 @@ Plan make_plan(int64_t n_cap, int B, const fgbd_params &p, const Tune &tune) {
     int64_t g = units < 1 ? 1 : (units < cap ? units : cap);
     return (int32_t)(g < B ? B : g);
   };
-  pl.grid[kGridMerge] = grid_for((n_cap + kBlock - 1) / kBlock, tune.cap[kGridMerge]);
+  pl.grid[kGridMerge] = grid_for((n_cap * merge_lanes(n_cap, p) + kBlock - 1) / kBlock, tune.cap[kGridMerge]);
   pl.grid[kGridSweep] = grid_for((n_cap + kBlock - 1) / kBlock, tune.cap[kGridSweep]);
   pl.grid[kGridNoise] = grid_for((n_cap + pl.TP - 1) / pl.TP, tune.cap[kGridNoise]);
   pl.E1 = 1 + pl.D * (pl.D + 1) / 2 + 3 * pl.D;

@@ -151,13 +151,15 @@ __device__ __forceinline__ void load_window(const uint64_t *__restrict__ srt, in
   }
 }
 
-constexpr uint32_t kKeyD2Max = 127;  // squared-distance field of the 31-bit keys
+constexpr int kKeyIndexBits = 24;    // most index bits of the 31-bit keys (clouds of up to 2^24 points)
+constexpr uint32_t kSqrtMax = 127;   // edge lengths up to its root come from a table
 
 struct MergeArgs {
   DirTable dt;
   SegArgs sa;
   int64_t stride;  // items per direction (capacity)
   int32_t window, K;
+  int32_t wide_rows;  // col and dist2 are aligned for 16-byte stores
 };
 
 // Exact (64-bit key) selection for one point, runtime window over positions
@@ -183,6 +185,84 @@ __device__ void select_exact(const MergeArgs &a, int i, int lo, int hi, int wind
   }
 }
 
+// Exact selection with a compile-time window on keys (d2 << 32 | index) held
+// as doubles: positive doubles order as their bits do (d2 stays far below the
+// exponent of infinity), and FP64 minimum and maximum are single full-width
+// instructions, where a 64-bit integer exchange takes five.  Denormal keys
+// (d2 below 2^20) pass through unchanged; the instructions are written out so
+// that the compiler adds no quieting of its own.
+__device__ __forceinline__ double min_f64(double a, double b) {
+  double d;
+  asm("v_min_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ double max_f64(double a, double b) {
+  double d;
+  asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ double key_f64(uint32_t hi, uint32_t lo) {
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+constexpr uint64_t kNoKey = 0x7fefffffffffffffull;  // the largest finite double: an empty slot
+// The candidate goes down the sorted list, each slot keeping the smaller;
+// one equal to a slot, or past every lane's last slot, changes nothing.
+template <int KM>
+__device__ __forceinline__ void insert_f64(double (&lst)[KM], double c) {
+  if (__builtin_amdgcn_ballot_w64(c < lst[KM - 1]) == 0) return;  // uniform
+  bool dup = false;
+#pragma unroll
+  for (int k = 0; k < KM; ++k) dup |= lst[k] == c;
+  c = dup ? __builtin_bit_cast(double, kNoKey) : c;
+#pragma unroll
+  for (int k = 0; k < KM; ++k) {
+    const double l = lst[k];
+    lst[k] = min_f64(l, c);
+    c = max_f64(l, c);
+  }
+}
+// Every direction's window is one batch of loads, as in k_merge.  Used where
+// the 31-bit keys would not do: clouds of more than 2^24 points, a kept
+// distance past their field (redone one candidate at a time, the few waves
+// that hold one held up the whole launch: 115 us for 180k points with K = 16
+// in 12 directions, 47 with this and the wider field), and rows that keep
+// every candidate, line wraps among them (the paper's graph on 300k points:
+// 25 -> 17 us).
+template <int KM, int WT>
+__device__ __forceinline__ void select_f64(const MergeArgs &a, int i, int lo, int hi,
+                                           const uint64_t *__restrict__ sorted, const uint32_t *__restrict__ rank,
+                                           uint64_t (&out)[KM]) {
+  double lst[KM];
+#pragma unroll
+  for (int k = 0; k < KM; ++k) lst[k] = __builtin_bit_cast(double, kNoKey);
+  constexpr int G = WT == 1 ? 4 : (WT == 2 ? 2 : 1);  // directions whose loads are in flight together
+  const int L = a.dt.num_dirs;
+  for (int d0 = 0; d0 < L; d0 += G) {
+    int r[G];
+    uint64_t w[G][2 * WT + 1];
+#pragma unroll
+    for (int g = 0; g < G; ++g) r[g] = (int)rank[(size_t)min(d0 + g, L - 1) * a.stride + i];
+#pragma unroll
+    for (int g = 0; g < G; ++g) load_window<WT>(sorted + (size_t)min(d0 + g, L - 1) * a.stride, r[g], lo, hi, w[g]);
+    const Pt pi = unpack_pt((uint32_t)(w[0][WT] >> 32), a.dt.bits);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (d0 + g >= L) break;  // uniform
+#pragma unroll
+      for (int s = 0; s <= 2 * WT; ++s) {
+        if (s == WT) continue;
+        const uint32_t d2 = pt_dist2(pi, (uint32_t)(w[g][s] >> 32), a.dt.bits);
+        insert_f64<KM>(lst, w[g][s] == ~0ull ? __builtin_bit_cast(double, kNoKey) : key_f64(d2, (uint32_t)w[g][s]));
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < KM; ++k) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, lst[k]);
+    out[k] = u == kNoKey ? ~0ull : u;
+  }
+}
+
 // One thread per point.  WT > 0 (compile-time window, clouds of at most 2^24
 // points; a block of a larger cloud takes the 64-bit selection): the
 // point's ranks in all directions go to LDS in one batch of loads; each
@@ -190,13 +270,19 @@ __device__ void select_exact(const MergeArgs &a, int i, int lo, int hi, int wind
 // then loaded as one batch and consumed (prefetching the next direction's
 // window would raise the register count from 83 to 109 and the occupancy from
 // six to four waves per SIMD, which measured slower); candidates are 31-bit
-// keys (min(d2, 127) << 24 | j - cloud start), exact whenever no kept entry has a clamped
+// keys (min(d2, max) << index bits | j - cloud start), exact whenever no kept entry has a clamped
 // distance, else the point is redone with 64-bit keys.  With w = 4 each
 // direction's 8 candidates are first sorted by a network: the first
 // direction's (distinct points, empty list) are the list, and later ones are
 // inserted in ascending order until no lane of the wave has one left that
 // could enter its list.
-template <int KM, int WT>
+// S > 1 (small clouds): S neighbouring lanes share a point, each selecting
+// from every S-th direction, then exchange their lists (each inserts the
+// other's): a wave's chain of window loads and insertions is S times shorter,
+// which is what a launch of at most two waves per SIMD takes its time for
+// (16k points: 24 us with S = 1, 15 with S = 4; 70k: 27 and 24).
+// ALL64: every point takes the 64-bit selection.
+template <int KM, int WT, int S = 1, bool ALL64 = false>
 __global__ __launch_bounds__(kBlock) void k_merge(MergeArgs a, const uint64_t *__restrict__ sorted,
                                                   const uint32_t *__restrict__ rank, int32_t *__restrict__ col,
                                                   int32_t *__restrict__ dist2,
@@ -205,46 +291,67 @@ __global__ __launch_bounds__(kBlock) void k_merge(MergeArgs a, const uint64_t *_
   __shared__ int s_rank[WT > 0 ? kMaxDirs : 1][kBlock];
   // edge lengths sqrt(d2) of the small squared distances, each computed once
   // per block (the same correctly rounded values as computing them inline)
-  __shared__ double s_sqrt[kKeyD2Max + 1];
+  __shared__ double s_sqrt[kSqrtMax + 1];
   double acc[3] = {0.0, 0.0, 0.0};  // edge lengths, edges, far edges
   const int L = a.dt.num_dirs;
   const int K = a.K;
   const int bits = a.dt.bits;
   const int t = threadIdx.x;
-  for (int v = t; v <= (int)kKeyD2Max; v += kBlock) s_sqrt[v] = sqrt((double)v);
+  for (int v = t; v <= (int)kSqrtMax; v += kBlock) s_sqrt[v] = sqrt((double)v);
   const SegBlock sb = seg_block(a.sa, kGridMerge);
   const int lo = (int)sb.begin, hi = (int)sb.end - 1;
-  // the 31-bit keys hold a cloud-local index in 24 bits: a cloud of 2^24 or
-  // more points takes the 64-bit selection (uniform over the block)
-  const bool fast = sb.end - sb.begin <= (int64_t)(1 << 24);
+  // the 31-bit keys hold a cloud-local index in up to 24 bits: a cloud of more
+  // than 2^24 points takes the 64-bit selection (uniform over the block)
+  const bool fast = sb.end - sb.begin <= (int64_t)(1 << kKeyIndexBits);
+  // the index takes as many bits as the cloud needs and the squared distance
+  // the rest (7 bits for 2^24 points, 11 for 2^20), so that few rows hold a
+  // distance that does not fit
+  const int ib = max(1, 32 - __clz((int)min(sb.end - sb.begin, (int64_t)(1 << kKeyIndexBits)) - 1));
+  const uint32_t d2_max = (1u << (31 - ib)) - 1u;
   const uint32_t gap = (uint32_t)far_gap(sb.end - sb.begin);  // an edge spanning more indices is far
   __syncthreads();
-  const Share sh = seg_share(sb, kBlock);
+  const Share sh = seg_share(sb, kBlock / S);
+  const int sub = S > 1 ? t % S : 0;
   for (int64_t base = sh.first; base < sh.end; base += sh.step) {
-    const int i = (int)(base + t);
+    const int i = (int)(base + t / S);
     if (i >= sh.end) continue;
     uint64_t lst[KM];
-    if (WT > 0 && !fast) {
-      select_exact<KM>(a, i, lo, hi, a.window, sorted, rank, lst);
+    if constexpr (ALL64) {
+      select_f64<KM, WT>(a, i, lo, hi, sorted, rank, lst);
+    } else if (WT > 0 && !fast) {
+      if constexpr (WT > 0) select_f64<KM, WT>(a, i, lo, hi, sorted, rank, lst);
     } else if constexpr (WT > 0) {
       // the first 8 directions' ranks load unconditionally (a direction
       // index past L - 1 re-reads the last one) so all loads are in flight
       // together; a conditional load per direction would be waited for
       // before the next is issued
       int rv[8];
+      if constexpr (S == 1) {
 #pragma unroll
-      for (int d = 0; d < 8; ++d) rv[d] = (int)rank[(size_t)min(d, L - 1) * a.stride + i];
+        for (int d = 0; d < 8; ++d) rv[d] = (int)rank[(size_t)min(d, L - 1) * a.stride + i];
 #pragma unroll
-      for (int d = 0; d < 8; ++d) s_rank[d][t] = rv[d];
-      for (int d = 8; d < L; ++d) s_rank[d][t] = (int)rank[(size_t)d * a.stride + i];
+        for (int d = 0; d < 8; ++d) s_rank[d][t] = rv[d];
+        for (int d = 8; d < L; ++d) s_rank[d][t] = (int)rank[(size_t)d * a.stride + i];
+      } else {  // the lane's own directions, sub, sub + S, ...
+        constexpr int U = (kMaxDirs + S - 1) / S;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int v = (int)rank[(size_t)min(u * S + sub, L - 1) * a.stride + i];
+          s_rank[u][t] = v;
+          if (u == 0) rv[0] = v;
+        }
+      }
       uint32_t key[KM];
 #pragma unroll
       for (int k = 0; k < KM; ++k) key[k] = ~0u;
       // the point's own packed coordinates (the same item in every order)
-      const Pt pi = unpack_pt((uint32_t)(sorted[rv[0]] >> 32), bits);
-      for (int d = 0; d < L; ++d) {
+      const Pt pi = unpack_pt((uint32_t)(sorted[(size_t)(S > 1 ? min(sub, L - 1) : 0) * a.stride + rv[0]] >> 32), bits);
+      for (int d0 = 0; d0 < L; d0 += S) {
+        // (with S > 1, a lane past the last direction repeats that one: its
+        // candidates are in the list already)
+        const int d = S > 1 ? min(d0 + sub, L - 1) : d0;
         const uint64_t *srt = sorted + (size_t)d * a.stride;
-        const int r = s_rank[d][t];
+        const int r = s_rank[S > 1 ? d0 / S : d][t];
         uint64_t cur[2 * WT + 1];
         uint32_t kc[2 * WT];
         // Wave-uniform: when every window of the wave lies inside the
@@ -259,7 +366,7 @@ __global__ __launch_bounds__(kBlock) void k_merge(MergeArgs a, const uint64_t *_
           for (int s = 0; s < 2 * WT; ++s) {
             const uint64_t it = cur[s < WT ? s : s + 1];
             const uint32_t d2 = pt_dist2(pi, (uint32_t)(it >> 32), bits);
-            kc[s] = (min(d2, kKeyD2Max) << 24) | ((uint32_t)it - (uint32_t)lo);
+            kc[s] = (min(d2, d2_max) << ib) | ((uint32_t)it - (uint32_t)lo);
           }
         } else {
           load_window<WT>(srt, r, lo, hi, cur);
@@ -267,12 +374,12 @@ __global__ __launch_bounds__(kBlock) void k_merge(MergeArgs a, const uint64_t *_
           for (int s = 0; s < 2 * WT; ++s) {
             const uint64_t it = cur[s < WT ? s : s + 1];
             const uint32_t d2 = pt_dist2(pi, (uint32_t)(it >> 32), bits);
-            kc[s] = it == ~0ull ? ~0u : ((min(d2, kKeyD2Max) << 24) | ((uint32_t)it - (uint32_t)lo));
+            kc[s] = it == ~0ull ? ~0u : ((min(d2, d2_max) << ib) | ((uint32_t)it - (uint32_t)lo));
           }
         }
         if constexpr (WT == 4) {
           sort8(kc);
-          if (d == 0) {
+          if (d0 == 0) {
 #pragma unroll
             for (int k = 0; k < 8 && k < KM; ++k) key[k] = kc[k];
             continue;
@@ -290,15 +397,28 @@ __global__ __launch_bounds__(kBlock) void k_merge(MergeArgs a, const uint64_t *_
           for (int s = 0; s < 2 * WT; ++s) topk_insert_minmax<KM>(key, kc[s]);
         }
       }
+      if constexpr (S > 1) {  // the lists of the point's other lanes
+#pragma unroll
+        for (int o = 1; o < S; o <<= 1) {
+          uint32_t other[KM];
+#pragma unroll
+          for (int k = 0; k < KM; ++k) other[k] = (uint32_t)__shfl_xor((int)key[k], o, kWave);
+#pragma unroll
+          for (int k = 0; k < KM; ++k) {
+            if (__builtin_amdgcn_ballot_w64(other[k] < key[KM - 1]) == 0) break;
+            topk_insert_med3<KM>(key, other[k]);
+          }
+        }
+      }
       bool clamped = false;
 #pragma unroll
-      for (int k = 0; k < KM; ++k) clamped |= (k < K) & (key[k] != ~0u) & ((key[k] >> 24) == kKeyD2Max);
+      for (int k = 0; k < KM; ++k) clamped |= (k < K) & (key[k] != ~0u) & ((key[k] >> ib) == d2_max);
       if (clamped) {
-        select_exact<KM>(a, i, lo, hi, WT, sorted, rank, lst);
+        select_f64<KM, WT>(a, i, lo, hi, sorted, rank, lst);
       } else {
 #pragma unroll
         for (int k = 0; k < KM; ++k)
-          lst[k] = key[k] == ~0u ? ~0ull : ((uint64_t)(key[k] >> 24) << 32) | ((key[k] & 0xffffffu) + (uint32_t)lo);
+          lst[k] = key[k] == ~0u ? ~0ull : ((uint64_t)(key[k] >> ib) << 32) | ((key[k] & ((1u << ib) - 1u)) + (uint32_t)lo);
       }
     } else {
       select_exact<KM>(a, i, lo, hi, a.window, sorted, rank, lst);
@@ -311,13 +431,39 @@ __global__ __launch_bounds__(kBlock) void k_merge(MergeArgs a, const uint64_t *_
       cv[k] = ok ? (int32_t)(uint32_t)lst[k] : -1;
 
       dv[k] = ok ? (int32_t)d2 : 0;
-      if (ok && k < K) {
-        acc[0] += d2 <= kKeyD2Max ? s_sqrt[d2] : sqrt((double)d2);
+      if (ok && k < K && sub == 0) {
+        acc[0] += d2 <= kSqrtMax ? s_sqrt[d2] : sqrt((double)d2);
         acc[1] += 1.0;
         acc[2] += (uint32_t)abs(cv[k] - i) > gap ? 1.0 : 0.0;
       }
     }
-    if (KM == 8 && K == 8) {
+    if constexpr (KM == 16 && S == 1) {
+      if (K == 16 && a.wide_rows) {
+        store_row<16>(col, (int64_t)i, 16, cv);
+        store_row<16>(dist2, (int64_t)i, 16, dv);
+        continue;
+      }
+    }
+    if (S == 4 && KM == 8 && K == 8) {  // two of the eight slots per lane
+      int c0 = cv[0], c1 = cv[1], e0 = dv[0], e1 = dv[1];
+#pragma unroll
+      for (int q = 1; q < 4; ++q) {
+        c0 = sub == q ? cv[2 * q] : c0;
+        c1 = sub == q ? cv[2 * q + 1] : c1;
+        e0 = sub == q ? dv[2 * q] : e0;
+        e1 = sub == q ? dv[2 * q + 1] : e1;
+      }
+      reinterpret_cast<int2 *>(col + (size_t)i * 8)[sub] = make_int2(c0, c1);
+      reinterpret_cast<int2 *>(dist2 + (size_t)i * 8)[sub] = make_int2(e0, e1);
+    } else if (S > 1) {
+#pragma unroll
+      for (int k = 0; k < KM; ++k) {
+        if (k < K && k % S == sub) {
+          col[(size_t)i * K + k] = cv[k];
+          dist2[(size_t)i * K + k] = dv[k];
+        }
+      }
+    } else if (KM == 8 && K == 8) {
       int4 *cr = reinterpret_cast<int4 *>(col + (size_t)i * 8);
       int4 *dr = reinterpret_cast<int4 *>(dist2 + (size_t)i * 8);
       cr[0] = make_int4(cv[0], cv[1], cv[2], cv[3]);
@@ -541,6 +687,7 @@ hipError_t launch_merge(const Run &r, const int32_t *xyz, const uint64_t *sorted
   a.sa = r.sa;
   a.stride = r.pl.stride;
   a.window = r.prm.window;
+  a.wide_rows = common_align(col, dist2) >= 16;
   a.K = r.prm.k;
   const int k = r.prm.k, window = r.prm.window;
   const int nb = r.pl.grid[kGridMerge];
@@ -557,21 +704,26 @@ hipError_t launch_merge(const Run &r, const int32_t *xyz, const uint64_t *sorted
     return hipGetLastError();
   }
   // the compile-time-window kernels take 64-bit keys for a cloud of more
-  // than 2^24 points (their 31-bit keys hold a cloud-local index)
+  // than 2^24 points (their 31-bit keys hold a cloud-local index); a graph
+  // that keeps every candidate keeps line wraps, whose distances need the
+  // 64-bit keys
+  const bool small = merge_lanes(r.pl.n_cap, r.prm) > 1;
+  const bool keeps_all = 2 * window * r.dt.num_dirs <= k;
+  using Fn = void (*)(MergeArgs, const uint64_t *, const uint32_t *, int32_t *, int32_t *, unsigned long long *);
+  Fn fn = k_merge<32, 0>;
   if (k <= 8 && window == 4)
-    k_merge<8, 4><<<nb, kBlock, 0, st>>>(a, sorted, rank, col, dist2, part);
+    fn = small ? k_merge<8, 4, kMergeLanes> : k_merge<8, 4>;
   else if (k <= 8 && window == 1)
-    k_merge<8, 1><<<nb, kBlock, 0, st>>>(a, sorted, rank, col, dist2, part);
+    fn = keeps_all ? k_merge<8, 1, 1, true> : k_merge<8, 1>;
   else if (k <= 8 && window == 2)
-    k_merge<8, 2><<<nb, kBlock, 0, st>>>(a, sorted, rank, col, dist2, part);
+    fn = keeps_all ? k_merge<8, 2, 1, true> : k_merge<8, 2>;
   else if (k <= 8)
-    k_merge<8, 0><<<nb, kBlock, 0, st>>>(a, sorted, rank, col, dist2, part);
+    fn = k_merge<8, 0>;
   else if (k <= 16 && window == 4)
-    k_merge<16, 4><<<nb, kBlock, 0, st>>>(a, sorted, rank, col, dist2, part);
+    fn = small ? k_merge<16, 4, kMergeLanes> : k_merge<16, 4>;
   else if (k <= 16)
-    k_merge<16, 0><<<nb, kBlock, 0, st>>>(a, sorted, rank, col, dist2, part);
-  else
-    k_merge<32, 0><<<nb, kBlock, 0, st>>>(a, sorted, rank, col, dist2, part);
+    fn = k_merge<16, 0>;
+  fn<<<nb, kBlock, 0, st>>>(a, sorted, rank, col, dist2, part);
   return hipGetLastError();
 }
 

@@ -491,6 +491,17 @@ constexpr int kDefaultMergeGrid = 4096;  // the merge gains from more blocks tha
 constexpr int kDefaultSweepGrid = 512;  // fewer, longer-running sweep blocks: less block start and sum traffic
 constexpr Tune kDefaultTune = {{kDefaultMergeGrid, kMaxGrid, kDefaultSweepGrid}, kDefaultSweepLaunches};
 
+// Lanes of a merge block that share a point (S of k_merge): four for up to
+// 81920 points, where the launch has at most five waves per SIMD even so and
+// is bound by each wave's chain of loads and insertions; more points fill the
+// chip with one lane each, whose lists need no exchange (130k points: 28 us
+// with four lanes, 26.5 with one; 250k: 49 and 27).
+constexpr int kMergeLanes = 4;
+constexpr int64_t kMergeSmall = 81920;
+inline int merge_lanes(int64_t n_cap, const fgbd_params &p) {
+  return n_cap <= kMergeSmall && p.window == 4 && p.k <= 16 && p.bits <= 10 ? kMergeLanes : 1;
+}
+
 Plan make_plan(int64_t n_cap, int B, const fgbd_params &p, const Tune &tune = kDefaultTune);
 
 // Workspace views of a plan.
