@@ -104,7 +104,8 @@ typedef struct {
                          code of the first num_dirs directions fits 63 bits (3b bits for the axis
                          directions, 3b + 1 for (1,1,0)-type diagonals, 3b + 2 for the rest): b <= 20
                          with all 16 directions, b = 21 with the three axis directions.  Codes above
-                         32 bits (b > 10) take more radix passes and a slower neighbour selection. */
+                         32 bits (b > 10) are sorted in more radix passes once the call holds more than
+                         2^(64 - code bits) points, and their neighbour selection is slower. */
   int32_t num_dirs;   /* L: scan directions 1..16; the first three are eqs. 1-3, the rest diagonal
                          lines (Sec. 2.2 mentions them as an alternative)                          */
   int32_t window;     /* w >= 1: candidates are the w predecessors and w successors in each scan
@@ -180,7 +181,7 @@ fgbd_status fgbd_set_workspace(fgbd_ctx ctx, void *dev, size_t bytes);
 
 /* Scan-line graph (Sec. 2.2).  For each of the first L directions, every
  * point gets a scan-line code (eqs. 1-3; the diagonal directions replace two
- * coordinates by line invariants); the codes are sorted by an LSD radix sort
+ * coordinates by line invariants); the codes are sorted by a stable radix sort
  * (equal codes keep index order); the w points before and after each point
  * in every sorted order are its candidates; the first K distinct candidates by
  * (squared distance, index) form its row.  Then sigma_g (params->sigma_g, or

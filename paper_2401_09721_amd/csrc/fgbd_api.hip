@@ -404,7 +404,7 @@ static void sort_policy(fgbd_ctx ctx, hipStream_t s, Run &r) {
 // stops after the merge: the sweeps then derive sigma_g and the weights.
 fgbd_status run_slg(const Run &r, const int32_t *xyz, int32_t *col, int32_t *dist2, float *p, fgbd_result *res,
                     const float *rgb = nullptr) {
-  const uint64_t *sorted = nullptr;
+  Sorted sorted = {nullptr, 0};
   HIP_TRY(launch_sort(r, xyz, res, &sorted), "radix sort launch");
   FGBD_PRE(r.pf, kMerge);
   HIP_TRY(launch_merge(r, xyz, sorted, col, dist2, res), "neighbour merge launch");

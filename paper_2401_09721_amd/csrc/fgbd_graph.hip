@@ -160,6 +160,8 @@ struct MergeArgs {
   int64_t stride;  // items per direction (capacity)
   int32_t window, K;
   int32_t wide_rows;  // col and dist2 are aligned for 16-byte stores
+  int32_t index_bits;   // of the sorted items (see Sorted); the wide kernels only
+  uint64_t index_mask;
 };
 
 // Exact (64-bit key) selection for one point, runtime window over positions
@@ -491,12 +493,196 @@ __global__ __launch_bounds__(kBlock) void k_merge(MergeArgs a, const uint64_t *_
   }
 }
 
-// Selection for grids above 2^10 (codes wider than 32 bits): the sorted items
-// hold only indices, so each candidate's coordinates come from the input;
-// squared distances are 64-bit and the K nearest are kept by (squared
-// distance, index) in a sorted list of pairs.  One thread per point, runtime
-// window.  dist2 saturates at 2^31 - 1 (FGBD_ST_DIST_CLAMPED), which only a
-// neighbour more than 46340 voxels away can reach.
+// Selection for grids above 2^10 (codes wider than 32 bits) with keys
+// (squared distance << index bits | index - cloud start) held as doubles, as
+// in select_f64: a squared distance is below 3/4 of 2^(2b+2), so while
+// 2b + 2 and the cloud's index bits make at most 63 the keys are positive
+// finite doubles.  The candidates' coordinates are packed in the sorted items
+// when the sort could hold them there (PACKED), else gathered from the input;
+// a direction's eight candidates are one batch of loads, sorted by a network,
+// and inserted until no lane's next one can enter.  BIG: squared distances of
+// more than 32 bits (b > 15).  700k points at b = 11: 458 us with the general
+// kernel below, 86 with this (139 with one 8-byte load per item: a capture
+// that is not in raster order touches a line per lane with every load).
+// 31-bit keys as in k_merge, the few points whose distances do not fit them
+// selected again by the whole wave, took 88.
+struct WidePt {
+  int x, y, z;
+};
+template <bool BIG>
+__device__ __forceinline__ uint64_t wide_dist2(const WidePt &p, const WidePt &q) {
+  const int dx = p.x - q.x, dy = p.y - q.y, dz = p.z - q.z;
+  if constexpr (BIG) return (uint64_t)((int64_t)dx * dx + (int64_t)dy * dy + (int64_t)dz * dz);
+  // (below 2^16 in magnitude: the sum is below 2^32)
+  return (uint32_t)mad_i24(dx, dx, mad_i24(dy, dy, __mul24(dz, dz)));
+}
+// The window without its centre.  When every window of the wave lies inside
+// the cloud (uniform; returns true), the items load from one base address,
+// two to a 16-byte load; else each position is clamped into lo..hi.
+template <int WT>
+__device__ __forceinline__ bool load_sides(const uint64_t *__restrict__ srt, int r, int lo, int hi,
+                                           uint64_t (&w)[2 * WT]) {
+  const bool inside = __builtin_amdgcn_ballot_w64(r - WT < lo || r + WT > hi) == 0;
+  if (inside) {
+    const uint64_t *wp = srt + (r - WT);
+#pragma unroll
+    for (int s = 0; s < 2 * WT; ++s) w[s] = wp[s < WT ? s : s + 1];
+  } else {
+#pragma unroll
+    for (int s = 0; s < 2 * WT; ++s) w[s] = srt[min(max(r + (s < WT ? s : s + 1) - WT, lo), hi)];
+  }
+  return inside;
+}
+// Sorts 8 keys ascending (the network of sort8).
+__device__ __forceinline__ void sort8_f64(double (&v)[8]) {
+  constexpr int net[19][2] = {{0, 2}, {1, 3}, {4, 6}, {5, 7}, {0, 4}, {1, 5}, {2, 6}, {3, 7}, {0, 1}, {2, 3},
+                              {4, 5}, {6, 7}, {2, 4}, {3, 5}, {1, 4}, {3, 6}, {1, 2}, {3, 4}, {5, 6}};
+#pragma unroll
+  for (int c = 0; c < 19; ++c) {
+    const double x = v[net[c][0]], y = v[net[c][1]];
+    v[net[c][0]] = min_f64(x, y);
+    v[net[c][1]] = max_f64(x, y);
+  }
+}
+template <int KM, bool PACKED, bool BIG>
+__global__ __launch_bounds__(kBlock) void k_merge_wide4(MergeArgs a, const int32_t *__restrict__ xyz,
+                                                        const uint64_t *__restrict__ sorted,
+                                                        const uint32_t *__restrict__ rank, int32_t *__restrict__ col,
+                                                        int32_t *__restrict__ dist2,
+                                                        unsigned long long *__restrict__ edge_acc,
+                                                        fgbd_result *__restrict__ res) {
+  constexpr int WT = 4;
+  __shared__ double s_red[4 * 3];
+  __shared__ double s_sqrt[kSqrtMax + 1];
+  __shared__ int s_rank[kMaxDirs][kBlock];  // the point's ranks, read in one batch
+  const int t = threadIdx.x;
+  for (int v = t; v <= (int)kSqrtMax; v += kBlock) s_sqrt[v] = sqrt((double)v);
+  __syncthreads();
+  double acc[3] = {0.0, 0.0, 0.0};  // edge lengths, edges, far edges
+  const int L = a.dt.num_dirs, K = a.K, bits = a.dt.bits, ib = a.index_bits;
+  const int top = (1 << bits) - 1;
+  const SegBlock sb = seg_block(a.sa, kGridMerge);
+  const int lo = (int)sb.begin, hi = (int)sb.end - 1;
+  const int kb = 32 - __clz(max((int)(sb.end - sb.begin) - 1, 1));  // index bits of the keys
+  const uint32_t gap = (uint32_t)far_gap(sb.end - sb.begin);
+  auto unpack = [&](uint64_t v) {  // (PACKED items)
+    if constexpr (!BIG) {  // b <= 15: ib + b is at least 32, so y and z lie in the upper word
+      const uint32_t vl = (uint32_t)v, vh = (uint32_t)(v >> 32);
+      return WidePt{(int)(__builtin_amdgcn_alignbit(vh, vl, (uint32_t)ib) & (uint32_t)top),
+                    (int)__builtin_amdgcn_ubfe(vh, (uint32_t)(ib + bits - 32), (uint32_t)bits),
+                    (int)(vh >> (ib + 2 * bits - 32))};
+    }
+    const uint64_t p = v >> ib;
+    return WidePt{(int)((uint32_t)p & (uint32_t)top), (int)((uint32_t)(p >> bits) & (uint32_t)top),
+                  (int)(uint32_t)(p >> (2 * bits))};
+  };
+  auto input = [&](uint32_t j) {
+    return WidePt{xyz[3 * (size_t)j + 0], xyz[3 * (size_t)j + 1], xyz[3 * (size_t)j + 2]};
+  };
+  const double none = __builtin_bit_cast(double, kNoKey);
+  int clamped = 0;
+  const Share sh = seg_share(sb, kBlock);
+  for (int64_t base = sh.first; base < sh.end; base += sh.step) {
+    const int i = (int)(base + threadIdx.x);
+    if (i >= sh.end) continue;
+    double lst[KM];
+#pragma unroll
+    for (int k = 0; k < KM; ++k) lst[k] = none;
+    const WidePt pi = input((uint32_t)i);
+    {
+      int rv[8];
+#pragma unroll
+      for (int d = 0; d < 8; ++d) rv[d] = (int)rank[(size_t)min(d, L - 1) * a.stride + i];
+#pragma unroll
+      for (int d = 0; d < 8; ++d) s_rank[d][t] = rv[d];
+      for (int d = 8; d < L; ++d) s_rank[d][t] = (int)rank[(size_t)d * a.stride + i];
+    }
+    for (int d = 0; d < L; ++d) {
+      const uint64_t *srt = sorted + (size_t)d * a.stride;
+      const int r = s_rank[d][t];
+      uint64_t w[2 * WT];
+      const bool inside = load_sides<WT>(srt, r, lo, hi, w);
+      WidePt q[2 * WT];
+#pragma unroll
+      for (int s = 0; s < 2 * WT; ++s) q[s] = PACKED ? unpack(w[s]) : input((uint32_t)(w[s] & a.index_mask));
+      double c[2 * WT];
+#pragma unroll
+      for (int s = 0; s < 2 * WT; ++s) {
+        const uint32_t j = ((uint32_t)w[s] & (uint32_t)a.index_mask) - (uint32_t)lo;
+        const uint64_t d2 = wide_dist2<BIG>(q[s], pi);
+        // (d2 << kb | j, by halves: kb is 1 to 31)
+        if constexpr (BIG)
+          c[s] = __builtin_bit_cast(double, d2 << kb | j);
+        else
+          c[s] = key_f64((uint32_t)d2 >> (32 - kb), (uint32_t)d2 << kb | j);
+      }
+      if (!inside) {
+        // positions outside the cloud's range are no candidates
+#pragma unroll
+        for (int s = 0; s < 2 * WT; ++s) {
+          const int pos = r + (s < WT ? s : s + 1) - WT;
+          if (pos < lo || pos > hi) c[s] = none;
+        }
+      }
+      sort8_f64(c);
+      if (d == 0) {
+#pragma unroll
+        for (int k = 0; k < 8 && k < KM; ++k) lst[k] = c[k];
+        continue;
+      }
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        if (__builtin_amdgcn_ballot_w64(c[s] < lst[KM - 1]) == 0) break;
+        insert_f64<KM>(lst, c[s]);
+      }
+    }
+    int cv[KM], dv[KM];
+#pragma unroll
+    for (int k = 0; k < KM; ++k) {
+      const uint64_t u = __builtin_bit_cast(uint64_t, lst[k]);
+      const bool ok = u != kNoKey && k < K;
+      const uint64_t d2 = u >> kb;
+      cv[k] = ok ? (int32_t)(((uint32_t)u & ((1u << kb) - 1u)) + (uint32_t)lo) : -1;
+      dv[k] = ok ? (d2 > 0x7fffffffull ? 0x7fffffff : (int32_t)d2) : 0;
+      if (ok) {
+        clamped |= d2 > 0x7fffffffull;
+        acc[0] += d2 <= kSqrtMax ? s_sqrt[d2] : sqrt((double)d2);
+        acc[1] += 1.0;
+        acc[2] += (uint32_t)abs(cv[k] - i) > gap ? 1.0 : 0.0;
+      }
+    }
+    if (K == KM && a.wide_rows) {
+      store_row<KM>(col, (int64_t)i, KM, cv);
+      store_row<KM>(dist2, (int64_t)i, KM, dv);
+    } else {
+#pragma unroll
+      for (int k = 0; k < KM; ++k) {
+        if (k < K) {
+          col[(size_t)i * K + k] = cv[k];
+          dist2[(size_t)i * K + k] = dv[k];
+        }
+      }
+    }
+  }
+  if (__builtin_amdgcn_ballot_w64(clamped != 0) != 0 && lane_id() == 0)
+    atomicOr(&res[sb.s].status, FGBD_ST_DIST_CLAMPED);
+  block_sum_f64<3>(acc, s_red);
+  if (threadIdx.x == 0) {
+    unsigned long long *e = edge_acc + ((size_t)sb.s * kEdgeSlots + sb.lb % kEdgeSlots) * kEdgeVals;
+    const double whole = floor(acc[0]);
+    atomicAdd(&e[0], (unsigned long long)whole);
+    atomicAdd(&e[1], (unsigned long long)llrint((acc[0] - whole) * kEdgeFrac));
+    atomicAdd(&e[2], (unsigned long long)acc[1]);
+    atomicAdd(&e[3], (unsigned long long)acc[2]);
+  }
+}
+
+// The general selection for grids above 2^10: any window and K, clouds whose
+// indices do not fit beside the distance.  Each candidate's coordinates come
+// from the input; squared distances are 64-bit and the K nearest are kept by
+// (squared distance, index) in a sorted list of pairs.  One thread per point,
+// runtime window.  dist2 saturates at 2^31 - 1 (FGBD_ST_DIST_CLAMPED), which
+// only a neighbour more than 46340 voxels away can reach.
 template <int KM>
 __global__ __launch_bounds__(kBlock) void k_merge_wide(MergeArgs a, const int32_t *__restrict__ xyz,
                                                        const uint64_t *__restrict__ sorted,
@@ -530,7 +716,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_wide(MergeArgs a, const int32_
       const int l = max(r - a.window, lo), h = min(r + a.window, hi);
       for (int rr = l; rr <= h; ++rr) {
         if (rr == r) continue;
-        const uint32_t j = (uint32_t)srt[rr];
+        const uint32_t j = (uint32_t)(srt[rr] & a.index_mask);
         const int64_t dx = xyz[3 * (size_t)j + 0] - px, dy = xyz[3 * (size_t)j + 1] - py,
                       dz = xyz[3 * (size_t)j + 2] - pz;
         uint64_t cd = (uint64_t)(dx * dx + dy * dy + dz * dz);
@@ -592,7 +778,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_wide(MergeArgs a, const int32_
 template <int KT>
 __global__ __launch_bounds__(kBlock) void k_relabel(SegArgs sa, int32_t k_rt, Segs *__restrict__ order,
                                                     const unsigned long long *__restrict__ edge_acc,
-                                                    const uint64_t *__restrict__ sorted0,
+                                                    const uint64_t *__restrict__ sorted0, uint64_t index_mask,
                                                     const uint32_t *__restrict__ rank0,
                                                     const int32_t *__restrict__ col, const int32_t *__restrict__ dist2,
                                                     const float *__restrict__ rgb, int32_t *__restrict__ col_w,
@@ -620,7 +806,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel(SegArgs sa, int32_t k_rt, Se
   for (int64_t base = sh.first; base < sh.end; base += sh.step) {
     const int64_t r = base + threadIdx.x;
     if (r >= sh.end) continue;
-    const int64_t i = (uint32_t)sorted0[r];  // the point at position r
+    const int64_t i = (uint32_t)(sorted0[r] & index_mask);  // the point at position r
     rgb_w[3 * r + 0] = rgb[3 * i + 0];
     rgb_w[3 * r + 1] = rgb[3 * i + 1];
     rgb_w[3 * r + 2] = rgb[3 * i + 2];
@@ -680,8 +866,9 @@ __global__ __launch_bounds__(kBlock) void k_weights(SegArgs sa, int32_t k_rt, in
 
 }  // namespace
 
-hipError_t launch_merge(const Run &r, const int32_t *xyz, const uint64_t *sorted, int32_t *col, int32_t *dist2,
+hipError_t launch_merge(const Run &r, const int32_t *xyz, const Sorted &srt, int32_t *col, int32_t *dist2,
                         fgbd_result *res) {
+  const uint64_t *sorted = srt.items;
   MergeArgs a;
   a.dt = r.dt;
   a.sa = r.sa;
@@ -694,7 +881,26 @@ hipError_t launch_merge(const Run &r, const int32_t *xyz, const uint64_t *sorted
   const uint32_t *rank = r.b.rank;
   unsigned long long *part = r.b.edge_acc;
   hipStream_t st = r.stream;
-  if (r.dt.passes > kSortPasses) {  // codes above 32 bits: items hold indices only
+  a.index_bits = srt.index_bits;
+  a.index_mask = srt.index_mask();
+  if (r.dt.passes > kSortPasses) {  // codes above 32 bits
+    int kb = 1;  // index bits of the largest cloud the call may hold
+    while (((int64_t)1 << kb) < r.pl.n_cap) ++kb;
+    // keys of at most 63 bits; other windows and longer rows are left to the
+    // general kernel (700k points at b = 11, K = 8: 86 us here, 458 there)
+    if (window == 4 && k <= 16 && 2 * r.dt.bits + 2 + kb <= 63 && kb < 32) {
+      using Fn = void (*)(MergeArgs, const int32_t *, const uint64_t *, const uint32_t *, int32_t *, int32_t *,
+                          unsigned long long *, fgbd_result *);
+      // [K > 8][packed][b > 15]
+      static const Fn table[2][2][2] = {
+          {{k_merge_wide4<8, false, false>, k_merge_wide4<8, false, true>},
+           {k_merge_wide4<8, true, false>, k_merge_wide4<8, true, true>}},
+          {{k_merge_wide4<16, false, false>, k_merge_wide4<16, false, true>},
+           {k_merge_wide4<16, true, false>, k_merge_wide4<16, true, true>}}};
+      table[k > 8][srt.index_bits > 0][r.dt.bits > 15]<<<nb, kBlock, 0, st>>>(a, xyz, sorted, rank, col, dist2, part,
+                                                                               res);
+      return hipGetLastError();
+    }
     if (k <= 8)
       k_merge_wide<8><<<nb, kBlock, 0, st>>>(a, xyz, sorted, rank, col, dist2, part, res);
     else if (k <= 16)
@@ -727,16 +933,17 @@ hipError_t launch_merge(const Run &r, const int32_t *xyz, const uint64_t *sorted
   return hipGetLastError();
 }
 
-hipError_t launch_relabel(const Run &r, const uint64_t *sorted, const int32_t *col, const int32_t *dist2,
+hipError_t launch_relabel(const Run &r, const Sorted &sorted, const int32_t *col, const int32_t *dist2,
                           const float *rgb) {
   if (!r.relabel_ok) return hipSuccess;
   const int nb = r.pl.grid[kGridMerge];
   if (r.prm.k == 8)
-    k_relabel<8><<<nb, kBlock, 0, r.stream>>>(r.sa, 8, r.b.segs, r.b.edge_acc, sorted, r.b.rank, col, dist2, rgb,
-                                              r.b.col_w, r.b.dist2_w, r.b.rgb_w);
+    k_relabel<8><<<nb, kBlock, 0, r.stream>>>(r.sa, 8, r.b.segs, r.b.edge_acc, sorted.items, sorted.index_mask(),
+                                              r.b.rank, col, dist2, rgb, r.b.col_w, r.b.dist2_w, r.b.rgb_w);
   else
-    k_relabel<0><<<nb, kBlock, 0, r.stream>>>(r.sa, r.prm.k, r.b.segs, r.b.edge_acc, sorted, r.b.rank, col, dist2,
-                                              rgb, r.b.col_w, r.b.dist2_w, r.b.rgb_w);
+    k_relabel<0><<<nb, kBlock, 0, r.stream>>>(r.sa, r.prm.k, r.b.segs, r.b.edge_acc, sorted.items,
+                                              sorted.index_mask(), r.b.rank, col, dist2, rgb, r.b.col_w, r.b.dist2_w,
+                                              r.b.rgb_w);
   return hipGetLastError();
 }
 

@@ -607,20 +607,36 @@ struct Run {
 hipError_t launch_setup(const Run &r, const int64_t *offsets, int64_t n_host, fgbd_result *res, int zero_result);
 SetupArgs setup_args(const Run &r, const int64_t *offsets, int64_t n_host, fgbd_result *res, int zero_result);
 
-hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, const uint64_t **sorted_out);
+// The sorted items of every direction: packed coordinates
+// (x | y << b | z << 2b) << index_bits | index, or the index alone
+// (index_bits 0: codes too wide for the points to be packed beside it).
+struct Sorted {
+  const uint64_t *items;
+  int index_bits;
+  uint64_t index_mask() const { return index_bits ? (1ull << index_bits) - 1ull : 0xffffffffull; }
+};
+// Index bits of the top-digit route's items, 0 when it does not apply: the
+// items hold the whole code above the index, so codes of up to 32 bits leave
+// 32 and wider ones 64 - code_bits, which must hold every index.
+inline int msd_index_bits(const DirTable &dt, int64_t n_cap) {
+  if (dt.code_bits <= 32) return 32;
+  const int ib = 64 - dt.code_bits;
+  return ib > 0 && ib < 32 && n_cap <= ((int64_t)1 << ib) ? ib : 0;
+}
+hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, Sorted *sorted);
 
 // With r.relabel_ok the merge also counts each cloud's far edges.
 // xyz: the input coordinates (read by the selection for codes above 32 bits);
 // res: FGBD_ST_DIST_CLAMPED is set there when a kept squared distance does not
 // fit int32.
-hipError_t launch_merge(const Run &r, const int32_t *xyz, const uint64_t *sorted, int32_t *col, int32_t *dist2,
+hipError_t launch_merge(const Run &r, const int32_t *xyz, const Sorted &sorted, int32_t *col, int32_t *dist2,
                         fgbd_result *res);
 
 // Relabelling (only when r.relabel_ok): for every cloud whose kept edges are
 // mostly far apart in the input numbering, the graph (col, dist2) and the
 // colours rgb renumbered along scan order 0 into r.b.col_w, dist2_w, rgb_w,
 // and the cloud's relabel flag set; other clouds are left as they are.
-hipError_t launch_relabel(const Run &r, const uint64_t *sorted, const int32_t *col, const int32_t *dist2,
+hipError_t launch_relabel(const Run &r, const Sorted &sorted, const int32_t *col, const int32_t *dist2,
                           const float *rgb);
 
 // sigma_g of each cloud (the fixed value or the mean merge edge length, into

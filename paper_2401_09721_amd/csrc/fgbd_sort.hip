@@ -48,6 +48,7 @@ struct SortArgs {
   int32_t passes;     // passes of the sort (4, or more for codes above 32 bits)
   int32_t fold;       // pass 0 only: the first blocks also do the call's setup
   SetupArgs su;
+  int32_t ib;         // top-digit pass: index bits of the items (32, or fewer for codes above 32 bits)
   int4 *win;          // top-digit pass: the range of each local-sort window (see k_msd_downsweep)
   int32_t nwin;       // windows per direction (the tiles' own numbering)
 };
@@ -174,13 +175,41 @@ __device__ __forceinline__ uint32_t decode_packed(const CodeGen &c, uint32_t cod
   return ((uint32_t)ga << c.sa) | ((uint32_t)gh << c.sh) | ((uint32_t)gm << c.sm);
 }
 
+// 64-bit shifts by launch constants on 32-bit halves: the instruction that
+// shifts 64 bits at once runs at a quarter of the rate.
+__device__ __forceinline__ uint32_t shr64_lo(uint64_t v, int s) {  // the low word of v >> s, 0 <= s < 64
+  const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  return s < 32 ? __builtin_amdgcn_alignbit(hi, lo, (uint32_t)s) : hi >> (s - 32);
+}
+__device__ __forceinline__ uint64_t shl64(uint32_t v, int s) {  // (uint64_t)v << s, 0 <= s < 64
+  const uint32_t lo = s < 32 ? v << s : 0u;
+  const uint32_t hi = s < 32 ? __builtin_amdgcn_alignbit(0u, v, (uint32_t)(32 - s) & 31u) : v << (s - 32);
+  return (uint64_t)(s == 0 ? 0u : hi) << 32 | lo;
+}
+
+// The inverse for codes of any width that sit above ib index bits of an item:
+// packed coordinates at the same place, the index kept.
+__device__ __forceinline__ uint64_t decode_packed_wide(const CodeGen &c, uint64_t item, int ib) {
+  const uint32_t top = (1u << c.bits) - 1u;
+  const int ga = (int)(shr64_lo(item, ib) & top);
+  const int em = (int)(shr64_lo(item, ib + c.bits) & ((1u << c.wm) - 1u));
+  const int eh = (int)shr64_lo(item, ib + c.bits + c.wm);
+  const int gm = em + c.um * ga - (int)c.om;
+  const int gh = eh + c.uh * ga - (int)c.oh;
+  return shl64((uint32_t)ga, ib + c.sa) | shl64((uint32_t)gh, ib + c.sh) | shl64((uint32_t)gm, ib + c.sm) |
+         ((uint32_t)item & ((1u << ib) - 1u));
+}
+
+template <bool WIDE = false>
 __device__ __forceinline__ uint64_t load_item(const SortArgs &a, const CodeGen &cg, const int32_t *__restrict__ xyz,
                                               const uint64_t *__restrict__ src, int d, int pos, int *bad) {
   if (a.pass == 0) {
     const int gx = xyz[3 * pos + 0], gy = xyz[3 * pos + 1], gz = xyz[3 * pos + 2];
     const int top = (1 << a.dt.bits) - 1;
     if ((unsigned)gx > (unsigned)top || (unsigned)gy > (unsigned)top || (unsigned)gz > (unsigned)top) *bad = 1;
-    return ((uint64_t)gen_code(cg, gx, gy, gz) << 32) | (uint32_t)pos;
+    const uint32_t code = gen_code(cg, gx, gy, gz);
+    if (WIDE) return (((uint64_t)gen_code_hi(cg, gx, gy, gz) << 32 | code) << a.ib) | (uint32_t)pos;
+    return ((uint64_t)code << 32) | (uint32_t)pos;
   }
   return src[(size_t)d * a.stride + pos];
 }
@@ -623,7 +652,9 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_downsweep(SortArgs a, con
 
 
 // ------------------------------------------------------------ hybrid sort
-// Codes of at most 32 bits (grids up to 2^10) take a shorter route.  One
+// Codes of at most 32 bits (grids up to 2^10), and wider ones that leave room
+// for the index in a 64-bit item (2^11 with 35-bit codes: 2^29 points; 2^13
+// with 41: 2^23; see msd_index_bits), take a shorter route.  One
 // pass on the kMsdBits most significant bits of each direction's code
 // (upsweep, scan and downsweep as above, with 2^kMsdBits digits, the codes
 // made from the coordinates) splits every cloud's points, stably, into
@@ -675,6 +706,7 @@ __device__ __forceinline__ uint32_t msd_digit(uint32_t code, int sh) {
 
 // Per-tile counts of the top digits, codes made from the coordinates (and
 // the call's setup folded in, as in pass 0 of the LSD sort).
+template <bool WIDE>
 __global__ __launch_bounds__(kSortThreads) void k_msd_upsweep(SortArgs a, const int32_t *__restrict__ xyz,
                                                               uint32_t *__restrict__ hist) {
   constexpr int kSub = 4, kSubStride = kMsdBins + 1;
@@ -707,7 +739,14 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_upsweep(SortArgs a, const 
 #pragma unroll
   for (int j = 0; j < kSortItems; ++j) {
     if (base + j * kWave < ti.end) {
-      const uint32_t digit = msd_digit(gen_code(cg, g[j][0], g[j][1], g[j][2]), sh);
+      uint32_t digit = 0;
+      if (WIDE) {  // the digit sits at bits sh .. sh + 9 of the whole code
+        const uint64_t code =
+            (uint64_t)gen_code_hi(cg, g[j][0], g[j][1], g[j][2]) << 32 | gen_code(cg, g[j][0], g[j][1], g[j][2]);
+        digit = (uint32_t)(code >> sh) & (kMsdBins - 1u);
+      } else {
+        digit = msd_digit(gen_code(cg, g[j][0], g[j][1], g[j][2]), sh);
+      }
       if (run_count != 0 && digit != run_digit) {
         atomicAdd(&s_h[run_digit], run_count);
         run_count = 0;
@@ -731,7 +770,9 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_upsweep(SortArgs a, const 
 
 // The stable partition by top digit: the LSD downsweep's ranking with
 // kMsdBits ballots, per-wave digit counts in LDS, staging in digit order and
-// runs written to their offsets.  Items keep their code (code << 32 | index).
+// runs written to their offsets.  Items keep their code (code << ib | index,
+// ib = 32 unless WIDE).
+template <bool WIDE>
 __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, const int32_t *__restrict__ xyz,
                                                                 uint64_t *__restrict__ dst,
                                                                 const uint32_t *__restrict__ hist,
@@ -765,13 +806,14 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
 
   uint64_t item[kSortItems];
   const CodeGen cg = code_gen(a.dt, d);
-  const int sh = msd_shift(a.dt, d);
+  // where the top digit sits in an item's upper word
+  const int sh = msd_shift(a.dt, d) + (WIDE ? a.ib - 32 : 0);
   const int base = ti.begin + wave * kWave * kSortItems + lane;
   int bad = 0;
 #pragma unroll
   for (int j = 0; j < kSortItems; ++j) {
     const int pos = base + j * kWave;
-    item[j] = (pos < ti.end) ? load_item(a, cg, xyz, nullptr, d, pos, &bad) : ~0ull;
+    item[j] = (pos < ti.end) ? load_item<WIDE>(a, cg, xyz, nullptr, d, pos, &bad) : ~0ull;
   }
   if (bad && d == 0) atomicOr(&res[ti.s].status, FGBD_ST_COORD_RANGE);
   __syncthreads();
@@ -898,7 +940,6 @@ constexpr int kPosBits = 13;                            // a position in an in-L
 constexpr int kBinBits = 13;
 constexpr int kBins = 1 << kBinBits;
 constexpr uint32_t kMaxBin = 512;                       // a larger bin sends its window to the slow path
-constexpr int kLenBits = 32 - kPosBits + 16 - kPosBits; // a bin's length less 1 has kLenBits - shift bits
 constexpr int kSlowItems = 4;                           // per thread and chunk, slow path
 static_assert(kLocalCap == 1 << kPosBits, "positions of the largest in-LDS range");
 
@@ -909,6 +950,7 @@ struct LocalArgs {
   const int4 *win;     // [L][nwin]: where each window's range starts (see k_msd_downsweep)
   int32_t nwin;
   int32_t *big;        // host-mapped flag set for a range of more than kBigRange items (NULL: none)
+  int32_t ib;          // index bits of the items (32 unless WIDE)
 };
 
 // Stable rank of an 8-bit digit among the wave's equal digits (the
@@ -961,16 +1003,21 @@ __device__ __forceinline__ uint32_t exclusive_scan_block(uint32_t v, uint32_t *s
 // two clouds: with windows laid over the whole batch, every window of a batch
 // of small clouds straddled some and took the slow path below (64 clouds of
 // 4k points: 144 us; 29 us with windows of their own).
+// WIDE: codes above 32 bits, with a.ib index bits below them.  Keys stay 32-bit
+// words, ranges of more than 32 code bits looking at whole items on ties
+// (64-bit keys in LDS leave one block a CU): 700k points at b = 11, 70 us, and
+// 74 with 64-bit keys.
+template <bool WIDE>
 __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
     LocalArgs a, uint64_t *__restrict__ src, uint64_t *__restrict__ dst, uint32_t *__restrict__ rank) {
   // in-LDS path: the bins' counts, then starts (two 16-bit values a word),
-  // then each position's rank; a slot's key and its bin's start
+  // then each position's rank; a slot's key and its bin
   __shared__ uint32_t s_key[kLocalCap + 4];
-  __shared__ uint32_t s_two[kLocalCap + 2];  // [kBins / 2 + 2] bins, then [kLocalCap] 16-bit bin starts
+  __shared__ uint32_t s_two[kLocalCap + 2];  // [kBins / 2 + 2] bins, then [kLocalCap] 16-bit bin numbers
   uint32_t *const s_bin = s_two;
-  uint16_t *const s_b0 = reinterpret_cast<uint16_t *>(s_two + kBins / 2 + 2);
+  uint16_t *const s_of = reinterpret_cast<uint16_t *>(s_two + kBins / 2 + 2);
   __shared__ uint32_t s_w[16];
-  __shared__ uint32_t s_max;
+  __shared__ unsigned long long s_max;
   // slow path
   uint32_t(*const s_cnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s_key);  // [kLocalWaves][256]
   uint32_t *const s_base = s_bin;                                          // [256]
@@ -1000,9 +1047,25 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   if (lo >= hi) return;  // no bucket starts in the window (uniform)
   const uint32_t df = (uint32_t)here.y, dl = (uint32_t)(last_win ? here.w : next.z) - 1u;
   const int R = hi - lo;
-  const uint32_t base = df << sh;
-  const int bits = sh + (dl > df ? 32 - __clz(dl - df) : 0);
   const CodeGen cg = code_gen(a.dt, d);
+  const uint64_t base = (uint64_t)df << sh;
+  const uint32_t id_mask = WIDE ? (1u << a.ib) - 1u : ~0u;
+  const int range_bits = sh + (dl > df ? 32 - __clz(dl - df) : 0);
+  // an item's code less the range's base, its top 32 bits where it has more
+  // (WIDE: the low `drop` bits then only break ties), and its final form
+  const int drop = WIDE && range_bits > 32 ? range_bits - 32 : 0;
+  const int bits = range_bits - drop;
+  auto rel = [&](uint64_t v) { return WIDE ? (v >> a.ib) - base : (uint64_t)((uint32_t)(v >> 32) - (uint32_t)base); };
+  const uint64_t base_item = WIDE ? base << a.ib : base << 32;
+  auto rel_top = [&](uint64_t v) {
+    return WIDE ? shr64_lo(v - base_item, a.ib + drop) : (uint32_t)(v >> 32) - (uint32_t)base;
+  };
+  auto final_item = [&](uint64_t v) {
+    if constexpr (WIDE)
+      return decode_packed_wide(cg, v, a.ib);
+    else
+      return (uint64_t)decode_packed(cg, (uint32_t)(v >> 32)) << 32 | (uint32_t)v;
+  };
   uint64_t *out = dst + dbase;
 
   if (R <= kLocalCap) {
@@ -1014,16 +1077,15 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
     const int J = (R + kLocalThreads - 1) / kLocalThreads;  // <= kLocalItems
     // (bits <= 32, so kPosBits + shift <= 32 and a key fits its word)
     const int shift = bits > kBinBits ? bits - kBinBits : 0;
-    uint32_t code[kLocalItems], id[kLocalItems], place[kLocalItems];
+    uint64_t item[kLocalItems];
+    uint32_t place[kLocalItems];
 #pragma unroll
     for (int j = 0; j < kLocalItems; ++j) {
       if (j >= J) break;  // uniform
-      const uint64_t v = items[lo + min(j * kLocalThreads + t, R - 1)];
-      code[j] = (uint32_t)(v >> 32) - base;
-      id[j] = (uint32_t)v;
+      item[j] = items[lo + min(j * kLocalThreads + t, R - 1)];
     }
     for (int i = t; i < kBins / 2 + 2; i += kLocalThreads) s_bin[i] = 0u;
-    if (t == 0) s_max = 0u;
+    if (t == 0) s_max = 0;
     __syncthreads();
     // (codes of coordinates outside the grid can exceed the range's bits: the
     // minimum keeps their bins inside the table)
@@ -1032,7 +1094,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
     for (int j = 0; j < kLocalItems; ++j) {
       if (j >= J) break;
       if (j * kLocalThreads + t < R) {
-        const uint32_t b = bin_of(code[j]), sh16 = 16u * (b & 1u);
+        const uint32_t b = bin_of(rel_top(item[j])), sh16 = 16u * (b & 1u);
         place[j] = (atomicAdd(&s_bin[b >> 1], 1u << sh16) >> sh16) & 0xffffu;
       }
     }
@@ -1047,7 +1109,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
         big = max(big, max(a0, a1));
         sum += a0 + a1;
       }
-      if (big > min(kMaxBin, 1u << (kLenBits - shift))) s_max = 1u;
+      if (big > kMaxBin) s_max = 1;
       uint32_t run = exclusive_scan_block(sum, s_w);
 #pragma unroll
       for (int q = 0; q < kPerT; ++q) {
@@ -1058,7 +1120,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
       if (t == kLocalThreads - 1) s_bin[kBins / 2] = run;
     }
     __syncthreads();
-    if (s_max == 0u) {  // uniform
+    if (s_max == 0) {  // uniform
       const uint16_t *start = reinterpret_cast<const uint16_t *>(s_bin);
       const uint32_t low = (1u << shift) - 1u;
 #pragma unroll
@@ -1066,27 +1128,32 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
         if (j >= J) break;
         const int pos = j * kLocalThreads + t;
         if (pos < R) {
-          const uint32_t b = bin_of(code[j]);
-          const uint32_t b0 = start[b], len = start[b + 1] - b0;
-          const uint32_t s = b0 + place[j];
-          s_key[s] = ((len - 1u) << shift | (code[j] & low)) << kPosBits | (uint32_t)pos;
-          s_b0[s] = (uint16_t)(b0 | (len - 1u) >> (32 - kPosBits - shift) << kPosBits);
+          const uint32_t c = rel_top(item[j]), b = bin_of(c);
+          const uint32_t s = start[b] + place[j];
+          s_key[s] = (c & low) << kPosBits | (uint32_t)pos;
+          s_of[s] = (uint16_t)b;
         }
       }
       __syncthreads();
-      uint16_t *s_rank = reinterpret_cast<uint16_t *>(s_bin);  // (the starts have been read)
 #pragma unroll
       for (int j = 0; j < kLocalItems; ++j) {
         if (j >= J) break;
         const int s = j * kLocalThreads + t;
         if (s < R) {
-          const uint32_t key = s_key[s], b = s_b0[s];
-          const uint32_t b0 = b & (kLocalCap - 1);
-          // (two shifts: kPosBits + shift can be 32)
-          const uint32_t len = (key >> kPosBits >> shift | b >> kPosBits << (32 - kPosBits - shift)) + 1u;
+          const uint32_t key = s_key[s], b = s_of[s];
+          const uint32_t b0 = start[b], len = start[b + 1] - b0;
           uint32_t r = b0;
           const uint32_t *bin = s_key + b0;
           uint32_t k = 0;
+          if (WIDE && drop > 0) {  // (uniform) equal keys but for the position: the whole items decide
+            const uint64_t mine = items[lo + (int)(key & (kLocalCap - 1))];
+            for (; k < len; ++k) {
+              const uint32_t v = bin[k];
+              bool less = v < key;
+              if (((v ^ key) >> kPosBits) == 0 && v != key) less = items[lo + (int)(v & (kLocalCap - 1))] < mine;
+              r += less ? 1u : 0u;
+            }
+          }
           for (; k + 8 <= len; k += 8) {
             uint32_t v[8];
 #pragma unroll
@@ -1101,8 +1168,15 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
 #pragma unroll
             for (int u = 0; u < 4; ++u) r += (k + u < len && v[u] < key) ? 1u : 0u;
           }
-          s_rank[key & (kLocalCap - 1)] = (uint16_t)r;
+          place[j] = r << kPosBits | (key & (kLocalCap - 1));
         }
+      }
+      __syncthreads();
+      uint16_t *s_rank = reinterpret_cast<uint16_t *>(s_bin);  // (the starts have been read)
+#pragma unroll
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        if (j * kLocalThreads + t < R) s_rank[place[j] & (kLocalCap - 1)] = (uint16_t)(place[j] >> kPosBits);
       }
       __syncthreads();
 #pragma unroll
@@ -1119,10 +1193,12 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
         if (j >= J) break;
         const int pos = j * kLocalThreads + t;
         if (pos < R) {
-          s_key[place[j]] = id[j];
-          s_two[place[j]] = decode_packed(cg, code[j] + base);
-          if (id[j] < (uint32_t)a.stride)  // (the id is a point of the range; the bound is a guard)
-            rank[dbase + id[j]] = (uint32_t)lo + place[j];
+          const uint64_t done = final_item(item[j]);
+          const uint32_t id = (uint32_t)item[j] & id_mask;
+          s_key[place[j]] = (uint32_t)done;
+          s_two[place[j]] = (uint32_t)(done >> 32);
+          if (id < (uint32_t)a.stride)  // (the id is a point of the range; the bound is a guard)
+            rank[dbase + id] = (uint32_t)lo + place[j];
         }
       }
       __syncthreads();
@@ -1143,18 +1219,17 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   // An odd number of passes (a first pass of digit 0, a plain stable copy,
   // when needed) ends in dst, in the final form.
   if (a.big && R > kBigRange && t == 0) *a.big = 1;  // (only ever set to 1)
-  if (t == 0) s_max = 0u;
+  if (t == 0) s_max = 0;
   __syncthreads();
-  auto rel = [&](uint64_t v) { return (uint32_t)(v >> 32) - base; };
   // the widest key of the range, for the pass count
   {
-    uint32_t mx = 0u;
-    for (int s = t; s < R; s += kLocalThreads) mx = max(mx, rel(items[lo + s]));
+    unsigned long long mx = 0;
+    for (int s = t; s < R; s += kLocalThreads) mx = max(mx, (unsigned long long)rel(items[lo + s]));
     atomicMax(&s_max, mx);
   }
   __syncthreads();
-  const uint32_t kmax = s_max;
-  int P = kmax ? (32 - __clz(kmax) + 7) / 8 : 0;
+  const unsigned long long kmax = s_max;
+  int P = kmax ? (64 - __clzll(kmax) + 7) / 8 : 0;
   const int extra = (P % 2 == 0) ? 1 : 0;
   P += extra;
   for (int q = 0; q < P; ++q) {
@@ -1165,7 +1240,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
     if (t < 256) s_base[t] = 0u;
     __syncthreads();
     for (int s = t; s < R; s += kLocalThreads) {
-      const uint32_t digit = q < extra ? 0u : (rel(rd[lo + s]) >> shift) & 255u;
+      const uint32_t digit = q < extra ? 0u : (uint32_t)(rel(rd[lo + s]) >> shift) & 255u;
       atomicAdd(&s_base[digit], 1u);
     }
     __syncthreads();
@@ -1186,7 +1261,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
 #pragma unroll
       for (int j = 0; j < kSlowItems; ++j) {
         const int s = c0 + (wave * kSlowItems + j) * kWave + lane;
-        dg[j] = s >= R ? 255u : (q < extra ? 0u : (rel(it[j]) >> shift) & 255u);
+        dg[j] = s >= R ? 255u : (q < extra ? 0u : (uint32_t)(rel(it[j]) >> shift) & 255u);
       }
 #pragma unroll
       for (int j = 0; j < kSlowItems; ++j) rk[j] = wave_rank8(dg[j], s_cnt[wave], bf[j]);
@@ -1211,8 +1286,8 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
         const uint32_t dest = s_cnt[wave][dg[j]] + rk[j];
         if (s < R && dest < (uint32_t)R) {  // (dest < R for counts that agree; the bound is a guard)
           if (last) {
-            const uint32_t idx = (uint32_t)it[j];
-            wr[lo + dest] = ((uint64_t)decode_packed(cg, (uint32_t)(it[j] >> 32)) << 32) | idx;
+            const uint32_t idx = (uint32_t)it[j] & id_mask;
+            wr[lo + dest] = final_item(it[j]);
             if (idx < (uint32_t)a.stride) rank[dbase + idx] = (uint32_t)(lo + dest);
           } else {
             wr[lo + dest] = it[j];
@@ -1258,7 +1333,7 @@ hipError_t launch_setup(const Run &r, const int64_t *offsets, int64_t n_host, fg
   return hipGetLastError();
 }
 
-hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, const uint64_t **sorted_out) {
+hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, Sorted *sorted) {
   SortArgs a;
   a.win = nullptr;
   a.nwin = 0;
@@ -1270,8 +1345,11 @@ hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, const
   a.su = r.setup;
   const int ntiles = r.sa.n_fixed >= 0 ? (r.sa.n_fixed + kSortTile - 1) / kSortTile : r.pl.ntiles_cap;
   const dim3 grid(ntiles > 0 ? ntiles : 1, r.dt.num_dirs);
-  if (r.dt.passes == kSortPasses && !r.sort_lsd) {
-    // codes of at most 32 bits: the MSD pass, then the windows' local sorts
+  const int ib = msd_index_bits(r.dt, r.pl.n_cap);
+  a.ib = ib;
+  if (ib > 0 && !r.sort_lsd) {
+    // the MSD pass, then the windows' local sorts
+    const bool wide = ib < 32;
     a.nwin = (int)grid.x;  // windows are numbered like the tiles
     a.win = r.b.win;
     a.pass = 0;
@@ -1280,13 +1358,14 @@ hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, const
     a.fold = r.fold_setup ? 1 : 0;
     if (a.fold && a.su.blocks > (int)(grid.x * grid.y)) a.su.blocks = (int)(grid.x * grid.y);
     FGBD_PRE(r.pf, kUpsweep);
-    k_msd_upsweep<<<grid, kSortThreads, 0, r.stream>>>(a, xyz, r.b.hist);
+    (wide ? k_msd_upsweep<true> : k_msd_upsweep<false>)<<<grid, kSortThreads, 0, r.stream>>>(a, xyz, r.b.hist);
     FGBD_POST(r.pf);
     FGBD_PRE(r.pf, kScan);
     k_sort_scan<kMsdBins><<<r.dt.num_dirs * (kMsdBins / kWave), kScanWaves * kWave, 0, r.stream>>>(a, r.b.hist);
     FGBD_POST(r.pf);
     FGBD_PRE(r.pf, kDownsweep);
-    k_msd_downsweep<<<grid, kSortThreads, 0, r.stream>>>(a, xyz, r.b.items_a, r.b.hist, res);
+    (wide ? k_msd_downsweep<true> : k_msd_downsweep<false>)<<<grid, kSortThreads, 0, r.stream>>>(a, xyz, r.b.items_a,
+                                                                                                r.b.hist, res);
     FGBD_POST(r.pf);
     LocalArgs la;
     la.dt = r.dt;
@@ -1295,9 +1374,10 @@ hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, const
     la.win = r.b.win;
     la.nwin = a.nwin;
     la.big = r.sort_big;
+    la.ib = ib;
     FGBD_PRE(r.pf, kLocalSort);
-    k_local_sort<<<dim3(a.nwin, r.dt.num_dirs), kLocalThreads, 0, r.stream>>>(la, r.b.items_a, r.b.items_b,
-                                                                              r.b.rank);
+    (wide ? k_local_sort<true> : k_local_sort<false>)<<<dim3(a.nwin, r.dt.num_dirs), kLocalThreads, 0, r.stream>>>(
+        la, r.b.items_a, r.b.items_b, r.b.rank);
     FGBD_POST(r.pf);
     if (r.sort_big && r.sort_ev) {
       if (hipEventRecord(r.sort_ev, r.stream) == hipSuccess)
@@ -1305,7 +1385,7 @@ hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, const
       else
         (void)hipGetLastError();
     }
-    *sorted_out = r.b.items_b;
+    *sorted = {r.b.items_b, ib};
     return hipGetLastError();
   }
   const uint64_t *src = nullptr;
@@ -1328,7 +1408,7 @@ hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, const
     FGBD_POST(r.pf);
     src = dst;
   }
-  *sorted_out = src;
+  *sorted = {src, r.dt.passes == kSortPasses ? 32 : 0};
   return hipGetLastError();
 }
 
