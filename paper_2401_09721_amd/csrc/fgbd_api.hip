@@ -6,7 +6,9 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <chrono>
 #include <mutex>
+#include <thread>
 #include <vector>
 
 #include "fgbd_internal.h"
@@ -67,23 +69,26 @@ struct fgbd_ctx_s {
   double ms[FGBD_NUM_KERNELS] = {0};
   int64_t launches[FGBD_NUM_KERNELS] = {0};
   // Sweep counts of recent eager calls, read back without waiting: the last
-  // finalising launch stores each cloud's count into host-mapped memory and
-  // an event marks it; a later call reads it once the event has completed.
+  // finalising launch stores each cloud's count and the call's tag in one
+  // word of host-mapped memory; a later call reads them once every cloud's
+  // word carries the tag.  (No events: each one recorded left the GPU idle
+  // for about 6 us.)
   int32_t *hint_host = nullptr;  // [kMaxSeg], hipHostMalloc'ed
   int32_t *hint_dev = nullptr;   // its device address
-  hipEvent_t hint_ev = nullptr;
+  int32_t hint_tag = 0;          // of the outstanding read-back, above the count's 16 bits
   bool hint_failed = false;      // could not set up: no adaptation
-  bool hint_pending = false;
+  bool hint_pending = false;     // launches that may write the words are outstanding
   int hint_B = 0;
   int hint_recent[8] = {0};      // ring of the last counts read (max over clouds)
   int hint_count = 0;
   // Sort route: a host-mapped flag the local sort sets when a block sorted a
   // very large range alone (points crowded into few top code digits, such as
   // a plane normal to a scan axis), read back without waiting like the sweep
-  // counts; while sort_lsd_left > 0, eager calls sort by LSD passes.
-  int32_t *sort_flag_host = nullptr;
+  // counts (the second word is the last watched call whose sort has ended);
+  // while sort_lsd_left > 0, eager calls sort by LSD passes.
+  int32_t *sort_flag_host = nullptr;  // [2]
   int32_t *sort_flag_dev = nullptr;
-  hipEvent_t sort_ev = nullptr;
+  int32_t sort_seq = 0;
   bool sort_failed = false;
   bool sort_pending = false;
   int sort_lsd_left = 0;
@@ -366,26 +371,19 @@ static void sort_policy(fgbd_ctx ctx, hipStream_t s, Run &r) {
   if (cs != hipStreamCaptureStatusNone) return;
   if (!ctx->sort_flag_host) {
     void *dev = nullptr;
-    if (hipHostMalloc((void **)&ctx->sort_flag_host, sizeof(int32_t), hipHostMallocMapped | hipHostMallocCoherent) !=
-            hipSuccess ||
-        hipHostGetDevicePointer(&dev, ctx->sort_flag_host, 0) != hipSuccess ||
-        hipEventCreateWithFlags(&ctx->sort_ev, hipEventDisableTiming) != hipSuccess) {
+    if (hipHostMalloc((void **)&ctx->sort_flag_host, 2 * sizeof(int32_t),
+                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+        hipHostGetDevicePointer(&dev, ctx->sort_flag_host, 0) != hipSuccess) {
       (void)hipGetLastError();
       ctx->sort_failed = true;
       return;
     }
     ctx->sort_flag_dev = (int32_t *)dev;
+    ctx->sort_flag_host[1] = 0;
   }
-  if (ctx->sort_pending) {
-    const hipError_t q = hipEventQuery(ctx->sort_ev);
-    if (q == hipSuccess) {
-      if (*(volatile int32_t *)ctx->sort_flag_host) ctx->sort_lsd_left = kSortLsdCalls;
-      ctx->sort_pending = false;
-    } else if (q != hipErrorNotReady) {
-      (void)hipGetLastError();
-      ctx->sort_failed = true;
-      return;
-    }
+  if (ctx->sort_pending && __atomic_load_n(&ctx->sort_flag_host[1], __ATOMIC_ACQUIRE) == ctx->sort_seq) {
+    if (__atomic_load_n(&ctx->sort_flag_host[0], __ATOMIC_RELAXED)) ctx->sort_lsd_left = kSortLsdCalls;
+    ctx->sort_pending = false;
   }
   if (ctx->sort_lsd_left > 0) {
     r.sort_lsd = true;
@@ -393,9 +391,10 @@ static void sort_policy(fgbd_ctx ctx, hipStream_t s, Run &r) {
     return;
   }
   if (!ctx->sort_pending) {
-    *(volatile int32_t *)ctx->sort_flag_host = 0;
+    __atomic_store_n(&ctx->sort_flag_host[0], 0, __ATOMIC_RELEASE);
+    ctx->sort_seq = ctx->sort_seq == INT32_MAX ? 1 : ctx->sort_seq + 1;
     r.sort_big = ctx->sort_flag_dev;
-    r.sort_ev = ctx->sort_ev;
+    r.sort_seq = ctx->sort_seq;
     r.sort_pending = &ctx->sort_pending;
   }
 }
@@ -405,6 +404,7 @@ static void sort_policy(fgbd_ctx ctx, hipStream_t s, Run &r) {
 fgbd_status run_slg(const Run &r, const int32_t *xyz, int32_t *col, int32_t *dist2, float *p, fgbd_result *res,
                     const float *rgb = nullptr) {
   Sorted sorted = {nullptr, 0};
+  if (r.sort_big) *r.sort_pending = true;  // (a launch that fails leaves it so: no further watch)
   HIP_TRY(launch_sort(r, xyz, res, &sorted), "radix sort launch");
   FGBD_PRE(r.pf, kMerge);
   HIP_TRY(launch_merge(r, xyz, sorted, col, dist2, res), "neighbour merge launch");
@@ -589,25 +589,26 @@ fgbd_status fgbd_create(fgbd_ctx *out, int32_t hip_device) {
   return ok();
 }
 
+// Launches that may still write the context's host-mapped words.
+static bool words_pending(fgbd_ctx ctx) {
+  if (ctx->sort_pending && __atomic_load_n(&ctx->sort_flag_host[1], __ATOMIC_ACQUIRE) != ctx->sort_seq) return true;
+  for (int i = 0; ctx->hint_pending && i < ctx->hint_B; ++i)
+    if ((__atomic_load_n(&ctx->hint_host[i], __ATOMIC_ACQUIRE) & ~0xffff) != ctx->hint_tag) return true;
+  return false;
+}
+
 fgbd_status fgbd_destroy(fgbd_ctx ctx) {
   if (!ctx) return ok();
-  if (ctx->own || !ctx->pool.empty() || !ctx->pending.empty() || ctx->hint_host || ctx->hint_ev ||
-      ctx->sort_flag_host || ctx->sort_ev) {
+  if (ctx->own || !ctx->pool.empty() || !ctx->pending.empty() || ctx->hint_host || ctx->sort_flag_host) {
     DeviceGuard g(ctx->device);
-    if (ctx->hint_ev) {
-      (void)hipEventSynchronize(ctx->hint_ev);
-      (void)hipEventDestroy(ctx->hint_ev);
-    }
+    // launches that may still write the host-mapped words or the workspace:
+    // the words usually tell of their end
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(100);
+    while (!ctx->own && words_pending(ctx) && std::chrono::steady_clock::now() < until) std::this_thread::yield();
+    if (ctx->own || words_pending(ctx)) (void)hipDeviceSynchronize();
     if (ctx->hint_host) (void)hipHostFree(ctx->hint_host);
-    if (ctx->sort_ev) {
-      (void)hipEventSynchronize(ctx->sort_ev);
-      (void)hipEventDestroy(ctx->sort_ev);
-    }
     if (ctx->sort_flag_host) (void)hipHostFree(ctx->sort_flag_host);
-    if (ctx->own) {
-      (void)hipDeviceSynchronize();
-      (void)hipFree(ctx->own);
-    }
+    if (ctx->own) (void)hipFree(ctx->own);
     for (auto &r : ctx->pending) {
       (void)hipEventDestroy(r.a);
       (void)hipEventDestroy(r.b);
@@ -681,6 +682,66 @@ fgbd_status fgbd_estimate_noise(fgbd_ctx ctx, const fgbd_graph *g, const float *
   return run_estimate_noise(r, g, rgb, res, patch_spread ? patch_spread : r.b.spread, eig3);
 }
 
+// Separate sweep launches for an eager call: the schedule's count, lowered to
+// the most sweeps any of the last eight read-back calls needed when those
+// counts agree (the finalising launch then applies the last sweep's sums
+// itself and finds the selection stopped), else to one more (a launch that
+// finds it stopped, so the in-launch loop after it returns at once).  A
+// context whose schedule nobody set goes above the default count the same
+// way when recent calls needed more sweeps: a separate sweep of 64 clouds of
+// 4k points takes 8.5 us, one in the loop many times that (the batch of 64:
+// 1513 us with 8 separate sweeps, 439 with as many as it needs).
+// Captured calls keep the schedule's count.  With no read-back outstanding the
+// call's finalising launch is told where to store its sweep counts (r.hint).
+static int adaptive_sweep_launches(fgbd_ctx ctx, hipStream_t s, Run &r, int B) {
+  const int cap = ctx->tune.sweep_launches;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone || ctx->hint_failed) return cap;
+  if (!ctx->hint_host) {
+    void *dev = nullptr;
+    if (hipHostMalloc((void **)&ctx->hint_host, kMaxSeg * sizeof(int32_t),
+                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+        hipHostGetDevicePointer(&dev, ctx->hint_host, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      ctx->hint_failed = true;
+      return cap;
+    }
+    ctx->hint_dev = (int32_t *)dev;
+    for (int i = 0; i < kMaxSeg; ++i) ctx->hint_host[i] = 0;
+  }
+  if (ctx->hint_pending) {
+    int m = 0, seen = 0;
+    for (; seen < ctx->hint_B; ++seen) {
+      const int32_t v = __atomic_load_n(&ctx->hint_host[seen], __ATOMIC_ACQUIRE);
+      if ((v & ~0xffff) != ctx->hint_tag) break;
+      m = (v & 0xffff) > m ? v & 0xffff : m;
+    }
+    if (seen == ctx->hint_B) {
+      ctx->hint_recent[ctx->hint_count % 8] = m;
+      ++ctx->hint_count;
+      ctx->hint_pending = false;
+    }
+  }
+  if (!ctx->hint_pending) {  // pending from here: a launch that fails leaves it so (no further read-back)
+    ctx->hint_tag = (ctx->hint_tag + 0x10000) & 0x7fff0000;
+    if (ctx->hint_tag == 0) ctx->hint_tag = 0x10000;
+    ctx->hint_pending = true;
+    ctx->hint_B = B;
+    r.hint = ctx->hint_dev;
+    r.hint_tag = ctx->hint_tag;
+  }
+  if (ctx->hint_count == 0) return cap;
+  int m = 0, lo = 1 << 30;
+  const int k = ctx->hint_count < 8 ? ctx->hint_count : 8;
+  for (int i = 0; i < k; ++i) {
+    m = ctx->hint_recent[i] > m ? ctx->hint_recent[i] : m;
+    lo = ctx->hint_recent[i] < lo ? ctx->hint_recent[i] : lo;
+  }
+  const int want = (k >= 2 && lo == m) ? m : m + 1;  // steady counts: no spare launch
+  const int most = ctx->tune_set ? cap : kMaxAdaptiveSweeps;
+  return want < 1 ? 1 : (want < most ? want : most);
+}
+
 fgbd_status fgbd_filter(fgbd_ctx ctx, const fgbd_graph *g, const float *rgb_in, const fgbd_params *params,
                         const fgbd_result *noise, const double *patch_spread, int32_t q_fixed, float *rgb_out,
                         fgbd_result *res, void *stream) {
@@ -706,80 +767,15 @@ fgbd_status fgbd_filter(fgbd_ctx ctx, const fgbd_graph *g, const float *rgb_in, 
   char *ws = nullptr;
   if ((st = get_workspace(ctx, pl.total, &ws)) != FGBD_OK) return st;
   EventProf ep(ctx, s);
-  const Run r = make_run(ctx, pl, ws, *params, n, s, &ep);
+  Run r = make_run(ctx, pl, ws, *params, n, s, &ep);
   HIP_TRY(launch_setup(r, nullptr, n, res, n == 0 ? 1 : 0), "setup launch");
   if (n == 0) return ok();
   const int q_limit = select ? params->q_max : q_fixed;
+  if (select) r.sweep_launches = adaptive_sweep_launches(ctx, s, r, 1);
   if ((st = run_filter(r, g->col, g->p, nullptr, rgb_in, patch_spread, noise, select, q_limit, rgb_out, res)) !=
       FGBD_OK)
     return st;
   return ok();
-}
-
-// Separate sweep launches for an eager call: the schedule's count, lowered to
-// the most sweeps any of the last eight read-back calls needed when those
-// counts agree (the finalising launch then applies the last sweep's sums
-// itself and finds the selection stopped), else to one more (a launch that
-// finds it stopped, so the in-launch loop after it returns at once).  A
-// context whose schedule nobody set goes above the default count the same
-// way when recent calls needed more sweeps: a separate sweep of 64 clouds of
-// 4k points takes 8.5 us, one in the loop many times that (the batch of 64:
-// 1513 us with 8 separate sweeps, 439 with as many as it needs).
-// Captured calls keep the schedule's count.  *hint receives where this call's finalising launch
-// should store its sweep counts (NULL: no read-back requested).
-static int adaptive_sweep_launches(fgbd_ctx ctx, hipStream_t s, int32_t **hint) {
-  *hint = nullptr;
-  const int cap = ctx->tune.sweep_launches;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone || ctx->hint_failed) return cap;
-  if (!ctx->hint_host) {
-    void *dev = nullptr;
-    if (hipHostMalloc((void **)&ctx->hint_host, kMaxSeg * sizeof(int32_t),
-                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
-        hipHostGetDevicePointer(&dev, ctx->hint_host, 0) != hipSuccess ||
-        hipEventCreateWithFlags(&ctx->hint_ev, hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      ctx->hint_failed = true;
-      return cap;
-    }
-    ctx->hint_dev = (int32_t *)dev;
-  }
-  if (ctx->hint_pending) {
-    const hipError_t q = hipEventQuery(ctx->hint_ev);
-    if (q == hipSuccess) {
-      int m = 0;
-      for (int i = 0; i < ctx->hint_B; ++i) m = ctx->hint_host[i] > m ? ctx->hint_host[i] : m;
-      ctx->hint_recent[ctx->hint_count % 8] = m;
-      ++ctx->hint_count;
-      ctx->hint_pending = false;
-    } else if (q != hipErrorNotReady) {
-      (void)hipGetLastError();
-      ctx->hint_failed = true;
-      return cap;
-    }
-  }
-  if (!ctx->hint_pending) *hint = ctx->hint_dev;
-  if (ctx->hint_count == 0) return cap;
-  int m = 0, lo = 1 << 30;
-  const int k = ctx->hint_count < 8 ? ctx->hint_count : 8;
-  for (int i = 0; i < k; ++i) {
-    m = ctx->hint_recent[i] > m ? ctx->hint_recent[i] : m;
-    lo = ctx->hint_recent[i] < lo ? ctx->hint_recent[i] : lo;
-  }
-  const int want = (k >= 2 && lo == m) ? m : m + 1;  // steady counts: no spare launch
-  const int most = ctx->tune_set ? cap : kMaxAdaptiveSweeps;
-  return want < 1 ? 1 : (want < most ? want : most);
-}
-
-// After the launches of an eager call that asked for a read-back: mark it.
-static void request_hint(fgbd_ctx ctx, hipStream_t s, int B) {
-  if (hipEventRecord(ctx->hint_ev, s) == hipSuccess) {
-    ctx->hint_pending = true;
-    ctx->hint_B = B;
-  } else {
-    (void)hipGetLastError();
-    ctx->hint_failed = true;
-  }
 }
 
 // The fused path over the call's segments (one cloud of host-known size, or
@@ -828,10 +824,9 @@ fgbd_status fgbd_denoise(fgbd_ctx ctx, const int32_t *xyz, const float *rgb_in, 
   // the first radix launch does the setup
   r.fold_setup = true;
   r.setup = setup_args(r, nullptr, n, res, 1);
-  r.sweep_launches = adaptive_sweep_launches(ctx, s, &r.hint);
+  r.sweep_launches = adaptive_sweep_launches(ctx, s, r, 1);
   r.relabel_ok = r.prm.patch_order == 0;  // index-ordered patches need the input numbering
   if ((st = run_denoise(r, xyz, rgb_in, rgb_out, res)) != FGBD_OK) return st;
-  if (r.hint) request_hint(ctx, s, 1);
   return ok();
 }
 
@@ -867,10 +862,9 @@ fgbd_status fgbd_denoise_batched(fgbd_ctx ctx, const int32_t *xyz, const float *
   sort_policy(ctx, s, r);
   HIP_TRY(launch_setup(r, offsets, 0, res, n_total == 0 ? 2 : 1), "setup launch");
   if (n_total == 0) return ok();
-  r.sweep_launches = adaptive_sweep_launches(ctx, s, &r.hint);
+  r.sweep_launches = adaptive_sweep_launches(ctx, s, r, batch);
   r.relabel_ok = r.prm.patch_order == 0;  // index-ordered patches need the input numbering
   if ((st = run_denoise(r, xyz, rgb_in, rgb_out, res)) != FGBD_OK) return st;
-  if (r.hint) request_hint(ctx, s, batch);
   return ok();
 }
 

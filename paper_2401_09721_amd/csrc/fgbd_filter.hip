@@ -461,13 +461,18 @@ __device__ bool cloud_barrier(uint32_t *count, uint32_t epoch, int blocks, long 
   return *s_flag != 0;
 }
 
+// A cloud's sweep count and the call's tag, in one word, to the host.
+__device__ __forceinline__ void report_sweeps(int32_t *hint, int s, int q, int32_t tag) {
+  __hip_atomic_store(hint + s, q | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The finalising work of one block, from the cloud's final state c: the
 // chosen iterate (or the input for q = 0) out, and block 0 of the cloud
 // writes its results (and its sweep count to hint when given).
 __device__ __forceinline__ void finalize_block(const SegBlock &sb, const SweepCtrl &c, int64_t buf_stride,
                                                const float *__restrict__ rgb_in, const float4 *__restrict__ xbuf,
                                                const fgbd_result *__restrict__ noise, float *__restrict__ rgb_out,
-                                               fgbd_result *__restrict__ res, int32_t *hint,
+                                               fgbd_result *__restrict__ res, int32_t *hint, int32_t hint_tag,
                                                const uint32_t *__restrict__ rank0) {
   const int best = c.best_buf;
   const Share sh = seg_share(sb, kBlock);
@@ -508,7 +513,7 @@ __device__ __forceinline__ void finalize_block(const SegBlock &sb, const SweepCt
     r->sweeps = c.q;
     if (rank0) r->status |= FGBD_ST_RELABELED;
     if (noise != nullptr && noise != res) r->sigma_est = noise[sb.s].sigma_est;
-    if (hint != nullptr) hint[sb.s] = c.q;
+    if (hint != nullptr) report_sweeps(hint, sb.s, c.q, hint_tag);
   }
 }
 
@@ -519,13 +524,14 @@ __global__ __launch_bounds__(kBlock) void k_finalize(SegArgs sa, int64_t buf_str
                                                      const SweepCtrl *__restrict__ ctrl_prev,
                                                      const fgbd_result *__restrict__ noise,
                                                      float *__restrict__ rgb_out, fgbd_result *__restrict__ res,
-                                                     int32_t *hint, const int32_t *__restrict__ relabel,
+                                                     int32_t *hint, int32_t hint_tag,
+                                                     const int32_t *__restrict__ relabel,
                                                      const uint32_t *__restrict__ rank0) {
   const SegBlock sb = seg_block(sa, kGridSweep);
   SweepCtrl c;
   load_state(c, ctrl_prev + sb.s, sums_prev + (size_t)sb.s * kSlotVals, sums_first + (size_t)sb.s * kSlotVals,
              (int)(sb.end - sb.begin));
-  finalize_block(sb, c, buf_stride, rgb_in, xbuf, noise, rgb_out, res, hint,
+  finalize_block(sb, c, buf_stride, rgb_in, xbuf, noise, rgb_out, res, hint, hint_tag,
                  relabel && relabel[sb.s] ? rank0 : nullptr);
 }
 
@@ -542,7 +548,8 @@ __global__ __launch_bounds__(kBlock) void k_sweep_tail(SweepArgs a, int q0, int 
                                                        const float *__restrict__ p, const float *__restrict__ rgb_in,
                                                        float4 *__restrict__ xbuf, const double *__restrict__ spread,
                                                        const fgbd_result *__restrict__ noise,
-                                                       float *__restrict__ rgb_out, int32_t *hint) {
+                                                       float *__restrict__ rgb_out, int32_t *hint,
+                                                       int32_t hint_tag) {
   __shared__ SweepLds<false> lds;
   __shared__ int s_flag;
   const SegBlock sb = seg_block(a.sa, kGridSweep);
@@ -563,6 +570,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_tail(SweepArgs a, int q0, int 
       // The selection cannot be completed: flag the cloud and leave every
       // point of this block's share defined (its input colour).
       if (threadIdx.x == 0) atomicOr(&a.res[sb.s].status, FGBD_ST_SWEEP_STALL);
+      if (hint != nullptr && sb.lb == 0 && threadIdx.x == 0) report_sweeps(hint, sb.s, q, hint_tag);
       const Share sh = seg_share(sb, kBlock);
       for (int64_t base = sh.first; base < sh.end; base += sh.step) {
         const int64_t i = base + threadIdx.x;
@@ -574,7 +582,8 @@ __global__ __launch_bounds__(kBlock) void k_sweep_tail(SweepArgs a, int q0, int 
       return;
     }
   }
-  finalize_block(sb, c, a.buf_stride, rgb_in, xbuf, noise, rgb_out, a.res, hint, renumbered ? a.rank0 : nullptr);
+  finalize_block(sb, c, a.buf_stride, rgb_in, xbuf, noise, rgb_out, a.res, hint, hint_tag,
+                 renumbered ? a.rank0 : nullptr);
 }
 
 SweepArgs sweep_args(const Run &r, const int32_t *dist2, float *p_out, fgbd_result *res, int select, int q_limit) {
@@ -644,9 +653,10 @@ long long wait_ticks(int64_t us) {
 template <int KT>
 hipError_t tail_kernel(int nb, hipStream_t st, const SweepArgs &a, int q0, int q_last, uint32_t *barrier,
                        long long ticks, const int32_t *col, const float *p, const float *rgb_in, float4 *xbuf,
-                       const double *spread, const fgbd_result *noise, float *rgb_out, int32_t *hint) {
+                       const double *spread, const fgbd_result *noise, float *rgb_out, int32_t *hint,
+                       int32_t hint_tag) {
   k_sweep_tail<KT><<<nb, kBlock, 0, st>>>(a, q0, q_last, barrier, ticks, col, p, rgb_in, xbuf, spread, noise, rgb_out,
-                                          hint);
+                                          hint, hint_tag);
   return hipGetLastError();
 }
 
@@ -702,11 +712,11 @@ hipError_t launch_sweep_tail(const Run &r, const int32_t *col, const float *p, c
   a.vec = row_vec(a.k, common_align(col, p));
   using Fn = hipError_t (*)(int, hipStream_t, const SweepArgs &, int, int, uint32_t *, long long,
                             const int32_t *, const float *, const float *, float4 *, const double *,
-                            const fgbd_result *, float *, int32_t *);
+                            const fgbd_result *, float *, int32_t *, int32_t);
   // the loop is a fallback: bounded rows serve every K but 8
   const Fn fn = a.k == 8 ? tail_kernel<8> : (a.k <= 8 ? tail_kernel<-8> : (a.k <= 16 ? tail_kernel<-16> : tail_kernel<-32>));
   return fn(nb, r.stream, a, q0, q_last, &r.b.segs->sweep_barrier[0][0], wait_ticks(r.wait_us), col, p,
-            rgb_in, r.b.xbuf, spread, noise, rgb_out, r.hint);
+            rgb_in, r.b.xbuf, spread, noise, rgb_out, r.hint, r.hint_tag);
 }
 
 hipError_t launch_finalize(const Run &r, const float *rgb_in, int q_launches, const fgbd_result *noise,
@@ -716,7 +726,7 @@ hipError_t launch_finalize(const Run &r, const float *rgb_in, int q_launches, co
   const SweepCtrl *cp = r.b.ctrl + (q_launches & 1) * r.pl.B;
   k_finalize<<<r.pl.grid[kGridSweep], kBlock, 0, r.stream>>>(r.sa, r.pl.n_cap, rgb_in, r.b.xbuf, sp, r.b.sums + 3 * S, cp,
                                                               noise,
-                                                              rgb_out, res, r.hint,
+                                                              rgb_out, res, r.hint, r.hint_tag,
                                                               r.relabel_ok ? r.b.segs->relabel : nullptr, r.b.rank);
   return hipGetLastError();
 }

@@ -162,7 +162,16 @@ struct MergeArgs {
   int32_t wide_rows;  // col and dist2 are aligned for 16-byte stores
   int32_t index_bits;   // of the sorted items (see Sorted); the wide kernels only
   uint64_t index_mask;
+  int32_t *sort_done;   // host-mapped, NULL: not watched (see Run::sort_big)
+  int32_t sort_seq;
 };
+// The sort before this launch has ended, so its flag is final: tells the host
+// (an event recorded between the sort and the merge left the GPU idle for 5.7
+// us on every call).
+__device__ __forceinline__ void report_sort(const MergeArgs &a) {
+  if (a.sort_done && blockIdx.x == 0 && threadIdx.x == 0)
+    __hip_atomic_store(a.sort_done, a.sort_seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Exact (64-bit key) selection for one point, runtime window over positions
 // lo..hi: used for every point of a cloud of more than 2^24 points and for
@@ -482,6 +491,7 @@ __global__ __launch_bounds__(kBlock) void k_merge(MergeArgs a, const uint64_t *_
       }
     }
   }
+  report_sort(a);
   block_sum_f64<3>(acc, s_red);
   if (threadIdx.x == 0) {
     unsigned long long *e = edge_acc + ((size_t)sb.s * kEdgeSlots + sb.lb % kEdgeSlots) * kEdgeVals;
@@ -666,6 +676,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_wide4(MergeArgs a, const int32
   }
   if (__builtin_amdgcn_ballot_w64(clamped != 0) != 0 && lane_id() == 0)
     atomicOr(&res[sb.s].status, FGBD_ST_DIST_CLAMPED);
+  report_sort(a);
   block_sum_f64<3>(acc, s_red);
   if (threadIdx.x == 0) {
     unsigned long long *e = edge_acc + ((size_t)sb.s * kEdgeSlots + sb.lb % kEdgeSlots) * kEdgeVals;
@@ -756,6 +767,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_wide(MergeArgs a, const int32_
   }
   if (__builtin_amdgcn_ballot_w64(clamped != 0) != 0 && lane_id() == 0)
     atomicOr(&res[sb.s].status, FGBD_ST_DIST_CLAMPED);
+  report_sort(a);
   block_sum_f64<3>(acc, s_red);
   if (threadIdx.x == 0) {
     unsigned long long *e = edge_acc + ((size_t)sb.s * kEdgeSlots + sb.lb % kEdgeSlots) * kEdgeVals;
@@ -883,6 +895,8 @@ hipError_t launch_merge(const Run &r, const int32_t *xyz, const Sorted &srt, int
   hipStream_t st = r.stream;
   a.index_bits = srt.index_bits;
   a.index_mask = srt.index_mask();
+  a.sort_done = r.sort_big ? r.sort_big + 1 : nullptr;
+  a.sort_seq = r.sort_seq;
   if (r.dt.passes > kSortPasses) {  // codes above 32 bits
     int kb = 1;  // index bits of the largest cloud the call may hold
     while (((int64_t)1 << kb) < r.pl.n_cap) ++kb;

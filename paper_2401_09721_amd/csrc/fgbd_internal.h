@@ -582,15 +582,17 @@ struct Run {
   // point order is incoherent (not for graphs handed to the caller, nor for
   // index-ordered patches)
   bool relabel_ok = false;
-  int32_t *hint = nullptr;  // host-mapped: the finalising launch stores each cloud's sweep count here
+  // host-mapped: the finalising launch stores each cloud's sweep count | hint_tag here
+  int32_t *hint = nullptr;
+  int32_t hint_tag = 0;
   // Sort route for codes of at most 32 bits: the top-digit pass and local
   // sorts unless sort_lsd.  sort_big (host-mapped, NULL: not watched): the
-  // local sort sets it when a block had to sort a range of more than
-  // kBigRange items alone; sort_ev is recorded after the sort, and
-  // *sort_pending marks the read-back outstanding.
+  // local sort sets sort_big[0] when a block had to sort a range of more
+  // than kBigRange items alone; the merge launch then stores sort_seq into
+  // sort_big[1], and *sort_pending marks the read-back outstanding.
   bool sort_lsd = false;
   int32_t *sort_big = nullptr;
-  hipEvent_t sort_ev = nullptr;
+  int32_t sort_seq = 0;
   bool *sort_pending = nullptr;
   // bound of each wait between sweeps in the in-launch sweep loop, in
   // microseconds (negative: half a second)

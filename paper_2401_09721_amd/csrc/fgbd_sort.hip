@@ -1379,12 +1379,6 @@ hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, Sorte
     (wide ? k_local_sort<true> : k_local_sort<false>)<<<dim3(a.nwin, r.dt.num_dirs), kLocalThreads, 0, r.stream>>>(
         la, r.b.items_a, r.b.items_b, r.b.rank);
     FGBD_POST(r.pf);
-    if (r.sort_big && r.sort_ev) {
-      if (hipEventRecord(r.sort_ev, r.stream) == hipSuccess)
-        *r.sort_pending = true;
-      else
-        (void)hipGetLastError();
-    }
     *sorted = {r.b.items_b, ib};
     return hipGetLastError();
   }

@@ -299,7 +299,7 @@ class Context:
         _check_outputs(self, rgb, out, res, n, max(batch, 1))
         self.reserve(prm, n, max(batch, 1))
         out = torch.empty_like(rgb) if out is None else out
-        res = new_result(self.device, max(batch, 1)) if res is None else res
+        res = _result_out(self, max(batch, 1)) if res is None else res
         sc = Schedule()
         _check(lib().fgbd_autotune(self.handle, _ptr(xyz), _ptr(rgb), n, _ptr(offsets), batch, ctypes.byref(prm),
                                    _ptr(out), _ptr(res), int(reps), ctypes.byref(sc), _stream(self)))
@@ -426,6 +426,11 @@ def new_result(device, count: int = 1) -> "object":
     return torch.zeros(RESULT_BYTES * count, dtype=torch.uint8, device=device)
 
 
+def _result_out(ctx, count: int = 1):
+    """Records for a call that writes every field of them (no fill launch)."""
+    return _torch().empty(RESULT_BYTES * count, dtype=_torch().uint8, device=ctx.device)
+
+
 def check_results(records: list) -> None:
     """Raise FgbdStallError when a decoded result carries FGBD_ST_SWEEP_STALL;
     warn on FGBD_ST_COORD_RANGE (coordinates outside the grid: the graph is
@@ -500,7 +505,7 @@ def build_slg(xyz, params=None, ctx: Optional[Context] = None, stream=None) -> S
     col = torch.empty((n, prm.k), dtype=torch.int32, device=ctx.device)
     dist2 = torch.empty((n, prm.k), dtype=torch.int32, device=ctx.device)
     p = torch.empty((n, prm.k), dtype=torch.float32, device=ctx.device)
-    res = new_result(ctx.device)
+    res = _result_out(ctx)
     g = SLGraph(col, dist2, p, res)
     gs = g.c_struct()
     _check(lib().fgbd_build_slg(ctx.handle, _ptr(xyz), n, ctypes.byref(prm), ctypes.byref(gs), _ptr(res),
@@ -591,7 +596,7 @@ def denoise(xyz, rgb, params=None, ctx: Optional[Context] = None, out=None, res=
     _check_outputs(ctx, rgb, out, res, n, 1)
     ctx.reserve(prm, n)
     out = torch.empty_like(rgb) if out is None else out
-    res = new_result(ctx.device) if res is None else res
+    res = _result_out(ctx) if res is None else res
     _check(lib().fgbd_denoise(ctx.handle, _ptr(xyz), _ptr(rgb), n, ctypes.byref(prm), _ptr(out), _ptr(res),
                               _stream(ctx, stream)))
     return out, res
@@ -634,7 +639,7 @@ def denoise_batched(xyz, rgb, offsets, params=None, ctx: Optional[Context] = Non
     _check_outputs(ctx, rgb, out, res, n, max(batch, 1))
     ctx.reserve(prm, n, max(batch, 1))
     out = torch.empty_like(rgb) if out is None else out
-    res = new_result(ctx.device, max(batch, 1)) if res is None else res
+    res = _result_out(ctx, max(batch, 1)) if res is None else res
     _check(lib().fgbd_denoise_batched(ctx.handle, _ptr(xyz), _ptr(rgb), n, _ptr(offsets), batch,
                                       ctypes.byref(prm), _ptr(out), _ptr(res), _stream(ctx, stream)))
     return out, res
@@ -653,7 +658,7 @@ def denoise_batched_fixed_q(xyz, rgb, offsets, q: int, params=None, ctx: Optiona
     _check_outputs(ctx, rgb, out, res, n, max(batch, 1))
     ctx.reserve(prm, n, max(batch, 1))
     out = torch.empty_like(rgb) if out is None else out
-    res = new_result(ctx.device, max(batch, 1)) if res is None else res
+    res = _result_out(ctx, max(batch, 1)) if res is None else res
     _check(lib().fgbd_denoise_batched_fixed_q(ctx.handle, _ptr(xyz), _ptr(rgb), n, _ptr(offsets), batch,
                                               ctypes.byref(prm), int(q), _ptr(out), _ptr(res),
                                               _stream(ctx, stream)))
@@ -695,7 +700,7 @@ def smooth_geometry(xyz, q: int, params=None, ctx: Optional[Context] = None, out
         _need_res(res, 1, ctx.device)
     ctx.reserve(prm, n)
     out = torch.empty((n, 3), dtype=torch.float32, device=ctx.device) if out is None else out
-    res = new_result(ctx.device) if res is None else res
+    res = _result_out(ctx) if res is None else res
     _check(lib().fgbd_smooth_geometry(ctx.handle, _ptr(xyz), n, ctypes.byref(prm), int(q), _ptr(out), _ptr(res),
                                       _stream(ctx, stream)))
     return out, res

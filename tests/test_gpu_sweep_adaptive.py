@@ -37,3 +37,33 @@ def test_more_sweeps_than_the_default_schedule(clouds):
                 compare_denoise(got[0][off[s]:off[s + 1]], got[1][s], xyz, rgb, prm)
         assert np.array_equal(got[0], ref[0]) and got[1] == ref[1], rep
     ctx.close()
+
+
+def test_counts_read_back_without_waiting():
+    """Calls enqueued one after another, on a context that is closed while
+    they run and on one whose counts are read between them, alternating with
+    the filter on a stored graph: the bits of a fresh context."""
+    prm = fgbd.default_params(bits=8)
+    xyz, rgb = shape_cloud(11, 3000)
+    x, c = dev(xyz, torch.int32), dev(rgb, torch.float32)
+    fresh = fgbd.Context()
+    ref, rres = fgbd.denoise(x, c, prm, ctx=fresh)
+    torch.cuda.synchronize()
+    fresh.close()
+    ctx = fgbd.Context()
+    g = fgbd.build_slg(x, prm, ctx=ctx)
+    noise, spread, _ = fgbd.estimate_noise(g, c, prm, ctx=ctx)
+    filtered = None
+    for rep in range(12):
+        closing = fgbd.Context()
+        a, ares = fgbd.denoise(x, c, prm, ctx=closing)
+        closing.close()
+        b, bres = fgbd.denoise(x, c, prm, ctx=ctx)
+        f, fres = fgbd.filter(g, c, prm, noise=noise, spread=spread, ctx=ctx)
+        if rep % 3 == 2:
+            torch.cuda.synchronize()
+        assert torch.equal(a, ref) and torch.equal(b, ref), rep
+        assert fgbd.read_result(ares) == fgbd.read_result(bres) == fgbd.read_result(rres), rep
+        filtered = f if filtered is None else filtered
+        assert torch.equal(f, filtered) and fgbd.read_result(fres)["q"] == fgbd.read_result(rres)["q"], rep
+    ctx.close()
