@@ -32,6 +32,8 @@
 // scanned counts of digit c, the cloud's count of c is P[next cloud's first
 // tile] - P[its first tile], so each tile's output offset for digit c is
 //   start[s] + (digits < c in cloud s) + (P[this tile] - P[cloud's first tile]).
+#include <type_traits>
+
 #include "fgbd_internal.h"
 
 namespace fgbd {
@@ -200,18 +202,22 @@ __device__ __forceinline__ uint64_t decode_packed_wide(const CodeGen &c, uint64_
          ((uint32_t)item & ((1u << ib) - 1u));
 }
 
-template <bool WIDE = false>
-__device__ __forceinline__ uint64_t load_item(const SortArgs &a, const CodeGen &cg, const int32_t *__restrict__ xyz,
-                                              const uint64_t *__restrict__ src, int d, int pos, int *bad) {
-  if (a.pass == 0) {
-    const int gx = xyz[3 * pos + 0], gy = xyz[3 * pos + 1], gz = xyz[3 * pos + 2];
-    const int top = (1 << a.dt.bits) - 1;
-    if ((unsigned)gx > (unsigned)top || (unsigned)gy > (unsigned)top || (unsigned)gz > (unsigned)top) *bad = 1;
-    const uint32_t code = gen_code(cg, gx, gy, gz);
-    if (WIDE) return (((uint64_t)gen_code_hi(cg, gx, gy, gz) << 32 | code) << a.ib) | (uint32_t)pos;
-    return ((uint64_t)code << 32) | (uint32_t)pos;
+// The coordinates of a thread's items, kWave apart from position base, all in
+// flight together: positions past the tile's end are clamped to its last
+// point, as a load in a branch is waited for there (16 latencies one after
+// the other were a quarter of the top-digit downsweep's time).
+__device__ __forceinline__ void load_points(const int32_t *__restrict__ xyz, int base, int end,
+                                            int (&g)[kSortItems][3]) {
+#pragma unroll
+  for (int j = 0; j < kSortItems; ++j) {
+    const int pos = min(base + j * kWave, end - 1);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) g[j][c] = xyz[3 * pos + c];
   }
-  return src[(size_t)d * a.stride + pos];
+}
+// Non-zero for a point outside the 2^bits grid.
+__device__ __forceinline__ int outside_grid(const int (&g)[3], int bits) {
+  return (int)((uint32_t)(g[0] | g[1] | g[2]) & ~0u << bits);
 }
 
 // All blocks clear the first sweep's sums and the noise moment accumulators;
@@ -528,11 +534,20 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_downsweep(SortArgs a, con
   const CodeGen cg = code_gen(a.dt, d);
   const int base = ti.begin + wave * kWave * kSortItems + lane;
   int bad = 0;
+  if (a.pass == 0) {
+    int g[kSortItems][3];
+    load_points(xyz, base, ti.end, g);
 #pragma unroll
-  for (int j = 0; j < kSortItems; ++j) {
-    const int pos = base + j * kWave;
-    item[j] = (pos < ti.end) ? load_item(a, cg, xyz, src, d, pos, &bad) : ~0ull;
+    for (int j = 0; j < kSortItems; ++j) {
+      bad |= outside_grid(g[j], a.dt.bits);
+      item[j] = (uint64_t)gen_code(cg, g[j][0], g[j][1], g[j][2]) << 32 | (uint32_t)(base + j * kWave);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kSortItems; ++j) item[j] = src[(size_t)d * a.stride + min(base + j * kWave, ti.end - 1)];
   }
+#pragma unroll
+  for (int j = 0; j < kSortItems; ++j) item[j] = base + j * kWave < ti.end ? item[j] : ~0ull;
   // pass 0: coordinates outside the grid (flagged once, by direction 0)
   if (bad && d == 0) atomicOr(&res[ti.s].status, FGBD_ST_COORD_RANGE);
   __syncthreads();
@@ -727,12 +742,7 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_upsweep(SortArgs a, const 
   const int lane = (int)lane_id();
   const int base = ti.begin + wave * kWave * kSortItems + lane;
   int g[kSortItems][3];
-#pragma unroll
-  for (int j = 0; j < kSortItems; ++j) {
-    const int pos = min(base + j * kWave, ti.end - 1);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) g[j][c] = xyz[3 * pos + c];
-  }
+  load_points(xyz, base, ti.end, g);
   const CodeGen cg = code_gen(a.dt, d);
   const int sh = msd_shift(a.dt, d);
   uint32_t run_digit = 0, run_count = 0;
@@ -768,10 +778,17 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_upsweep(SortArgs a, const 
   }
 }
 
-// The stable partition by top digit: the LSD downsweep's ranking with
-// kMsdBits ballots, per-wave digit counts in LDS, staging in digit order and
-// runs written to their offsets.  Items keep their code (code << ib | index,
-// ib = 32 unless WIDE).
+// The partition by top digit: per-wave digit counts in LDS, staging in digit
+// order and runs written to their offsets.  Items keep their code
+// (code << ib | index, ib = 32 unless WIDE).
+// Lanes next to each other mostly hold points next to each other, so equal
+// digits come in runs: the first lane of a run adds the run's length to the
+// wave's count of its digit (one LDS atomic an item instead serialises on the
+// same word: 52 us on 1M points in 8 directions against 29).  The partition
+// is then stable between the 64-point chunks of the input, not inside one,
+// where a digit may have several runs; k_local_sort orders equal codes by
+// index.  Ranks from kMsdBits ballots an item, stable inside the chunk too,
+// were 58 % of the vector instructions here: 44 us.
 template <bool WIDE>
 __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, const int32_t *__restrict__ xyz,
                                                                 uint64_t *__restrict__ dst,
@@ -779,10 +796,10 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
                                                                 fgbd_result *__restrict__ res) {
   constexpr int kPer = kMsdBins / kSortThreads;  // digits per thread: kPer t .. kPer t + kPer - 1
   static_assert(kPer == 4, "one 16-byte count load per tile row and thread");
-  __shared__ uint32_t s_wh[4][kMsdBins];
+  __shared__ __align__(16) uint32_t s_wh[4][kMsdBins / 2];  // per wave, two 16-bit counts a word, then starts
+  __shared__ uint64_t s_stage[kSortTile];
   __shared__ uint32_t s_off[kMsdBins];
   __shared__ uint32_t s_tmp[2][4];
-  __shared__ uint64_t s_stage[kSortTile];
 
   int d, tile;
   xcd_tile(d, tile);
@@ -793,7 +810,7 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
   const int lane = (int)lane_id();
   const int valid = ti.end - ti.begin;
   const int seg_end = a.sa.n_fixed >= 0 ? a.sa.n_fixed : a.sa.segs->start[ti.s + 1];
-  for (int i = t; i < 4 * kMsdBins; i += kSortThreads) (&s_wh[0][0])[i] = 0;
+  for (int i = t; i < 2 * kMsdBins; i += kSortThreads) (&s_wh[0][0])[i] = 0;
   // scanned counts of the thread's digits: the cloud's count and this tile's
   // offset inside the cloud
   const uint32_t *hd = hist + (size_t)d * a.row * kMsdBins + kPer * t;
@@ -804,48 +821,61 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
   const uint32_t off_q[kPer] = {pt.x - pf.x, pt.y - pf.y, pt.z - pf.z, pt.w - pf.w};
   const uint32_t below_q[kPer] = {pn.x - pf.x, pn.y - pf.y, pn.z - pf.z, pn.w - pf.w};
 
-  uint64_t item[kSortItems];
+  // (the index is the position: without it, a narrow item is its code)
+  std::conditional_t<WIDE, uint64_t, uint32_t> held[kSortItems];
+  auto top_of = [&](int j) { return (uint32_t)(WIDE ? (uint64_t)held[j] >> 32 : held[j]); };
   const CodeGen cg = code_gen(a.dt, d);
   // where the top digit sits in an item's upper word
   const int sh = msd_shift(a.dt, d) + (WIDE ? a.ib - 32 : 0);
   const int base = ti.begin + wave * kWave * kSortItems + lane;
   int bad = 0;
+  {
+    int g[kSortItems][3];
+    load_points(xyz, base, ti.end, g);
 #pragma unroll
-  for (int j = 0; j < kSortItems; ++j) {
-    const int pos = base + j * kWave;
-    item[j] = (pos < ti.end) ? load_item<WIDE>(a, cg, xyz, nullptr, d, pos, &bad) : ~0ull;
+    for (int j = 0; j < kSortItems; ++j) {
+      bad |= outside_grid(g[j], a.dt.bits);
+      const uint32_t code = gen_code(cg, g[j][0], g[j][1], g[j][2]);
+      if constexpr (WIDE)
+        held[j] = ((uint64_t)gen_code_hi(cg, g[j][0], g[j][1], g[j][2]) << 32 | code) << a.ib |
+                  (uint32_t)(base + j * kWave);
+      else
+        held[j] = code;
+    }
   }
   if (bad && d == 0) atomicOr(&res[ti.s].status, FGBD_ST_COORD_RANGE);
   __syncthreads();
 
-  // stable rank among the wave's equal digits (as in k_sort_downsweep);
-  // items past the tile's end have the largest digit and come last
-  uint32_t rk[kSortItems], before[kSortItems];
+  // rank among the wave's equal digits: the first lane of each run of equal
+  // digits adds the run's length to the count, and the run's lanes take its
+  // result and their place in the run
+  uint32_t rk[kSortItems];  // digit << 16 | rank
+  const uint64_t upto = ~0ull >> (63 - lane);  // lanes up to this one
+  constexpr int kGroup = 4;                    // (atomics in flight; more spill)
 #pragma unroll
-  for (int j = 0; j < kSortItems; ++j) {
-    const uint32_t digit = msd_digit((uint32_t)(item[j] >> 32), sh);
-    int32_t m[kMsdBits];
-    uint64_t vote[kMsdBits];
+  for (int g = 0; g < kSortItems; g += kGroup) {
+    uint32_t head[kGroup], dg[kGroup], both[kGroup];
 #pragma unroll
-    for (int b = 0; b < kMsdBits; ++b) {
-      m[b] = bit_mask(digit, b);
-      vote[b] = __builtin_amdgcn_ballot_w64(m[b] != 0);
+    for (int u = 0; u < kGroup; ++u) {
+      const int j = g + u;
+      const bool in = base + j * kWave < ti.end;
+      dg[u] = in ? msd_digit(top_of(j), sh) : ~0u;
+      const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(~(int)dg[u], (int)dg[u], 0x138, 0xf, 0xf, false);
+      const uint64_t heads = __builtin_amdgcn_ballot_w64(dg[u] != prev);  // (wave_shr:1; lane 0 is one)
+      head[u] = 63u - (uint32_t)__builtin_clzll(heads & upto);
+      if (in && head[u] == (uint32_t)lane) {
+        const uint64_t after = heads & ~upto;  // (no run after the last one)
+        const uint32_t next = after ? (uint32_t)__builtin_ctzll(after) : 64u;
+        both[u] = atomicAdd(&s_wh[wave][dg[u] >> 1], (next - (uint32_t)lane) << 16 * (dg[u] & 1u));
+      }
     }
-    uint32_t plo = ~0u, phi = ~0u;
 #pragma unroll
-    for (int b = 0; b < kMsdBits; ++b) {
-      plo &= ~((uint32_t)vote[b] ^ (uint32_t)m[b]);
-      phi &= ~((uint32_t)(vote[b] >> 32) ^ (uint32_t)m[b]);
+    for (int u = 0; u < kGroup; ++u) {
+      const uint32_t v = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * head[u]), (int)both[u]);
+      rk[g + u] = dg[u] << 16 | (__builtin_amdgcn_ubfe(v, 16 * (dg[u] & 1u), 16) + ((uint32_t)lane - head[u]));
     }
-    const uint64_t peers = ((uint64_t)phi << 32) | plo;
-    before[j] = count_below(peers);
-    rk[j] = __hip_atomic_load(&s_wh[wave][digit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (before[j] == 0)
-      __hip_atomic_fetch_add(&s_wh[wave][digit], (uint32_t)__popcll(peers), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_sched_barrier(0);
   }
-#pragma unroll
-  for (int j = 0; j < kSortItems; ++j) rk[j] += before[j];
   __syncthreads();
 
   // per digit: exclusive over the tile's digits and over the cloud's digit
@@ -856,30 +886,40 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
     uint32_t c[4][kPer], ex_in[kPer], ex_below[kPer];
     uint32_t run_in = 0, run_below = 0;
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
+    for (int w = 0; w < 4; ++w) {
+      const uint2 v = *reinterpret_cast<const uint2 *>(&s_wh[w][2 * t]);
+      c[w][0] = v.x & 0xffffu;
+      c[w][1] = v.x >> 16;
+      c[w][2] = v.y & 0xffffu;
+      c[w][3] = v.y >> 16;
+    }
 #pragma unroll
-      for (int w = 0; w < 4; ++w) c[w][q] = s_wh[w][kPer * t + q];
+    for (int q = 0; q < kPer; ++q) {
       ex_in[q] = run_in;
       run_in += c[0][q] + c[1][q] + c[2][q] + c[3][q];
       ex_below[q] = run_below;
       run_below += below_q[q];
     }
     block_exclusive_scan2_256(run_in, run_below, s_tmp);
+    uint32_t e[kPer];
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-      const uint32_t e = run_in + ex_in[q];
-      s_wh[0][kPer * t + q] = e;
-      s_wh[1][kPer * t + q] = e + c[0][q];
-      s_wh[2][kPer * t + q] = e + c[0][q] + c[1][q];
-      s_wh[3][kPer * t + q] = e + c[0][q] + c[1][q] + c[2][q];
-      s_off[kPer * t + q] = (uint32_t)ti.seg_start + run_below + ex_below[q] + off_q[q] - e;
+      e[q] = run_in + ex_in[q];
+      s_off[kPer * t + q] = (uint32_t)ti.seg_start + run_below + ex_below[q] + off_q[q] - e[q];
+    }
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      *reinterpret_cast<uint2 *>(&s_wh[w][2 * t]) = make_uint2(e[0] | e[1] << 16, e[2] | e[3] << 16);
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) e[q] += c[w][q];
     }
   }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kSortItems; ++j) {
-    const uint32_t digit = msd_digit((uint32_t)(item[j] >> 32), sh);
-    s_stage[s_wh[wave][digit] + rk[j]] = item[j];
+    if (base + j * kWave < ti.end)
+      s_stage[reinterpret_cast<const uint16_t *>(s_wh[wave])[rk[j] >> 16] + (rk[j] & 0xffffu)] =
+          WIDE ? (uint64_t)held[j] : (uint64_t)held[j] << 32 | (uint32_t)(base + j * kWave);
   }
   __syncthreads();
   uint64_t *out = dst + (size_t)d * a.stride;
@@ -899,16 +939,17 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
   // The cloud's first tile records the range of each of the cloud's windows,
   // the buckets that start in it: the range's first position, the digit of the
   // items there, the first digit whose bucket starts at or after the window's
-  // base, and (in the cloud's last window) the digit after the cloud's last.  A binary search over the bucket starts (here a bucket starts
-  // at s_off + s_wh[0], the first tile's offset inside every bucket being 0)
-  // finds the first digit whose bucket starts at or after a position; an
-  // empty bucket shares the start of the next one that is not.  One store per
-  // window; an atomic minimum per bucket took 45 us instead of 26 on 64
+  // base, and (in the cloud's last window) the digit after the cloud's last.
+  // A binary search over the bucket starts finds the first digit whose bucket
+  // starts at or after a position; an empty bucket shares the start of the
+  // next one that is not.  One store per window; an atomic minimum per bucket took 45 us instead of 26 on 64
   // clouds of 4k points, whose every tile is a first one.
   if (tile == ti.first) {  // (uniform)
     __syncthreads();       // the staged tile has been read
-    uint32_t *s_start = s_wh[1];
-    for (int c = t; c < kMsdBins; c += kSortThreads) s_start[c] = s_off[c] + s_wh[0][c];
+    uint32_t *s_start = reinterpret_cast<uint32_t *>(s_stage);
+    // (the first tile's offset inside every bucket is 0)
+    for (int c = t; c < kMsdBins; c += kSortThreads)
+      s_start[c] = s_off[c] + reinterpret_cast<const uint16_t *>(s_wh[0])[c];
     __syncthreads();
     auto first_at = [&](uint32_t pos) {
       int l = 0, h = kMsdBins;
@@ -1018,6 +1059,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   uint16_t *const s_of = reinterpret_cast<uint16_t *>(s_two + kBins / 2 + 2);
   __shared__ uint32_t s_w[16];
   __shared__ unsigned long long s_max;
+  __shared__ int s_swap;  // equal codes out of index order
   // slow path
   uint32_t(*const s_cnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s_key);  // [kLocalWaves][256]
   uint32_t *const s_base = s_bin;                                          // [256]
@@ -1066,6 +1108,8 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
     else
       return (uint64_t)decode_packed(cg, (uint32_t)(v >> 32)) << 32 | (uint32_t)v;
   };
+  // (final forms are equal above the index where the codes are)
+  auto same_code = [&](uint64_t u, uint64_t v) { return ((u ^ v) >> (WIDE ? a.ib : 32)) == 0; };
   uint64_t *out = dst + dbase;
 
   if (R <= kLocalCap) {
@@ -1085,7 +1129,10 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
       item[j] = items[lo + min(j * kLocalThreads + t, R - 1)];
     }
     for (int i = t; i < kBins / 2 + 2; i += kLocalThreads) s_bin[i] = 0u;
-    if (t == 0) s_max = 0;
+    if (t == 0) {
+      s_max = 0;
+      s_swap = 0;
+    }
     __syncthreads();
     // (codes of coordinates outside the grid can exceed the range's bits: the
     // minimum keeps their bins inside the table)
@@ -1206,7 +1253,36 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
       for (int j = 0; j < kLocalItems; ++j) {
         if (j >= J) break;
         const int s = j * kLocalThreads + t;
-        if (s < R) out[lo + s] = (uint64_t)s_two[s] << 32 | s_key[s];
+        if (s < R) {
+          const uint64_t v = (uint64_t)s_two[s] << 32 | s_key[s];
+          out[lo + s] = v;
+          if (s + 1 < R && s_two[s + 1] == s_two[s]) {  // (the upper word: rarely equal but for equal codes)
+            const uint64_t nx = (uint64_t)s_two[s + 1] << 32 | s_key[s + 1];
+            if (same_code(v, nx) && nx < v) s_swap = 1;
+          }
+        }
+      }
+      __syncthreads();
+      if (s_swap == 0) return;
+      // Points of one voxel that the top-digit pass left out of index order:
+      // every item counts the smaller ones among its equals.
+      for (int s = t; s < R; s += kLocalThreads) {
+        const uint64_t v = (uint64_t)s_two[s] << 32 | s_key[s];
+        int r = s, u = s - 1;
+        for (; u >= 0; --u) {
+          const uint64_t o = (uint64_t)s_two[u] << 32 | s_key[u];
+          if (!same_code(v, o)) break;
+          r -= o > v ? 1 : 0;
+        }
+        for (u = s + 1; u < R; ++u) {
+          const uint64_t o = (uint64_t)s_two[u] << 32 | s_key[u];
+          if (!same_code(v, o)) break;
+          r += o < v ? 1 : 0;
+        }
+        if (r == s) continue;
+        const uint32_t id = (uint32_t)v & id_mask;
+        out[lo + r] = v;
+        if (id < (uint32_t)a.stride) rank[dbase + id] = (uint32_t)(lo + r);
       }
       return;
     }
@@ -1216,8 +1292,10 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   // ---- slow path: the block sorts its range alone, LSD over 8-bit digits of
   // the code less the range's base, in chunks of kSlowItems * kLocalThreads
   // items per round, through the two item buffers (its own range of each).
-  // An odd number of passes (a first pass of digit 0, a plain stable copy,
-  // when needed) ends in dst, in the final form.
+  // The first pass puts the points of each 64-point chunk of the input that
+  // share a top digit, which lie next to each other, into index order; an
+  // even number of stable ones (the last of digit 0 when needed) then ends in
+  // dst, in the final form.
   if (a.big && R > kBigRange && t == 0) *a.big = 1;  // (only ever set to 1)
   if (t == 0) s_max = 0;
   __syncthreads();
@@ -1230,17 +1308,50 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   __syncthreads();
   const unsigned long long kmax = s_max;
   int P = kmax ? (64 - __clzll(kmax) + 7) / 8 : 0;
-  const int extra = (P % 2 == 0) ? 1 : 0;
-  P += extra;
-  for (int q = 0; q < P; ++q) {
+  P += (P & 1) + 1;
+  {
+    const int dsh = sh + (WIDE ? a.ib - 32 : 0);
+    auto put = [&](int at, uint64_t v) {
+      if (P > 1) {
+        out[lo + at] = v;
+      } else {
+        const uint32_t idx = (uint32_t)v & id_mask;
+        out[lo + at] = final_item(v);
+        if (idx < (uint32_t)a.stride) rank[dbase + idx] = (uint32_t)(lo + at);
+      }
+    };
+    const uint32_t first = (uint32_t)(a.sa.n_fixed >= 0 ? 0 : a.sa.segs->start[ti.s]);
+    auto near = [&](uint64_t u, uint64_t v) {
+      return msd_digit((uint32_t)(u >> 32), dsh) == msd_digit((uint32_t)(v >> 32), dsh) &&
+             ((uint32_t)u & id_mask) - first >> 6 == ((uint32_t)v & id_mask) - first >> 6;
+    };
+    for (int s = t; s < R; s += kLocalThreads) {
+      const uint64_t v = items[lo + s];
+      const uint32_t idx = (uint32_t)v & id_mask;
+      int r = s;
+      for (int u = s - 1; u >= 0 && s - u < kWave; --u) {
+        const uint64_t o = items[lo + u];
+        if (!near(v, o)) break;
+        r -= ((uint32_t)o & id_mask) > idx ? 1 : 0;
+      }
+      for (int u = s + 1; u < R && u - s < kWave; ++u) {
+        const uint64_t o = items[lo + u];
+        if (!near(v, o)) break;
+        r += ((uint32_t)o & id_mask) < idx ? 1 : 0;
+      }
+      put(r, v);
+    }
+    __syncthreads();
+  }
+  for (int q = 1; q < P; ++q) {
     const uint64_t *rd = ((q & 1) == 0 ? src : dst) + dbase;
     uint64_t *wr = ((q & 1) == 0 ? dst : src) + dbase;
     const bool last = q == P - 1;
-    const int shift = 8 * (q - extra);  // q < extra: the copy pass (digit 0)
+    const int shift = 8 * (q - 1);
     if (t < 256) s_base[t] = 0u;
     __syncthreads();
     for (int s = t; s < R; s += kLocalThreads) {
-      const uint32_t digit = q < extra ? 0u : (uint32_t)(rel(rd[lo + s]) >> shift) & 255u;
+      const uint32_t digit = (uint32_t)(rel(rd[lo + s]) >> shift) & 255u;
       atomicAdd(&s_base[digit], 1u);
     }
     __syncthreads();
@@ -1261,7 +1372,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
 #pragma unroll
       for (int j = 0; j < kSlowItems; ++j) {
         const int s = c0 + (wave * kSlowItems + j) * kWave + lane;
-        dg[j] = s >= R ? 255u : (q < extra ? 0u : (uint32_t)(rel(it[j]) >> shift) & 255u);
+        dg[j] = s >= R ? 255u : (uint32_t)(rel(it[j]) >> shift) & 255u;
       }
 #pragma unroll
       for (int j = 0; j < kSlowItems; ++j) rk[j] = wave_rank8(dg[j], s_cnt[wave], bf[j]);

@@ -68,3 +68,15 @@ def test_batch_windows(sizes):
     for s, (xyz, rgb) in enumerate(clouds):
         if len(xyz):
             compare_denoise(out[off[s]:off[s + 1]], recs[s], xyz, rgb, prm)
+
+
+@pytest.mark.parametrize("bits", [10, 11])
+@pytest.mark.parametrize("voxels,times", [(2, 100), (2, 3000), (3, 1000), (7, 300), (64, 33), (65, 64), (300, 60)])
+def test_duplicates_in_turn(bits, voxels, times):
+    """A few voxels again and again in turn, so that every 64-point chunk of
+    the input has several runs of each top digit: equal codes keep index
+    order, in ranges sorted in LDS and in longer ones."""
+    rng = np.random.default_rng(voxels)
+    v = rng.integers(0, 1 << bits, size=(voxels, 3))
+    g = np.concatenate([np.tile(v, (times, 1)), rng.integers(0, 1 << bits, size=(777, 3)), np.tile(v[::-1], (5, 1))])
+    check_graph(g.astype(np.int32), fgbd.default_params(bits=bits, num_dirs=8, window=4, k=8))
