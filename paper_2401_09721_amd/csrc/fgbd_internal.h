@@ -382,18 +382,29 @@ __device__ __forceinline__ void fill_exp_table(double sg, double *s_exp) {
 template <int KB>
 __device__ __forceinline__ void row_weights(const int (&cv)[KB], const int (&dv)[KB], double sg,
                                             const double *s_exp, float (&pw)[KB]) {
-  const double inv = sg > 0.0 ? 1.0 / (sg * sg) : 0.0;
+  // every slot reads the table (an empty slot its first entry), all reads in
+  // flight together; the few gaps past its end are put right after (a branch
+  // and a wait for each slot: 54.3 us for the noise launch on 1M points
+  // against 50.6)
   double w[KB];
-  double s = 0.0;
-  const int d0 = dv[0];
+  uint32_t gap[KB], top = 0;
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
-    w[k] = 0.0;
-    if (cv[k] >= 0) {
-      const int gap = dv[k] - d0;
-      w[k] = gap < kExpTable ? s_exp[gap] : (sg > 0.0 ? exp(-(double)gap * inv) : 0.0);
-      s += w[k];
-    }
+    gap[k] = cv[k] >= 0 ? (uint32_t)(dv[k] - dv[0]) : 0u;
+    top = max(top, gap[k]);
+    w[k] = s_exp[min(gap[k], (uint32_t)kExpTable - 1u)];
+  }
+  if (__builtin_amdgcn_ballot_w64(top >= (uint32_t)kExpTable) != 0) {
+    const double inv = sg > 0.0 ? 1.0 / (sg * sg) : 0.0;
+#pragma unroll
+    for (int k = 0; k < KB; ++k)
+      if (gap[k] >= (uint32_t)kExpTable) w[k] = sg > 0.0 ? exp(-(double)(int)gap[k] * inv) : 0.0;
+  }
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < KB; ++k) {
+    w[k] = cv[k] >= 0 ? w[k] : 0.0;
+    s += w[k];
   }
   const double rs = s > 0.0 ? 1.0 / s : 0.0;
 #pragma unroll

@@ -408,6 +408,16 @@ __device__ double tridiag_eig_groups(const double (&d)[DT], const double (&e)[DT
 // The FSLR spread (and optionally the 3x3 eigenvalues) of one complete patch
 // held in registers (channel c, entry k: the point, then its PT neighbours),
 // in FP64, after writing the patch's three rows to LDS.
+// v / N, rounded to nearest like the division: the product with the rounded
+// reciprocal, corrected by its exact remainder (Markstein's division; three
+// instructions instead of the general one's twelve).
+template <int N>
+__device__ __forceinline__ double div_by(double v) {
+  constexpr double y = 1.0 / (double)N;
+  const double q = v * y;
+  return fma(fma(-(double)N, q, v), y, q);
+}
+
 template <int PT, bool EIG3>
 __device__ __forceinline__ void patch_stats(int64_t i, const float (&v)[3][PT + 1], float *r0, float *r1, float *r2,
                                             double *__restrict__ spread, float *__restrict__ eig3) {
@@ -423,7 +433,7 @@ __device__ __forceinline__ void patch_stats(int64_t i, const float (&v)[3][PT + 
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k <= PT; ++k) s += (double)v[c][k];
-    mean[c] = s / (double)(PT + 1);
+    mean[c] = div_by<PT + 1>(s);
   }
 #pragma unroll
   for (int k = 0; k <= PT; ++k) {
@@ -442,7 +452,7 @@ __device__ __forceinline__ void patch_stats(int64_t i, const float (&v)[3][PT + 
   const double invD = 1.0 / (double)(PT + 1);
 #pragma unroll
   for (int m = 0; m < 6; ++m) cov[m] *= invD;
-  spread[i] = (sqrt(cov[0]) + sqrt(cov[3]) + sqrt(cov[5])) / 3.0;
+  spread[i] = div_by<3>(sqrt(cov[0]) + sqrt(cov[3]) + sqrt(cov[5]));
   if (EIG3) {
     double ev[3];
     eig3_sym(cov[0], cov[1], cov[2], cov[3], cov[4], cov[5], ev);
@@ -738,6 +748,15 @@ __global__ __launch_bounds__(kBlock) void k_noise(NoiseArgs a, const int32_t *__
 }
 
 
+// The value of the lane four above, in a ring of 16 lanes.
+__device__ __forceinline__ double next_block(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  constexpr int kRor12 = 0x12c;  // (rotating by 12 down is by 4 up)
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, kRor12, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kRor12, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 // The same statistics with the tile's patch moments as one FP64 Gram matrix
 // on the matrix cores.  Each patch row (one channel of one patch) becomes the
 // vector of its D = 9 colour entries and three channel indicators (1 in the
@@ -749,13 +768,16 @@ __global__ __launch_bounds__(kBlock) void k_noise(NoiseArgs a, const int32_t *__
 // 4 x 4 products per instruction, each summing four rows.  In block b of an
 // instruction, lane l supplies A[i][k] and B[k][j] with b = (l / 4) % 4,
 // i = j = l % 4, k = l / 16 (the row), and holds C[l / 16][l % 4] (layout
-// checked on the device with one-hot operands).  Per pair of row groups
-// (8 rows): one instruction each for blocks (0,0), (0,1), (0,2), (1,1), and
-// one for (1,2), (2,2) of both groups, so 3 instructions instead of the 2
-// that a 16 x 16 product would need at six times the cost per instruction
-// on this GPU (measured).  Independent accumulators, operands read from LDS
-// without branches, and the partial sums added in a fixed order.  Products
-// of floats are exact in FP64; the accumulation order is fixed.
+// checked on the device with one-hot operands).  Per row group (4 rows) one
+// instruction for blocks (0,0), (1,1), (2,2), whose operands are one register,
+// and one for (0,1), (1,2), (2,0), whose second operand is the first one
+// rotated by a block inside 16 lanes; the fourth block is spare.  So a group
+// takes one LDS read and one conversion to FP64 (a quarter-rate instruction)
+// a lane.  Blocks (0,0), (0,1), (0,2), (1,1) in one instruction and (1,2),
+// (2,2) of two groups in another, 3 instead of 4 for two groups, took six of
+// each: 50.6 us on 1M points against 44.4.  Independent accumulators, operands
+// read without branches, and the partial sums added in a fixed order.
+// Products of floats are exact in FP64; the accumulation order is fixed.
 template <int PT, bool EIG3, bool FUSE>
 __global__ __launch_bounds__(kBlock, 4) void k_noise_mfma(NoiseArgs a, const int32_t *__restrict__ col,
                                                        const float *__restrict__ rgb_in, double *__restrict__ spread,
@@ -771,14 +793,13 @@ __global__ __launch_bounds__(kBlock, 4) void k_noise_mfma(NoiseArgs a, const int
   // the accumulators stay in place across its iterations
   const int wave = __builtin_amdgcn_readfirstlane(t / kWave), lane = (int)lane_id();
   const int bsel = (lane >> 2) & 3, inner = lane & 3, krow = lane >> 4;
-  // instruction 1 (per row group): blocks (0,0), (0,1), (0,2), (1,1)
-  const int p1 = bsel == 3 ? 1 : 0, q1 = bsel == 3 ? 1 : bsel;
-  // instruction 2 (per pair of groups): blocks (1,2), (2,2) of group 2P and of group 2P + 1
-  const int p2 = (bsel & 1) ? 2 : 1, g2 = bsel >> 1;
-  const int fa1 = 4 * p1 + inner, fb1 = 4 * q1 + inner, fa2 = 4 * p2 + inner, fb2 = 8 + inner;
-  const int pairs = 3 * TP / 8;  // pairs of four-row groups
+  const int fg = 4 * (bsel % 3) + inner;  // the lane's feature (block 3: group 0 again, for the rotation)
+  const int groups = 3 * TP / 4;          // four-row groups
   constexpr int kWaves = kBlock / kWave;
-  double c1[4] = {0.0, 0.0, 0.0, 0.0}, c2[2] = {0.0, 0.0};
+  constexpr int U = 4;  // groups per step
+  double c1[U], c2[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) c1[u] = c2[u] = 0.0;
 
   const SegBlock sb = seg_block(a.sa, kGridNoise);
   // a renumbered cloud reads its graph and colours in scan-order-0 numbering
@@ -826,21 +847,14 @@ __global__ __launch_bounds__(kBlock, 4) void k_noise_mfma(NoiseArgs a, const int
       }
     }
     __syncthreads();
-    // two pairs of row groups per step (P and P + kWaves), six independent
-    // instructions
-    for (int pp = wave; pp < pairs; pp += 2 * kWaves) {
+    for (int g0 = wave; g0 < groups; g0 += U * kWaves) {  // (3 TP / 4 is a multiple of U kWaves)
+      double x[U];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int P = pp + u * kWaves;
-        if (P < pairs) {  // uniform over the wave
-          const float *r0 = s_v + (size_t)(8 * P + krow) * W;  // group 2P
-          const float *r1 = r0 + 4 * W;                        // group 2P + 1
-          const float *r2 = r0 + (size_t)(4 * g2) * W;         // group 2P + g2
-          const double a0 = r0[fa1], b0 = r0[fb1], a1 = r1[fa1], b1 = r1[fb1], a2 = r2[fa2], b2 = r2[fb2];
-          c1[2 * u] = __builtin_amdgcn_mfma_f64_4x4x4f64(a0, b0, c1[2 * u], 0, 0, 0);
-          c1[2 * u + 1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a1, b1, c1[2 * u + 1], 0, 0, 0);
-          c2[u] = __builtin_amdgcn_mfma_f64_4x4x4f64(a2, b2, c2[u], 0, 0, 0);
-        }
+      for (int u = 0; u < U; ++u) x[u] = (double)s_v[(size_t)(4 * (g0 + u * kWaves) + krow) * W + fg];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        c1[u] = __builtin_amdgcn_mfma_f64_4x4x4f64(x[u], x[u], c1[u], 0, 0, 0);
+        c2[u] = __builtin_amdgcn_mfma_f64_4x4x4f64(x[u], next_block(x[u]), c2[u], 0, 0, 0);
       }
     }
     __syncthreads();
@@ -852,10 +866,14 @@ __global__ __launch_bounds__(kBlock, 4) void k_noise_mfma(NoiseArgs a, const int
   // in 3 * TP * W floats).
   double(*s_g)[256] = reinterpret_cast<double(*)[256]>(s_v);
   const double tot1 = (c1[0] + c1[1]) + (c1[2] + c1[3]);
-  const double tot2h = c2[0] + c2[1];
-  const double tot2 = tot2h + __shfl_xor(tot2h, 8, kWave);  // the two groups' halves of (1,2), (2,2)
-  s_g[wave][(4 * p1 + krow) * 16 + 4 * q1 + inner] = tot1;
-  if (bsel < 2) s_g[wave][(4 * p2 + krow) * 16 + 8 + inner] = tot2;
+  const double tot2 = (c2[0] + c2[1]) + (c2[2] + c2[3]);
+  if (bsel < 3) {
+    s_g[wave][(4 * bsel + krow) * 16 + 4 * bsel + inner] = tot1;
+    if (bsel < 2)
+      s_g[wave][(4 * bsel + krow) * 16 + 4 * (bsel + 1) + inner] = tot2;
+    else  // (2,0), stored as (0,2)
+      s_g[wave][inner * 16 + 8 + krow] = tot2;
+  }
   __syncthreads();
   const double gsum = (s_g[0][t] + s_g[1][t]) + (s_g[2][t] + s_g[3][t]);
   __syncthreads();
