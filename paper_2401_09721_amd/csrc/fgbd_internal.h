@@ -379,8 +379,9 @@ __device__ __forceinline__ void fill_exp_table(double sg, double *s_exp) {
     s_exp[g] = sg > 0.0 ? exp(-(double)g * inv) : (g == 0 ? 1.0 : 0.0);
 }
 
+// Returns the factor that normalises the row (0 for a row without edges).
 template <int KB>
-__device__ __forceinline__ void row_weights(const int (&cv)[KB], const int (&dv)[KB], double sg,
+__device__ __forceinline__ double row_weights(const int (&cv)[KB], const int (&dv)[KB], double sg,
                                             const double *s_exp, float (&pw)[KB]) {
   // every slot reads the table (an empty slot its first entry), all reads in
   // flight together; the few gaps past its end are put right after (a branch
@@ -409,6 +410,7 @@ __device__ __forceinline__ void row_weights(const int (&cv)[KB], const int (&dv)
   const double rs = s > 0.0 ? 1.0 / s : 0.0;
 #pragma unroll
   for (int k = 0; k < KB; ++k) pw[k] = (float)(w[k] * rs);
+  return rs;
 }
 
 // ---------------------------------------------------------------- control

@@ -40,6 +40,27 @@ namespace {
 // T's diagonal per point (the forward call stores it with p in saved, so the
 // backward steps read 4 bytes per point instead of the first slot of each
 // neighbour row).
+// KT = 8: instead of dp, what the steps derive p and dp from (see PolyRow),
+// in dp's place: 24 bytes a point where p and dp are 64.
+struct PolyRow {
+  double scale;  // the row's normalising factor, -1 when a gap does not fit its byte
+  double mean;   // sum_k' p_ik' a_ik'
+};
+constexpr uint32_t kPolyGap = 255;  // gaps of a packed row are below this
+// dp of a slot (the same operations wherever it is formed)
+__device__ __forceinline__ float poly_dp(float pw, double a_scale, int gap, double mean) {
+  return (float)((double)pw * fma(a_scale, (double)gap, -mean));
+}
+__device__ __forceinline__ double poly_a_scale(double sg) { return sg > 0.0 ? 2.0 / (sg * sg * sg) : 0.0; }
+template <int KB>
+__device__ __forceinline__ double poly_mean(const float (&pw)[KB], const int (&cv)[KB], const int (&dv)[KB],
+                                            double a_scale) {
+  double m = 0.0;
+#pragma unroll
+  for (int k = 0; k < KB; ++k)
+    if (cv[0] >= 0 && cv[k] >= 0) m = fma((double)pw[k] * a_scale, (double)(dv[k] - dv[0]), m);
+  return m;
+}
 template <int KT>
 __global__ __launch_bounds__(kBlock) void k_poly_weights(int32_t n, int32_t k_rt, const int32_t *__restrict__ col,
                                                          const int32_t *__restrict__ dist2,
@@ -70,36 +91,34 @@ __global__ __launch_bounds__(kBlock) void k_poly_weights(int32_t n, int32_t k_rt
       }
     }
     float pw[KB];
-    row_weights<KB>(cv, dv, sg, s_exp, pw);
+    const double rs = row_weights<KB>(cv, dv, sg, s_exp, pw);
     if (diag) diag[i] = cv[0] >= 0 ? 0.5f : 1.0f;  // T's diagonal: 1/2 with edges, 1 without
-    if (KT == 8) {
+    const double a_scale = poly_a_scale(sg);
+    if constexpr (KT == 8) {
       float4 *pr = reinterpret_cast<float4 *>(p + i * 8);
       pr[0] = make_float4(pw[0], pw[1], pw[2], pw[3]);
       pr[1] = make_float4(pw[4], pw[5], pw[6], pw[7]);
+      uint32_t gaps[2] = {0, 0};
+      bool fits = true;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const uint32_t gap = cv[k] >= 0 ? (uint32_t)(dv[k] - dv[0]) : 0u;
+        fits &= gap < kPolyGap;
+        gaps[k >> 2] |= (gap & 255u) << (8 * (k & 3));
+      }
+      PolyRow *rows = reinterpret_cast<PolyRow *>(dp);
+      rows[i] = {fits ? rs : -1.0, poly_mean<KB>(pw, cv, dv, a_scale)};
+      reinterpret_cast<uint2 *>(rows + n)[i] = make_uint2(gaps[0], gaps[1]);
     } else {
 #pragma unroll
       for (int k = 0; k < KB; ++k)
         if (k < K) p[i * K + k] = pw[k];
-    }
-    if (dp) {
-      const double a_scale = sg > 0.0 ? 2.0 / (sg * sg * sg) : 0.0;
-      float dw[KB];
-      double pa = 0.0;
+      const double mean = poly_mean<KB>(pw, cv, dv, a_scale);
 #pragma unroll
-      for (int k = 0; k < KB; ++k)
-        if (k < K && cv[0] >= 0 && cv[k] >= 0) pa += (double)pw[k] * a_scale * (double)(dv[k] - dv[0]);
-#pragma unroll
-      for (int k = 0; k < KB; ++k)
-        dw[k] = (k < K && cv[0] >= 0 && cv[k] >= 0) ? (float)((double)pw[k] * (a_scale * (double)(dv[k] - dv[0]) - pa))
-                                                    : 0.0f;
-      if (KT == 8) {
-        float4 *dr = reinterpret_cast<float4 *>(dp + i * 8);
-        dr[0] = make_float4(dw[0], dw[1], dw[2], dw[3]);
-        dr[1] = make_float4(dw[4], dw[5], dw[6], dw[7]);
-      } else {
-#pragma unroll
-        for (int k = 0; k < KB; ++k)
-          if (k < K) dp[i * K + k] = dw[k];
+      for (int k = 0; k < KB; ++k) {
+        if (k < K) {
+          dp[i * K + k] = (cv[0] >= 0 && cv[k] >= 0) ? poly_dp(pw[k], a_scale, dv[k] - dv[0], mean) : 0.0f;
+        }
       }
     }
   }
@@ -231,12 +250,27 @@ __device__ __forceinline__ void st3(float *__restrict__ x, int64_t i, float a, f
 
 // One sweep x_k = T x_{k-1} (k >= 1) into saved[k].  The last sweep
 // (k == ncoef - 1) also forms out = sum_k c_k x_k from the saved iterates.
+// KT = 8: p and dp are formed again from the row's gaps, with the operations
+// and so the bits of k_poly_weights: a step is bound by the bytes of the
+// graph, and 2M points read 112 MB of it so instead of 192 (46 us a step with
+// stored p and dp, 36 so).
 template <int KT>
 __global__ __launch_bounds__(kBlock) void k_poly_step(int32_t n, int32_t k_rt, int k, int ncoef,
-                                                      const int32_t *__restrict__ col, const float *__restrict__ p,
-                                                      const float *__restrict__ dp, const float *__restrict__ coef,
-                                                      float *__restrict__ saved, float *__restrict__ out) {
+                                                      const int32_t *__restrict__ col,
+                                                      const int32_t *__restrict__ dist2,
+                                                      const double *__restrict__ sigma_g,
+                                                      const float *__restrict__ p, const float *__restrict__ dp,
+                                                      const float *__restrict__ coef, float *__restrict__ saved,
+                                                      float *__restrict__ out) {
+  __shared__ double s_exp[KT == 8 ? kExpTable : 1];
   const int K = KT > 0 ? KT : k_rt;
+  double a_scale = 0.0;
+  if constexpr (KT == 8) {
+    const double sg = *sigma_g;
+    fill_exp_table(sg, s_exp);
+    a_scale = poly_a_scale(sg);
+    __syncthreads();
+  }
   const size_t S = (size_t)n * 3;
   const float *xp = saved + (size_t)(k - 1) * S;
   float *xs = saved + (size_t)k * S;
@@ -248,13 +282,26 @@ __global__ __launch_bounds__(kBlock) void k_poly_step(int32_t n, int32_t k_rt, i
     int c0;
     if (KT == 8) {
       const int4 *cr = reinterpret_cast<const int4 *>(col + i * 8);
-      const float4 *pr = reinterpret_cast<const float4 *>(p + i * 8);
-      const float4 *dr = reinterpret_cast<const float4 *>(dp + i * 8);
       const int4 ca = cr[0], cb = cr[1];
-      const float4 pa = pr[0], pb = pr[1], da = dr[0], db = dr[1];
+      const PolyRow *rows = reinterpret_cast<const PolyRow *>(dp);
+      const PolyRow row = rows[i];
+      const uint2 gaps = reinterpret_cast<const uint2 *>(rows + n)[i];
       const int cv[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
-      const float pv[8] = {pa.x, pa.y, pa.z, pa.w, pb.x, pb.y, pb.z, pb.w};
-      const float dv[8] = {da.x, da.y, da.z, da.w, db.x, db.y, db.z, db.w};
+      float pv[8], dv[8];
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        const uint32_t gap = (kk < 4 ? gaps.x : gaps.y) >> (8 * (kk & 3)) & 255u;
+        const float w = (float)(s_exp[gap] * row.scale);
+        pv[kk] = cv[kk] >= 0 ? w : 0.0f;
+        dv[kk] = cv[kk] >= 0 ? poly_dp(w, a_scale, (int)gap, row.mean) : 0.0f;
+      }
+      if (row.scale < 0.0) {  // a gap past its byte
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+          pv[kk] = p[8 * i + kk];
+          dv[kk] = cv[kk] >= 0 ? poly_dp(pv[kk], a_scale, dist2[8 * i + kk] - dist2[8 * i], row.mean) : 0.0f;
+        }
+      }
       c0 = cv[0];
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
@@ -318,10 +365,19 @@ __global__ __launch_bounds__(kBlock) void k_poly_first(int32_t n, int ncoef, con
                                                        const float *__restrict__ coef, float *__restrict__ saved,
                                                        float *__restrict__ out) {
   const float c0 = coef[0];
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < 3 * (int64_t)n; i += (int64_t)gridDim.x * kBlock) {
-    const float v = x[i];
-    saved[i] = v;
-    if (ncoef == 1) out[i] = c0 * v;
+  constexpr int U = 8;  // values in flight per thread
+  const int64_t m = 3 * (int64_t)n, stride = (int64_t)gridDim.x * kBlock;
+  for (int64_t i0 = (int64_t)blockIdx.x * kBlock + threadIdx.x; i0 < m; i0 += U * stride) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = x[min(i0 + u * stride, m - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + u * stride;
+      if (i >= m) break;
+      saved[i] = v[u];
+      if (ncoef == 1) out[i] = c0 * v[u];
+    }
   }
 }
 
@@ -357,8 +413,15 @@ __global__ __launch_bounds__(kBlock) void k_poly_ptrans(int32_t n, const int32_t
 // <z_m[j], u_m[j]> / 2 from the saved u_m and the coefficient product
 // <g[j], x_{m-1}[j]> (and <g[j], x_m[j]> at the last step, where
 // z_m = c_m g).  Only the adjoint is gathered.
-template <int KT>
-__global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, int m, int last, int nb, int ncoef,
+// The in-edges of a block's kBlock points are consecutive, so the block reads
+// their ids and weights in order, gathers an edge a lane, and leaves weights
+// and gathered values in LDS, where each point then adds its own, in the
+// edges' order.  With a point's edges read by its lane, every load touched 16
+// lines and the lines were read 2.7 times from L2: 64 us a step on 2M points,
+// 56 so.
+constexpr int kBackEdges = 8 * kBlock;  // edges in LDS at a time
+template <int KT, bool LAST>
+__global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, int m, int nb, int ncoef,
                                                       const float *__restrict__ diag, const int32_t *__restrict__ off,
                                                       const int32_t *__restrict__ tsrc, const float *__restrict__ pt,
                                                       const float *__restrict__ coef, const float *__restrict__ g,
@@ -366,77 +429,87 @@ __global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, i
                                                       float *__restrict__ zout, double *__restrict__ sig_part,
                                                       double *__restrict__ cpart) {
   __shared__ double s_red[8 * 3];
+  // (a slot in eight is left out: rows of eight edges start in different banks)
+  __shared__ float s_e[4][kBackEdges + kBackEdges / 8];
   const int K = KT > 0 ? KT : k_rt;
+  const int t = threadIdx.x;
   const float cm = coef[m], cm1 = coef[m - 1];
   const size_t S = (size_t)n * 3;
   const float *xprev = saved + (size_t)(m - 1) * S;
   const float *xcur = saved + (size_t)m * S;
   const float *um = saved + (size_t)(ncoef + m - 1) * S;
   // z_{m+1} is c_m g on the last step (m = ncoef - 1), else the previous step's
-  // output; <g, x_m> is needed on the last step only (yrow reads x_{m-1} again
-  // otherwise, from cache)
-  const float *zsrc = last ? g : zin;
-  const float zs = last ? cm : 1.0f;
-  const float *yrow = last ? xcur : xprev;
+  // output; <g, x_m> is needed on the last step only
+  const float *zsrc = LAST ? g : zin;
+  const float zs = LAST ? cm : 1.0f;
   // acc[0]: sigma_g term; acc[1]: <g, x_{m-1}>; acc[2]: <g, x_m> (last step only)
   double acc[3] = {0.0, 0.0, 0.0};
-  for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += (int64_t)gridDim.x * kBlock) {
-    // every load of the row is unconditional (the step's kind only picks the
-    // pointers), so they are all in flight together
+  for (int64_t j0 = (int64_t)blockIdx.x * kBlock; j0 < n; j0 += (int64_t)gridDim.x * kBlock) {
+    const bool in = j0 + t < n;
+    const int64_t j = in ? j0 + t : n - 1;
+    const int first = off[j0], end = off[min(j0 + kBlock, (int64_t)n)];
+    const int a = off[j], b = in ? off[j + 1] : a;
     float g0, g1, g2, z0, z1, z2, x0, x1, x2, y0, y1, y2, u0, u1, u2;
     ld3(g, j, g0, g1, g2);
     ld3(zsrc, j, z0, z1, z2);
     ld3(xprev, j, x0, x1, x2);
-    ld3(yrow, j, y0, y1, y2);
+    if (LAST) ld3(xcur, j, y0, y1, y2);
     ld3(um, j, u0, u1, u2);
-    z0 *= zs;
-    z1 *= zs;
-    z2 *= zs;
-    acc[1] += (double)g0 * x0 + (double)g1 * x1 + (double)g2 * x2;
-    const double gy = (double)g0 * y0 + (double)g1 * y1 + (double)g2 * y2;
-    acc[2] += last ? gy : 0.0;
-    acc[0] += 0.5 * ((double)z0 * u0 + (double)z1 * u1 + (double)z2 * u2);
-    // T^T z_m at j
     const float tjj = diag[j];
-    float r0 = tjj * z0, r1 = tjj * z1, r2 = tjj * z2;
-    // in-edges four at a time (their ids, weights and gathers all in flight
-    // together), then the rest one by one; the order of the additions is the
-    // edges' order either way
-    const int a = off[j], b = off[j + 1];
-    int u = a;
-    for (; u + 4 <= b; u += 4) {
-      int64_t sr[4];
-      float w[4], s[4][3];
+    // (nothing waits for these loads before the first edges' are under way)
+    float r0, r1, r2;
+    auto own = [&] {  // T_jj z_m at j
+      r0 = tjj * (zs * z0);
+      r1 = tjj * (zs * z1);
+      r2 = tjj * (zs * z2);
+    };
+    if (first == end) own();  // (uniform)
+    for (int c0 = first; c0 < end; c0 += kBackEdges) {
+      constexpr int U = kBackEdges / kBlock;
+      int src[U];
+      float w[U], v[U][3];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        sr[e] = tsrc[u + e] / K;
-        w[e] = pt[u + e];
+      for (int u = 0; u < U; ++u) {
+        const int e = min(c0 + t + u * kBlock, end - 1);
+        src[u] = tsrc[e];
+        w[u] = pt[e];
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ld3(zsrc, sr[e], s[e][0], s[e][1], s[e][2]);
+      for (int u = 0; u < U; ++u) ld3(zsrc, src[u] / K, v[u][0], v[u][1], v[u][2]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        r0 = fmaf(w[e], zs * s[e][0], r0);
-        r1 = fmaf(w[e], zs * s[e][1], r1);
-        r2 = fmaf(w[e], zs * s[e][2], r2);
+      for (int u = 0; u < U; ++u) {
+        const int q = t + u * kBlock, at = q + (q >> 3);
+        s_e[0][at] = w[u];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s_e[1 + c][at] = zs * v[u][c];
       }
+      __syncthreads();
+      if (c0 == first) own();
+      const int hi = min(b, c0 + kBackEdges) - c0;
+      for (int q = max(a, c0) - c0; q < hi; ++q) {
+        const int at = q + (q >> 3);
+        const float we = s_e[0][at];
+        r0 = fmaf(we, s_e[1][at], r0);
+        r1 = fmaf(we, s_e[2][at], r1);
+        r2 = fmaf(we, s_e[3][at], r2);
+      }
+      __syncthreads();
     }
-    for (; u < b; ++u) {
-      const int64_t src = tsrc[u] / K;
-      const float w = pt[u];
-      float s0, s1, s2;
-      ld3(zsrc, src, s0, s1, s2);
-      r0 = fmaf(w, zs * s0, r0);
-      r1 = fmaf(w, zs * s1, r1);
-      r2 = fmaf(w, zs * s2, r2);
+    if (in) {
+      z0 *= zs;
+      z1 *= zs;
+      z2 *= zs;
+      acc[1] += (double)g0 * x0 + (double)g1 * x1 + (double)g2 * x2;
+      if (LAST) acc[2] += (double)g0 * y0 + (double)g1 * y1 + (double)g2 * y2;
+      acc[0] += 0.5 * ((double)z0 * u0 + (double)z1 * u1 + (double)z2 * u2);
+      st3(zout, j, fmaf(cm1, g0, r0), fmaf(cm1, g1, r1), fmaf(cm1, g2, r2));
     }
-    st3(zout, j, fmaf(cm1, g0, r0), fmaf(cm1, g1, r1), fmaf(cm1, g2, r2));
   }
   block_sum_f64<3>(acc, s_red);
   if (threadIdx.x == 0) {
     sig_part[blockIdx.x] = acc[0];
     cpart[(size_t)(m - 1) * nb + blockIdx.x] = acc[1];
-    if (last) cpart[(size_t)m * nb + blockIdx.x] = acc[2];
+    if (LAST) cpart[(size_t)m * nb + blockIdx.x] = acc[2];
   }
 }
 
@@ -601,9 +674,9 @@ hipError_t launch_poly_forward(int64_t n, int k, const int32_t *col, const int32
     k_poly_weights<0><<<G, kBlock, 0, s>>>((int32_t)n, k, col, dist2, sigma_g, p, pb.aux, diag);
   for (int kk = 1; kk < ncoef; ++kk) {
     if (k == 8)
-      k_poly_step<8><<<G, kBlock, 0, s>>>((int32_t)n, k, kk, ncoef, col, p, pb.aux, coef, saved, out);
+      k_poly_step<8><<<G, kBlock, 0, s>>>((int32_t)n, k, kk, ncoef, col, dist2, sigma_g, p, pb.aux, coef, saved, out);
     else
-      k_poly_step<0><<<G, kBlock, 0, s>>>((int32_t)n, k, kk, ncoef, col, p, pb.aux, coef, saved, out);
+      k_poly_step<0><<<G, kBlock, 0, s>>>((int32_t)n, k, kk, ncoef, col, dist2, sigma_g, p, pb.aux, coef, saved, out);
   }
   return hipGetLastError();
 }
@@ -634,14 +707,11 @@ hipError_t launch_poly_backward(int64_t n, int k, const int32_t *col, const int3
   const float *zin = nullptr;
   for (int m = ncoef - 1; m >= 1; --m) {
     float *zout = (m == 1) ? grad_x : pb.z[m & 1];
-    if (k == 8)
-      k_poly_back<8><<<G, kBlock, 0, s>>>((int32_t)n, k, m, m == ncoef - 1, G, ncoef, diag, t_off, t_edge, pb.aux,
-                                          coef, grad_out, saved, zin, zout, pb.sig_part + (size_t)m * G,
-                                          pb.coef_part);
-    else
-      k_poly_back<0><<<G, kBlock, 0, s>>>((int32_t)n, k, m, m == ncoef - 1, G, ncoef, diag, t_off, t_edge, pb.aux,
-                                          coef, grad_out, saved, zin, zout, pb.sig_part + (size_t)m * G,
-                                          pb.coef_part);
+    const bool last = m == ncoef - 1;
+    const auto fn = k == 8 ? (last ? k_poly_back<8, true> : k_poly_back<8, false>)
+                           : (last ? k_poly_back<0, true> : k_poly_back<0, false>);
+    fn<<<G, kBlock, 0, s>>>((int32_t)n, k, m, G, ncoef, diag, t_off, t_edge, pb.aux, coef, grad_out, saved, zin, zout,
+                            pb.sig_part + (size_t)m * G, pb.coef_part);
     zin = zout;
   }
   k_poly_reduce<<<1, kReduceWaves * kWave, 0, s>>>(ncoef, G, pb.coef_part, pb.sig_part, grad_coef, grad_sigma);
