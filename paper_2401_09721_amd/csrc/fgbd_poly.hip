@@ -17,9 +17,9 @@
 //     a_ik = 2 (d2_ik - d2_i0) / sigma_g^3 (the row shift cancels).
 // T^T pulls along an explicit transpose of the directed graph: for every point
 // j the edge ids e = i * K + slot with col[e] = j, in increasing order (built
-// once per graph by fgbd_graph_transpose, or per call); the backward call
-// first lays the weights out in that order (p_T[u] = p[edge[u]] / 2), so a
-// step reads them contiguously and gathers only the adjoint.  One launch per
+// once per graph by fgbd_graph_transpose, or per call); the first backward
+// step lays the weights out in that order (p_T[u] = p[edge[u]] / 2), so the
+// others read them contiguously and gather only the adjoint.  One launch per
 // backward step computes z_{m-1}, the step's sigma_g term and the
 // coefficient products <g, x_{m-1}> together.  Scalar gradients are FP64
 // per-block partials summed in block order by a one-block kernel.  No
@@ -382,32 +382,12 @@ __global__ __launch_bounds__(kBlock) void k_poly_first(int32_t n, int ncoef, con
 }
 
 // ---------------------------------------------------------------- backward
-// p_T[u] = p[edge[u]] / 2 for u < off[n]: the weights (with T's factor 1/2)
-// in the transpose's order, so each backward step reads them contiguously.
-__global__ __launch_bounds__(kBlock) void k_poly_ptrans(int32_t n, const int32_t *__restrict__ off,
-                                                        const int32_t *__restrict__ tsrc, const float *__restrict__ p,
-                                                        float *__restrict__ pt) {
-  const int64_t E = off[n];
-  if (E <= 0) return;
-  // four edges per thread and round, their id loads and then their gathers
-  // in flight together (indices clamped, so no load needs a branch)
-  constexpr int U = 4;
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  for (int64_t u0 = (int64_t)blockIdx.x * kBlock + threadIdx.x; u0 < E; u0 += U * stride) {
-    int32_t e[U];
-    float w[U];
-#pragma unroll
-    for (int j = 0; j < U; ++j) e[j] = tsrc[min(u0 + j * stride, E - 1)];
-#pragma unroll
-    for (int j = 0; j < U; ++j) w[j] = p[e[j]];
-#pragma unroll
-    for (int j = 0; j < U; ++j)
-      if (u0 + j * stride < E) pt[u0 + j * stride] = 0.5f * w[j];
-  }
-}
-
 // One backward step m (z_m in, z_{m-1} out) per point j:
 //   z_{m-1}[j] = c_{m-1} g[j] + T_jj z_m[j] + sum over edges e = (i -> j) of p_T z_m[i]
+// with p_T[u] = p[edge[u]] / 2, the weights (with T's factor 1/2) in the
+// transpose's order, which the first launch (LAST, step ncoef - 1) gathers and
+// stores, so that the others read them in order (a launch of its own for them
+// took 58 us on 2M points)
 // (T_jj = 1/2 for a point with edges, 1 without, read from diag, which the
 // forward's weights launch stored in saved), with the sigma_g term
 // <z_m[j], u_m[j]> / 2 from the saved u_m and the coefficient product
@@ -423,9 +403,10 @@ constexpr int kBackEdges = 8 * kBlock;  // edges in LDS at a time
 template <int KT, bool LAST>
 __global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, int m, int nb, int ncoef,
                                                       const float *__restrict__ diag, const int32_t *__restrict__ off,
-                                                      const int32_t *__restrict__ tsrc, const float *__restrict__ pt,
-                                                      const float *__restrict__ coef, const float *__restrict__ g,
-                                                      const float *__restrict__ saved, const float *__restrict__ zin,
+                                                      const int32_t *__restrict__ tsrc, const float *__restrict__ p,
+                                                      float *__restrict__ pt, const float *__restrict__ coef,
+                                                      const float *__restrict__ g, const float *__restrict__ saved,
+                                                      const float *__restrict__ zin,
                                                       float *__restrict__ zout, double *__restrict__ sig_part,
                                                       double *__restrict__ cpart) {
   __shared__ double s_red[8 * 3];
@@ -472,10 +453,21 @@ __global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, i
       for (int u = 0; u < U; ++u) {
         const int e = min(c0 + t + u * kBlock, end - 1);
         src[u] = tsrc[e];
-        w[u] = pt[e];
+        if (!LAST) w[u] = pt[e];
+      }
+      if (LAST) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = p[src[u]];
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) ld3(zsrc, src[u] / K, v[u][0], v[u][1], v[u][2]);
+      if (LAST) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          w[u] *= 0.5f;
+          if (c0 + t + u * kBlock < end) pt[c0 + t + u * kBlock] = w[u];
+        }
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int q = t + u * kBlock, at = q + (q >> 3);
@@ -702,7 +694,6 @@ hipError_t launch_poly_backward(int64_t n, int k, const int32_t *col, const int3
   // the forward's weights and T's diagonal, from saved
   const float *p = saved + poly_saved_p_offset(n, ncoef);
   const float *diag = p + (size_t)n * k;
-  k_poly_ptrans<<<grid_for(n * k), kBlock, 0, s>>>((int32_t)n, t_off, t_edge, p, pb.aux);
   // reverse Horner; coefficient products ride along
   const float *zin = nullptr;
   for (int m = ncoef - 1; m >= 1; --m) {
@@ -710,7 +701,7 @@ hipError_t launch_poly_backward(int64_t n, int k, const int32_t *col, const int3
     const bool last = m == ncoef - 1;
     const auto fn = k == 8 ? (last ? k_poly_back<8, true> : k_poly_back<8, false>)
                            : (last ? k_poly_back<0, true> : k_poly_back<0, false>);
-    fn<<<G, kBlock, 0, s>>>((int32_t)n, k, m, G, ncoef, diag, t_off, t_edge, pb.aux, coef, grad_out, saved, zin, zout,
+    fn<<<G, kBlock, 0, s>>>((int32_t)n, k, m, G, ncoef, diag, t_off, t_edge, p, pb.aux, coef, grad_out, saved, zin, zout,
                             pb.sig_part + (size_t)m * G, pb.coef_part);
     zin = zout;
   }
