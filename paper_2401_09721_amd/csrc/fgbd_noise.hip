@@ -405,9 +405,6 @@ __device__ double tridiag_eig_groups(const double (&d)[DT], const double (&e)[DT
   return 0.5 * (lo + hi);
 }
 
-// The FSLR spread (and optionally the 3x3 eigenvalues) of one complete patch
-// held in registers (channel c, entry k: the point, then its PT neighbours),
-// in FP64, after writing the patch's three rows to LDS.
 // v / N, rounded to nearest like the division: the product with the rounded
 // reciprocal, corrected by its exact remainder (Markstein's division; three
 // instructions instead of the general one's twelve).
@@ -418,6 +415,9 @@ __device__ __forceinline__ double div_by(double v) {
   return fma(fma(-(double)N, q, v), y, q);
 }
 
+// The FSLR spread (and optionally the 3x3 eigenvalues) of one complete patch
+// held in registers (channel c, entry k: the point, then its PT neighbours),
+// in FP64, after writing the patch's three rows to LDS.
 template <int PT, bool EIG3>
 __device__ __forceinline__ void patch_stats(int64_t i, const float (&v)[3][PT + 1], float *r0, float *r1, float *r2,
                                             double *__restrict__ spread, float *__restrict__ eig3) {

@@ -1,10 +1,12 @@
 // Scan-line codes and the radix sort of Sec. 2.2 (the paper orders the
 // points of each code with a radix sort).  One launch covers all L directions
 // (grid.y = direction).  Items are 64-bit: code << 32 | point index, so each
-// pass moves 8 bytes per item and ties (duplicate points) keep index order
-// because every pass is stable.  Codes of at most 32 bits take the top-digit
-// route at the end of this file (one pass on the top 10 bits, then each
-// window's buckets sorted in LDS); the LSD passes below sort wider codes.
+// pass moves 8 bytes per item and ties (duplicate points) keep index order:
+// the LSD passes are stable, and the top-digit route restores it.  That route,
+// at the end of this file (one pass on the top 10 bits, then each window's
+// buckets sorted in LDS), takes every code that leaves room for the index in
+// 64 bits; the LSD passes below sort the others, and any code while the
+// context has found ranges that one block would sort alone.
 //
 // Per 8-bit digit pass (4 passes for 32-bit codes):
 //   upsweep   per tile digit histogram            -> hist[dir][tile][digit]
@@ -672,16 +674,17 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_downsweep(SortArgs a, con
 // with 41: 2^23; see msd_index_bits), take a shorter route.  One
 // pass on the kMsdBits most significant bits of each direction's code
 // (upsweep, scan and downsweep as above, with 2^kMsdBits digits, the codes
-// made from the coordinates) splits every cloud's points, stably, into
-// buckets of equal top digit; the downsweep also records, from its counts,
+// made from the coordinates) splits every cloud's points, in the order of the
+// input's 64-point chunks, into buckets of equal top digit; the downsweep also records, from its counts,
 // which buckets start in every window of kLocalWin of a cloud's sorted
 // positions.
 // k_local_sort then gives each window of a direction one block, which sorts
 // the buckets that start in its window (up to the first bucket of the next
-// window), stably, by their codes less the smallest top digit's base.
+// window), by their codes less the smallest top digit's base.
 // Buckets are ordered by their top digits already, so sorting a range by the
 // whole code sorts each bucket and keeps the buckets in place; ties keep the
-// MSD pass's order, which is the input's.  The block writes the sorted items
+// MSD pass's order, and those of one chunk that it left out of index order
+// are put right at the end.  The block writes the sorted items
 // in their final form and rank, as the last LSD pass does.  A range of more
 // than kLocalCap items, or with more than kMaxBin items in one bin, is sorted
 // by its block through the two item buffers: correct for any input, slow for
