@@ -1295,10 +1295,10 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   // ---- slow path: the block sorts its range alone, LSD over 8-bit digits of
   // the code less the range's base, in chunks of kSlowItems * kLocalThreads
   // items per round, through the two item buffers (its own range of each).
-  // The first pass puts the points of each 64-point chunk of the input that
-  // share a top digit, which lie next to each other, into index order; an
-  // even number of stable ones (the last of digit 0 when needed) then ends in
-  // dst, in the final form.
+  // An odd number of passes (a first pass of digit 0, a plain stable copy,
+  // when needed) ends in dst, in the final form; then the points of one voxel
+  // and one 64-point chunk of the input, which lie next to each other, are put
+  // into index order where the top-digit pass left them out of it.
   if (a.big && R > kBigRange && t == 0) *a.big = 1;  // (only ever set to 1)
   if (t == 0) s_max = 0;
   __syncthreads();
@@ -1311,50 +1311,17 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   __syncthreads();
   const unsigned long long kmax = s_max;
   int P = kmax ? (64 - __clzll(kmax) + 7) / 8 : 0;
-  P += (P & 1) + 1;
-  {
-    const int dsh = sh + (WIDE ? a.ib - 32 : 0);
-    auto put = [&](int at, uint64_t v) {
-      if (P > 1) {
-        out[lo + at] = v;
-      } else {
-        const uint32_t idx = (uint32_t)v & id_mask;
-        out[lo + at] = final_item(v);
-        if (idx < (uint32_t)a.stride) rank[dbase + idx] = (uint32_t)(lo + at);
-      }
-    };
-    const uint32_t first = (uint32_t)(a.sa.n_fixed >= 0 ? 0 : a.sa.segs->start[ti.s]);
-    auto near = [&](uint64_t u, uint64_t v) {
-      return msd_digit((uint32_t)(u >> 32), dsh) == msd_digit((uint32_t)(v >> 32), dsh) &&
-             ((uint32_t)u & id_mask) - first >> 6 == ((uint32_t)v & id_mask) - first >> 6;
-    };
-    for (int s = t; s < R; s += kLocalThreads) {
-      const uint64_t v = items[lo + s];
-      const uint32_t idx = (uint32_t)v & id_mask;
-      int r = s;
-      for (int u = s - 1; u >= 0 && s - u < kWave; --u) {
-        const uint64_t o = items[lo + u];
-        if (!near(v, o)) break;
-        r -= ((uint32_t)o & id_mask) > idx ? 1 : 0;
-      }
-      for (int u = s + 1; u < R && u - s < kWave; ++u) {
-        const uint64_t o = items[lo + u];
-        if (!near(v, o)) break;
-        r += ((uint32_t)o & id_mask) < idx ? 1 : 0;
-      }
-      put(r, v);
-    }
-    __syncthreads();
-  }
-  for (int q = 1; q < P; ++q) {
+  const int extra = (P % 2 == 0) ? 1 : 0;
+  P += extra;
+  for (int q = 0; q < P; ++q) {
     const uint64_t *rd = ((q & 1) == 0 ? src : dst) + dbase;
     uint64_t *wr = ((q & 1) == 0 ? dst : src) + dbase;
     const bool last = q == P - 1;
-    const int shift = 8 * (q - 1);
+    const int shift = 8 * (q - extra);  // q < extra: the copy pass (digit 0)
     if (t < 256) s_base[t] = 0u;
     __syncthreads();
     for (int s = t; s < R; s += kLocalThreads) {
-      const uint32_t digit = (uint32_t)(rel(rd[lo + s]) >> shift) & 255u;
+      const uint32_t digit = q < extra ? 0u : (uint32_t)(rel(rd[lo + s]) >> shift) & 255u;
       atomicAdd(&s_base[digit], 1u);
     }
     __syncthreads();
@@ -1375,7 +1342,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
 #pragma unroll
       for (int j = 0; j < kSlowItems; ++j) {
         const int s = c0 + (wave * kSlowItems + j) * kWave + lane;
-        dg[j] = s >= R ? 255u : (uint32_t)(rel(it[j]) >> shift) & 255u;
+        dg[j] = s >= R ? 255u : (q < extra ? 0u : (uint32_t)(rel(it[j]) >> shift) & 255u);
       }
 #pragma unroll
       for (int j = 0; j < kSlowItems; ++j) rk[j] = wave_rank8(dg[j], s_cnt[wave], bf[j]);
@@ -1412,6 +1379,32 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
       if (t < 256) s_base[t] += tot;
     }
     __syncthreads();
+  }
+  // One thread per run of equals; reordering a run changes nothing that tells
+  // another thread where runs begin.
+  const uint32_t first = (uint32_t)(a.sa.n_fixed >= 0 ? 0 : a.sa.segs->start[ti.s]);
+  auto alike = [&](uint64_t u, uint64_t v) {
+    return same_code(u, v) && ((uint32_t)u & id_mask) - first >> 6 == ((uint32_t)v & id_mask) - first >> 6;
+  };
+  for (int s = t; s + 1 < R; s += kLocalThreads) {
+    const uint64_t v = out[lo + s];
+    if (!alike(v, out[lo + s + 1]) || (s > 0 && alike(out[lo + s - 1], v))) continue;
+    int e = s + 1;
+    for (; e < R && e - s < kWave; ++e) {  // insertion
+      const uint64_t w = out[lo + e];
+      if (!alike(v, w)) break;
+      int at = e;
+      for (; at > s; --at) {
+        const uint64_t u = out[lo + at - 1];
+        if (u < w) break;
+        out[lo + at] = u;
+      }
+      if (at != e) out[lo + at] = w;
+    }
+    for (int u = s; u < e; ++u) {
+      const uint32_t idx = (uint32_t)out[lo + u] & id_mask;
+      if (idx < (uint32_t)a.stride) rank[dbase + idx] = (uint32_t)(lo + u);
+    }
   }
 }
 

@@ -80,3 +80,22 @@ def test_duplicates_in_turn(bits, voxels, times):
     v = rng.integers(0, 1 << bits, size=(voxels, 3))
     g = np.concatenate([np.tile(v, (times, 1)), rng.integers(0, 1 << bits, size=(777, 3)), np.tile(v[::-1], (5, 1))])
     check_graph(g.astype(np.int32), fgbd.default_params(bits=bits, num_dirs=8, window=4, k=8))
+
+
+def _planes(rng, n, extra):
+    """Planes of n points normal to each scan axis, in no order, and others."""
+    out = [rng.integers(0, 1024, size=(extra, 3))]
+    for axis in range(3):
+        flat = rng.choice(1 << 20, size=n, replace=False)
+        p = np.stack([flat >> 10, flat & 1023], 1)
+        out.append(np.insert(p, axis, 300 + 7 * axis, axis=1))
+    return np.concatenate(out)
+
+
+@pytest.mark.parametrize("n", [8193, 9500, 16384, 16385, 24000, 32700, 33000])
+def test_planes_past_the_lds(n):
+    """Ranges of more than a block's LDS holds, sorted through the two item
+    buffers, from one item more to past the flag's length."""
+    rng = np.random.default_rng(n)
+    g = _planes(rng, n, 5000).astype(np.int32)
+    check_graph(g, fgbd.default_params(bits=10, num_dirs=8, window=4, k=8))
