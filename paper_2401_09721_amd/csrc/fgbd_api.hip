@@ -1019,6 +1019,10 @@ fgbd_status fgbd_autotune(fgbd_ctx ctx, const int32_t *xyz, const float *rgb_in,
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (st == FGBD_OK && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess))
     st = fail(FGBD_E_HIP, "hipEventCreate failed");
+  // (the candidates bound the trial calls' counts: on a context with no
+  // schedule set, recent calls' counts could go above them, and every
+  // candidate timed the same)
+  ctx->tune_set = true;
   double best_ms = 1e300;
   for (int c = 0; c < 7 && st == FGBD_OK; ++c) {
     ctx->tune = best;
