@@ -695,6 +695,27 @@ hipError_t launch_sweep_tail(const Run &r, const int32_t *col, const float *p, c
 hipError_t launch_finalize(const Run &r, const float *rgb_in, int q_launches, const fgbd_result *noise,
                            float *rgb_out, fgbd_result *res);
 
+// A block's in-edges c0 .. end - 1 of a transposed graph, kBackEdges at a
+// time.  Unsigned: a graph may hold 2^31 - 1 edges, and the positions past the
+// last pass, which are formed before they are clamped, still fit then.
+constexpr int kBackEdges = 8 * kBlock;
+struct EdgePass {
+  uint32_t c0, end;
+  __host__ __device__ bool more() const { return c0 < end; }
+  __host__ __device__ void next() { c0 += (uint32_t)kBackEdges; }
+  // edge q of the pass (0 <= q < kBackEdges), the last edge past the end
+  __host__ __device__ uint32_t edge(int q) const {
+    const uint32_t e = c0 + (uint32_t)q;
+    return e < end ? e : end - 1u;
+  }
+  __host__ __device__ bool holds(int q) const { return c0 + (uint32_t)q < end; }
+  // the place in the pass of edge b, at most kBackEdges; negative for one of an earlier pass
+  __host__ __device__ int below(uint32_t b) const {
+    const uint32_t top = c0 + (uint32_t)kBackEdges;
+    return (int)((b < top ? b : top) - c0);
+  }
+};
+
 // Polynomial filter and its adjoint (ws: at least poly_workspace bytes).
 constexpr int kMaxPoly = 32;
 // grid cap of the polynomial filter's grid-stride kernels; also the length

@@ -399,7 +399,6 @@ __global__ __launch_bounds__(kBlock) void k_poly_first(int32_t n, int ncoef, con
 // edges' order.  With a point's edges read by its lane, every load touched 16
 // lines and the lines were read 2.7 times from L2: 64 us a step on 2M points,
 // 56 so.
-constexpr int kBackEdges = 8 * kBlock;  // edges in LDS at a time
 template <int KT, bool LAST>
 __global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, int m, int nb, int ncoef,
                                                       const float *__restrict__ diag, const int32_t *__restrict__ off,
@@ -428,8 +427,9 @@ __global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, i
   for (int64_t j0 = (int64_t)blockIdx.x * kBlock; j0 < n; j0 += (int64_t)gridDim.x * kBlock) {
     const bool in = j0 + t < n;
     const int64_t j = in ? j0 + t : n - 1;
-    const int first = off[j0], end = off[min(j0 + kBlock, (int64_t)n)];
-    const int a = off[j], b = in ? off[j + 1] : a;
+    EdgePass pass = {(uint32_t)off[j0], (uint32_t)off[min(j0 + kBlock, (int64_t)n)]};
+    const uint32_t first = pass.c0;
+    const uint32_t a = (uint32_t)off[j], b = in ? (uint32_t)off[j + 1] : a;
     float g0, g1, g2, z0, z1, z2, x0, x1, x2, y0, y1, y2, u0, u1, u2;
     ld3(g, j, g0, g1, g2);
     ld3(zsrc, j, z0, z1, z2);
@@ -444,14 +444,14 @@ __global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, i
       r1 = tjj * (zs * z1);
       r2 = tjj * (zs * z2);
     };
-    if (first == end) own();  // (uniform)
-    for (int c0 = first; c0 < end; c0 += kBackEdges) {
+    if (!pass.more()) own();  // (uniform)
+    for (; pass.more(); pass.next()) {
       constexpr int U = kBackEdges / kBlock;
       int src[U];
       float w[U], v[U][3];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int e = min(c0 + t + u * kBlock, end - 1);
+        const uint32_t e = pass.edge(t + u * kBlock);
         src[u] = tsrc[e];
         if (!LAST) w[u] = pt[e];
       }
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, i
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           w[u] *= 0.5f;
-          if (c0 + t + u * kBlock < end) pt[c0 + t + u * kBlock] = w[u];
+          if (pass.holds(t + u * kBlock)) pt[pass.edge(t + u * kBlock)] = w[u];
         }
       }
 #pragma unroll
@@ -476,9 +476,9 @@ __global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, i
         for (int c = 0; c < 3; ++c) s_e[1 + c][at] = zs * v[u][c];
       }
       __syncthreads();
-      if (c0 == first) own();
-      const int hi = min(b, c0 + kBackEdges) - c0;
-      for (int q = max(a, c0) - c0; q < hi; ++q) {
+      if (pass.c0 == first) own();
+      const int hi = pass.below(b);
+      for (int q = max(pass.below(a), 0); q < hi; ++q) {
         const int at = q + (q >> 3);
         const float we = s_e[0][at];
         r0 = fmaf(we, s_e[1][at], r0);

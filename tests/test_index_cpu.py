@@ -1,0 +1,71 @@
+"""Index arithmetic of the kernels at the largest sizes that the calls accept,
+run on the host: a program built from the library's own header walks the
+indexes that a block forms and prints what it finds."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2401_09721_amd import build
+
+HEAD = """
+#include <cstdio>
+#include <cstdlib>
+#include "fgbd_internal.h"
+using namespace fgbd;
+"""
+
+
+def run(tmp_path, body, *args):
+    """Build a host program (no device code) around `body` and return its output's words."""
+    src, exe = tmp_path / "t.hip", tmp_path / "t"
+    src.write_text(HEAD + body)
+    obj = tmp_path / "t.o"
+    subprocess.run([build.hipcc(), "--offload-host-only", "-std=c++17", "-O1", f"-I{build.INCLUDE}", f"-I{build.CSRC}",
+                    "-c", str(src), "-o", str(obj)], check=True, capture_output=True, timeout=110)
+    subprocess.run([build.hipcc(), str(obj), "-o", str(exe)], check=True, capture_output=True, timeout=110)
+    out = subprocess.run([str(exe), *map(str, args)], check=True, capture_output=True, text=True, timeout=30)
+    return out.stdout.split()
+
+
+EDGES = """
+int main(int argc, char **argv) {
+  // a block's edges first .. end - 1, walked as the adjoint's step does
+  for (int i = 1; i + 1 < argc; i += 2) {
+    const long long first = atoll(argv[i]), end = atoll(argv[i + 1]);
+    long long passes = 0, stored = 0, bad = 0;
+    EdgePass p;
+    p.c0 = (uint32_t)first;
+    p.end = (uint32_t)end;
+    for (; p.more() && passes < 100000000; p.next(), ++passes) {
+      const long long c0 = first + passes * kBackEdges;
+      for (int q = 0; q < kBackEdges; q += (c0 + kBackEdges < end ? kBackEdges - 1 : 1)) {
+        const long long want = c0 + q < end ? c0 + q : end - 1;
+        bad += (long long)p.edge(q) != want || p.holds(q) != (c0 + q < end);
+        stored += p.holds(q);
+      }
+      for (long long b : {first, c0, c0 + 1, end}) {
+        const long long top = b < c0 + kBackEdges ? b : c0 + kBackEdges;
+        bad += b <= end && (long long)p.below((uint32_t)b) != top - c0;
+      }
+    }
+    printf("%lld %lld %lld\\n", passes, stored, bad);
+  }
+}
+"""
+
+
+def test_adjoint_edges_at_the_limit(tmp_path):
+    """Graphs of n * k edges up to 2^31 - 1: the last block of points, a block
+    that holds none, one that holds every edge, and ends around the limit."""
+    top = 2**31 - 1
+    step = 2048
+    blocks = [(0, 0), (0, 1), (0, step), (0, step + 1), (2_147_481_600, 2_147_483_640), (top - 1, top), (top - step, top),
+              (top - step - 1, top), (top - 3 * step, top - step + 5), (0, top)]
+    words = run(tmp_path, EDGES, *[v for b in blocks for v in b])
+    for i, (first, end) in enumerate(blocks):
+        passes, stored, bad = map(int, words[3 * i:3 * i + 3])
+        assert bad == 0, (first, end)
+        assert passes == -(-(end - first) // step), (first, end)
+        tail = (end - first) - (passes - 1) * step if passes else 0
+        assert stored == tail + 2 * max(passes - 1, 0), (first, end)
