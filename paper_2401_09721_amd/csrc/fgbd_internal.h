@@ -174,6 +174,12 @@ __host__ __device__ inline int64_t far_gap(int64_t cloud_n) {
   return cloud_n / 16 > 4096 ? cloud_n / 16 : 4096;
 }
 
+// The coordinates of point `pos`, found by 64 bits: three times the largest
+// point index that the calls accept does not fit 32.  With the first point of
+// a tile in pos, which is uniform, the items of the tile are 32-bit offsets
+// from it.
+__host__ __device__ inline const int32_t *point_at(const int32_t *xyz, int pos) { return xyz + 3 * (int64_t)pos; }
+
 // How kernels find their cloud: n_fixed >= 0 means one cloud of n_fixed
 // points known on the host (the table is not read); otherwise B clouds from
 // the device table.

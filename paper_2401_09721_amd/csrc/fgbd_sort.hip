@@ -208,13 +208,17 @@ __device__ __forceinline__ uint64_t decode_packed_wide(const CodeGen &c, uint64_
 // flight together: positions past the tile's end are clamped to its last
 // point, as a load in a branch is waited for there (16 latencies one after
 // the other were a quarter of the top-digit downsweep's time).
-__device__ __forceinline__ void load_points(const int32_t *__restrict__ xyz, int base, int end,
+__device__ __forceinline__ void load_points(const int32_t *__restrict__ xyz, const TileInfo &ti, int base,
                                             int (&g)[kSortItems][3]) {
+  const char *tile = reinterpret_cast<const char *>(point_at(xyz, ti.begin));
+  const uint32_t at = (uint32_t)(base - ti.begin), last = (uint32_t)(ti.end - ti.begin) - 1u;
 #pragma unroll
   for (int j = 0; j < kSortItems; ++j) {
-    const int pos = min(base + j * kWave, end - 1);
+    // (bytes: with the offset in elements the three loads were not one)
+    const uint32_t off = 12u * min(at + (uint32_t)(j * kWave), last);
+    const int32_t *p = reinterpret_cast<const int32_t *>(tile + off);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) g[j][c] = xyz[3 * pos + c];
+    for (int c = 0; c < 3; ++c) g[j][c] = p[c];
   }
 }
 // Non-zero for a point outside the 2^bits grid.
@@ -326,12 +330,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_upsweep(SortArgs a, const
     const int lane = (int)lane_id();
     const int base = ti.begin + wave * kWave * kSortItems + lane;
     int g[kSortItems][3];
-#pragma unroll
-    for (int j = 0; j < kSortItems; ++j) {
-      const int pos = min(base + j * kWave, ti.end - 1);  // a tile holds at least one point
-#pragma unroll
-      for (int c = 0; c < 3; ++c) g[j][c] = xyz[3 * pos + c];
-    }
+    load_points(xyz, ti, base, g);  // (a tile holds at least one point)
     // Runs of equal digits are counted in registers and added once: with
     // the input in a raster order, the digit (low bits of the position
     // along the line) is often the same for a thread's items, and for every
@@ -538,7 +537,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_downsweep(SortArgs a, con
   int bad = 0;
   if (a.pass == 0) {
     int g[kSortItems][3];
-    load_points(xyz, base, ti.end, g);
+    load_points(xyz, ti, base, g);
 #pragma unroll
     for (int j = 0; j < kSortItems; ++j) {
       bad |= outside_grid(g[j], a.dt.bits);
@@ -745,7 +744,7 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_upsweep(SortArgs a, const 
   const int lane = (int)lane_id();
   const int base = ti.begin + wave * kWave * kSortItems + lane;
   int g[kSortItems][3];
-  load_points(xyz, base, ti.end, g);
+  load_points(xyz, ti, base, g);
   const CodeGen cg = code_gen(a.dt, d);
   const int sh = msd_shift(a.dt, d);
   uint32_t run_digit = 0, run_count = 0;
@@ -834,7 +833,7 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
   int bad = 0;
   {
     int g[kSortItems][3];
-    load_points(xyz, base, ti.end, g);
+    load_points(xyz, ti, base, g);
 #pragma unroll
     for (int j = 0; j < kSortItems; ++j) {
       bad |= outside_grid(g[j], a.dt.bits);

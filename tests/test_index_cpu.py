@@ -69,3 +69,20 @@ def test_adjoint_edges_at_the_limit(tmp_path):
         assert passes == -(-(end - first) // step), (first, end)
         tail = (end - first) - (passes - 1) * step if passes else 0
         assert stored == tail + 2 * max(passes - 1, 0), (first, end)
+
+
+POINTS = """
+int main(int argc, char **argv) {
+  for (int i = 1; i < argc; ++i) {
+    const int pos = atoi(argv[i]);
+    const int32_t *xyz = (const int32_t *)0x10000;  // (never read)
+    printf("%lld\\n", (long long)((uintptr_t)point_at(xyz, pos) - (uintptr_t)xyz));
+  }
+}
+"""
+
+
+def test_point_offsets_at_the_limit(tmp_path):
+    """Coordinates are 12 bytes a point up to the largest n that the calls take."""
+    at = [0, 1, 4096, 715_827_882, 715_827_883, 1_500_000_000, 2**31 - 1 - 4096]
+    assert [int(w) for w in run(tmp_path, POINTS, *at)] == [12 * p for p in at]
