@@ -1,0 +1,117 @@
+// What a context remembers of its recent eager calls to choose the launches of
+// the next: plain host code over words that the device stores into host-mapped
+// memory, read back without waiting.
+#pragma once
+
+#include <stdint.h>
+
+namespace fgbd {
+
+// What predicts the sweeps that a call needs: the entry point, the clouds in
+// the call and the magnitude (power of two) of its size.  Calls of one kind follow each
+// other's counts only: with one record for the whole context, a 1M-point frame
+// of 4 sweeps after a batch that needed 31 was given 32 launches for its next
+// eight calls.
+enum CallEntry { kCallDenoise = 0, kCallBatched, kCallFilter };
+struct CallKind {
+  int32_t entry, clouds, magnitude;
+  bool operator==(const CallKind &o) const {
+    return entry == o.entry && clouds == o.clouds && magnitude == o.magnitude;
+  }
+};
+inline CallKind call_kind(int entry, int clouds, int64_t n) {
+  int32_t m = 0;
+  for (; n > 1; n >>= 1) ++m;
+  return {entry, clouds, m};
+}
+
+// Sweep counts of recent calls.  The last finalising launch of a call that
+// asked for it stores each cloud's count and the call's tag in one word; a
+// later call reads them once every cloud's word carries the tag.  (No events:
+// each one recorded left the GPU idle for about 6 us.)
+class SweepCounts {
+ public:
+  static constexpr int kKinds = 8;   // records kept, the least recently used goes
+  static constexpr int kRecent = 8;  // counts per record
+
+  bool pending() const { return pending_; }
+
+  // Takes the outstanding counts into their record once they are all there.
+  void poll(const int32_t *words) {
+    if (!pending_) return;
+    int32_t most = 0;
+    for (int i = 0; i < clouds_; ++i) {
+      const int32_t v = __atomic_load_n(&words[i], __ATOMIC_ACQUIRE);
+      if ((v & ~0xffff) != tag_) return;
+      most = (v & 0xffff) > most ? v & 0xffff : most;
+    }
+    Record &r = record(asked_);
+    r.recent[r.at] = most;
+    r.at = (r.at + 1) % kRecent;
+    r.count += r.count < kRecent ? 1 : 0;
+    pending_ = false;
+  }
+
+  // A call of this kind asks for its counts (none may be outstanding).
+  // Returns the tag for its words.
+  int32_t ask(const CallKind &kind, int clouds) {
+    tag_ = (tag_ + 0x10000) & 0x7fff0000;
+    if (tag_ == 0) tag_ = 0x10000;
+    pending_ = true;
+    asked_ = kind;
+    clouds_ = clouds;
+    return tag_;
+  }
+
+  // Whether launches may still store counts.
+  bool outstanding(const int32_t *words) const {
+    for (int i = 0; pending_ && i < clouds_; ++i)
+      if ((__atomic_load_n(&words[i], __ATOMIC_ACQUIRE) & ~0xffff) != tag_) return true;
+    return false;
+  }
+
+  // Separate sweep launches for a call of this kind: the most that its recent
+  // calls needed where those agree, one more where they do not, within
+  // 1..limit; `unknown` before any count was read.
+  int launches(const CallKind &kind, int unknown, int limit) {
+    const Record &r = record(kind);
+    if (r.count == 0) return unknown;
+    int32_t most = 0, least = INT32_MAX;
+    for (int i = 0; i < r.count; ++i) {
+      most = r.recent[i] > most ? r.recent[i] : most;
+      least = r.recent[i] < least ? r.recent[i] : least;
+    }
+    const int want = (r.count >= 2 && least == most) ? most : most + 1;  // steady counts: no spare launch
+    return want < 1 ? 1 : (want < limit ? want : limit);
+  }
+
+ private:
+  struct Record {
+    CallKind kind = {-1, 0, 0};
+    int32_t recent[kRecent] = {0};
+    int32_t count = 0, at = 0;
+    uint64_t used = 0;
+  };
+  Record &record(const CallKind &kind) {
+    Record *old = &records_[0];
+    for (Record &r : records_) {
+      if (r.kind == kind) {
+        r.used = ++clock_;
+        return r;
+      }
+      if (r.used < old->used) old = &r;
+    }
+    *old = Record();
+    old->kind = kind;
+    old->used = ++clock_;
+    return *old;
+  }
+  Record records_[kKinds];
+  uint64_t clock_ = 0;
+  bool pending_ = false;
+  int32_t tag_ = 0;  // of the outstanding counts, above the count's 16 bits
+  CallKind asked_ = {-1, 0, 0};
+  int clouds_ = 0;
+};
+
+}  // namespace fgbd

@@ -11,6 +11,7 @@
 #include <thread>
 #include <vector>
 
+#include "fgbd_adapt.h"
 #include "fgbd_internal.h"
 
 using namespace fgbd;
@@ -68,19 +69,11 @@ struct fgbd_ctx_s {
   std::vector<Record> pending;
   double ms[FGBD_NUM_KERNELS] = {0};
   int64_t launches[FGBD_NUM_KERNELS] = {0};
-  // Sweep counts of recent eager calls, read back without waiting: the last
-  // finalising launch stores each cloud's count and the call's tag in one
-  // word of host-mapped memory; a later call reads them once every cloud's
-  // word carries the tag.  (No events: each one recorded left the GPU idle
-  // for about 6 us.)
+  // Sweep counts of recent eager calls, read back without waiting.
+  SweepCounts sweeps;
   int32_t *hint_host = nullptr;  // [kMaxSeg], hipHostMalloc'ed
   int32_t *hint_dev = nullptr;   // its device address
-  int32_t hint_tag = 0;          // of the outstanding read-back, above the count's 16 bits
   bool hint_failed = false;      // could not set up: no adaptation
-  bool hint_pending = false;     // launches that may write the words are outstanding
-  int hint_B = 0;
-  int hint_recent[8] = {0};      // ring of the last counts read (max over clouds)
-  int hint_count = 0;
   // Sort route: a host-mapped flag the local sort sets when a block sorted a
   // very large range alone (points crowded into few top code digits, such as
   // a plane normal to a scan axis), read back without waiting like the sweep
@@ -592,9 +585,7 @@ fgbd_status fgbd_create(fgbd_ctx *out, int32_t hip_device) {
 // Launches that may still write the context's host-mapped words.
 static bool words_pending(fgbd_ctx ctx) {
   if (ctx->sort_pending && __atomic_load_n(&ctx->sort_flag_host[1], __ATOMIC_ACQUIRE) != ctx->sort_seq) return true;
-  for (int i = 0; ctx->hint_pending && i < ctx->hint_B; ++i)
-    if ((__atomic_load_n(&ctx->hint_host[i], __ATOMIC_ACQUIRE) & ~0xffff) != ctx->hint_tag) return true;
-  return false;
+  return ctx->sweeps.outstanding(ctx->hint_host);
 }
 
 fgbd_status fgbd_destroy(fgbd_ctx ctx) {
@@ -683,8 +674,8 @@ fgbd_status fgbd_estimate_noise(fgbd_ctx ctx, const fgbd_graph *g, const float *
 }
 
 // Separate sweep launches for an eager call: the schedule's count, lowered to
-// the most sweeps any of the last eight read-back calls needed when those
-// counts agree (the finalising launch then applies the last sweep's sums
+// the most sweeps any of the last eight read-back calls of its kind needed when
+// those counts agree (the finalising launch then applies the last sweep's sums
 // itself and finds the selection stopped), else to one more (a launch that
 // finds it stopped, so the in-launch loop after it returns at once).  A
 // context whose schedule nobody set goes above the default count the same
@@ -693,7 +684,7 @@ fgbd_status fgbd_estimate_noise(fgbd_ctx ctx, const fgbd_graph *g, const float *
 // 1513 us with 8 separate sweeps, 439 with as many as it needs).
 // Captured calls keep the schedule's count.  With no read-back outstanding the
 // call's finalising launch is told where to store its sweep counts (r.hint).
-static int adaptive_sweep_launches(fgbd_ctx ctx, hipStream_t s, Run &r, int B) {
+static int adaptive_sweep_launches(fgbd_ctx ctx, hipStream_t s, Run &r, CallEntry entry) {
   const int cap = ctx->tune.sweep_launches;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone || ctx->hint_failed) return cap;
@@ -709,37 +700,13 @@ static int adaptive_sweep_launches(fgbd_ctx ctx, hipStream_t s, Run &r, int B) {
     ctx->hint_dev = (int32_t *)dev;
     for (int i = 0; i < kMaxSeg; ++i) ctx->hint_host[i] = 0;
   }
-  if (ctx->hint_pending) {
-    int m = 0, seen = 0;
-    for (; seen < ctx->hint_B; ++seen) {
-      const int32_t v = __atomic_load_n(&ctx->hint_host[seen], __ATOMIC_ACQUIRE);
-      if ((v & ~0xffff) != ctx->hint_tag) break;
-      m = (v & 0xffff) > m ? v & 0xffff : m;
-    }
-    if (seen == ctx->hint_B) {
-      ctx->hint_recent[ctx->hint_count % 8] = m;
-      ++ctx->hint_count;
-      ctx->hint_pending = false;
-    }
-  }
-  if (!ctx->hint_pending) {  // pending from here: a launch that fails leaves it so (no further read-back)
-    ctx->hint_tag = (ctx->hint_tag + 0x10000) & 0x7fff0000;
-    if (ctx->hint_tag == 0) ctx->hint_tag = 0x10000;
-    ctx->hint_pending = true;
-    ctx->hint_B = B;
+  const CallKind kind = call_kind(entry, r.pl.B, r.pl.n_cap);
+  ctx->sweeps.poll(ctx->hint_host);
+  if (!ctx->sweeps.pending()) {  // pending from here: a launch that fails leaves it so (no further read-back)
     r.hint = ctx->hint_dev;
-    r.hint_tag = ctx->hint_tag;
+    r.hint_tag = ctx->sweeps.ask(kind, r.pl.B);
   }
-  if (ctx->hint_count == 0) return cap;
-  int m = 0, lo = 1 << 30;
-  const int k = ctx->hint_count < 8 ? ctx->hint_count : 8;
-  for (int i = 0; i < k; ++i) {
-    m = ctx->hint_recent[i] > m ? ctx->hint_recent[i] : m;
-    lo = ctx->hint_recent[i] < lo ? ctx->hint_recent[i] : lo;
-  }
-  const int want = (k >= 2 && lo == m) ? m : m + 1;  // steady counts: no spare launch
-  const int most = ctx->tune_set ? cap : kMaxAdaptiveSweeps;
-  return want < 1 ? 1 : (want < most ? want : most);
+  return ctx->sweeps.launches(kind, cap, ctx->tune_set ? cap : kMaxAdaptiveSweeps);
 }
 
 fgbd_status fgbd_filter(fgbd_ctx ctx, const fgbd_graph *g, const float *rgb_in, const fgbd_params *params,
@@ -771,7 +738,7 @@ fgbd_status fgbd_filter(fgbd_ctx ctx, const fgbd_graph *g, const float *rgb_in, 
   HIP_TRY(launch_setup(r, nullptr, n, res, n == 0 ? 1 : 0), "setup launch");
   if (n == 0) return ok();
   const int q_limit = select ? params->q_max : q_fixed;
-  if (select) r.sweep_launches = adaptive_sweep_launches(ctx, s, r, 1);
+  if (select) r.sweep_launches = adaptive_sweep_launches(ctx, s, r, kCallFilter);
   if ((st = run_filter(r, g->col, g->p, nullptr, rgb_in, patch_spread, noise, select, q_limit, rgb_out, res)) !=
       FGBD_OK)
     return st;
@@ -824,7 +791,7 @@ fgbd_status fgbd_denoise(fgbd_ctx ctx, const int32_t *xyz, const float *rgb_in, 
   // the first radix launch does the setup
   r.fold_setup = true;
   r.setup = setup_args(r, nullptr, n, res, 1);
-  r.sweep_launches = adaptive_sweep_launches(ctx, s, r, 1);
+  r.sweep_launches = adaptive_sweep_launches(ctx, s, r, kCallDenoise);
   r.relabel_ok = r.prm.patch_order == 0;  // index-ordered patches need the input numbering
   if ((st = run_denoise(r, xyz, rgb_in, rgb_out, res)) != FGBD_OK) return st;
   return ok();
@@ -862,7 +829,7 @@ fgbd_status fgbd_denoise_batched(fgbd_ctx ctx, const int32_t *xyz, const float *
   sort_policy(ctx, s, r);
   HIP_TRY(launch_setup(r, offsets, 0, res, n_total == 0 ? 2 : 1), "setup launch");
   if (n_total == 0) return ok();
-  r.sweep_launches = adaptive_sweep_launches(ctx, s, r, batch);
+  r.sweep_launches = adaptive_sweep_launches(ctx, s, r, kCallBatched);
   r.relabel_ok = r.prm.patch_order == 0;  // index-ordered patches need the input numbering
   if ((st = run_denoise(r, xyz, rgb_in, rgb_out, res)) != FGBD_OK) return st;
   return ok();

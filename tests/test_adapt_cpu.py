@@ -1,0 +1,57 @@
+"""What a context remembers of its recent calls, run on the host: sequences of
+calls, the words that their launches would store, and the launches chosen."""
+from host_program import run
+
+HEAD = '#include "fgbd_adapt.h"\n'
+
+# calls "entry clouds n needed": the call asks when nothing is outstanding, its
+# words are stored at once, and the chosen count is printed
+CALLS = """
+int main(int argc, char **argv) {
+  SweepCounts s;
+  int32_t words[64] = {0};
+  for (int i = 1; i + 3 < argc; i += 4) {
+    const int clouds = atoi(argv[i + 1]), needed = atoi(argv[i + 3]);
+    const CallKind kind = call_kind(atoi(argv[i]), clouds, atoll(argv[i + 2]));
+    s.poll(words);
+    if (!s.pending()) {
+      const int32_t tag = s.ask(kind, clouds);
+      for (int c = 0; c < clouds; ++c) words[c] = (c ? 1 : needed) | tag;
+    }
+    printf("%d\\n", s.launches(kind, 8, 64));
+  }
+}
+"""
+DENOISE, BATCHED, FILTER = 0, 1, 2
+
+
+def chosen(tmp_path, calls):
+    return [int(w) for w in run(tmp_path, HEAD, CALLS, *[v for c in calls for v in c])]
+
+
+def test_follows_the_calls_of_one_kind(tmp_path):
+    frame, batch = (DENOISE, 1, 1000000, 4), (BATCHED, 64, 262144, 31)
+    got = chosen(tmp_path, [frame] * 3 + [batch] * 3 + [frame, batch] * 4 + [frame] * 2)
+    assert got[:3] == [8, 5, 4]  # nothing known, one count, two that agree
+    assert got[3:6] == [8, 32, 31]
+    assert got[6::2][:4] == [4] * 4 and got[7::2][:4] == [31] * 4 and got[-2:] == [4, 4]
+
+
+def test_kinds_are_entry_clouds_and_magnitude(tmp_path):
+    kinds = [(DENOISE, 1, 5000), (FILTER, 1, 5000), (BATCHED, 1, 5000), (BATCHED, 2, 5000), (DENOISE, 1, 100000)]
+    needed = [3, 7, 12, 20, 40]
+    rounds = [(*k, q) for _ in range(4) for k, q in zip(kinds, needed)]
+    assert chosen(tmp_path, rounds)[-5:] == needed
+
+
+def test_counts_that_vary_and_the_limit(tmp_path):
+    got = chosen(tmp_path, [(DENOISE, 1, 777, q) for q in (3, 9, 3, 3, 3, 3, 3, 3, 3, 3, 3, 200, 3)])
+    assert got == [8, 4] + [10] * 8 + [3, 3, 64]
+
+
+def test_more_kinds_than_records(tmp_path):
+    """The least recently used kind is forgotten, not a wrong one taken for it."""
+    many = [(BATCHED, b, 5000, b) for b in range(1, 10)]
+    got = chosen(tmp_path, many * 3)
+    assert all(g in (8, b[3], b[3] + 1) for g, b in zip(got, many * 3))
+    assert got[-1] == 8 and chosen(tmp_path, many[:8] * 3)[-8:] == list(range(1, 9))

@@ -1,32 +1,9 @@
 """Index arithmetic of the kernels at the largest sizes that the calls accept,
 run on the host: a program built from the library's own header walks the
 indexes that a block forms and prints what it finds."""
-import os
-import subprocess
+from host_program import run
 
-import pytest
-
-from paper_2401_09721_amd import build
-
-HEAD = """
-#include <cstdio>
-#include <cstdlib>
-#include "fgbd_internal.h"
-using namespace fgbd;
-"""
-
-
-def run(tmp_path, body, *args):
-    """Build a host program (no device code) around `body` and return its output's words."""
-    src, exe = tmp_path / "t.hip", tmp_path / "t"
-    src.write_text(HEAD + body)
-    obj = tmp_path / "t.o"
-    subprocess.run([build.hipcc(), "--offload-host-only", "-std=c++17", "-O1", f"-I{build.INCLUDE}", f"-I{build.CSRC}",
-                    "-c", str(src), "-o", str(obj)], check=True, capture_output=True, timeout=110)
-    subprocess.run([build.hipcc(), str(obj), "-o", str(exe)], check=True, capture_output=True, timeout=110)
-    out = subprocess.run([str(exe), *map(str, args)], check=True, capture_output=True, text=True, timeout=30)
-    return out.stdout.split()
-
+HEAD = '#include "fgbd_internal.h"\n'
 
 EDGES = """
 int main(int argc, char **argv) {
@@ -62,7 +39,7 @@ def test_adjoint_edges_at_the_limit(tmp_path):
     step = 2048
     blocks = [(0, 0), (0, 1), (0, step), (0, step + 1), (2_147_481_600, 2_147_483_640), (top - 1, top), (top - step, top),
               (top - step - 1, top), (top - 3 * step, top - step + 5), (0, top)]
-    words = run(tmp_path, EDGES, *[v for b in blocks for v in b])
+    words = run(tmp_path, HEAD, EDGES, *[v for b in blocks for v in b])
     for i, (first, end) in enumerate(blocks):
         passes, stored, bad = map(int, words[3 * i:3 * i + 3])
         assert bad == 0, (first, end)
@@ -85,4 +62,4 @@ int main(int argc, char **argv) {
 def test_point_offsets_at_the_limit(tmp_path):
     """Coordinates are 12 bytes a point up to the largest n that the calls take."""
     at = [0, 1, 4096, 715_827_882, 715_827_883, 1_500_000_000, 2**31 - 1 - 4096]
-    assert [int(w) for w in run(tmp_path, POINTS, *at)] == [12 * p for p in at]
+    assert [int(w) for w in run(tmp_path, HEAD, POINTS, *at)] == [12 * p for p in at]
