@@ -42,7 +42,7 @@ class SweepCounts {
     int32_t most = 0;
     for (int i = 0; i < clouds_; ++i) {
       const int32_t v = __atomic_load_n(&words[i], __ATOMIC_ACQUIRE);
-      if ((v & ~0xffff) != tag_) return;
+      if (tag_of(v) != tag_) return;
       most = (v & 0xffff) > most ? v & 0xffff : most;
     }
     Record &r = record(asked_);
@@ -53,20 +53,21 @@ class SweepCounts {
   }
 
   // A call of this kind asks for its counts (none may be outstanding).
-  // Returns the tag for its words.
-  int32_t ask(const CallKind &kind, int clouds) {
-    tag_ = (tag_ + 0x10000) & 0x7fff0000;
-    if (tag_ == 0) tag_ = 0x10000;
+  // Returns the tag for its words, which are cleared: tags come round again,
+  // and a word that a larger batch left long ago must not pass for a new one.
+  int32_t ask(const CallKind &kind, int clouds, int32_t *words) {
+    tag_ = tag_ == 0x7fff0000u ? 0x10000u : tag_ + 0x10000u;
+    for (int i = 0; i < clouds; ++i) __atomic_store_n(&words[i], 0, __ATOMIC_RELEASE);
     pending_ = true;
     asked_ = kind;
     clouds_ = clouds;
-    return tag_;
+    return (int32_t)tag_;
   }
 
   // Whether launches may still store counts.
   bool outstanding(const int32_t *words) const {
     for (int i = 0; pending_ && i < clouds_; ++i)
-      if ((__atomic_load_n(&words[i], __ATOMIC_ACQUIRE) & ~0xffff) != tag_) return true;
+      if (tag_of(__atomic_load_n(&words[i], __ATOMIC_ACQUIRE)) != tag_) return true;
     return false;
   }
 
@@ -86,6 +87,7 @@ class SweepCounts {
   }
 
  private:
+  static uint32_t tag_of(int32_t word) { return (uint32_t)word & ~0xffffu; }
   struct Record {
     CallKind kind = {-1, 0, 0};
     int32_t recent[kRecent] = {0};
@@ -109,7 +111,7 @@ class SweepCounts {
   Record records_[kKinds];
   uint64_t clock_ = 0;
   bool pending_ = false;
-  int32_t tag_ = 0;  // of the outstanding counts, above the count's 16 bits
+  uint32_t tag_ = 0;  // of the outstanding counts: 15 bits above the count's 16
   CallKind asked_ = {-1, 0, 0};
   int clouds_ = 0;
 };

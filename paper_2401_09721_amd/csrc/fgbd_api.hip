@@ -704,7 +704,7 @@ static int adaptive_sweep_launches(fgbd_ctx ctx, hipStream_t s, Run &r, CallEntr
   ctx->sweeps.poll(ctx->hint_host);
   if (!ctx->sweeps.pending()) {  // pending from here: a launch that fails leaves it so (no further read-back)
     r.hint = ctx->hint_dev;
-    r.hint_tag = ctx->sweeps.ask(kind, r.pl.B);
+    r.hint_tag = ctx->sweeps.ask(kind, r.pl.B, ctx->hint_host);
   }
   return ctx->sweeps.launches(kind, cap, ctx->tune_set ? cap : kMaxAdaptiveSweeps);
 }

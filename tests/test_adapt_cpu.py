@@ -15,7 +15,7 @@ int main(int argc, char **argv) {
     const CallKind kind = call_kind(atoi(argv[i]), clouds, atoll(argv[i + 2]));
     s.poll(words);
     if (!s.pending()) {
-      const int32_t tag = s.ask(kind, clouds);
+      const int32_t tag = s.ask(kind, clouds, words);
       for (int c = 0; c < clouds; ++c) words[c] = (c ? 1 : needed) | tag;
     }
     printf("%d\\n", s.launches(kind, 8, 64));
@@ -55,3 +55,42 @@ def test_more_kinds_than_records(tmp_path):
     got = chosen(tmp_path, many * 3)
     assert all(g in (8, b[3], b[3] + 1) for g, b in zip(got, many * 3))
     assert got[-1] == 8 and chosen(tmp_path, many[:8] * 3)[-8:] == list(range(1, 9))
+
+
+# a batch of 64 once, then single frames until the tags have come round, then a
+# batch whose clouds are stored one by one
+TAGS = """
+int main(int argc, char **argv) {
+  SweepCounts s;
+  int32_t words[64] = {0};
+  const CallKind frame = call_kind(kCallDenoise, 1, 1000), batch = call_kind(kCallBatched, 64, 4096);
+  int64_t bad = 0;
+  int32_t tag = s.ask(batch, 64, words);
+  const int32_t first = tag;
+  for (int c = 0; c < 64; ++c) words[c] = 50 | tag;
+  s.poll(words);
+  do {
+    tag = s.ask(frame, 1, words);
+    bad += tag <= 0 || (tag & 0xffff) != 0 || !s.pending() || !s.outstanding(words);
+    words[0] = 4 | tag;
+    bad += s.outstanding(words);
+    s.poll(words);
+    bad += s.pending();
+  } while (tag != 0x7fff0000);  // the largest tag; the batch's own is next
+  tag = s.ask(batch, 64, words);
+  bad += tag != first;
+  for (int c = 0; c < 64; ++c) {
+    s.poll(words);
+    bad += !s.pending() || !s.outstanding(words);
+    words[c] = 7 | tag;
+  }
+  bad += s.outstanding(words);
+  s.poll(words);
+  bad += s.pending() || s.launches(batch, 8, 64) != 51 || s.launches(frame, 8, 64) != 4;
+  printf("%lld\\n", (long long)bad);
+}
+"""
+
+
+def test_tags_that_come_round(tmp_path):
+    assert run(tmp_path, HEAD, TAGS) == ["0"]
