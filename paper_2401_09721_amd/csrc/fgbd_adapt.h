@@ -64,7 +64,17 @@ class SweepCounts {
     return (int32_t)tag_;
   }
 
-  // Whether launches may still store counts.
+  // The call that asked failed: its launches may or may not have been
+  // enqueued, so later calls ask anew, and the words are in use until the
+  // device has been waited for.
+  void cancel() {
+    pending_ = false;
+    unsure_ = true;
+  }
+
+  // Whether a wait for the device has to come before the words are freed
+  // whatever they hold, and whether launches may still store counts.
+  bool unsure() const { return unsure_; }
   bool outstanding(const int32_t *words) const {
     for (int i = 0; pending_ && i < clouds_; ++i)
       if (tag_of(__atomic_load_n(&words[i], __ATOMIC_ACQUIRE)) != tag_) return true;
@@ -110,10 +120,53 @@ class SweepCounts {
   }
   Record records_[kKinds];
   uint64_t clock_ = 0;
-  bool pending_ = false;
+  bool pending_ = false, unsure_ = false;
   uint32_t tag_ = 0;  // of the outstanding counts: 15 bits above the count's 16
   CallKind asked_ = {-1, 0, 0};
   int clouds_ = 0;
+};
+
+// The radix sort's route.  words[0] is set by the local sort of a call that
+// asked when a block sorted a very large range alone (points crowded into few
+// top code digits, such as a plane normal to a scan axis), words[1] by the
+// launch after that sort, to the call's number.  A call that finds it set
+// sends itself and the next ones through the LSD passes.
+class SortWatch {
+ public:
+  // Whether a call sorts by LSD passes.
+  bool lsd(const int32_t *words, int calls) {
+    if (pending_ && __atomic_load_n(&words[1], __ATOMIC_ACQUIRE) == seq_) {
+      if (__atomic_load_n(&words[0], __ATOMIC_RELAXED)) left_ = calls;
+      pending_ = false;
+    }
+    if (left_ == 0) return false;
+    --left_;
+    return true;
+  }
+
+  bool pending() const { return pending_; }
+
+  // A call asks (none may be outstanding).  Returns its number.
+  int32_t ask(int32_t *words) {
+    __atomic_store_n(&words[0], 0, __ATOMIC_RELEASE);
+    seq_ = seq_ == INT32_MAX ? 1 : seq_ + 1;
+    pending_ = true;
+    return seq_;
+  }
+
+  // As in SweepCounts.
+  void cancel() {
+    pending_ = false;
+    unsure_ = true;
+  }
+  bool unsure() const { return unsure_; }
+  bool outstanding(const int32_t *words) const {
+    return pending_ && __atomic_load_n(&words[1], __ATOMIC_ACQUIRE) != seq_;
+  }
+
+ private:
+  int32_t seq_ = 0, left_ = 0;
+  bool pending_ = false, unsure_ = false;
 };
 
 }  // namespace fgbd

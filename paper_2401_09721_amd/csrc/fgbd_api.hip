@@ -74,17 +74,12 @@ struct fgbd_ctx_s {
   int32_t *hint_host = nullptr;  // [kMaxSeg], hipHostMalloc'ed
   int32_t *hint_dev = nullptr;   // its device address
   bool hint_failed = false;      // could not set up: no adaptation
-  // Sort route: a host-mapped flag the local sort sets when a block sorted a
-  // very large range alone (points crowded into few top code digits, such as
-  // a plane normal to a scan axis), read back without waiting like the sweep
-  // counts (the second word is the last watched call whose sort has ended);
-  // while sort_lsd_left > 0, eager calls sort by LSD passes.
+  // Sort route: read back without waiting like the sweep counts; eager calls
+  // after one that found a very large range sort by LSD passes for a while.
+  SortWatch sort;
   int32_t *sort_flag_host = nullptr;  // [2]
   int32_t *sort_flag_dev = nullptr;
-  int32_t sort_seq = 0;
   bool sort_failed = false;
-  bool sort_pending = false;
-  int sort_lsd_left = 0;
   int64_t wait_us = -1;  // fgbd_set_sweep_wait
 };
 
@@ -361,7 +356,7 @@ static void sort_policy(fgbd_ctx ctx, hipStream_t s, Run &r) {
     (void)hipGetLastError();
     return;
   }
-  if (cs != hipStreamCaptureStatusNone) return;
+  if (cs != hipStreamCaptureStatusNone || r.pl.n_cap == 0) return;
   if (!ctx->sort_flag_host) {
     void *dev = nullptr;
     if (hipHostMalloc((void **)&ctx->sort_flag_host, 2 * sizeof(int32_t),
@@ -372,32 +367,38 @@ static void sort_policy(fgbd_ctx ctx, hipStream_t s, Run &r) {
       return;
     }
     ctx->sort_flag_dev = (int32_t *)dev;
-    ctx->sort_flag_host[1] = 0;
+    ctx->sort_flag_host[0] = ctx->sort_flag_host[1] = 0;
   }
-  if (ctx->sort_pending && __atomic_load_n(&ctx->sort_flag_host[1], __ATOMIC_ACQUIRE) == ctx->sort_seq) {
-    if (__atomic_load_n(&ctx->sort_flag_host[0], __ATOMIC_RELAXED)) ctx->sort_lsd_left = kSortLsdCalls;
-    ctx->sort_pending = false;
-  }
-  if (ctx->sort_lsd_left > 0) {
-    r.sort_lsd = true;
-    --ctx->sort_lsd_left;
-    return;
-  }
-  if (!ctx->sort_pending) {
-    __atomic_store_n(&ctx->sort_flag_host[0], 0, __ATOMIC_RELEASE);
-    ctx->sort_seq = ctx->sort_seq == INT32_MAX ? 1 : ctx->sort_seq + 1;
+  r.sort_lsd = ctx->sort.lsd(ctx->sort_flag_host, kSortLsdCalls);
+  if (!r.sort_lsd && !ctx->sort.pending()) {
     r.sort_big = ctx->sort_flag_dev;
-    r.sort_seq = ctx->sort_seq;
-    r.sort_pending = &ctx->sort_pending;
+    r.sort_seq = ctx->sort.ask(ctx->sort_flag_host);
   }
 }
+
+// The read-backs that a call asked for, given up when the call returns before
+// all of its launches were made.
+struct ReadBacks {
+  fgbd_ctx ctx;
+  const Run &r;
+  bool launched = false;
+  ReadBacks(fgbd_ctx c, const Run &run) : ctx(c), r(run) {}
+  ~ReadBacks() {
+    if (launched) return;
+    if (r.sort_big) ctx->sort.cancel();
+    if (r.hint) ctx->sweeps.cancel();
+  }
+  fgbd_status done(fgbd_status st) {
+    launched = st == FGBD_OK;
+    return st;
+  }
+};
 
 // Graph construction into (col, dist2, p); sigma_g into res.  p == NULL
 // stops after the merge: the sweeps then derive sigma_g and the weights.
 fgbd_status run_slg(const Run &r, const int32_t *xyz, int32_t *col, int32_t *dist2, float *p, fgbd_result *res,
                     const float *rgb = nullptr) {
   Sorted sorted = {nullptr, 0};
-  if (r.sort_big) *r.sort_pending = true;  // (a launch that fails leaves it so: no further watch)
   HIP_TRY(launch_sort(r, xyz, res, &sorted), "radix sort launch");
   FGBD_PRE(r.pf, kMerge);
   HIP_TRY(launch_merge(r, xyz, sorted, col, dist2, res), "neighbour merge launch");
@@ -584,8 +585,7 @@ fgbd_status fgbd_create(fgbd_ctx *out, int32_t hip_device) {
 
 // Launches that may still write the context's host-mapped words.
 static bool words_pending(fgbd_ctx ctx) {
-  if (ctx->sort_pending && __atomic_load_n(&ctx->sort_flag_host[1], __ATOMIC_ACQUIRE) != ctx->sort_seq) return true;
-  return ctx->sweeps.outstanding(ctx->hint_host);
+  return ctx->sort.outstanding(ctx->sort_flag_host) || ctx->sweeps.outstanding(ctx->hint_host);
 }
 
 fgbd_status fgbd_destroy(fgbd_ctx ctx) {
@@ -595,8 +595,9 @@ fgbd_status fgbd_destroy(fgbd_ctx ctx) {
     // launches that may still write the host-mapped words or the workspace:
     // the words usually tell of their end
     const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(100);
-    while (!ctx->own && words_pending(ctx) && std::chrono::steady_clock::now() < until) std::this_thread::yield();
-    if (ctx->own || words_pending(ctx)) (void)hipDeviceSynchronize();
+    const bool wait = ctx->own || ctx->sort.unsure() || ctx->sweeps.unsure();
+    while (!wait && words_pending(ctx) && std::chrono::steady_clock::now() < until) std::this_thread::yield();
+    if (wait || words_pending(ctx)) (void)hipDeviceSynchronize();
     if (ctx->hint_host) (void)hipHostFree(ctx->hint_host);
     if (ctx->sort_flag_host) (void)hipHostFree(ctx->sort_flag_host);
     if (ctx->own) (void)hipFree(ctx->own);
@@ -652,9 +653,10 @@ fgbd_status fgbd_build_slg(fgbd_ctx ctx, const int32_t *xyz, int64_t n, const fg
   EventProf ep(ctx, s);
   Run r = make_run(ctx, pl, ws, *params, n, s, &ep);
   sort_policy(ctx, s, r);
+  ReadBacks rb(ctx, r);
   HIP_TRY(launch_setup(r, nullptr, n, res, 1), "setup launch");
   if (n == 0) return ok();
-  if ((st = run_slg(r, xyz, g->col, g->dist2, g->p, res)) != FGBD_OK) return st;
+  if ((st = rb.done(run_slg(r, xyz, g->col, g->dist2, g->p, res))) != FGBD_OK) return st;
   return ok();
 }
 
@@ -702,7 +704,7 @@ static int adaptive_sweep_launches(fgbd_ctx ctx, hipStream_t s, Run &r, CallEntr
   }
   const CallKind kind = call_kind(entry, r.pl.B, r.pl.n_cap);
   ctx->sweeps.poll(ctx->hint_host);
-  if (!ctx->sweeps.pending()) {  // pending from here: a launch that fails leaves it so (no further read-back)
+  if (!ctx->sweeps.pending()) {
     r.hint = ctx->hint_dev;
     r.hint_tag = ctx->sweeps.ask(kind, r.pl.B, ctx->hint_host);
   }
@@ -739,8 +741,9 @@ fgbd_status fgbd_filter(fgbd_ctx ctx, const fgbd_graph *g, const float *rgb_in, 
   if (n == 0) return ok();
   const int q_limit = select ? params->q_max : q_fixed;
   if (select) r.sweep_launches = adaptive_sweep_launches(ctx, s, r, kCallFilter);
-  if ((st = run_filter(r, g->col, g->p, nullptr, rgb_in, patch_spread, noise, select, q_limit, rgb_out, res)) !=
-      FGBD_OK)
+  ReadBacks rb(ctx, r);
+  if ((st = rb.done(run_filter(r, g->col, g->p, nullptr, rgb_in, patch_spread, noise, select, q_limit, rgb_out,
+                               res))) != FGBD_OK)
     return st;
   return ok();
 }
@@ -784,6 +787,7 @@ fgbd_status fgbd_denoise(fgbd_ctx ctx, const int32_t *xyz, const float *rgb_in, 
   EventProf ep(ctx, s);
   Run r = make_run(ctx, pl, ws, *params, n, s, &ep);
   sort_policy(ctx, s, r);
+  ReadBacks rb(ctx, r);
   if (n == 0) {
     HIP_TRY(launch_setup(r, nullptr, n, res, 2), "setup launch");
     return ok();
@@ -793,7 +797,7 @@ fgbd_status fgbd_denoise(fgbd_ctx ctx, const int32_t *xyz, const float *rgb_in, 
   r.setup = setup_args(r, nullptr, n, res, 1);
   r.sweep_launches = adaptive_sweep_launches(ctx, s, r, kCallDenoise);
   r.relabel_ok = r.prm.patch_order == 0;  // index-ordered patches need the input numbering
-  if ((st = run_denoise(r, xyz, rgb_in, rgb_out, res)) != FGBD_OK) return st;
+  if ((st = rb.done(run_denoise(r, xyz, rgb_in, rgb_out, res))) != FGBD_OK) return st;
   return ok();
 }
 
@@ -827,11 +831,12 @@ fgbd_status fgbd_denoise_batched(fgbd_ctx ctx, const int32_t *xyz, const float *
   EventProf ep(ctx, s);
   Run r = make_run(ctx, pl, ws, *params, -1, s, &ep);
   sort_policy(ctx, s, r);
+  ReadBacks rb(ctx, r);
   HIP_TRY(launch_setup(r, offsets, 0, res, n_total == 0 ? 2 : 1), "setup launch");
   if (n_total == 0) return ok();
   r.sweep_launches = adaptive_sweep_launches(ctx, s, r, kCallBatched);
   r.relabel_ok = r.prm.patch_order == 0;  // index-ordered patches need the input numbering
-  if ((st = run_denoise(r, xyz, rgb_in, rgb_out, res)) != FGBD_OK) return st;
+  if ((st = rb.done(run_denoise(r, xyz, rgb_in, rgb_out, res))) != FGBD_OK) return st;
   return ok();
 }
 
@@ -850,13 +855,14 @@ fgbd_status fgbd_denoise_batched_fixed_q(fgbd_ctx ctx, const int32_t *xyz, const
   EventProf ep(ctx, s);
   Run r = make_run(ctx, pl, ws, *params, -1, s, &ep);
   sort_policy(ctx, s, r);
+  ReadBacks rb(ctx, r);
   HIP_TRY(launch_setup(r, offsets, 0, res, n_total == 0 ? 2 : 1), "setup launch");
   if (n_total == 0) return ok();
   // SLG, then q_fixed sweeps whose first derives sigma_g and the weights;
   // no noise estimate and no selection (every sweep is a launch of its own)
   r.relabel_ok = true;
   if ((st = run_slg(r, xyz, r.b.col, r.b.dist2, nullptr, res, rgb_in)) != FGBD_OK) return st;
-  return run_filter(r, r.b.col, r.b.p, r.b.dist2, rgb_in, nullptr, nullptr, 0, q_fixed, rgb_out, res);
+  return rb.done(run_filter(r, r.b.col, r.b.p, r.b.dist2, rgb_in, nullptr, nullptr, 0, q_fixed, rgb_out, res));
 }
 
 fgbd_status fgbd_smooth_geometry(fgbd_ctx ctx, const int32_t *xyz, int64_t n, const fgbd_params *params, int32_t q,
@@ -879,6 +885,7 @@ fgbd_status fgbd_smooth_geometry(fgbd_ctx ctx, const int32_t *xyz, int64_t n, co
   EventProf ep(ctx, s);
   Run r = make_run(ctx, pl, ws, *params, n, s, &ep);
   sort_policy(ctx, s, r);
+  ReadBacks rb(ctx, r);
   HIP_TRY(launch_setup(r, nullptr, n, res, n == 0 ? 2 : 1), "setup launch");
   if (n == 0) return ok();
   // the coordinates become the signal in the output buffer; with a fixed q
@@ -886,7 +893,7 @@ fgbd_status fgbd_smooth_geometry(fgbd_ctx ctx, const int32_t *xyz, int64_t n, co
   // after the last, so it runs in place
   HIP_TRY(launch_coords_f32(xyz, 3 * n, xyz_out, s), "coordinate launch");
   if ((st = run_slg(r, xyz, r.b.col, r.b.dist2, nullptr, res)) != FGBD_OK) return st;
-  return run_filter(r, r.b.col, r.b.p, r.b.dist2, xyz_out, nullptr, nullptr, 0, q, xyz_out, res);
+  return rb.done(run_filter(r, r.b.col, r.b.p, r.b.dist2, xyz_out, nullptr, nullptr, 0, q, xyz_out, res));
 }
 
 static fgbd_status check_schedule(const fgbd_schedule *s) {

@@ -608,11 +608,10 @@ struct Run {
   // sorts unless sort_lsd.  sort_big (host-mapped, NULL: not watched): the
   // local sort sets sort_big[0] when a block had to sort a range of more
   // than kBigRange items alone; the merge launch then stores sort_seq into
-  // sort_big[1], and *sort_pending marks the read-back outstanding.
+  // sort_big[1].
   bool sort_lsd = false;
   int32_t *sort_big = nullptr;
   int32_t sort_seq = 0;
-  bool *sort_pending = nullptr;
   // bound of each wait between sweeps in the in-launch sweep loop, in
   // microseconds (negative: half a second)
   int64_t wait_us = -1;

@@ -94,3 +94,48 @@ int main(int argc, char **argv) {
 
 def test_tags_that_come_round(tmp_path):
     assert run(tmp_path, HEAD, TAGS) == ["0"]
+
+
+FAILED = """
+int main(int argc, char **argv) {
+  int64_t bad = 0;
+  const CallKind kind = call_kind(kCallDenoise, 1, 1000);
+  SweepCounts s;
+  int32_t words[64] = {0};
+  s.ask(kind, 1, words);
+  s.cancel();  // the call failed: nothing will be stored
+  s.poll(words);
+  bad += s.pending() || s.outstanding(words) || !s.unsure();
+  for (int i = 0; i < 3; ++i) {  // later calls adapt as before
+    words[0] = 5 | s.ask(kind, 1, words);
+    s.poll(words);
+  }
+  bad += s.pending() || s.launches(kind, 8, 64) != 5;
+  // a count that the failed call's launches did store is not taken for another's
+  const int32_t late = 60 | s.ask(kind, 1, words);
+  s.cancel();
+  s.ask(kind, 1, words);
+  words[0] = late;
+  s.poll(words);
+  bad += !s.pending() || !s.outstanding(words) || s.launches(kind, 8, 64) != 5;
+
+  SortWatch w;
+  int32_t flag[2] = {0, 0};
+  bad += w.lsd(flag, 3) || w.unsure();
+  w.ask(flag);
+  w.cancel();
+  bad += w.pending() || w.outstanding(flag) || !w.unsure() || w.lsd(flag, 3);
+  const int32_t seq = w.ask(flag);
+  bad += !w.pending() || !w.outstanding(flag) || w.lsd(flag, 3);
+  flag[0] = 1;
+  flag[1] = seq;
+  bad += w.outstanding(flag);
+  for (int i = 0; i < 3; ++i) bad += !w.lsd(flag, 3) || w.pending();
+  bad += w.lsd(flag, 3);
+  printf("%lld\\n", (long long)bad);
+}
+"""
+
+
+def test_a_call_that_failed(tmp_path):
+    assert run(tmp_path, HEAD, FAILED) == ["0"]
