@@ -126,6 +126,24 @@ class SweepCounts {
   int clouds_ = 0;
 };
 
+// The mark that a context's schedule was chosen, over trials of candidates: set
+// while they run (they bound the trial calls' sweep launches), and after them
+// only if a schedule was kept; a tuning that fails leaves the mark as it was.
+class ScheduleTrial {
+ public:
+  explicit ScheduleTrial(bool &chosen) : chosen_(chosen), before_(chosen) {}
+  ~ScheduleTrial() { chosen_ = kept_ || before_; }
+  ScheduleTrial(const ScheduleTrial &) = delete;
+  ScheduleTrial &operator=(const ScheduleTrial &) = delete;
+  void start() { chosen_ = true; }
+  void keep() { kept_ = true; }
+
+ private:
+  bool &chosen_;
+  const bool before_;
+  bool kept_ = false;
+};
+
 // The radix sort's route.  words[0] is set by the local sort of a call that
 // asked when a block sorted a very large range alone (points crowded into few
 // top code digits, such as a plane normal to a scan axis), words[1] by the

@@ -996,7 +996,8 @@ fgbd_status fgbd_autotune(fgbd_ctx ctx, const int32_t *xyz, const float *rgb_in,
   // (the candidates bound the trial calls' counts: on a context with no
   // schedule set, recent calls' counts could go above them, and every
   // candidate timed the same)
-  ctx->tune_set = true;
+  ScheduleTrial trial(ctx->tune_set);
+  trial.start();
   double best_ms = 1e300;
   for (int c = 0; c < 7 && st == FGBD_OK; ++c) {
     ctx->tune = best;
@@ -1017,9 +1018,9 @@ fgbd_status fgbd_autotune(fgbd_ctx ctx, const int32_t *xyz, const float *rgb_in,
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   ctx->tune = best;
-  ctx->tune_set = true;
   ctx->profile = was_profiling;
   if (st != FGBD_OK) return st;
+  trial.keep();
   HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
   if (chosen) (void)fgbd_get_schedule(ctx, chosen);
   return ok();

@@ -139,3 +139,26 @@ int main(int argc, char **argv) {
 
 def test_a_call_that_failed(tmp_path):
     assert run(tmp_path, HEAD, FAILED) == ["0"]
+
+
+TRIALS = """
+int main(int argc, char **argv) {
+  for (int before = 0; before < 2; ++before)
+    for (int kept = 0; kept < 2; ++kept) {
+      bool chosen = before;
+      int during = 0;
+      {
+        ScheduleTrial t(chosen);
+        t.start();
+        during = chosen;
+        if (kept) t.keep();
+      }
+      printf("%d%d\\n", during, (int)chosen);
+    }
+}
+"""
+
+
+def test_a_tuning_that_fails_leaves_the_mark(tmp_path):
+    # (not chosen before: failed, kept; chosen before: failed, kept)
+    assert run(tmp_path, HEAD, TRIALS) == ["10", "11", "11", "11"]
