@@ -76,8 +76,9 @@ struct fgbd_ctx_s {
   bool hint_failed = false;      // could not set up: no adaptation
   // Sort route: read back without waiting like the sweep counts; eager calls
   // after one that found a very large range sort by LSD passes for a while.
-  SortWatch sort;
-  int32_t *sort_flag_host = nullptr;  // [2]
+  // Codes above 32 bits and others each follow their own calls.
+  SortWatch sort[2];
+  int32_t *sort_flag_host = nullptr;  // [2][2]
   int32_t *sort_flag_dev = nullptr;
   bool sort_failed = false;
   int64_t wait_us = -1;  // fgbd_set_sweep_wait
@@ -359,7 +360,7 @@ static void sort_policy(fgbd_ctx ctx, hipStream_t s, Run &r) {
   if (cs != hipStreamCaptureStatusNone || r.pl.n_cap == 0) return;
   if (!ctx->sort_flag_host) {
     void *dev = nullptr;
-    if (hipHostMalloc((void **)&ctx->sort_flag_host, 2 * sizeof(int32_t),
+    if (hipHostMalloc((void **)&ctx->sort_flag_host, 4 * sizeof(int32_t),
                       hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
         hipHostGetDevicePointer(&dev, ctx->sort_flag_host, 0) != hipSuccess) {
       (void)hipGetLastError();
@@ -367,12 +368,15 @@ static void sort_policy(fgbd_ctx ctx, hipStream_t s, Run &r) {
       return;
     }
     ctx->sort_flag_dev = (int32_t *)dev;
-    ctx->sort_flag_host[0] = ctx->sort_flag_host[1] = 0;
+    for (int i = 0; i < 4; ++i) ctx->sort_flag_host[i] = 0;
   }
-  r.sort_lsd = ctx->sort.lsd(ctx->sort_flag_host, kSortLsdCalls);
-  if (!r.sort_lsd && !ctx->sort.pending()) {
-    r.sort_big = ctx->sort_flag_dev;
-    r.sort_seq = ctx->sort.ask(ctx->sort_flag_host);
+  const int w = wide_codes(r.dt);
+  SortWatch &watch = ctx->sort[w];
+  int32_t *words = ctx->sort_flag_host + 2 * w;
+  r.sort_lsd = watch.lsd(words, kSortLsdCalls);
+  if (!r.sort_lsd && !watch.pending()) {
+    r.sort_big = ctx->sort_flag_dev + 2 * w;
+    r.sort_seq = watch.ask(words);
   }
 }
 
@@ -385,7 +389,7 @@ struct ReadBacks {
   ReadBacks(fgbd_ctx c, const Run &run) : ctx(c), r(run) {}
   ~ReadBacks() {
     if (launched) return;
-    if (r.sort_big) ctx->sort.cancel();
+    if (r.sort_big) ctx->sort[wide_codes(r.dt)].cancel();
     if (r.hint) ctx->sweeps.cancel();
   }
   fgbd_status done(fgbd_status st) {
@@ -585,7 +589,9 @@ fgbd_status fgbd_create(fgbd_ctx *out, int32_t hip_device) {
 
 // Launches that may still write the context's host-mapped words.
 static bool words_pending(fgbd_ctx ctx) {
-  return ctx->sort.outstanding(ctx->sort_flag_host) || ctx->sweeps.outstanding(ctx->hint_host);
+  for (int w = 0; w < 2; ++w)
+    if (ctx->sort[w].outstanding(ctx->sort_flag_host + 2 * w)) return true;
+  return ctx->sweeps.outstanding(ctx->hint_host);
 }
 
 fgbd_status fgbd_destroy(fgbd_ctx ctx) {
@@ -595,7 +601,7 @@ fgbd_status fgbd_destroy(fgbd_ctx ctx) {
     // launches that may still write the host-mapped words or the workspace:
     // the words usually tell of their end
     const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(100);
-    const bool wait = ctx->own || ctx->sort.unsure() || ctx->sweeps.unsure();
+    const bool wait = ctx->own || ctx->sort[0].unsure() || ctx->sort[1].unsure() || ctx->sweeps.unsure();
     while (!wait && words_pending(ctx) && std::chrono::steady_clock::now() < until) std::this_thread::yield();
     if (wait || words_pending(ctx)) (void)hipDeviceSynchronize();
     if (ctx->hint_host) (void)hipHostFree(ctx->hint_host);

@@ -643,6 +643,7 @@ inline int msd_index_bits(const DirTable &dt, int64_t n_cap) {
   const int ib = 64 - dt.code_bits;
   return ib > 0 && ib < 32 && n_cap <= ((int64_t)1 << ib) ? ib : 0;
 }
+inline int wide_codes(const DirTable &dt) { return dt.code_bits > 32 ? 1 : 0; }
 hipError_t launch_sort(const Run &r, const int32_t *xyz, fgbd_result *res, Sorted *sorted);
 
 // With r.relabel_ok the merge also counts each cloud's far edges.

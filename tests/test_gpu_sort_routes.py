@@ -1,0 +1,69 @@
+"""Which route the sort takes, counted by the context's profiling, each case on
+a context of its own so that no call before it decides: one top-digit pass and
+the local sort, or 8-bit passes.  Graphs are compared with the oracle's,
+exactly."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle as O  # noqa: E402
+from paper_2401_09721_amd import fgbd  # noqa: E402
+
+from gpu_helpers import dev  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+class Sorter:
+    """build_slg on one context: the graph's check and the route taken."""
+
+    def __init__(self):
+        self.ctx = fgbd.Context("cuda")
+        self.ctx.profile(True)
+
+    def route(self):
+        kinds = self.ctx.profile_read()
+        return kinds["local_sort"][1], kinds["radix_downsweep"][1]
+
+    def __call__(self, xyz, prm, check=True):
+        self.ctx.profile_read()
+        g = fgbd.build_slg(dev(xyz, torch.int32), prm, ctx=self.ctx)
+        torch.cuda.synchronize()  # lets the next call read what this one found
+        if check:
+            col, d2 = O.slg_graph(xyz, prm.bits, prm.num_dirs, prm.window, prm.k)
+            assert np.array_equal(g.col.cpu().numpy(), col)
+            assert np.array_equal(g.dist2.cpu().numpy(), np.minimum(d2, (1 << 31) - 1))
+        return self.route()
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, *e):
+        self.ctx.close()
+
+
+TOP_DIGIT = (1, 1)
+
+
+def plane(rng, bits, n):
+    """n points of one plane normal to a scan axis: one top digit holds all."""
+    flat = rng.choice(1 << (2 * min(bits, 10)), size=n, replace=False)
+    return np.stack([flat >> min(bits, 10), flat & ((1 << min(bits, 10)) - 1), np.full(n, 300)], 1).astype(np.int32)
+
+
+def test_code_widths_do_not_route_each_other():
+    rng = np.random.default_rng(1)
+    wide, narrow = plane(rng, 11, 40000), rng.integers(0, 1024, size=(5000, 3)).astype(np.int32)
+    pw, pn = fgbd.default_params(bits=11), fgbd.default_params(bits=10)
+    with Sorter() as s:
+        assert s(wide, pw, check=False) == TOP_DIGIT  # its range is found to be very large
+        assert s(narrow, pn) == TOP_DIGIT
+        assert s(wide, pw) == (0, 5)  # 35-bit codes: five passes of 8 bits
+        assert s(narrow, pn) == TOP_DIGIT
+    with Sorter() as s:
+        crowded = plane(rng, 10, 40000)
+        assert s(crowded, pn, check=False) == TOP_DIGIT
+        assert s(wide[:5000], pw) == TOP_DIGIT
+        assert s(crowded, pn) == (0, 4)
+        assert s(wide[:5000], pw) == TOP_DIGIT
