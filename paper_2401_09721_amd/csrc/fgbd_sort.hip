@@ -982,7 +982,7 @@ constexpr int kLocalCap = kLocalThreads * kLocalItems;  // 8192 items
 constexpr int kPosBits = 13;                            // a position in an in-LDS range
 constexpr int kBinBits = 13;
 constexpr int kBins = 1 << kBinBits;
-constexpr uint32_t kMaxBin = 512;                       // a larger bin sends its window to the slow path
+constexpr uint32_t kMaxBin = 512;                       // a larger bin makes its window's keys take LSD passes
 constexpr int kSlowItems = 4;                           // per thread and chunk, slow path
 static_assert(kLocalCap == 1 << kPosBits, "positions of the largest in-LDS range");
 
@@ -1020,6 +1020,14 @@ __device__ __forceinline__ uint32_t wave_rank8(uint32_t digit, uint32_t *cnt, ui
   if (before == 0)
     __hip_atomic_fetch_add(&cnt[digit], (uint32_t)__popcll(peers), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   return r;
+}
+
+// A value that every lane holds, in scalar registers (the compiler cannot tell
+// of one loaded from memory that kernels write): branches on it are scalar, and
+// nothing has to live through the side not taken.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int4 uniform(int4 v) {
+  return make_int4(uniform(v.x), uniform(v.y), uniform(v.z), uniform(v.w));
 }
 
 // Exclusive prefix of v over the threads of the block (up to 16 waves);
@@ -1061,7 +1069,8 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   uint16_t *const s_of = reinterpret_cast<uint16_t *>(s_two + kBins / 2 + 2);
   __shared__ uint32_t s_w[16];
   __shared__ unsigned long long s_max;
-  __shared__ int s_swap;  // equal codes out of index order
+  __shared__ int s_swap;   // equal codes out of index order
+  __shared__ int s_heavy;  // a bin holds more than kMaxBin items
   // slow path
   uint32_t(*const s_cnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s_key);  // [kLocalWaves][256]
   uint32_t *const s_base = s_bin;                                          // [256]
@@ -1084,9 +1093,9 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   // where the cloud's next window's starts.  The digit before the next
   // window's first one that starts at or after its base is never empty.
   const int4 *wrow = a.win + (size_t)d * a.nwin;
-  const int4 here = wrow[win], next = wrow[min(win + 1, a.nwin - 1)];
+  const int4 here = uniform(wrow[win]), next = uniform(wrow[min(win + 1, a.nwin - 1)]);
   const bool last_win = win + 1 == ti.next_first;
-  const int seg_end = a.sa.n_fixed >= 0 ? a.sa.n_fixed : (int)a.sa.segs->start[ti.s + 1];
+  const int seg_end = uniform(a.sa.n_fixed >= 0 ? a.sa.n_fixed : (int)a.sa.segs->start[ti.s + 1]);
   const int lo = here.x, hi = last_win ? seg_end : next.x;
   if (lo >= hi) return;  // no bucket starts in the window (uniform)
   const uint32_t df = (uint32_t)here.y, dl = (uint32_t)(last_win ? here.w : next.z) - 1u;
@@ -1112,7 +1121,36 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   };
   // (final forms are equal above the index where the codes are)
   auto same_code = [&](uint64_t u, uint64_t v) { return ((u ^ v) >> (WIDE ? a.ib : 32)) == 0; };
+  // (of one 64-point chunk of the input too, inside which the top-digit pass
+  // does not keep the order of equal digits)
+  auto alike = [&](uint64_t u, uint64_t v) {
+    const uint32_t first = (uint32_t)ti.seg_start;
+    return same_code(u, v) && ((uint32_t)u & id_mask) - first >> 6 == ((uint32_t)v & id_mask) - first >> 6;
+  };
   uint64_t *out = dst + dbase;
+  // Points of one voxel that the top-digit pass left out of index order, which
+  // are of one chunk of the input and so lie next to each other: each sorted
+  // item at(s) counts the smaller ones among them (form: its final form).
+  auto put_right = [&](auto at, auto form) {
+    for (int s = t; s < R; s += kLocalThreads) {
+      const uint64_t v = at(s);
+      int r = s;
+      for (int u = s - 1; u >= 0; --u) {
+        const uint64_t o = at(u);
+        if (!alike(v, o)) break;
+        r -= o > v ? 1 : 0;
+      }
+      for (int u = s + 1; u < R; ++u) {
+        const uint64_t o = at(u);
+        if (!alike(v, o)) break;
+        r += o < v ? 1 : 0;
+      }
+      if (r == s) continue;
+      const uint32_t id = (uint32_t)v & id_mask;
+      out[lo + r] = form(v);
+      if (id < (uint32_t)a.stride) rank[dbase + id] = (uint32_t)(lo + r);
+    }
+  };
 
   if (R <= kLocalCap) {
     // ---- in LDS.  Items stay with their thread (position j kLocalThreads + t
@@ -1131,8 +1169,11 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
       item[j] = items[lo + min(j * kLocalThreads + t, R - 1)];
     }
     for (int i = t; i < kBins / 2 + 2; i += kLocalThreads) s_bin[i] = 0u;
+    // (few codes, so few and long bins whose counts would wait for each other:
+    // one LSD pass at once; 400k points on a 2^3 grid, 65 us with bins first)
+    const bool few = bits <= 8;
     if (t == 0) {
-      s_max = 0;
+      s_heavy = few ? 1 : 0;
       s_swap = 0;
     }
     __syncthreads();
@@ -1141,7 +1182,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
     auto bin_of = [&](uint32_t c) { return min(c >> shift, (uint32_t)kBins - 1u); };
 #pragma unroll
     for (int j = 0; j < kLocalItems; ++j) {
-      if (j >= J) break;
+      if (j >= J || few) break;
       if (j * kLocalThreads + t < R) {
         const uint32_t b = bin_of(rel_top(item[j])), sh16 = 16u * (b & 1u);
         place[j] = (atomicAdd(&s_bin[b >> 1], 1u << sh16) >> sh16) & 0xffffu;
@@ -1158,7 +1199,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
         big = max(big, max(a0, a1));
         sum += a0 + a1;
       }
-      if (big > kMaxBin) s_max = 1;
+      if (big > kMaxBin) s_heavy = 1;
       uint32_t run = exclusive_scan_block(sum, s_w);
 #pragma unroll
       for (int q = 0; q < kPerT; ++q) {
@@ -1169,126 +1210,177 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
       if (t == kLocalThreads - 1) s_bin[kBins / 2] = run;
     }
     __syncthreads();
-    if (s_max == 0) {  // uniform
-      const uint16_t *start = reinterpret_cast<const uint16_t *>(s_bin);
-      const uint32_t low = (1u << shift) - 1u;
+    // (a scalar branch and marked unlikely, or the other path's items spill around it)
+    if (__builtin_expect(uniform(s_heavy) != 0, 0)) {
+      // Long bins (many points in one voxel, or along one scan line): 8-bit
+      // LSD passes in LDS over the positions, whose keys stay in place.  Slot
+      // (wave J + j) 64 + lane in visiting order; slots past the range hold
+      // keys of all ones and so stay after every item.
+      uint32_t(*const s_cnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s_two);  // [kLocalWaves][256]
+      uint16_t *const s_pos = reinterpret_cast<uint16_t *>(s_two + kLocalWaves * 256);
+      const int low_passes = WIDE && drop > 0 ? (drop + 7) / 8 : 0;
+      const int passes = low_passes + (bits + 7) / 8;
+      const int first_slot = wave * J * kWave + lane;
+      for (int s = t; s < J * kLocalThreads; s += kLocalThreads) {
+        s_key[s] = s < R ? rel_top(items[lo + min(s, R - 1)]) : ~0u;
+        s_pos[s] = (uint16_t)s;
+      }
+      for (int pass = 0; pass < passes; ++pass) {
+        for (int i = t; i < kLocalWaves * 256; i += kLocalThreads) (&s_cnt[0][0])[i] = 0u;
+        __syncthreads();
+        auto digit_of_pos = [&](uint32_t pos) {
+          if (pass >= low_passes) return s_key[pos] >> 8 * (pass - low_passes) & 255u;
+          return (int)pos < R ? (uint32_t)(rel(items[lo + (int)pos]) >> 8 * pass) & 255u : 255u;
+        };
+        uint32_t pv[kLocalItems];  // rank among the wave's equal digits << 16 | position
 #pragma unroll
-      for (int j = 0; j < kLocalItems; ++j) {
-        if (j >= J) break;
-        const int pos = j * kLocalThreads + t;
-        if (pos < R) {
-          const uint32_t c = rel_top(item[j]), b = bin_of(c);
-          const uint32_t s = start[b] + place[j];
-          s_key[s] = (c & low) << kPosBits | (uint32_t)pos;
-          s_of[s] = (uint16_t)b;
+        for (int j = 0; j < kLocalItems; ++j) {
+          if (j >= J) break;
+          pv[j] = s_pos[first_slot + j * kWave];
+          uint32_t before;
+          const uint32_t count = wave_rank8(digit_of_pos(pv[j]), s_cnt[wave], before);
+          pv[j] |= (count + before) << 16;
+          asm volatile("" : "+v"(pv[j]));  // (one register an item: its parts kept for later spill)
         }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < kLocalItems; ++j) {
-        if (j >= J) break;
-        const int s = j * kLocalThreads + t;
-        if (s < R) {
-          const uint32_t key = s_key[s], b = s_of[s];
-          const uint32_t b0 = start[b], len = start[b + 1] - b0;
-          uint32_t r = b0;
-          const uint32_t *bin = s_key + b0;
-          uint32_t k = 0;
-          if (WIDE && drop > 0) {  // (uniform) equal keys but for the position: the whole items decide
-            const uint64_t mine = items[lo + (int)(key & (kLocalCap - 1))];
-            for (; k < len; ++k) {
-              const uint32_t v = bin[k];
-              bool less = v < key;
-              if (((v ^ key) >> kPosBits) == 0 && v != key) less = items[lo + (int)(v & (kLocalCap - 1))] < mine;
-              r += less ? 1u : 0u;
-            }
-          }
-          for (; k + 8 <= len; k += 8) {
-            uint32_t v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = bin[k + u];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) r += v[u] < key ? 1u : 0u;
-          }
-          for (; k < len; k += 4) {
-            uint32_t v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = bin[k + u];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) r += (k + u < len && v[u] < key) ? 1u : 0u;
-          }
-          place[j] = r << kPosBits | (key & (kLocalCap - 1));
+        __syncthreads();
+        uint32_t tot = 0;
+        if (t < 256) {
+#pragma unroll 4
+          for (int w = 0; w < kLocalWaves; ++w) tot += s_cnt[w][t];
         }
-      }
-      __syncthreads();
-      uint16_t *s_rank = reinterpret_cast<uint16_t *>(s_bin);  // (the starts have been read)
-#pragma unroll
-      for (int j = 0; j < kLocalItems; ++j) {
-        if (j >= J) break;
-        if (j * kLocalThreads + t < R) s_rank[place[j] & (kLocalCap - 1)] = (uint16_t)(place[j] >> kPosBits);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < kLocalItems; ++j) {
-        if (j >= J) break;
-        const int pos = j * kLocalThreads + t;
-        if (pos < R) place[j] = s_rank[pos];
-      }
-      __syncthreads();
-      // rank is written in the order of the range (near the input's inside a
-      // bucket), the items in sorted order through LDS
-#pragma unroll
-      for (int j = 0; j < kLocalItems; ++j) {
-        if (j >= J) break;
-        const int pos = j * kLocalThreads + t;
-        if (pos < R) {
-          const uint64_t done = final_item(item[j]);
-          const uint32_t id = (uint32_t)item[j] & id_mask;
-          s_key[place[j]] = (uint32_t)done;
-          s_two[place[j]] = (uint32_t)(done >> 32);
-          if (id < (uint32_t)a.stride)  // (the id is a point of the range; the bound is a guard)
-            rank[dbase + id] = (uint32_t)lo + place[j];
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < kLocalItems; ++j) {
-        if (j >= J) break;
-        const int s = j * kLocalThreads + t;
-        if (s < R) {
-          const uint64_t v = (uint64_t)s_two[s] << 32 | s_key[s];
-          out[lo + s] = v;
-          if (s + 1 < R && s_two[s + 1] == s_two[s]) {  // (the upper word: rarely equal but for equal codes)
-            const uint64_t nx = (uint64_t)s_two[s + 1] << 32 | s_key[s + 1];
-            if (same_code(v, nx) && nx < v) s_swap = 1;
+        const uint32_t ex = exclusive_scan_block(tot, s_w);
+        if (t < 256) {
+          uint32_t run = ex;
+#pragma unroll 4
+          for (int w = 0; w < kLocalWaves; ++w) {
+            const uint32_t c = s_cnt[w][t];
+            s_cnt[w][t] = run;
+            run += c;
           }
         }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kLocalItems; ++j) {
+          if (j >= J) break;
+          const uint32_t pos = pv[j] & 0xffffu;
+          s_pos[s_cnt[wave][digit_of_pos(pos)] + (pv[j] >> 16)] = (uint16_t)pos;
+        }
+        __syncthreads();
       }
-      __syncthreads();
-      if (s_swap == 0) return;
-      // Points of one voxel that the top-digit pass left out of index order:
-      // every item counts the smaller ones among its equals.
+      // (small loops: the items' registers of the other path do not live here)
+      auto at = [&](int s) { return items[lo + (int)s_pos[s]]; };
       for (int s = t; s < R; s += kLocalThreads) {
-        const uint64_t v = (uint64_t)s_two[s] << 32 | s_key[s];
-        int r = s, u = s - 1;
-        for (; u >= 0; --u) {
-          const uint64_t o = (uint64_t)s_two[u] << 32 | s_key[u];
-          if (!same_code(v, o)) break;
-          r -= o > v ? 1 : 0;
-        }
-        for (u = s + 1; u < R; ++u) {
-          const uint64_t o = (uint64_t)s_two[u] << 32 | s_key[u];
-          if (!same_code(v, o)) break;
-          r += o < v ? 1 : 0;
-        }
-        if (r == s) continue;
+        const uint64_t v = at(s);
         const uint32_t id = (uint32_t)v & id_mask;
-        out[lo + r] = v;
-        if (id < (uint32_t)a.stride) rank[dbase + id] = (uint32_t)(lo + r);
+        out[lo + s] = final_item(v);
+        if (id < (uint32_t)a.stride) rank[dbase + id] = (uint32_t)(lo + s);
+        if (s + 1 < R) {
+          const uint64_t nx = at(s + 1);
+          if (alike(v, nx) && nx < v) s_swap = 1;
+        }
       }
+      __syncthreads();
+      if (uniform(s_swap) != 0) put_right(at, final_item);
       return;
     }
+    const uint16_t *start = reinterpret_cast<const uint16_t *>(s_bin);
+    const uint32_t low = (1u << shift) - 1u;
+#pragma unroll
+    for (int j = 0; j < kLocalItems; ++j) {
+      if (j >= J) break;
+      const int pos = j * kLocalThreads + t;
+      if (pos < R) {
+        const uint32_t c = rel_top(item[j]), b = bin_of(c);
+        const uint32_t s = start[b] + place[j];
+        s_key[s] = (c & low) << kPosBits | (uint32_t)pos;
+        s_of[s] = (uint16_t)b;
+      }
+    }
     __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kLocalItems; ++j) {
+      if (j >= J) break;
+      const int s = j * kLocalThreads + t;
+      if (s < R) {
+        const uint32_t key = s_key[s], b = s_of[s];
+        const uint32_t b0 = start[b], len = start[b + 1] - b0;
+        uint32_t r = b0;
+        const uint32_t *bin = s_key + b0;
+        uint32_t k = 0;
+        if (WIDE && drop > 0) {  // (uniform) equal keys but for the position: the whole items decide
+          const uint64_t mine = items[lo + (int)(key & (kLocalCap - 1))];
+          for (; k < len; ++k) {
+            const uint32_t v = bin[k];
+            bool less = v < key;
+            if (((v ^ key) >> kPosBits) == 0 && v != key) less = items[lo + (int)(v & (kLocalCap - 1))] < mine;
+            r += less ? 1u : 0u;
+          }
+        }
+        for (; k + 8 <= len; k += 8) {
+          uint32_t v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v[u] = bin[k + u];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) r += v[u] < key ? 1u : 0u;
+        }
+        for (; k < len; k += 4) {
+          uint32_t v[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[u] = bin[k + u];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) r += (k + u < len && v[u] < key) ? 1u : 0u;
+        }
+        place[j] = r << kPosBits | (key & (kLocalCap - 1));
+      }
+    }
+    __syncthreads();
+    uint16_t *s_rank = reinterpret_cast<uint16_t *>(s_bin);  // (the starts have been read)
+#pragma unroll
+    for (int j = 0; j < kLocalItems; ++j) {
+      if (j >= J) break;
+      if (j * kLocalThreads + t < R) s_rank[place[j] & (kLocalCap - 1)] = (uint16_t)(place[j] >> kPosBits);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kLocalItems; ++j) {
+      if (j >= J) break;
+      const int pos = j * kLocalThreads + t;
+      if (pos < R) place[j] = s_rank[pos];
+    }
+    __syncthreads();
+    // rank is written in the order of the range (near the input's inside a
+    // bucket), the items in sorted order through LDS
+#pragma unroll
+    for (int j = 0; j < kLocalItems; ++j) {
+      if (j >= J) break;
+      const int pos = j * kLocalThreads + t;
+      if (pos < R) {
+        const uint64_t done = final_item(item[j]);
+        const uint32_t id = (uint32_t)item[j] & id_mask;
+        s_key[place[j]] = (uint32_t)done;
+        s_two[place[j]] = (uint32_t)(done >> 32);
+        if (id < (uint32_t)a.stride)  // (the id is a point of the range; the bound is a guard)
+          rank[dbase + id] = (uint32_t)lo + place[j];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kLocalItems; ++j) {
+      if (j >= J) break;
+      const int s = j * kLocalThreads + t;
+      if (s < R) {
+        const uint64_t v = (uint64_t)s_two[s] << 32 | s_key[s];
+        out[lo + s] = v;
+        if (s + 1 < R && s_two[s + 1] == s_two[s]) {  // (the upper word: rarely equal but for equal codes)
+          const uint64_t nx = (uint64_t)s_two[s + 1] << 32 | s_key[s + 1];
+          if (same_code(v, nx) && nx < v) s_swap = 1;
+        }
+      }
+    }
+    __syncthreads();
+    if (uniform(s_swap) == 0) return;
+    put_right([&](int s) { return (uint64_t)s_two[s] << 32 | s_key[s]; }, [](uint64_t v) { return v; });
+    return;
   }
 
   // ---- slow path: the block sorts its range alone, LSD over 8-bit digits of
@@ -1381,10 +1473,6 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   }
   // One thread per run of equals; reordering a run changes nothing that tells
   // another thread where runs begin.
-  const uint32_t first = (uint32_t)(a.sa.n_fixed >= 0 ? 0 : a.sa.segs->start[ti.s]);
-  auto alike = [&](uint64_t u, uint64_t v) {
-    return same_code(u, v) && ((uint32_t)u & id_mask) - first >> 6 == ((uint32_t)v & id_mask) - first >> 6;
-  };
   for (int s = t; s + 1 < R; s += kLocalThreads) {
     const uint64_t v = out[lo + s];
     if (!alike(v, out[lo + s + 1]) || (s > 0 && alike(out[lo + s - 1], v))) continue;

@@ -67,3 +67,26 @@ def test_code_widths_do_not_route_each_other():
         assert s(wide[:5000], pw) == TOP_DIGIT
         assert s(crowded, pn) == (0, 4)
         assert s(wide[:5000], pw) == TOP_DIGIT
+
+
+def crowded_voxels(rng, bits, voxels, times, others, turn):
+    """`voxels` voxels of one scan-line neighbourhood, `times` points each, one
+    voxel after the other or in turn, and scattered points."""
+    v = rng.integers(0, 1 << bits, size=(1, 3)) // 2 + rng.integers(0, 3, size=(voxels, 3))
+    many = np.tile(v, (times, 1)) if turn else np.repeat(v, times, axis=0)
+    g = np.concatenate([many, rng.integers(0, 1 << bits, size=(others, 3))])
+    return np.minimum(g, (1 << bits) - 1).astype(np.int32)
+
+
+@pytest.mark.parametrize("turn", [False, True], ids=["runs", "turn"])
+@pytest.mark.parametrize("bits,voxels,times,others", [(10, 1, 513, 1), (10, 1, 1024, 0), (10, 3, 700, 1025),
+                                                      (10, 8, 1024, 0), (10, 2, 4000, 191), (3, 40, 200, 90),
+                                                      (11, 5, 1500, 600), (16, 4, 2000, 3000), (17, 3, 600, 200)])
+def test_long_bins(bits, voxels, times, others, turn):
+    """Bins past the length that is ranked by counting: the window's keys take
+    digit passes in LDS (at 16 and 17 bits also over the code bits below the
+    keys), and equal codes keep index order."""
+    rng = np.random.default_rng(voxels * times)
+    g = crowded_voxels(rng, bits, voxels, times, others, turn)
+    with Sorter() as s:
+        assert s(g, fgbd.default_params(bits=bits)) == TOP_DIGIT
