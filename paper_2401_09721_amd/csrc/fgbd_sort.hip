@@ -1225,6 +1225,7 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
         s_key[s] = s < R ? rel_top(items[lo + min(s, R - 1)]) : ~0u;
         s_pos[s] = (uint16_t)s;
       }
+      __syncthreads();  // (there may be no pass: one code)
       for (int pass = 0; pass < passes; ++pass) {
         for (int i = t; i < kLocalWaves * 256; i += kLocalThreads) (&s_cnt[0][0])[i] = 0u;
         __syncthreads();

@@ -90,3 +90,12 @@ def test_long_bins(bits, voxels, times, others, turn):
     g = crowded_voxels(rng, bits, voxels, times, others, turn)
     with Sorter() as s:
         assert s(g, fgbd.default_params(bits=bits)) == TOP_DIGIT
+
+
+@pytest.mark.parametrize("n", [1, 65, 1024, 1025, 5000, 8192])
+@pytest.mark.parametrize("bits", [1, 2, 3, 10])
+def test_one_code(bits, n):
+    """Every point in one voxel: no digit differs, index order alone decides."""
+    g = np.tile(np.array([[1, 0, 1]], np.int32), (n, 1))
+    with Sorter() as s:
+        assert s(g, fgbd.default_params(bits=bits)) == TOP_DIGIT
