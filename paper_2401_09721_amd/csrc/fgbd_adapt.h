@@ -145,8 +145,8 @@ class ScheduleTrial {
 };
 
 // The radix sort's route.  words[0] is set by the local sort of a call that
-// asked when a block sorted a very large range alone (points crowded into few
-// top code digits, such as a plane normal to a scan axis), words[1] by the
+// asked when it found a very large range (points crowded into few top code
+// digits, such as a plane normal to a scan axis), words[1] by the
 // launch after that sort, to the call's number.  A call that finds it set
 // sends itself and the next ones through the LSD passes.
 class SortWatch {

@@ -347,8 +347,8 @@ Run make_run(fgbd_ctx ctx, const Plan &pl, char *ws, const fgbd_params &prm, int
 }
 
 // The sort route of an eager call (captured calls keep the top-digit sort and
-// watch nothing).  A completed read-back that found a very large range sorted
-// by one block switches the context to LSD passes for kSortLsdCalls calls;
+// watch nothing).  A completed read-back that found a very large range
+// switches the context to LSD passes for kSortLsdCalls calls;
 // otherwise, with no read-back outstanding, the call arms the flag.
 static void sort_policy(fgbd_ctx ctx, hipStream_t s, Run &r) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;

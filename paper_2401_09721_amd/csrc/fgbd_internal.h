@@ -472,8 +472,8 @@ constexpr int kSortPasses = 4;                        // 8-bit digits of 32-bit 
 constexpr int kMsdBits = 10;
 constexpr int kMsdBins = 1 << kMsdBits;
 constexpr int kLocalWin = kSortTile;  // sorted positions per local-sort window (windows are numbered like the tiles)
-// a range this large sorted by one block makes later eager calls on the
-// context sort by LSD passes for kSortLsdCalls calls
+// a range this large makes later eager calls on the context sort by LSD passes
+// for kSortLsdCalls calls
 constexpr int kBigRange = 32768;
 constexpr int kSortLsdCalls = 32;
 
@@ -606,9 +606,8 @@ struct Run {
   int32_t hint_tag = 0;
   // Sort route for codes of at most 32 bits: the top-digit pass and local
   // sorts unless sort_lsd.  sort_big (host-mapped, NULL: not watched): the
-  // local sort sets sort_big[0] when a block had to sort a range of more
-  // than kBigRange items alone; the merge launch then stores sort_seq into
-  // sort_big[1].
+  // local sort sets sort_big[0] when a range had more than kBigRange items;
+  // the merge launch then stores sort_seq into sort_big[1].
   bool sort_lsd = false;
   int32_t *sort_big = nullptr;
   int32_t sort_seq = 0;

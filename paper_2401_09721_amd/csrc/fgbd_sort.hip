@@ -6,7 +6,7 @@
 // at the end of this file (one pass on the top 10 bits, then each window's
 // buckets sorted in LDS), takes every code that leaves room for the index in
 // 64 bits; the LSD passes below sort the others, and any code while the
-// context has found ranges that one block would sort alone.
+// context has found very large ranges.
 //
 // Per 8-bit digit pass (4 passes for 32-bit codes):
 //   upsweep   per tile digit histogram            -> hist[dir][tile][digit]
@@ -685,12 +685,14 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_downsweep(SortArgs a, con
 // MSD pass's order, and those of one chunk that it left out of index order
 // are put right at the end.  The block writes the sorted items
 // in their final form and rank, as the last LSD pass does.  A range of more
-// than kLocalCap items, or with more than kMaxBin items in one bin, is sorted
-// by its block through the two item buffers: correct for any input, slow for
-// a very large range (points crowded into few top digits, such as a plane
-// normal to a scan axis), which the block then reports through a host-mapped
-// flag so that the caller's context can choose the LSD passes for its next
-// calls.
+// than kLocalCap items ends in a bucket that reaches several windows, whose
+// blocks sort it between them, each reading it all: fast for the planes of a
+// scan (three floors of 90,000 points each beside 400,000 others on a 2^11
+// grid: 305 us for the graph, 965 with a block alone on each and 538 with the
+// LSD passes), slow where most of a large cloud has one top digit (a million
+// points in one plane: 1.6 ms, 0.6 with the LSD passes), which a block then
+// reports through a host-mapped flag so that the caller's context can choose
+// the LSD passes for its next calls.
 //
 // In LDS a range of R items is sorted by counting: the codes, less the base,
 // are split by their top 13 bits into bins (one LDS atomic per item gives its
@@ -703,6 +705,8 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_downsweep(SortArgs a, con
 // 1M frame against 32 M for three 8-bit LSD passes in LDS whose stable ranks
 // came from 8 ballots per item and pass; 90 -> 61 us there, 410 -> 250 us on
 // 8 clouds of 4.4M points, 81 -> 51 us on 421k points in 16 directions.
+// Where a bin holds more than kMaxBin items, or the codes have few bits, the
+// range takes stable 8-bit passes in LDS instead.
 // Items stay in registers; 65 KB of LDS and 1024 threads let two blocks (all
 // 32 waves) share a CU.
 
@@ -941,7 +945,8 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
   // The cloud's first tile records the range of each of the cloud's windows,
   // the buckets that start in it: the range's first position, the digit of the
   // items there, the first digit whose bucket starts at or after the window's
-  // base, and (in the cloud's last window) the digit after the cloud's last.
+  // base, and where the bucket that reaches the next window's base starts (in
+  // the cloud's last window: the digit after the cloud's last).
   // A binary search over the bucket starts finds the first digit whose bucket
   // starts at or after a position; an empty bucket shares the start of the
   // next one that is not.  One store per window; an atomic minimum per bucket took 45 us instead of 26 on 64
@@ -969,8 +974,10 @@ __global__ __launch_bounds__(kSortThreads) void k_msd_downsweep(SortArgs a, cons
       const uint32_t lo = l < kMsdBins ? s_start[l] : (uint32_t)seg_end;
       // when bucket l is empty, the items at lo are of a later digit
       const int held = l + 1 < kMsdBins && s_start[l + 1] == lo ? first_at(lo + 1u) - 1 : l;
-      const int end_digit = tile + w + 1 == ti.next_first ? first_at((uint32_t)seg_end) : 0;
-      a.win[(size_t)d * a.nwin + tile + w] = make_int4((int)lo, held, l, end_digit);
+      const bool last = tile + w + 1 == ti.next_first;
+      const int end_digit = first_at((uint32_t)(last ? seg_end : ti.seg_start + (w + 1) * kLocalWin));
+      const int reach = last ? end_digit : (int)s_start[max(end_digit - 1, 0)];
+      a.win[(size_t)d * a.nwin + tile + w] = make_int4((int)lo, held, l, reach);
     }
   }
 }
@@ -983,8 +990,12 @@ constexpr int kPosBits = 13;                            // a position in an in-L
 constexpr int kBinBits = 13;
 constexpr int kBins = 1 << kBinBits;
 constexpr uint32_t kMaxBin = 512;                       // a larger bin makes its window's keys take LSD passes
-constexpr int kSlowItems = 4;                           // per thread and chunk, slow path
 static_assert(kLocalCap == 1 << kPosBits, "positions of the largest in-LDS range");
+// A window's part of a large bucket: some less than a range holds, as the bins
+// that start in it are taken whole.  Every part costs three reads of the
+// bucket, so few are better: a million points in one plane, 2.2 ms with parts
+// of a window's 4096.
+constexpr int kShare = 6144;
 
 struct LocalArgs {
   DirTable dt;
@@ -1030,6 +1041,10 @@ __device__ __forceinline__ int4 uniform(int4 v) {
   return make_int4(uniform(v.x), uniform(v.y), uniform(v.z), uniform(v.w));
 }
 
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return (uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32 | (uint32_t)uniform((int)v);
+}
+
 // Exclusive prefix of v over the threads of the block (up to 16 waves);
 // every thread calls it.  s_w: 16 words.
 __device__ __forceinline__ uint32_t exclusive_scan_block(uint32_t v, uint32_t *s_w) {
@@ -1049,31 +1064,34 @@ __device__ __forceinline__ uint32_t exclusive_scan_block(uint32_t v, uint32_t *s
   return b + x - v;
 }
 
+// A bucket of one top digit that several windows sort together.
+struct LargeBucket {
+  int start, end;   // its positions
+  int parts, part;  // the windows that share it, and this one among them
+};
+
 // One block per (direction, window).  A window is kLocalWin sorted positions
 // of one cloud, numbered like the radix tiles, so no window holds points of
 // two clouds: with windows laid over the whole batch, every window of a batch
-// of small clouds straddled some and took the slow path below (64 clouds of
-// 4k points: 144 us; 29 us with windows of their own).
+// of small clouds straddled some and was sorted through global memory (64
+// clouds of 4k points: 144 us; 29 us with windows of their own).
 // WIDE: codes above 32 bits, with a.ib index bits below them.  Keys stay 32-bit
 // words, ranges of more than 32 code bits looking at whole items on ties
 // (64-bit keys in LDS leave one block a CU): 700k points at b = 11, 70 us, and
 // 74 with 64-bit keys.
 template <bool WIDE>
-__global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
-    LocalArgs a, uint64_t *__restrict__ src, uint64_t *__restrict__ dst, uint32_t *__restrict__ rank) {
-  // in-LDS path: the bins' counts, then starts (two 16-bit values a word),
-  // then each position's rank; a slot's key and its bin
+__global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(LocalArgs a, const uint64_t *src, uint64_t *dst,
+                                                                 uint32_t *__restrict__ rank) {
+  // the bins' counts, then starts (two 16-bit values a word), then each
+  // position's rank; a slot's key and its bin
   __shared__ uint32_t s_key[kLocalCap + 4];
   __shared__ uint32_t s_two[kLocalCap + 2];  // [kBins / 2 + 2] bins, then [kLocalCap] 16-bit bin numbers
   uint32_t *const s_bin = s_two;
   uint16_t *const s_of = reinterpret_cast<uint16_t *>(s_two + kBins / 2 + 2);
   __shared__ uint32_t s_w[16];
-  __shared__ unsigned long long s_max;
   __shared__ int s_swap;   // equal codes out of index order
   __shared__ int s_heavy;  // a bin holds more than kMaxBin items
-  // slow path
-  uint32_t(*const s_cnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s_key);  // [kLocalWaves][256]
-  uint32_t *const s_base = s_bin;                                          // [256]
+  __shared__ unsigned long long s_min, s_max;
 
   // Consecutive windows of a direction go to the XCDs in turn.  Windows differ
   // in cost by direction and by part of the cloud: with one direction per XCD
@@ -1085,33 +1103,39 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   const int wave = t / kWave;
   const int lane = (int)lane_id();
   const size_t dbase = (size_t)d * a.stride;
-  const uint64_t *items = src + dbase;
   const int sh = msd_shift(a.dt, d);
 
-  // The range as the top-digit pass recorded it from its counts (never taken
-  // from the items, which a neighbouring block may be reordering): it ends
-  // where the cloud's next window's starts.  The digit before the next
-  // window's first one that starts at or after its base is never empty.
+  // The range as the top-digit pass recorded it from its counts: it ends where
+  // the cloud's next window's starts.  The digit before the next window's
+  // first one that starts at or after its base is never empty.
   const int4 *wrow = a.win + (size_t)d * a.nwin;
   const int4 here = uniform(wrow[win]), next = uniform(wrow[min(win + 1, a.nwin - 1)]);
+  const int before = uniform(wrow[max(win - 1, 0)].w);
   const bool last_win = win + 1 == ti.next_first;
   const int seg_end = uniform(a.sa.n_fixed >= 0 ? a.sa.n_fixed : (int)a.sa.segs->start[ti.s + 1]);
-  const int lo = here.x, hi = last_win ? seg_end : next.x;
-  if (lo >= hi) return;  // no bucket starts in the window (uniform)
+  const int hi = last_win ? seg_end : next.x;
   const uint32_t df = (uint32_t)here.y, dl = (uint32_t)(last_win ? here.w : next.z) - 1u;
-  const int R = hi - lo;
+  // A range past the LDS capacity ends in a bucket that reaches past the next
+  // window's base; the windows whose base it reaches sort it between them
+  // (below), and what comes before it is left to this one.
+  const bool large = hi - here.x > kLocalCap;
+  if (large && a.big && hi - here.x > kBigRange && t == 0) *a.big = 1;  // (only ever set to 1)
   const CodeGen cg = code_gen(a.dt, d);
-  const uint64_t base = (uint64_t)df << sh;
   const uint32_t id_mask = WIDE ? (1u << a.ib) - 1u : ~0u;
-  const int range_bits = sh + (dl > df ? 32 - __clz(dl - df) : 0);
+  uint64_t *out = dst + dbase;
+
+  // the range at hand: its items, first position, length, the smallest code it
+  // may hold and the bits of a code less that one
+  const uint64_t *items = src + dbase;
+  int lo = here.x, R = (large ? here.w : hi) - here.x;
+  uint64_t base = (uint64_t)df << sh;
+  int range_bits = sh + (dl > df ? 32 - __clz(dl - df) : 0);
   // an item's code less the range's base, its top 32 bits where it has more
   // (WIDE: the low `drop` bits then only break ties), and its final form
-  const int drop = WIDE && range_bits > 32 ? range_bits - 32 : 0;
-  const int bits = range_bits - drop;
+  int drop = WIDE && range_bits > 32 ? range_bits - 32 : 0;
   auto rel = [&](uint64_t v) { return WIDE ? (v >> a.ib) - base : (uint64_t)((uint32_t)(v >> 32) - (uint32_t)base); };
-  const uint64_t base_item = WIDE ? base << a.ib : base << 32;
   auto rel_top = [&](uint64_t v) {
-    return WIDE ? shr64_lo(v - base_item, a.ib + drop) : (uint32_t)(v >> 32) - (uint32_t)base;
+    return WIDE ? shr64_lo(v - (base << a.ib), a.ib + drop) : (uint32_t)(v >> 32) - (uint32_t)base;
   };
   auto final_item = [&](uint64_t v) {
     if constexpr (WIDE)
@@ -1123,15 +1147,32 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
   auto same_code = [&](uint64_t u, uint64_t v) { return ((u ^ v) >> (WIDE ? a.ib : 32)) == 0; };
   // (of one 64-point chunk of the input too, inside which the top-digit pass
   // does not keep the order of equal digits)
-  auto alike = [&](uint64_t u, uint64_t v) {
+  auto same_chunk = [&](uint64_t u, uint64_t v) {
     const uint32_t first = (uint32_t)ti.seg_start;
-    return same_code(u, v) && ((uint32_t)u & id_mask) - first >> 6 == ((uint32_t)v & id_mask) - first >> 6;
+    return ((uint32_t)u & id_mask) - first >> 6 == ((uint32_t)v & id_mask) - first >> 6;
   };
-  uint64_t *out = dst + dbase;
-  // Points of one voxel that the top-digit pass left out of index order, which
-  // are of one chunk of the input and so lie next to each other: each sorted
-  // item at(s) counts the smaller ones among them (form: its final form).
-  auto put_right = [&](auto at, auto form) {
+  auto alike = [&](uint64_t u, uint64_t v) { return same_code(u, v) && same_chunk(u, v); };
+  // The sorted range from LDS (final forms, s_two above s_key) to dst.  Points
+  // of one voxel that the top-digit pass left out of index order are of one
+  // chunk of the input and so lie next to each other: if there are any, each
+  // item counts the smaller ones among them.
+  auto store_sorted = [&] {
+    auto at = [&](int s) { return (uint64_t)s_two[s] << 32 | s_key[s]; };
+#pragma unroll
+    for (int j = 0; j < kLocalItems; ++j) {
+      if (j * kLocalThreads >= R) break;
+      const int s = j * kLocalThreads + t;
+      if (s < R) {
+        const uint64_t v = at(s);
+        out[lo + s] = v;
+        if (s + 1 < R && s_two[s + 1] == s_two[s]) {  // (the upper word: rarely equal but for equal codes)
+          const uint64_t nx = at(s + 1);
+          if (alike(v, nx) && nx < v) s_swap = 1;
+        }
+      }
+    }
+    __syncthreads();
+    if (uniform(s_swap) == 0) return;
     for (int s = t; s < R; s += kLocalThreads) {
       const uint64_t v = at(s);
       int r = s;
@@ -1147,18 +1188,105 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
       }
       if (r == s) continue;
       const uint32_t id = (uint32_t)v & id_mask;
-      out[lo + r] = form(v);
+      out[lo + r] = v;
       if (id < (uint32_t)a.stride) rank[dbase + id] = (uint32_t)(lo + r);
     }
   };
+  // The range at hand by 8-bit LSD passes in LDS over the positions, whose keys
+  // stay in place.  Slot (wave J + j) 64 + lane in visiting order; slots past
+  // the range hold keys of all ones and so stay after every item.
+  auto digit_sort = [&] {
+    // (opaque: formed anew here, or what comes from it is held over the caller's loop and spills)
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    const int wave = uniform(t / kWave), lane = t % kWave;
+    const int J = (R + kLocalThreads - 1) / kLocalThreads, bits = range_bits - drop;
+    uint32_t(*const s_cnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s_two);  // [kLocalWaves][256]
+    uint16_t *const s_pos = reinterpret_cast<uint16_t *>(s_two + kLocalWaves * 256);
+    const int low_passes = WIDE && drop > 0 ? (drop + 7) / 8 : 0;
+    const int passes = low_passes + (bits + 7) / 8;
+    const int first_slot = wave * J * kWave + lane;
+    for (int s = t; s < J * kLocalThreads; s += kLocalThreads) {
+      s_key[s] = s < R ? rel_top(items[lo + min(s, R - 1)]) : ~0u;
+      s_pos[s] = (uint16_t)s;
+    }
+    __syncthreads();  // (there may be no pass: one code)
+    for (int pass = 0; pass < passes; ++pass) {
+      for (int i = t; i < kLocalWaves * 256; i += kLocalThreads) (&s_cnt[0][0])[i] = 0u;
+      __syncthreads();
+      auto digit_of_pos = [&](uint32_t pos) {
+        if (pass >= low_passes) return s_key[pos] >> 8 * (pass - low_passes) & 255u;
+        return (int)pos < R ? (uint32_t)(rel(items[lo + (int)pos]) >> 8 * pass) & 255u : 255u;
+      };
+      uint32_t pv[kLocalItems];  // rank among the wave's equal digits << 16 | position
+#pragma unroll
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        pv[j] = s_pos[first_slot + j * kWave];
+        uint32_t before;
+        const uint32_t count = wave_rank8(digit_of_pos(pv[j]), s_cnt[wave], before);
+        pv[j] |= (count + before) << 16;
+        asm volatile("" : "+v"(pv[j]));  // (one register an item: its parts kept for later spill)
+      }
+      __syncthreads();
+      uint32_t tot = 0;
+      if (t < 256) {
+#pragma unroll 4
+        for (int w = 0; w < kLocalWaves; ++w) tot += s_cnt[w][t];
+      }
+      const uint32_t ex = exclusive_scan_block(tot, s_w);
+      if (t < 256) {
+        uint32_t run = ex;
+#pragma unroll 4
+        for (int w = 0; w < kLocalWaves; ++w) {
+          const uint32_t c = s_cnt[w][t];
+          s_cnt[w][t] = run;
+          run += c;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        const uint32_t pos = pv[j] & 0xffffu;
+        s_pos[s_cnt[wave][digit_of_pos(pos)] + (pv[j] >> 16)] = (uint16_t)pos;
+      }
+      __syncthreads();
+    }
+    // Items in sorted order through LDS, as below.  (A range of a large bucket
+    // stands where its result goes: every item is read before one is written.)
+    uint32_t pv[kLocalItems];
+#pragma unroll
+    for (int j = 0; j < kLocalItems; ++j) {
+      if (j >= J) break;
+      pv[j] = s_pos[j * kLocalThreads + t];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kLocalItems; ++j) {
+      if (j >= J) break;
+      const int s = j * kLocalThreads + t;
+      if (s < R) {
+        const uint64_t v = items[lo + (int)pv[j]], done = final_item(v);
+        const uint32_t id = (uint32_t)v & id_mask;
+        s_key[s] = (uint32_t)done;
+        s_two[s] = (uint32_t)(done >> 32);
+        if (id < (uint32_t)a.stride) rank[dbase + id] = (uint32_t)(lo + s);
+      }
+    }
+    __syncthreads();
+    store_sorted();
+  };
 
-  if (R <= kLocalCap) {
+  bool digits = false;  // the range at hand is left to digit_sort
+  if (R > 0) {          // (else no bucket starts in the window)
+    const int J = (R + kLocalThreads - 1) / kLocalThreads;  // <= kLocalItems
+    const int bits = range_bits - drop;
     // ---- in LDS.  Items stay with their thread (position j kLocalThreads + t
     // of the range); their codes less the range's base are counted into
     // 2^kBinBits bins by the top bits, the key of each item (the low bits,
     // then the position) goes to a slot of its bin, and the rank of a slot's
     // key among its bin's keys is counted.
-    const int J = (R + kLocalThreads - 1) / kLocalThreads;  // <= kLocalItems
     // (bits <= 32, so kPosBits + shift <= 32 and a key fits its word)
     const int shift = bits > kBinBits ? bits - kBinBits : 0;
     uint64_t item[kLocalItems];
@@ -1210,289 +1338,312 @@ __global__ __launch_bounds__(kLocalThreads, 8) void k_local_sort(
       if (t == kLocalThreads - 1) s_bin[kBins / 2] = run;
     }
     __syncthreads();
-    // (a scalar branch and marked unlikely, or the other path's items spill around it)
-    if (__builtin_expect(uniform(s_heavy) != 0, 0)) {
-      // Long bins (many points in one voxel, or along one scan line): 8-bit
-      // LSD passes in LDS over the positions, whose keys stay in place.  Slot
-      // (wave J + j) 64 + lane in visiting order; slots past the range hold
-      // keys of all ones and so stay after every item.
-      uint32_t(*const s_cnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s_two);  // [kLocalWaves][256]
-      uint16_t *const s_pos = reinterpret_cast<uint16_t *>(s_two + kLocalWaves * 256);
-      const int low_passes = WIDE && drop > 0 ? (drop + 7) / 8 : 0;
-      const int passes = low_passes + (bits + 7) / 8;
-      const int first_slot = wave * J * kWave + lane;
-      for (int s = t; s < J * kLocalThreads; s += kLocalThreads) {
-        s_key[s] = s < R ? rel_top(items[lo + min(s, R - 1)]) : ~0u;
-        s_pos[s] = (uint16_t)s;
-      }
-      __syncthreads();  // (there may be no pass: one code)
-      for (int pass = 0; pass < passes; ++pass) {
-        for (int i = t; i < kLocalWaves * 256; i += kLocalThreads) (&s_cnt[0][0])[i] = 0u;
-        __syncthreads();
-        auto digit_of_pos = [&](uint32_t pos) {
-          if (pass >= low_passes) return s_key[pos] >> 8 * (pass - low_passes) & 255u;
-          return (int)pos < R ? (uint32_t)(rel(items[lo + (int)pos]) >> 8 * pass) & 255u : 255u;
-        };
-        uint32_t pv[kLocalItems];  // rank among the wave's equal digits << 16 | position
+    // long bins: many points in one voxel, or along one scan line
+    digits = uniform(s_heavy) != 0;
+    if (!digits) {
+      const uint16_t *start = reinterpret_cast<const uint16_t *>(s_bin);
+      const uint32_t low = (1u << shift) - 1u;
 #pragma unroll
-        for (int j = 0; j < kLocalItems; ++j) {
-          if (j >= J) break;
-          pv[j] = s_pos[first_slot + j * kWave];
-          uint32_t before;
-          const uint32_t count = wave_rank8(digit_of_pos(pv[j]), s_cnt[wave], before);
-          pv[j] |= (count + before) << 16;
-          asm volatile("" : "+v"(pv[j]));  // (one register an item: its parts kept for later spill)
-        }
-        __syncthreads();
-        uint32_t tot = 0;
-        if (t < 256) {
-#pragma unroll 4
-          for (int w = 0; w < kLocalWaves; ++w) tot += s_cnt[w][t];
-        }
-        const uint32_t ex = exclusive_scan_block(tot, s_w);
-        if (t < 256) {
-          uint32_t run = ex;
-#pragma unroll 4
-          for (int w = 0; w < kLocalWaves; ++w) {
-            const uint32_t c = s_cnt[w][t];
-            s_cnt[w][t] = run;
-            run += c;
-          }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kLocalItems; ++j) {
-          if (j >= J) break;
-          const uint32_t pos = pv[j] & 0xffffu;
-          s_pos[s_cnt[wave][digit_of_pos(pos)] + (pv[j] >> 16)] = (uint16_t)pos;
-        }
-        __syncthreads();
-      }
-      // (small loops: the items' registers of the other path do not live here)
-      auto at = [&](int s) { return items[lo + (int)s_pos[s]]; };
-      for (int s = t; s < R; s += kLocalThreads) {
-        const uint64_t v = at(s);
-        const uint32_t id = (uint32_t)v & id_mask;
-        out[lo + s] = final_item(v);
-        if (id < (uint32_t)a.stride) rank[dbase + id] = (uint32_t)(lo + s);
-        if (s + 1 < R) {
-          const uint64_t nx = at(s + 1);
-          if (alike(v, nx) && nx < v) s_swap = 1;
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        const int pos = j * kLocalThreads + t;
+        if (pos < R) {
+          const uint32_t c = rel_top(item[j]), b = bin_of(c);
+          const uint32_t s = start[b] + place[j];
+          s_key[s] = (c & low) << kPosBits | (uint32_t)pos;
+          s_of[s] = (uint16_t)b;
         }
       }
       __syncthreads();
-      if (uniform(s_swap) != 0) put_right(at, final_item);
-      return;
-    }
-    const uint16_t *start = reinterpret_cast<const uint16_t *>(s_bin);
-    const uint32_t low = (1u << shift) - 1u;
 #pragma unroll
-    for (int j = 0; j < kLocalItems; ++j) {
-      if (j >= J) break;
-      const int pos = j * kLocalThreads + t;
-      if (pos < R) {
-        const uint32_t c = rel_top(item[j]), b = bin_of(c);
-        const uint32_t s = start[b] + place[j];
-        s_key[s] = (c & low) << kPosBits | (uint32_t)pos;
-        s_of[s] = (uint16_t)b;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kLocalItems; ++j) {
-      if (j >= J) break;
-      const int s = j * kLocalThreads + t;
-      if (s < R) {
-        const uint32_t key = s_key[s], b = s_of[s];
-        const uint32_t b0 = start[b], len = start[b + 1] - b0;
-        uint32_t r = b0;
-        const uint32_t *bin = s_key + b0;
-        uint32_t k = 0;
-        if (WIDE && drop > 0) {  // (uniform) equal keys but for the position: the whole items decide
-          const uint64_t mine = items[lo + (int)(key & (kLocalCap - 1))];
-          for (; k < len; ++k) {
-            const uint32_t v = bin[k];
-            bool less = v < key;
-            if (((v ^ key) >> kPosBits) == 0 && v != key) less = items[lo + (int)(v & (kLocalCap - 1))] < mine;
-            r += less ? 1u : 0u;
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        const int s = j * kLocalThreads + t;
+        if (s < R) {
+          const uint32_t key = s_key[s], b = s_of[s];
+          const uint32_t b0 = start[b], len = start[b + 1] - b0;
+          uint32_t r = b0;
+          const uint32_t *bin = s_key + b0;
+          uint32_t k = 0;
+          if (WIDE && drop > 0) {  // (uniform) equal keys but for the position: the whole items decide
+            const uint64_t mine = items[lo + (int)(key & (kLocalCap - 1))];
+            for (; k < len; ++k) {
+              const uint32_t v = bin[k];
+              bool less = v < key;
+              if (((v ^ key) >> kPosBits) == 0 && v != key) less = items[lo + (int)(v & (kLocalCap - 1))] < mine;
+              r += less ? 1u : 0u;
+            }
           }
-        }
-        for (; k + 8 <= len; k += 8) {
-          uint32_t v[8];
+          for (; k + 8 <= len; k += 8) {
+            uint32_t v[8];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) v[u] = bin[k + u];
+            for (int u = 0; u < 8; ++u) v[u] = bin[k + u];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) r += v[u] < key ? 1u : 0u;
-        }
-        for (; k < len; k += 4) {
-          uint32_t v[4];
+            for (int u = 0; u < 8; ++u) r += v[u] < key ? 1u : 0u;
+          }
+          for (; k < len; k += 4) {
+            uint32_t v[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = bin[k + u];
+            for (int u = 0; u < 4; ++u) v[u] = bin[k + u];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) r += (k + u < len && v[u] < key) ? 1u : 0u;
-        }
-        place[j] = r << kPosBits | (key & (kLocalCap - 1));
-      }
-    }
-    __syncthreads();
-    uint16_t *s_rank = reinterpret_cast<uint16_t *>(s_bin);  // (the starts have been read)
-#pragma unroll
-    for (int j = 0; j < kLocalItems; ++j) {
-      if (j >= J) break;
-      if (j * kLocalThreads + t < R) s_rank[place[j] & (kLocalCap - 1)] = (uint16_t)(place[j] >> kPosBits);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kLocalItems; ++j) {
-      if (j >= J) break;
-      const int pos = j * kLocalThreads + t;
-      if (pos < R) place[j] = s_rank[pos];
-    }
-    __syncthreads();
-    // rank is written in the order of the range (near the input's inside a
-    // bucket), the items in sorted order through LDS
-#pragma unroll
-    for (int j = 0; j < kLocalItems; ++j) {
-      if (j >= J) break;
-      const int pos = j * kLocalThreads + t;
-      if (pos < R) {
-        const uint64_t done = final_item(item[j]);
-        const uint32_t id = (uint32_t)item[j] & id_mask;
-        s_key[place[j]] = (uint32_t)done;
-        s_two[place[j]] = (uint32_t)(done >> 32);
-        if (id < (uint32_t)a.stride)  // (the id is a point of the range; the bound is a guard)
-          rank[dbase + id] = (uint32_t)lo + place[j];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kLocalItems; ++j) {
-      if (j >= J) break;
-      const int s = j * kLocalThreads + t;
-      if (s < R) {
-        const uint64_t v = (uint64_t)s_two[s] << 32 | s_key[s];
-        out[lo + s] = v;
-        if (s + 1 < R && s_two[s + 1] == s_two[s]) {  // (the upper word: rarely equal but for equal codes)
-          const uint64_t nx = (uint64_t)s_two[s + 1] << 32 | s_key[s + 1];
-          if (same_code(v, nx) && nx < v) s_swap = 1;
+            for (int u = 0; u < 4; ++u) r += (k + u < len && v[u] < key) ? 1u : 0u;
+          }
+          place[j] = r << kPosBits | (key & (kLocalCap - 1));
         }
       }
+      __syncthreads();
+      uint16_t *s_rank = reinterpret_cast<uint16_t *>(s_bin);  // (the starts have been read)
+#pragma unroll
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        if (j * kLocalThreads + t < R) s_rank[place[j] & (kLocalCap - 1)] = (uint16_t)(place[j] >> kPosBits);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        const int pos = j * kLocalThreads + t;
+        if (pos < R) place[j] = s_rank[pos];
+      }
+      __syncthreads();
+      // rank is written in the order of the range (near the input's inside a
+      // bucket), the items in sorted order through LDS
+#pragma unroll
+      for (int j = 0; j < kLocalItems; ++j) {
+        if (j >= J) break;
+        const int pos = j * kLocalThreads + t;
+        if (pos < R) {
+          const uint64_t done = final_item(item[j]);
+          const uint32_t id = (uint32_t)item[j] & id_mask;
+          s_key[place[j]] = (uint32_t)done;
+          s_two[place[j]] = (uint32_t)(done >> 32);
+          if (id < (uint32_t)a.stride)  // (the id is a point of the range; the bound is a guard)
+            rank[dbase + id] = (uint32_t)lo + place[j];
+        }
+      }
+      __syncthreads();
+      store_sorted();
     }
-    __syncthreads();
-    if (uniform(s_swap) == 0) return;
-    put_right([&](int s) { return (uint64_t)s_two[s] << 32 | s_key[s]; }, [](uint64_t v) { return v; });
-    return;
   }
 
-  // ---- slow path: the block sorts its range alone, LSD over 8-bit digits of
-  // the code less the range's base, in chunks of kSlowItems * kLocalThreads
-  // items per round, through the two item buffers (its own range of each).
-  // An odd number of passes (a first pass of digit 0, a plain stable copy,
-  // when needed) ends in dst, in the final form; then the points of one voxel
-  // and one 64-point chunk of the input, which lie next to each other, are put
-  // into index order where the top-digit pass left them out of it.
-  if (a.big && R > kBigRange && t == 0) *a.big = 1;  // (only ever set to 1)
-  if (t == 0) s_max = 0;
-  __syncthreads();
-  // the widest key of the range, for the pass count
-  {
-    unsigned long long mx = 0;
-    for (int s = t; s < R; s += kLocalThreads) mx = max(mx, (unsigned long long)rel(items[lo + s]));
-    atomicMax(&s_max, mx);
-  }
-  __syncthreads();
-  const unsigned long long kmax = s_max;
-  int P = kmax ? (64 - __clzll(kmax) + 7) / 8 : 0;
-  const int extra = (P % 2 == 0) ? 1 : 0;
-  P += extra;
-  for (int q = 0; q < P; ++q) {
-    const uint64_t *rd = ((q & 1) == 0 ? src : dst) + dbase;
-    uint64_t *wr = ((q & 1) == 0 ? dst : src) + dbase;
-    const bool last = q == P - 1;
-    const int shift = 8 * (q - extra);  // q < extra: the copy pass (digit 0)
-    if (t < 256) s_base[t] = 0u;
-    __syncthreads();
-    for (int s = t; s < R; s += kLocalThreads) {
-      const uint32_t digit = q < extra ? 0u : (uint32_t)(rel(rd[lo + s]) >> shift) & 255u;
-      atomicAdd(&s_base[digit], 1u);
+  // ---- this window's part of a large bucket.  The windows that share it each
+  // read it all: its codes, less the bucket's base, are counted into 2^kBinBits
+  // bins, and a window takes the bins whose sorted positions start in its even
+  // share of them.  It copies their items, in the order in which they stand,
+  // to the place in dst where they will be, and sorts them there like any other
+  // range.  Nothing writes the items that others read and nobody waits.  Items
+  // that the bins leave too close (a bin of more than kLocalCap) are split
+  // again by their own bits, and more points of one code than that are only
+  // copied.
+  // A bucket that starts in an earlier window and reaches this one's base, in
+  // a range past the LDS capacity (`before` is its start only if it reaches it).
+  bool share = win > ti.first && here.x > ti.begin && here.x - before > kLocalCap - kLocalWin;
+  if (__builtin_expect(!digits && !share, 1)) return;
+  const int owner = ti.first + (before - ti.seg_start) / kLocalWin;
+  share = share && here.x - uniform(wrow[max(owner, 0)].x) > kLocalCap;
+  LargeBucket lb;
+  lb.start = before;
+  lb.end = here.x;
+  lb.parts = (here.x - before + kShare - 1) / kShare;  // (at most the windows it reaches: they are two or more)
+  lb.part = win - owner - 1;
+  share = share && lb.part < lb.parts;
+  uint64_t k0 = 0, k1 = 0;   // keys of the window's items not sorted yet, k0 <= key < k1
+  int left = -1, at_pos = 0; // their number (-1: not known yet), and where they begin in the bucket
+  const uint64_t bucket = (uint64_t)(uint32_t)(here.z - 1) << sh;  // its smallest code
+  const uint64_t key_mask = (1ull << sh) - 1ull;  // (codes of coordinates outside the grid: some place all the same)
+  // an item's code (narrow: the upper word alone), and its key
+  using Code = std::conditional_t<WIDE, uint64_t, uint32_t>;
+  auto code_at = [&](int q) -> Code {
+    const uint64_t *v = src + dbase + (size_t)(lb.start + q);
+    if constexpr (WIDE)
+      return *v >> a.ib;
+    else
+      return reinterpret_cast<const uint32_t *>(v)[1];
+  };
+  auto key_of = [&](Code c) { return (c - (Code)bucket) & (Code)key_mask; };
+  // f(code, place in the bucket, whether there is one): the bucket's items,
+  // each wave a contiguous part in order, some loads in flight (more spill)
+  const int lsize = lb.end - lb.start;
+  auto each_item = [&](auto f) {
+    constexpr int U = WIDE ? 2 : 4;
+    const int per = (lsize + kLocalThreads - 1) / kLocalThreads * kWave;
+    const int q1 = min(uniform(wave) * per + per, lsize);
+    for (int q = uniform(wave) * per; q < q1; q += U * kWave) {
+      Code c[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) c[u] = code_at(min(q + u * kWave + lane, lsize - 1));
+#pragma unroll
+      for (int u = 0; u < U; ++u) f(c[u], q + u * kWave + lane, q + u * kWave + lane < q1);
     }
+  };
+  // the starts of the bins of the keys from..to (inclusive) into s_key[0 .. kBins]; returns the keys' shift
+  auto count_bins = [&](uint64_t from, uint64_t to) {
+    const int width = to > from ? 64 - __clzll((long long)(to - from)) : 0;
+    const int g = width > kBinBits ? width - kBinBits : 0;
     __syncthreads();
-    const uint32_t hv = t < 256 ? s_base[t] : 0u;
-    const uint32_t hex = exclusive_scan_block(hv, s_w);
-    if (t < 256) s_base[t] = hex;
+    for (int i = t; i <= kBins; i += kLocalThreads) s_key[i] = 0u;
     __syncthreads();
-    for (int c0 = 0; c0 < R; c0 += kSlowItems * kLocalThreads) {
-      for (int i = t; i < kLocalWaves * 256; i += kLocalThreads) (&s_cnt[0][0])[i] = 0u;
-      __syncthreads();
-      uint64_t it[kSlowItems];
-      uint32_t dg[kSlowItems], rk[kSlowItems], bf[kSlowItems];
-#pragma unroll
-      for (int j = 0; j < kSlowItems; ++j) {
-        const int s = c0 + (wave * kSlowItems + j) * kWave + lane;
-        it[j] = rd[lo + min(s, R - 1)];
+    each_item([&](Code c, int, bool in) {
+      const Code k = key_of(c);
+      const uint32_t bin = in && k >= (Code)from && k <= (Code)to ? (uint32_t)((k - (Code)from) >> g) : ~0u;
+      // (runs of lanes with one bin add once: the input's order is often the keys')
+      const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(~(int)bin, (int)bin, 0x138, 0xf, 0xf, false);
+      const uint64_t heads = __builtin_amdgcn_ballot_w64(bin != prev);
+      if (bin != prev && bin != ~0u) {
+        const uint64_t after = heads & ~(~0ull >> (63 - lane));
+        atomicAdd(&s_key[bin], (after ? (uint32_t)__builtin_ctzll(after) : 64u) - (uint32_t)lane);
       }
+    });
+    __syncthreads();
+    constexpr int kPerT = kBins / kLocalThreads;
+    uint32_t sum = 0;
 #pragma unroll
-      for (int j = 0; j < kSlowItems; ++j) {
-        const int s = c0 + (wave * kSlowItems + j) * kWave + lane;
-        dg[j] = s >= R ? 255u : (q < extra ? 0u : (uint32_t)(rel(it[j]) >> shift) & 255u);
-      }
+    for (int q = 0; q < kPerT; ++q) sum += s_key[t * kPerT + q];
+    uint32_t run = exclusive_scan_block(sum, s_w);
 #pragma unroll
-      for (int j = 0; j < kSlowItems; ++j) rk[j] = wave_rank8(dg[j], s_cnt[wave], bf[j]);
-#pragma unroll
-      for (int j = 0; j < kSlowItems; ++j) rk[j] += bf[j];
-      __syncthreads();
-      uint32_t tot = 0;
-      if (t < 256) {
-        uint32_t run = s_base[t];
-#pragma unroll
-        for (int w = 0; w < kLocalWaves; ++w) {
-          const uint32_t c = s_cnt[w][t];
-          s_cnt[w][t] = run;
-          run += c;
-          tot += c;
+    for (int q = 0; q < kPerT; ++q) {
+      const uint32_t c = s_key[t * kPerT + q];
+      s_key[t * kPerT + q] = run;
+      run += c;
+    }
+    if (t == kLocalThreads - 1) s_key[kBins] = run;
+    __syncthreads();
+    return g;
+  };
+  auto first_bin = [&](uint32_t pos) {  // the first bin that starts at or after pos
+    int l = 0, h = kBins;
+    while (l < h) {
+      const int m = (l + h) >> 1;
+      if (uniform((int)s_key[m]) >= (int)pos)
+        h = m;
+      else
+        l = m + 1;
+    }
+    return l;
+  };
+  // f(place, sorted position) for the items of keys k0 .. kp - 1, in the order in which they stand
+  auto in_order = [&](uint64_t kp, auto f) {
+    auto mine = [&](Code c, bool in) {
+      const Code k = key_of(c);
+      return in && k >= (Code)k0 && k < (Code)kp;
+    };
+    int n = 0;
+    each_item([&](Code c, int, bool in) { n += (int)__popcll(__builtin_amdgcn_ballot_w64(mine(c, in))); });
+    __syncthreads();
+    if (lane == 0) s_w[wave] = (uint32_t)n;
+    __syncthreads();
+    int to = at_pos;
+    for (int w = 0; w < uniform(wave); ++w) to += uniform((int)s_w[w]);
+    each_item([&](Code c, int q, bool in) {
+      const bool m = mine(c, in);
+      const uint64_t all = __builtin_amdgcn_ballot_w64(m);
+      if (m) f(q, to + (int)count_below(all));
+      to += (int)__popcll(all);
+    });
+    __syncthreads();
+  };
+  // an item of more than kLocalCap of one key, at sorted position `to` by the
+  // order in which they stand, to its place by index: only items of its chunk,
+  // which stand together, may come before it out of order
+  auto store_one_key = [&](int q, int to) {
+    const uint64_t v = src[dbase + (size_t)(lb.start + q)];
+    const Code key = key_of(code_at(q));
+    for (int u = q - 1; u >= 0; --u) {
+      const uint64_t o = src[dbase + (size_t)(lb.start + u)];
+      if (!same_chunk(o, v)) break;
+      to -= key_of(code_at(u)) == key && o > v ? 1 : 0;
+    }
+    for (int u = q + 1; u < lsize; ++u) {
+      const uint64_t o = src[dbase + (size_t)(lb.start + u)];
+      if (!same_chunk(o, v)) break;
+      to += key_of(code_at(u)) == key && o < v ? 1 : 0;
+    }
+    const uint32_t id = (uint32_t)v & id_mask;
+    out[lb.start + to] = final_item(v);
+    if (id < (uint32_t)a.stride) rank[dbase + id] = (uint32_t)(lb.start + to);
+  };
+  // sets the range at hand to the window's next items; false when there are none
+  auto next_range = [&]() {
+    if (left < 0) {  // the window's share
+      const int even = (lsize + lb.parts - 1) / lb.parts, first = lb.part * even;
+      uint64_t lowest = 0, highest = key_mask;
+      if (WIDE && sh > 2 * kBinBits) {  // (many bits: the bins cover those in use)
+        uint64_t mn = ~0ull, mx = 0ull;
+        each_item([&](Code c, int, bool) {
+          const uint64_t k = key_of(c);
+          mn = k < mn ? k : mn;
+          mx = k > mx ? k : mx;
+        });
+        if (t == 0) {
+          s_min = ~0ull;
+          s_max = 0ull;
         }
+        __syncthreads();
+        atomicMin(&s_min, (unsigned long long)mn);
+        atomicMax(&s_max, (unsigned long long)mx);
+        __syncthreads();
+        lowest = uniform64(s_min);
+        highest = uniform64(s_max);
       }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < kSlowItems; ++j) {
-        const int s = c0 + (wave * kSlowItems + j) * kWave + lane;
-        const uint32_t dest = s_cnt[wave][dg[j]] + rk[j];
-        if (s < R && dest < (uint32_t)R) {  // (dest < R for counts that agree; the bound is a guard)
-          if (last) {
-            const uint32_t idx = (uint32_t)it[j] & id_mask;
-            wr[lo + dest] = final_item(it[j]);
-            if (idx < (uint32_t)a.stride) rank[dbase + idx] = (uint32_t)(lo + dest);
-          } else {
-            wr[lo + dest] = it[j];
-          }
-        }
+      left = 0;
+      if (lowest == highest) {  // one code: the items stay where they are
+        int q = first + t;
+        asm volatile("" : "+v"(q));  // (its addresses spill when formed before the loop around this)
+        for (; q < min(first + even, lsize); q += kLocalThreads) store_one_key(q, q);
+        return false;
       }
-      __syncthreads();
-      if (t < 256) s_base[t] += tot;
+      const int g = count_bins(lowest, highest);
+      const int b0 = first_bin((uint32_t)first);
+      const int b1 = lb.part + 1 == lb.parts ? kBins : first_bin((uint32_t)(first + even));
+      at_pos = uniform((int)s_key[b0]);
+      left = uniform((int)s_key[b1]) - at_pos;
+      k0 = lowest + ((uint64_t)b0 << g);
+      k1 = lowest + ((uint64_t)b1 << g);
     }
-    __syncthreads();
-  }
-  // One thread per run of equals; reordering a run changes nothing that tells
-  // another thread where runs begin.
-  for (int s = t; s + 1 < R; s += kLocalThreads) {
-    const uint64_t v = out[lo + s];
-    if (!alike(v, out[lo + s + 1]) || (s > 0 && alike(out[lo + s - 1], v))) continue;
-    int e = s + 1;
-    for (; e < R && e - s < kWave; ++e) {  // insertion
-      const uint64_t w = out[lo + e];
-      if (!alike(v, w)) break;
-      int at = e;
-      for (; at > s; --at) {
-        const uint64_t u = out[lo + at - 1];
-        if (u < w) break;
-        out[lo + at] = u;
+    uint64_t kp = k1;
+    int c = left;
+    while (c > kLocalCap) {
+      if (kp - k0 == 1) {
+        in_order(kp, store_one_key);
+        at_pos += c;
+        left -= c;
+        k0 = kp;
+        kp = k1;
+        c = left;
+        continue;
       }
-      if (at != e) out[lo + at] = w;
+      const int g = count_bins(k0, kp - 1);
+      const int b = first_bin(kLocalCap + 1) - 1;  // the last bin that starts within a range's length
+      const int s0 = uniform((int)s_key[b]);
+      const uint64_t kb = k0 + ((uint64_t)b << g);
+      if (s0 > 0) {
+        c = s0;
+        kp = kb;
+      } else {  // the bins below it are empty, and it holds more than a range
+        c = uniform((int)s_key[b + 1]);
+        k0 = kb;
+        kp = min(kp, kb + (1ull << g));
+      }
     }
-    for (int u = s; u < e; ++u) {
-      const uint32_t idx = (uint32_t)out[lo + u] & id_mask;
-      if (idx < (uint32_t)a.stride) rank[dbase + idx] = (uint32_t)(lo + u);
-    }
+    if (c == 0) return false;
+    in_order(kp, [&](int q, int to) { out[lb.start + to] = src[dbase + (size_t)(lb.start + q)]; });
+    items = out;
+    lo = lb.start + at_pos;
+    R = c;
+    base = bucket + k0;
+    range_bits = kp - k0 > 1 ? 64 - __clzll((long long)(kp - k0 - 1)) : 0;
+    drop = WIDE && range_bits > 32 ? range_bits - 32 : 0;
+    at_pos += c;
+    left -= c;
+    k0 = kp;
+    return true;
+  };
+  for (;;) {
+    if (!digits && (!share || !next_range())) return;
+    digits = false;
+    if (t == 0) s_swap = 0;
+    digit_sort();
+    __syncthreads();  // (the LDS is the next range's)
   }
 }
 

@@ -10,7 +10,7 @@ torch = pytest.importorskip("torch")
 import oracle as O  # noqa: E402
 from paper_2401_09721_amd import fgbd  # noqa: E402
 
-from gpu_helpers import dev  # noqa: E402
+from gpu_helpers import compare_denoise, dev  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -99,3 +99,71 @@ def test_one_code(bits, n):
     g = np.tile(np.array([[1, 0, 1]], np.int32), (n, 1))
     with Sorter() as s:
         assert s(g, fgbd.default_params(bits=bits)) == TOP_DIGIT
+
+
+def planes(rng, bits, n, others, side=None):
+    """Planes of n points normal to each scan axis, and scattered points."""
+    side = side or min(1 << bits, 1024)
+    out = [rng.integers(0, 1 << bits, size=(others, 3))]
+    for axis in range(3):
+        flat = rng.choice(side * side, size=n, replace=n > side * side)
+        out.append(np.insert(np.stack([flat // side, flat % side], 1), axis, (1 << bits) // 3 + axis, axis=1))
+    return np.concatenate(out).astype(np.int32)
+
+
+@pytest.mark.parametrize("order", ["raster", "shuffled"])
+@pytest.mark.parametrize("bits,n,others", [(10, 8193, 0), (10, 12288, 4096), (10, 28000, 5000), (10, 70000, 20000),
+                                           (7, 16384, 300), (11, 9000, 1), (11, 40000, 9000), (13, 30000, 3000),
+                                           (14, 20000, 500), (15, 10000, 2000), (16, 5400, 100)])
+def test_large_buckets(bits, n, others, order):
+    """One top digit with more points than a block's LDS holds, a first call's
+    route: the windows that the bucket reaches share it."""
+    rng = np.random.default_rng(n + bits)
+    g = planes(rng, bits, n, others)
+    g = g[rng.permutation(len(g))] if order == "shuffled" else g[np.lexsort((g[:, 2], g[:, 1], g[:, 0]))]
+    with Sorter() as s:
+        assert s(g, fgbd.default_params(bits=bits)) == TOP_DIGIT
+
+
+@pytest.mark.parametrize("order", ["runs", "turn", "shuffled"])
+@pytest.mark.parametrize("bits,voxels,times,others", [(10, 1, 8193, 0), (10, 1, 20000, 3000), (10, 3, 9000, 9000),
+                                                      (10, 60, 700, 0), (11, 2, 10000, 500), (13, 1, 30000, 30000),
+                                                      (16, 1, 9000, 7000)])
+def test_large_buckets_of_few_voxels(bits, voxels, times, others, order):
+    """Bins of a large bucket that hold more than a range does, down to one code."""
+    rng = np.random.default_rng(times + voxels)
+    g = crowded_voxels(rng, bits, voxels, times, others, order == "turn")
+    g[-others // 2:, 2] = g[0, 2]  # (half of the others in the bucket's plane)
+    if order == "shuffled":
+        g = g[rng.permutation(len(g))]
+    with Sorter() as s:
+        assert s(g, fgbd.default_params(bits=bits)) == TOP_DIGIT
+
+
+@pytest.mark.parametrize("bits,L,n", [(1, 8, 50000), (2, 3, 60000), (3, 8, 60000), (11, 8, 40000)])
+def test_large_buckets_of_one_code(bits, L, n):
+    """Buckets in which every code is the same, shared as they stand."""
+    rng = np.random.default_rng(n)
+    g = rng.integers(0, 2, size=(n, 3)).astype(np.int32) * ((1 << min(bits, 3)) - 1)
+    with Sorter() as s:
+        assert s(g, fgbd.default_params(bits=bits, num_dirs=L)) == TOP_DIGIT
+
+
+@pytest.mark.parametrize("bits", [10, 11])
+def test_large_buckets_of_a_batch(bits):
+    prm = fgbd.default_params(bits=bits)
+    rng = np.random.default_rng(bits)
+    xyz = [planes(rng, bits, n, others) for n, others in ((9000, 100), (30, 20), (13000, 5000), (8200, 0))]
+    xyz = [x[np.lexsort((x[:, 2], x[:, 1], x[:, 0]))] for x in xyz]
+    rgb = [rng.uniform(0, 255, size=x.shape).astype(np.float32) for x in xyz]
+    off = np.concatenate([[0], np.cumsum([len(x) for x in xyz])]).astype(np.int64)
+    ctx = fgbd.Context("cuda")
+    ctx.profile(True)
+    out, res = fgbd.denoise_batched(dev(np.concatenate(xyz), torch.int32), dev(np.concatenate(rgb), torch.float32),
+                                    dev(off, torch.int64), prm, ctx=ctx)
+    torch.cuda.synchronize()
+    assert ctx.profile_read()["local_sort"][1] == 1
+    out, recs = out.cpu().numpy(), fgbd.read_results(res)
+    for s in range(len(xyz)):
+        compare_denoise(out[off[s]:off[s + 1]], recs[s], xyz[s], rgb[s], prm)
+    ctx.close()
