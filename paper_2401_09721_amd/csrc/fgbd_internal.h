@@ -472,10 +472,9 @@ constexpr int kSortPasses = 4;                        // 8-bit digits of 32-bit 
 constexpr int kMsdBits = 10;
 constexpr int kMsdBins = 1 << kMsdBits;
 constexpr int kLocalWin = kSortTile;  // sorted positions per local-sort window (windows are numbered like the tiles)
-// a range this large makes later eager calls on the context sort by LSD passes
-// for kSortLsdCalls calls
+// a range this large makes later calls on the context sort by LSD passes for a
+// while (SortWatch)
 constexpr int kBigRange = 32768;
-constexpr int kSortLsdCalls = 32;
 
 constexpr int kBlock = 256;
 constexpr int kMaxGrid = 1024;  // default grid cap of the grid-stride kernels

@@ -121,17 +121,17 @@ int main(int argc, char **argv) {
 
   SortWatch w;
   int32_t flag[2] = {0, 0};
-  bad += w.lsd(flag, 3) || w.unsure();
+  bad += w.lsd(flag) || w.unsure();
   w.ask(flag);
   w.cancel();
-  bad += w.pending() || w.outstanding(flag) || !w.unsure() || w.lsd(flag, 3);
+  bad += w.pending() || w.outstanding(flag) || !w.unsure() || w.lsd(flag);
   const int32_t seq = w.ask(flag);
-  bad += !w.pending() || !w.outstanding(flag) || w.lsd(flag, 3);
+  bad += !w.pending() || !w.outstanding(flag) || w.lsd(flag);
   flag[0] = 1;
   flag[1] = seq;
   bad += w.outstanding(flag);
-  for (int i = 0; i < 3; ++i) bad += !w.lsd(flag, 3) || w.pending();
-  bad += w.lsd(flag, 3);
+  for (int i = 0; i < SortWatch::kCalls; ++i) bad += !w.lsd(flag) || w.pending();
+  bad += w.lsd(flag);
   printf("%lld\\n", (long long)bad);
 }
 """
@@ -162,3 +162,35 @@ int main(int argc, char **argv) {
 def test_a_tuning_that_fails_leaves_the_mark(tmp_path):
     # (not chosen before: failed, kept; chosen before: failed, kept)
     assert run(tmp_path, HEAD, TRIALS) == ["10", "11", "11", "11"]
+
+
+ROUTES = """
+int main(int argc, char **argv) {
+  int64_t bad = 0;
+  SortWatch w;
+  int32_t flag[2] = {0, 0};
+  auto asked = [&](bool crowded, int32_t seq) {
+    flag[0] = crowded;
+    flag[1] = seq;
+  };
+  // nothing known: calls made ahead of the first answer keep the default
+  bad += w.last_crowded(flag) || w.lsd(flag);
+  int32_t seq = w.ask(flag);
+  for (int i = 0; i < 50; ++i) bad += w.lsd(flag) || w.last_crowded(flag);
+  asked(true, seq);
+  bad += !w.last_crowded(flag);  // (a captured call: counts as no call)
+  for (int round = 0; round < 3; ++round) {
+    for (int i = 0; i < SortWatch::kCalls; ++i) bad += !w.lsd(flag) || w.pending();
+    bad += w.lsd(flag);  // this one asks again ...
+    seq = w.ask(flag);
+    for (int i = 0; i < 50; ++i) bad += !w.lsd(flag) || !w.last_crowded(flag);  // ... and those ahead of its answer do not try
+    asked(round < 2, seq);
+  }
+  for (int i = 0; i < 50; ++i) bad += w.lsd(flag) || w.last_crowded(flag) || w.pending();
+  printf("%lld\\n", (long long)bad);
+}
+"""
+
+
+def test_routes_ahead_of_the_answer(tmp_path):
+    assert run(tmp_path, HEAD, ROUTES) == ["0"]

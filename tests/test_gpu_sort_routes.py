@@ -167,3 +167,48 @@ def test_large_buckets_of_a_batch(bits):
     for s in range(len(xyz)):
         compare_denoise(out[off[s]:off[s + 1]], recs[s], xyz[s], rgb[s], prm)
     ctx.close()
+
+
+@pytest.mark.parametrize("bits,passes", [(10, 4), (11, 5)])
+def test_calls_ahead_of_the_answer(bits, passes):
+    """Calls made one after another, none waited for: once crowded points were
+    found, one call in 33 tries the top-digit route again."""
+    g = plane(np.random.default_rng(3), bits, 40000)
+    prm = fgbd.default_params(bits=bits)
+    with Sorter() as s:
+        assert s(g, prm, check=False) == TOP_DIGIT
+        x = dev(g, torch.int32)
+        graphs = [fgbd.build_slg(x, prm, ctx=s.ctx) for _ in range(60)]
+        torch.cuda.synchronize()
+        assert s.route() == (1, 1 + 59 * passes)
+        for other in graphs[1:]:
+            assert torch.equal(other.col, graphs[0].col) and torch.equal(other.dist2, graphs[0].dist2)
+        assert s(g, prm) == (0, passes)
+
+
+@pytest.mark.parametrize("bits", [10, 11])
+def test_captured_after_a_crowded_call(bits):
+    """A captured call takes the route that the eager call before it found; its
+    replays give the oracle's graph for crowded and for scattered points."""
+    rng = np.random.default_rng(9)
+    prm = fgbd.default_params(bits=bits)
+    crowded, other = plane(rng, bits, 40000), rng.integers(0, 1 << bits, size=(40000, 3)).astype(np.int32)
+    for first in (crowded, other):
+        ctx = fgbd.Context("cuda")
+        ctx.reserve(prm, len(first))
+        x = dev(first, torch.int32)
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            fgbd.build_slg(x, prm, ctx=ctx)
+        torch.cuda.synchronize()
+        captured = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(captured):
+            g = fgbd.build_slg(x, prm, ctx=ctx)
+        for points in (crowded, other, crowded):
+            x.copy_(dev(points, torch.int32))
+            captured.replay()
+            torch.cuda.synchronize()
+            col, d2 = O.slg_graph(points, prm.bits, prm.num_dirs, prm.window, prm.k)
+            assert np.array_equal(g.col.cpu().numpy(), col) and np.array_equal(g.dist2.cpu().numpy(), d2)
+        ctx.close()
