@@ -40,12 +40,20 @@ namespace {
 // T's diagonal per point (the forward call stores it with p in saved, so the
 // backward steps read 4 bytes per point instead of the first slot of each
 // neighbour row).
-// KT = 8: instead of dp, what the steps derive p and dp from (see PolyRow),
-// in dp's place: 24 bytes a point where p and dp are 64.
+// PACK (KT = 8, many points): in dp's place, what the steps derive p and dp
+// from, 24 bytes a point where p and dp are 64: for each 64 points (a wave's)
+// 64 PolyRow and 64 uint2 of gaps, a byte each.  Where a gap of the 64 points
+// does not fit its byte they have dp there as without PACK, and form[] of the
+// 64 says so.
 struct PolyRow {
-  double scale;  // the row's normalising factor, -1 when a gap does not fit its byte
+  double scale;  // the row's normalising factor
   double mean;   // sum_k' p_ik' a_ik'
 };
+// Points from which a call packs: fewer read p and dp faster, from caches, than
+// they fill a table in every block and form the weights again (7 steps on 30k
+// points 37 us against 52, on 250k 86 and 95, on 500k 138 and 141; 700k 178 and
+// 176, 2M 438 and 362).
+constexpr int64_t kPolyPack = 600000;
 constexpr uint32_t kPolyGap = 255;  // gaps of a packed row are below this
 // dp of a slot (the same operations wherever it is formed)
 __device__ __forceinline__ float poly_dp(float pw, double a_scale, int gap, double mean) {
@@ -61,12 +69,13 @@ __device__ __forceinline__ double poly_mean(const float (&pw)[KB], const int (&c
     if (cv[0] >= 0 && cv[k] >= 0) m = fma((double)pw[k] * a_scale, (double)(dv[k] - dv[0]), m);
   return m;
 }
-template <int KT>
+template <int KT, bool PACK>
 __global__ __launch_bounds__(kBlock) void k_poly_weights(int32_t n, int32_t k_rt, const int32_t *__restrict__ col,
                                                          const int32_t *__restrict__ dist2,
                                                          const double *__restrict__ sigma_g,
                                                          float *__restrict__ p, float *__restrict__ dp,
-                                                         float *__restrict__ diag) {
+                                                         uint32_t *__restrict__ form, float *__restrict__ diag) {
+  static_assert(!PACK || KT == 8, "rows of 8 only");
   __shared__ double s_exp[kExpTable];
   const int K = KT > 0 ? KT : k_rt;
   const double sg = *sigma_g;
@@ -98,17 +107,33 @@ __global__ __launch_bounds__(kBlock) void k_poly_weights(int32_t n, int32_t k_rt
       float4 *pr = reinterpret_cast<float4 *>(p + i * 8);
       pr[0] = make_float4(pw[0], pw[1], pw[2], pw[3]);
       pr[1] = make_float4(pw[4], pw[5], pw[6], pw[7]);
-      uint32_t gaps[2] = {0, 0};
-      bool fits = true;
+      const double mean = poly_mean<KB>(pw, cv, dv, a_scale);
+      bool packed = false;
+      if constexpr (PACK) {
+        uint32_t gaps[2] = {0, 0};
+        bool fits = true;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const uint32_t gap = cv[k] >= 0 ? (uint32_t)(dv[k] - dv[0]) : 0u;
-        fits &= gap < kPolyGap;
-        gaps[k >> 2] |= (gap & 255u) << (8 * (k & 3));
+        for (int k = 0; k < 8; ++k) {
+          const uint32_t gap = cv[k] >= 0 ? (uint32_t)(dv[k] - dv[0]) : 0u;
+          fits &= gap < kPolyGap;
+          gaps[k >> 2] |= (gap & 255u) << (8 * (k & 3));
+        }
+        packed = __builtin_amdgcn_ballot_w64(!fits) == 0;  // (a wave's points are 64 in a row from a multiple of 64)
+        if ((i & (kWave - 1)) == 0) form[i / kWave] = packed ? 1u : 0u;
+        if (packed) {
+          PolyRow *rows = reinterpret_cast<PolyRow *>(dp + i / kWave * kWave * 8);
+          rows[i & (kWave - 1)] = {rs, mean};
+          reinterpret_cast<uint2 *>(rows + kWave)[i & (kWave - 1)] = make_uint2(gaps[0], gaps[1]);
+        }
       }
-      PolyRow *rows = reinterpret_cast<PolyRow *>(dp);
-      rows[i] = {fits ? rs : -1.0, poly_mean<KB>(pw, cv, dv, a_scale)};
-      reinterpret_cast<uint2 *>(rows + n)[i] = make_uint2(gaps[0], gaps[1]);
+      if (!packed) {
+        float dw[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) dw[k] = (cv[0] >= 0 && cv[k] >= 0) ? poly_dp(pw[k], a_scale, dv[k] - dv[0], mean) : 0.0f;
+        float4 *dr = reinterpret_cast<float4 *>(dp + i * 8);
+        dr[0] = make_float4(dw[0], dw[1], dw[2], dw[3]);
+        dr[1] = make_float4(dw[4], dw[5], dw[6], dw[7]);
+      }
     } else {
 #pragma unroll
       for (int k = 0; k < KB; ++k)
@@ -250,22 +275,24 @@ __device__ __forceinline__ void st3(float *__restrict__ x, int64_t i, float a, f
 
 // One sweep x_k = T x_{k-1} (k >= 1) into saved[k].  The last sweep
 // (k == ncoef - 1) also forms out = sum_k c_k x_k from the saved iterates.
-// KT = 8: p and dp are formed again from the row's gaps, with the operations
-// and so the bits of k_poly_weights: a step is bound by the bytes of the
-// graph, and 2M points read 112 MB of it so instead of 192 (46 us a step with
-// stored p and dp, 36 so).
-template <int KT>
+// PACK: p and dp are formed again from the row's gaps, with the operations and
+// so the bits of k_poly_weights: a step on many points is bound by the bytes of
+// the graph, and 2M points read 112 MB of it so instead of 192 (46 us a step
+// with stored p and dp, 36 so).
+template <int KT, bool PACK>
 __global__ __launch_bounds__(kBlock) void k_poly_step(int32_t n, int32_t k_rt, int k, int ncoef,
                                                       const int32_t *__restrict__ col,
-                                                      const int32_t *__restrict__ dist2,
                                                       const double *__restrict__ sigma_g,
                                                       const float *__restrict__ p, const float *__restrict__ dp,
+                                                      const uint32_t *__restrict__ form,
                                                       const float *__restrict__ coef, float *__restrict__ saved,
                                                       float *__restrict__ out) {
-  __shared__ double s_exp[KT == 8 ? kExpTable : 1];
+  __shared__ double s_exp[PACK ? kExpTable : 1];
   const int K = KT > 0 ? KT : k_rt;
   double a_scale = 0.0;
-  if constexpr (KT == 8) {
+  uint32_t next_form = 0;  // of the wave's next 64 points, loaded a round ahead
+  if constexpr (PACK) {
+    next_form = form[min(((int)blockIdx.x * kBlock + (int)threadIdx.x) / kWave, (n - 1) / kWave)];
     const double sg = *sigma_g;
     fill_exp_table(sg, s_exp);
     a_scale = poly_a_scale(sg);
@@ -283,24 +310,29 @@ __global__ __launch_bounds__(kBlock) void k_poly_step(int32_t n, int32_t k_rt, i
     if (KT == 8) {
       const int4 *cr = reinterpret_cast<const int4 *>(col + i * 8);
       const int4 ca = cr[0], cb = cr[1];
-      const PolyRow *rows = reinterpret_cast<const PolyRow *>(dp);
-      const PolyRow row = rows[i];
-      const uint2 gaps = reinterpret_cast<const uint2 *>(rows + n)[i];
       const int cv[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
       float pv[8], dv[8];
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        const uint32_t gap = (kk < 4 ? gaps.x : gaps.y) >> (8 * (kk & 3)) & 255u;
-        const float w = (float)(s_exp[gap] * row.scale);
-        pv[kk] = cv[kk] >= 0 ? w : 0.0f;
-        dv[kk] = cv[kk] >= 0 ? poly_dp(w, a_scale, (int)gap, row.mean) : 0.0f;
-      }
-      if (row.scale < 0.0) {  // a gap past its byte
+      const bool packed = PACK && __builtin_amdgcn_readfirstlane((int)next_form) != 0;
+      if constexpr (PACK) next_form = form[min((i + (int64_t)gridDim.x * kBlock) / kWave, (int64_t)(n - 1) / kWave)];
+      if (packed) {
+        const PolyRow *rows = reinterpret_cast<const PolyRow *>(dp + i / kWave * kWave * 8);
+        const PolyRow row = rows[i & (kWave - 1)];
+        const uint2 gaps = reinterpret_cast<const uint2 *>(rows + kWave)[i & (kWave - 1)];
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
-          pv[kk] = p[8 * i + kk];
-          dv[kk] = cv[kk] >= 0 ? poly_dp(pv[kk], a_scale, dist2[8 * i + kk] - dist2[8 * i], row.mean) : 0.0f;
+          const uint32_t gap = (kk < 4 ? gaps.x : gaps.y) >> (8 * (kk & 3)) & 255u;
+          const float w = (float)(s_exp[gap] * row.scale);
+          pv[kk] = cv[kk] >= 0 ? w : 0.0f;
+          dv[kk] = cv[kk] >= 0 ? poly_dp(w, a_scale, (int)gap, row.mean) : 0.0f;
         }
+      } else {
+        const float4 *pr = reinterpret_cast<const float4 *>(p + i * 8);
+        const float4 *dr = reinterpret_cast<const float4 *>(dp + i * 8);
+        const float4 pa = pr[0], pb = pr[1], da = dr[0], db = dr[1];
+        pv[0] = pa.x; pv[1] = pa.y; pv[2] = pa.z; pv[3] = pa.w;
+        pv[4] = pb.x; pv[5] = pb.y; pv[6] = pb.z; pv[7] = pb.w;
+        dv[0] = da.x; dv[1] = da.y; dv[2] = da.z; dv[3] = da.w;
+        dv[4] = db.x; dv[5] = db.y; dv[6] = db.z; dv[7] = db.w;
       }
       c0 = cv[0];
 #pragma unroll
@@ -576,7 +608,8 @@ size_t poly_workspace(int64_t n, int k, int ncoef, int nblocks) {
   const size_t N = (size_t)(n > 0 ? n : 1);
   size_t b = 0;
   auto take = [&](size_t bytes) { b += (bytes + 255) & ~(size_t)255; };
-  take(N * k * 4);                     // dp (forward) or p in the transpose's order (backward)
+  take((N + 63) / 64 * 64 * k * 4);    // dp (forward) or p in the transpose's order (backward)
+  take((N + 63) / 64 * 4);             // the form of each 64 points' dp
   take((N + 1) * 4);                   // offsets (when no transpose is given)
   take(N * k * 4);                     // transposed edge ids (same)
   take(2 * N * 3 * 4);                 // z ping-pong
@@ -588,6 +621,7 @@ size_t poly_workspace(int64_t n, int k, int ncoef, int nblocks) {
 
 struct PolyBufs {
   float *aux;
+  uint32_t *form;
   int32_t *off, *tsrc;
   float *z[2];
   double *coef_part, *sig_part;
@@ -603,7 +637,8 @@ static PolyBufs poly_carve(char *ws, int64_t n, int k, int ncoef, int nblocks) {
     o += (bytes + 255) & ~(size_t)255;
     return ptr;
   };
-  pb.aux = (float *)take(N * k * 4);
+  pb.aux = (float *)take((N + 63) / 64 * 64 * k * 4);
+  pb.form = (uint32_t *)take((N + 63) / 64 * 4);
   pb.off = (int32_t *)take((N + 1) * 4);
   pb.tsrc = (int32_t *)take(N * k * 4);
   pb.z[0] = (float *)take(N * 3 * 4);
@@ -660,16 +695,12 @@ hipError_t launch_poly_forward(int64_t n, int k, const int32_t *col, const int32
   if (ncoef == 1) return hipGetLastError();
   float *p = saved + poly_saved_p_offset(n, ncoef);
   float *diag = p + (size_t)n * k;
-  if (k == 8)
-    k_poly_weights<8><<<G, kBlock, 0, s>>>((int32_t)n, k, col, dist2, sigma_g, p, pb.aux, diag);
-  else
-    k_poly_weights<0><<<G, kBlock, 0, s>>>((int32_t)n, k, col, dist2, sigma_g, p, pb.aux, diag);
-  for (int kk = 1; kk < ncoef; ++kk) {
-    if (k == 8)
-      k_poly_step<8><<<G, kBlock, 0, s>>>((int32_t)n, k, kk, ncoef, col, dist2, sigma_g, p, pb.aux, coef, saved, out);
-    else
-      k_poly_step<0><<<G, kBlock, 0, s>>>((int32_t)n, k, kk, ncoef, col, dist2, sigma_g, p, pb.aux, coef, saved, out);
-  }
+  const bool pack = k == 8 && n >= kPolyPack;
+  const auto weights = pack ? k_poly_weights<8, true> : (k == 8 ? k_poly_weights<8, false> : k_poly_weights<0, false>);
+  const auto step = pack ? k_poly_step<8, true> : (k == 8 ? k_poly_step<8, false> : k_poly_step<0, false>);
+  weights<<<G, kBlock, 0, s>>>((int32_t)n, k, col, dist2, sigma_g, p, pb.aux, pb.form, diag);
+  for (int kk = 1; kk < ncoef; ++kk)
+    step<<<G, kBlock, 0, s>>>((int32_t)n, k, kk, ncoef, col, sigma_g, p, pb.aux, pb.form, coef, saved, out);
   return hipGetLastError();
 }
 
