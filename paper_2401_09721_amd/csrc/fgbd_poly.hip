@@ -18,8 +18,9 @@
 // T^T pulls along an explicit transpose of the directed graph: for every point
 // j the edge ids e = i * K + slot with col[e] = j, in increasing order (built
 // once per graph by fgbd_graph_transpose, or per call); the first backward
-// step lays the weights out in that order (p_T[u] = p[edge[u]] / 2), so the
-// others read them contiguously and gather only the adjoint.  One launch per
+// step, or for small graphs a launch before it, lays the weights out in that
+// order (p_T[u] = p[edge[u]] / 2), so the others read them contiguously and
+// gather only the adjoint.  One launch per
 // backward step computes z_{m-1}, the step's sigma_g term and the
 // coefficient products <g, x_{m-1}> together.  Scalar gradients are FP64
 // per-block partials summed in block order by a one-block kernel.  No
@@ -50,10 +51,10 @@ struct PolyRow {
   double mean;   // sum_k' p_ik' a_ik'
 };
 // Points from which a call packs: fewer read p and dp faster, from caches, than
-// they fill a table in every block and form the weights again (7 steps on 30k
-// points 37 us against 52, on 250k 86 and 95, on 500k 138 and 141; 700k 178 and
-// 176, 2M 438 and 362).
-constexpr int64_t kPolyPack = 600000;
+// they fill a table in every block and form the weights again (a call of 7 steps
+// on 100k points 49 us against 52, on 200k 74 and 81, on 400k 120 and 122; on
+// 500k 137 and 131, on 1.5M 331 and 287).
+constexpr int64_t kPolyPack = 450000;
 constexpr uint32_t kPolyGap = 255;  // gaps of a packed row are below this
 // dp of a slot (the same operations wherever it is formed)
 __device__ __forceinline__ float poly_dp(float pw, double a_scale, int gap, double mean) {
@@ -537,6 +538,117 @@ __global__ __launch_bounds__(kBlock) void k_poly_back(int32_t n, int32_t k_rt, i
   }
 }
 
+// The same step with a point's in-edges read by its lane, for small graphs
+// (by_rows): the chain of a step is shorter so, with no LDS and no barriers, and
+// its lines stay in L2.  The weights' order is a launch of its own: their gather
+// in a point's own loop lengthened the first step's chain by more.
+// p_T[u] = p[edge[u]] / 2 for u < off[n]: the weights (with T's factor 1/2)
+// in the transpose's order, so each backward step reads them contiguously.
+__global__ __launch_bounds__(kBlock) void k_poly_ptrans(int32_t n, const int32_t *__restrict__ off,
+                                                        const int32_t *__restrict__ tsrc, const float *__restrict__ p,
+                                                        float *__restrict__ pt) {
+  const int64_t E = off[n];
+  if (E <= 0) return;
+  // four edges per thread and round, their id loads and then their gathers
+  // in flight together (indices clamped, so no load needs a branch)
+  constexpr int U = 4;
+  const int64_t stride = (int64_t)gridDim.x * kBlock;
+  for (int64_t u0 = (int64_t)blockIdx.x * kBlock + threadIdx.x; u0 < E; u0 += U * stride) {
+    int32_t e[U];
+    float w[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) e[j] = tsrc[min(u0 + j * stride, E - 1)];
+#pragma unroll
+    for (int j = 0; j < U; ++j) w[j] = p[e[j]];
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      if (u0 + j * stride < E) pt[u0 + j * stride] = 0.5f * w[j];
+  }
+}
+
+template <int KT>
+__global__ __launch_bounds__(kBlock) void k_poly_back_rows(int32_t n, int32_t k_rt, int m, int last, int nb, int ncoef,
+                                                      const float *__restrict__ diag, const int32_t *__restrict__ off,
+                                                      const int32_t *__restrict__ tsrc, const float *__restrict__ pt,
+                                                      const float *__restrict__ coef, const float *__restrict__ g,
+                                                      const float *__restrict__ saved, const float *__restrict__ zin,
+                                                      float *__restrict__ zout, double *__restrict__ sig_part,
+                                                      double *__restrict__ cpart) {
+  __shared__ double s_red[8 * 3];
+  const int K = KT > 0 ? KT : k_rt;
+  const float cm = coef[m], cm1 = coef[m - 1];
+  const size_t S = (size_t)n * 3;
+  const float *xprev = saved + (size_t)(m - 1) * S;
+  const float *xcur = saved + (size_t)m * S;
+  const float *um = saved + (size_t)(ncoef + m - 1) * S;
+  // z_{m+1} is c_m g on the last step (m = ncoef - 1), else the previous step's
+  // output; <g, x_m> is needed on the last step only (yrow reads x_{m-1} again
+  // otherwise, from cache)
+  const float *zsrc = last ? g : zin;
+  const float zs = last ? cm : 1.0f;
+  const float *yrow = last ? xcur : xprev;
+  // acc[0]: sigma_g term; acc[1]: <g, x_{m-1}>; acc[2]: <g, x_m> (last step only)
+  double acc[3] = {0.0, 0.0, 0.0};
+  for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += (int64_t)gridDim.x * kBlock) {
+    // every load of the row is unconditional (the step's kind only picks the
+    // pointers), so they are all in flight together
+    float g0, g1, g2, z0, z1, z2, x0, x1, x2, y0, y1, y2, u0, u1, u2;
+    ld3(g, j, g0, g1, g2);
+    ld3(zsrc, j, z0, z1, z2);
+    ld3(xprev, j, x0, x1, x2);
+    ld3(yrow, j, y0, y1, y2);
+    ld3(um, j, u0, u1, u2);
+    z0 *= zs;
+    z1 *= zs;
+    z2 *= zs;
+    acc[1] += (double)g0 * x0 + (double)g1 * x1 + (double)g2 * x2;
+    const double gy = (double)g0 * y0 + (double)g1 * y1 + (double)g2 * y2;
+    acc[2] += last ? gy : 0.0;
+    acc[0] += 0.5 * ((double)z0 * u0 + (double)z1 * u1 + (double)z2 * u2);
+    // T^T z_m at j
+    const float tjj = diag[j];
+    float r0 = tjj * z0, r1 = tjj * z1, r2 = tjj * z2;
+    // in-edges four at a time (their ids, weights and gathers all in flight
+    // together), then the rest one by one; the order of the additions is the
+    // edges' order either way
+    const int a = off[j], b = off[j + 1];
+    int u = a;
+    for (; u + 4 <= b; u += 4) {
+      int64_t sr[4];
+      float w[4], s[4][3];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sr[e] = tsrc[u + e] / K;
+        w[e] = pt[u + e];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ld3(zsrc, sr[e], s[e][0], s[e][1], s[e][2]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        r0 = fmaf(w[e], zs * s[e][0], r0);
+        r1 = fmaf(w[e], zs * s[e][1], r1);
+        r2 = fmaf(w[e], zs * s[e][2], r2);
+      }
+    }
+    for (; u < b; ++u) {
+      const int64_t src = tsrc[u] / K;
+      const float w = pt[u];
+      float s0, s1, s2;
+      ld3(zsrc, src, s0, s1, s2);
+      r0 = fmaf(w, zs * s0, r0);
+      r1 = fmaf(w, zs * s1, r1);
+      r2 = fmaf(w, zs * s2, r2);
+    }
+    st3(zout, j, fmaf(cm1, g0, r0), fmaf(cm1, g1, r1), fmaf(cm1, g2, r2));
+  }
+  block_sum_f64<3>(acc, s_red);
+  if (threadIdx.x == 0) {
+    sig_part[blockIdx.x] = acc[0];
+    cpart[(size_t)(m - 1) * nb + blockIdx.x] = acc[1];
+    if (last) cpart[(size_t)m * nb + blockIdx.x] = acc[2];
+  }
+}
+
 // One coefficient: z_0 = c_0 g and <g, x_0>.
 __global__ __launch_bounds__(kBlock) void k_scale(int32_t n, const float *__restrict__ coef,
                                                   const float *__restrict__ g, const float *__restrict__ x0,
@@ -704,6 +816,15 @@ hipError_t launch_poly_forward(int64_t n, int k, const int32_t *col, const int32
   return hipGetLastError();
 }
 
+// Whether the adjoint's steps read in-edges by rows.  8 coefficients, by rows
+// and through LDS, in us: K = 8 and 30k points 52 and 54, 180k 91 and 96, 220k
+// 112 and 113; K = 16 and 30k 68 and 82, 120k 101 and 114, 140k 136 and 133; K =
+// 32 and 30k 103 and 157, 100k 214 and 202; K = 6 and 30k 52 and 44.  The launch
+// that orders the weights takes as long as three steps gain.
+static bool by_rows(int64_t n, int k, int ncoef) {
+  return k >= 7 && ncoef >= 4 && n <= (k <= 8 ? 200000 : 131072) && n * k <= 2900000;
+}
+
 hipError_t launch_poly_backward(int64_t n, int k, const int32_t *col, const int32_t *dist2, const int32_t *t_off,
                                 const int32_t *t_edge, const float *saved, const float *coef, int ncoef,
                                 const double *sigma_g, const float *grad_out, float *grad_x, float *grad_coef,
@@ -727,9 +848,18 @@ hipError_t launch_poly_backward(int64_t n, int k, const int32_t *col, const int3
   const float *diag = p + (size_t)n * k;
   // reverse Horner; coefficient products ride along
   const float *zin = nullptr;
+  const bool rows = by_rows(n, k, ncoef);
+  if (rows) k_poly_ptrans<<<grid_for(n * k), kBlock, 0, s>>>((int32_t)n, t_off, t_edge, p, pb.aux);
   for (int m = ncoef - 1; m >= 1; --m) {
     float *zout = (m == 1) ? grad_x : pb.z[m & 1];
     const bool last = m == ncoef - 1;
+    if (rows) {
+      (k == 8 ? k_poly_back_rows<8> : k_poly_back_rows<0>)<<<G, kBlock, 0, s>>>(
+          (int32_t)n, k, m, last, G, ncoef, diag, t_off, t_edge, pb.aux, coef, grad_out, saved, zin, zout,
+          pb.sig_part + (size_t)m * G, pb.coef_part);
+      zin = zout;
+      continue;
+    }
     const auto fn = k == 8 ? (last ? k_poly_back<8, true> : k_poly_back<8, false>)
                            : (last ? k_poly_back<0, true> : k_poly_back<0, false>);
     fn<<<G, kBlock, 0, s>>>((int32_t)n, k, m, G, ncoef, diag, t_off, t_edge, p, pb.aux, coef, grad_out, saved, zin, zout,

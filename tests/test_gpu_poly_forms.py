@@ -1,7 +1,9 @@
-"""The polynomial filter around the number of points from which its steps read
-packed rows (600,000), with groups of 64 points whose gaps all fit a byte, none
+"""The polynomial filter at the lines of its variants.  Forward, around the
+number of points from which its steps read packed rows (450,000), with groups of 64 points whose gaps all fit a byte, none
 do, or some: against the oracle, with the tolerances of this filter's other
-tests; and the same results from a graph's first points as from those alone."""
+tests; and the same results from a graph's first points as from those alone.
+Backward, on both sides of each line between in-edges read by rows and through
+LDS, and at small sizes, against the oracle."""
 import numpy as np
 import pytest
 
@@ -29,7 +31,7 @@ def _points(n, spread, seed):
     return g.astype(np.int32)
 
 
-@pytest.mark.parametrize("n", [599_999, 600_000, 600_001, 600_063])
+@pytest.mark.parametrize("n", [449_999, 450_000, 450_001, 450_063])
 @pytest.mark.parametrize("spread,sg", [(0, 1.3), (7, 1.3), (1, 900.0)])
 def test_forms_around_the_line(n, spread, sg):
     g = fgbd.build_slg(dev(_points(n, spread, n), torch.int32), fgbd.default_params(bits=15, num_dirs=3))
@@ -41,7 +43,7 @@ def test_forms_give_the_same_bits(spread):
     """Rows of the first points, whose neighbours are all among them, in a
     graph past the line and in one of these points alone: every output of the
     forward call has the same bits."""
-    n, m = 600_000, 120_000
+    n, m = 450_000, 120_000
     prm = fgbd.default_params(bits=15, num_dirs=3)
     part = fgbd.build_slg(dev(_points(m, spread, 5), torch.int32), prm)
     filler = torch.full((n - m, 8), -1, dtype=torch.int32, device="cuda")
@@ -57,3 +59,14 @@ def test_forms_give_the_same_bits(spread):
     assert torch.equal(out[:m], pout)
     rows = 2 * 4 - 1  # the iterates, then u_m
     assert torch.equal(saved[:rows * 3 * n].view(rows, n, 3)[:, :m], psaved[:rows * 3 * m].view(rows, m, 3))
+
+
+@pytest.mark.parametrize("n,k,ncoef", [(200_000, 8, 4), (200_001, 8, 4), (131_072, 12, 4), (131_073, 12, 4), (90_625, 32, 4),
+                                       (90_626, 32, 4), (3000, 7, 4), (3000, 6, 4), (3000, 16, 3), (257, 16, 5),
+                                       (1, 8, 4)])
+def test_adjoint_lines(n, k, ncoef):
+    rng = np.random.default_rng(n + k)
+    side = max(8, int((4 * n) ** (1 / 3)))
+    xyz = rng.integers(0, side, size=(n, 3)).astype(np.int32)
+    g = fgbd.build_slg(dev(xyz, torch.int32), fgbd.default_params(bits=10, num_dirs=8, k=k))
+    check(g, n, ncoef, 1.5, n)
