@@ -371,10 +371,15 @@ __device__ __forceinline__ void sweep_step(const SweepArgs &a, const SegBlock &s
       load_row<KT>(p, i, K, a.vec, 0.0f, ww);
     }
     // Branch-free gathers: an empty slot (col = -1, weight 0) reads the point
-    // itself.  All neighbour loads are issued before any is consumed.
+    // itself.  All neighbour loads are issued before any is consumed; slots
+    // past K (uniform) gather nothing.
     float gx[KB], gy[KB], gz[KB];
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
+      if (KT < 0 && k >= K) {
+        gx[k] = gy[k] = gz[k] = 0.0f;
+        continue;
+      }
       const int64_t cj = cc[k] >= 0 ? (int64_t)cc[k] : i;
       if (!FROM_X) {
         gx[k] = rgb_in[3 * cj + 0];

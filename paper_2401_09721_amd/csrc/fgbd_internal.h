@@ -254,10 +254,12 @@ __device__ __forceinline__ Share seg_share(const SegBlock &sb, int chunk) {
 // Kernels that hold a point's row in registers are instantiated for a row
 // kind KT: KT > 0 is K = KT exactly, its loads as wide as KT allows (16 bytes
 // for multiples of 4, 8 for other even K); KT < 0 any K <= -KT, loads `vec`
-// elements wide and clamped into the row (so all are issued without a branch;
-// slots past K are then filled).  The sweeps, weights and patches of other K
-// than 8 all ran 32-slot rows before: 21 us for a sweep of 180k points with
-// K = 16 against 10.5 now, 17 against 10 for 300k points with K = 6.
+// elements wide, slots past K filled.  Loads past K are skipped by uniform
+// branches: clamped into the row instead, they took their share of the address
+// rate (6 sweeps of 200k points, K = 9: 110 us, 89 with them and the gathers of
+// these slots skipped; K = 24 248 and 167).  The sweeps, weights and patches of
+// other K than 8 all ran 32-slot rows before: 21 us for a sweep of 180k points
+// with K = 16 against 10.5 now, 17 against 10 for 300k points with K = 6.
 constexpr int row_cap(int KT) { return KT > 0 ? KT : -KT; }
 template <typename T, int N>
 struct alignas(sizeof(T) * N) RowVec {
@@ -281,13 +283,16 @@ __device__ __forceinline__ void load_row(const T *__restrict__ base, int64_t i, 
     if (vec == 4) {  // uniform over the launch
 #pragma unroll
       for (int q = 0; q < KB / 4; ++q) {
-        const RowVec<T, 4> x = *reinterpret_cast<const RowVec<T, 4> *>(r + min(4 * q, K - 4));
+        if (4 * q < K) {
+          const RowVec<T, 4> x = *reinterpret_cast<const RowVec<T, 4> *>(r + 4 * q);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[4 * q + u] = x.v[u];
+          for (int u = 0; u < 4; ++u) v[4 * q + u] = x.v[u];
+        }
       }
     } else {
 #pragma unroll
-      for (int k = 0; k < KB; ++k) v[k] = r[min(k, K - 1)];
+      for (int k = 0; k < KB; ++k)
+        if (k < K) v[k] = r[k];
     }
 #pragma unroll
     for (int k = 0; k < KB; ++k)
