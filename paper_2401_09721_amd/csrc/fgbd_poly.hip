@@ -51,9 +51,10 @@ struct PolyRow {
   double mean;   // sum_k' p_ik' a_ik'
 };
 // Points from which a call packs: fewer read p and dp faster, from caches, than
-// they fill a table in every block and form the weights again (a call of 7 steps
-// on 100k points 49 us against 52, on 200k 74 and 81, on 400k 120 and 122; on
-// 500k 137 and 131, on 1.5M 331 and 287).
+// they form the weights again (a call of 7 steps, without packed rows and with
+// them: 200k points 74 us and 81, 300k 97 and 103, 400k 120 and 118, 500k 136
+// and 129, 2M 430 and 345; with no gap that fits 500k 138 and 142, 2M 432 and
+// 443).
 constexpr int64_t kPolyPack = 450000;
 constexpr uint32_t kPolyGap = 255;  // gaps of a packed row are below this
 // dp of a slot (the same operations wherever it is formed)
@@ -75,13 +76,19 @@ __global__ __launch_bounds__(kBlock) void k_poly_weights(int32_t n, int32_t k_rt
                                                          const int32_t *__restrict__ dist2,
                                                          const double *__restrict__ sigma_g,
                                                          float *__restrict__ p, float *__restrict__ dp,
-                                                         uint32_t *__restrict__ form, float *__restrict__ diag) {
+                                                         uint32_t *__restrict__ form, double *__restrict__ table,
+                                                         float *__restrict__ diag) {
   static_assert(!PACK || KT == 8, "rows of 8 only");
   __shared__ double s_exp[kExpTable];
   const int K = KT > 0 ? KT : k_rt;
   const double sg = *sigma_g;
   fill_exp_table(sg, s_exp);
   __syncthreads();
+  if (PACK && blockIdx.x == 0) {  // the steps' copy, and the factor of a_ik
+    static_assert(kExpTable == kBlock, "one entry a thread");
+    table[threadIdx.x] = s_exp[threadIdx.x];
+    if (threadIdx.x == 0) table[kExpTable] = poly_a_scale(sg);
+  }
   constexpr int KB = KT > 0 ? KT : kMaxK;
   for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
     int cv[KB], dv[KB];
@@ -119,7 +126,9 @@ __global__ __launch_bounds__(kBlock) void k_poly_weights(int32_t n, int32_t k_rt
           fits &= gap < kPolyGap;
           gaps[k >> 2] |= (gap & 255u) << (8 * (k & 3));
         }
-        packed = __builtin_amdgcn_ballot_w64(!fits) == 0;  // (a wave's points are 64 in a row from a multiple of 64)
+        // (a wave's points are 64 in a row from a multiple of 64; the last ones
+        // are not packed if they are fewer: the steps' waves read the table whole)
+        packed = __builtin_amdgcn_ballot_w64(fits) == ~0ull;
         if ((i & (kWave - 1)) == 0) form[i / kWave] = packed ? 1u : 0u;
         if (packed) {
           PolyRow *rows = reinterpret_cast<PolyRow *>(dp + i / kWave * kWave * 8);
@@ -283,21 +292,21 @@ __device__ __forceinline__ void st3(float *__restrict__ x, int64_t i, float a, f
 template <int KT, bool PACK>
 __global__ __launch_bounds__(kBlock) void k_poly_step(int32_t n, int32_t k_rt, int k, int ncoef,
                                                       const int32_t *__restrict__ col,
-                                                      const double *__restrict__ sigma_g,
                                                       const float *__restrict__ p, const float *__restrict__ dp,
                                                       const uint32_t *__restrict__ form,
+                                                      const double *__restrict__ table,
                                                       const float *__restrict__ coef, float *__restrict__ saved,
                                                       float *__restrict__ out) {
-  __shared__ double s_exp[PACK ? kExpTable : 1];
+  // a wave's own copy of the table, read at its first packed points: no barrier,
+  // and none where no points are packed
+  __shared__ double s_table[PACK ? kBlock / kWave : 1][PACK ? kExpTable : 1];
+  double *const s_exp = s_table[PACK ? threadIdx.x / kWave : 0];
+  bool have_table = false;
   const int K = KT > 0 ? KT : k_rt;
   double a_scale = 0.0;
   uint32_t next_form = 0;  // of the wave's next 64 points, loaded a round ahead
   if constexpr (PACK) {
     next_form = form[min(((int)blockIdx.x * kBlock + (int)threadIdx.x) / kWave, (n - 1) / kWave)];
-    const double sg = *sigma_g;
-    fill_exp_table(sg, s_exp);
-    a_scale = poly_a_scale(sg);
-    __syncthreads();
   }
   const size_t S = (size_t)n * 3;
   const float *xp = saved + (size_t)(k - 1) * S;
@@ -316,6 +325,12 @@ __global__ __launch_bounds__(kBlock) void k_poly_step(int32_t n, int32_t k_rt, i
       const bool packed = PACK && __builtin_amdgcn_readfirstlane((int)next_form) != 0;
       if constexpr (PACK) next_form = form[min((i + (int64_t)gridDim.x * kBlock) / kWave, (int64_t)(n - 1) / kWave)];
       if (packed) {
+        if (!have_table) {  // (uniform over the wave)
+          for (int e = (int)lane_id(); e < kExpTable; e += kWave) s_exp[e] = table[e];
+          a_scale = table[kExpTable];
+          have_table = true;
+          __builtin_amdgcn_wave_barrier();
+        }
         const PolyRow *rows = reinterpret_cast<const PolyRow *>(dp + i / kWave * kWave * 8);
         const PolyRow row = rows[i & (kWave - 1)];
         const uint2 gaps = reinterpret_cast<const uint2 *>(rows + kWave)[i & (kWave - 1)];
@@ -722,6 +737,7 @@ size_t poly_workspace(int64_t n, int k, int ncoef, int nblocks) {
   auto take = [&](size_t bytes) { b += (bytes + 255) & ~(size_t)255; };
   take((N + 63) / 64 * 64 * k * 4);    // dp (forward) or p in the transpose's order (backward)
   take((N + 63) / 64 * 4);             // the form of each 64 points' dp
+  take((kExpTable + 1) * 8);           // the weights' table, for the steps
   take((N + 1) * 4);                   // offsets (when no transpose is given)
   take(N * k * 4);                     // transposed edge ids (same)
   take(2 * N * 3 * 4);                 // z ping-pong
@@ -734,6 +750,7 @@ size_t poly_workspace(int64_t n, int k, int ncoef, int nblocks) {
 struct PolyBufs {
   float *aux;
   uint32_t *form;
+  double *table;
   int32_t *off, *tsrc;
   float *z[2];
   double *coef_part, *sig_part;
@@ -751,6 +768,7 @@ static PolyBufs poly_carve(char *ws, int64_t n, int k, int ncoef, int nblocks) {
   };
   pb.aux = (float *)take((N + 63) / 64 * 64 * k * 4);
   pb.form = (uint32_t *)take((N + 63) / 64 * 4);
+  pb.table = (double *)take((kExpTable + 1) * 8);
   pb.off = (int32_t *)take((N + 1) * 4);
   pb.tsrc = (int32_t *)take(N * k * 4);
   pb.z[0] = (float *)take(N * 3 * 4);
@@ -810,9 +828,9 @@ hipError_t launch_poly_forward(int64_t n, int k, const int32_t *col, const int32
   const bool pack = k == 8 && n >= kPolyPack;
   const auto weights = pack ? k_poly_weights<8, true> : (k == 8 ? k_poly_weights<8, false> : k_poly_weights<0, false>);
   const auto step = pack ? k_poly_step<8, true> : (k == 8 ? k_poly_step<8, false> : k_poly_step<0, false>);
-  weights<<<G, kBlock, 0, s>>>((int32_t)n, k, col, dist2, sigma_g, p, pb.aux, pb.form, diag);
+  weights<<<G, kBlock, 0, s>>>((int32_t)n, k, col, dist2, sigma_g, p, pb.aux, pb.form, pb.table, diag);
   for (int kk = 1; kk < ncoef; ++kk)
-    step<<<G, kBlock, 0, s>>>((int32_t)n, k, kk, ncoef, col, sigma_g, p, pb.aux, pb.form, coef, saved, out);
+    step<<<G, kBlock, 0, s>>>((int32_t)n, k, kk, ncoef, col, p, pb.aux, pb.form, pb.table, coef, saved, out);
   return hipGetLastError();
 }
 
