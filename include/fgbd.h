@@ -456,9 +456,10 @@ const char *fgbd_last_error(void);
  *   2 radix downsweep (stable scatter), 3 neighbour merge, 4 edge weights,
  *   5 patch statistics, 6 noise eigen-solve, 7 filter sweep, 8 finalise,
  *   9 renumbering of clouds stored in no spatial order, 10 local sort of the
- *   buckets left by the top-digit pass (codes of at most 32 bits, which sort
- *   with one top-digit pass of kinds 0-2 and this launch instead of four
- *   LSD passes).
+ *   buckets left by the top-digit pass (codes beside which the point's index
+ *   fits in 64 bits sort with one top-digit pass of kinds 0-2 and this launch
+ *   instead of four or more LSD passes, unless the inputs lately had most of
+ *   a cloud in one bucket).
  * The event records add a little time of their own between launches.
  * ms, launches: host arrays of `count` entries (count <= FGBD_NUM_KERNELS). */
 #define FGBD_NUM_KERNELS 11

@@ -290,8 +290,8 @@ __device__ __forceinline__ void select_f64(const MergeArgs &a, int i, int lo, in
 // S > 1 (small clouds): S neighbouring lanes share a point, each selecting
 // from every S-th direction, then exchange their lists (each inserts the
 // other's): a wave's chain of window loads and insertions is S times shorter,
-// which is what a launch of at most two waves per SIMD takes its time for
-// (16k points: 24 us with S = 1, 15 with S = 4; 70k: 27 and 24).
+// which is what a launch of few waves per SIMD takes its time for (16k points:
+// 24 us with S = 1, 15 with S = 4; 70k: 27 and 24; up to kMergeSmall points).
 // ALL64: every point takes the 64-bit selection.
 template <int KM, int WT, int S = 1, bool ALL64 = false>
 __global__ __launch_bounds__(kBlock) void k_merge(MergeArgs a, const uint64_t *__restrict__ sorted,
@@ -523,7 +523,7 @@ template <bool BIG>
 __device__ __forceinline__ uint64_t wide_dist2(const WidePt &p, const WidePt &q) {
   const int dx = p.x - q.x, dy = p.y - q.y, dz = p.z - q.z;
   if constexpr (BIG) return (uint64_t)((int64_t)dx * dx + (int64_t)dy * dy + (int64_t)dz * dz);
-  // (below 2^16 in magnitude: the sum is below 2^32)
+  // (b <= 15: differences below 2^15 in magnitude, the sum below 3 * 2^30)
   return (uint32_t)mad_i24(dx, dx, mad_i24(dy, dy, __mul24(dz, dz)));
 }
 // The window without its centre.  When every window of the wave lies inside

@@ -473,7 +473,8 @@ constexpr int kSortThreads = 256;
 constexpr int kSortItems = 16;
 constexpr int kSortTile = kSortThreads * kSortItems;  // 4096 keys per tile
 constexpr int kSortPasses = 4;                        // 8-bit digits of 32-bit codes
-// codes of at most 32 bits: one pass on the top kMsdBits bits, then local sorts
+// codes beside which the index fits in an item: one pass on the top kMsdBits
+// bits, then local sorts
 constexpr int kMsdBits = 10;
 constexpr int kMsdBins = 1 << kMsdBits;
 constexpr int kLocalWin = kSortTile;  // sorted positions per local-sort window (windows are numbered like the tiles)
@@ -531,7 +532,7 @@ Plan make_plan(int64_t n_cap, int B, const fgbd_params &p, const Tune &tune = kD
 struct Bufs {
   Segs *segs;
   uint64_t *items_a, *items_b;  // [L][n_cap]
-  uint32_t *hist;               // [L][ntiles_cap + 1][256]
+  uint32_t *hist;               // [L][ntiles_cap + 1][kMsdBins]
   uint32_t *rank;               // [L][stride]
   uint8_t *digits;              // [L][stride]: the next radix pass's digit of each sorted item
   int4 *win;                    // [L][ntiles_cap]: each local-sort window's range and its first and last top digit
@@ -608,8 +609,8 @@ struct Run {
   // host-mapped: the finalising launch stores each cloud's sweep count | hint_tag here
   int32_t *hint = nullptr;
   int32_t hint_tag = 0;
-  // Sort route for codes of at most 32 bits: the top-digit pass and local
-  // sorts unless sort_lsd.  sort_big (host-mapped, NULL: not watched): the
+  // Sort route for codes beside which the index fits: the top-digit pass and
+  // local sorts unless sort_lsd.  sort_big (host-mapped, NULL: not watched): the
   // local sort sets sort_big[0] when a range had more than kBigRange items;
   // the merge launch then stores sort_seq into sort_big[1].
   bool sort_lsd = false;

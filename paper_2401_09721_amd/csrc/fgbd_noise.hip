@@ -904,7 +904,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_noise_mfma(NoiseArgs a, const int
 // zero), all upper 4 x 4 sub-blocks of the Gram matrix, four per instruction.
 // k_noise<0> before it kept one or three entries of the moments per thread
 // and walked the rows with scalar FP64: 46 us for 180k points with P = 16
-// (21 now), 25 us for 300k points with P = 6 (16 now).
+// (21 now), 25 us for 300k points with P = 6 (16 now), 100 us for an estimate
+// on 200k points with P = 12 (54 now, solve included).
 template <int PT, bool EIG3>
 __global__ __launch_bounds__(kBlock, 2) void k_noise_gram(NoiseArgs a, const int32_t *__restrict__ col,
                                                           const float *__restrict__ rgb_in,
@@ -1027,7 +1028,8 @@ constexpr int kRowEigGroups = 5;
 // entry, one lane per slot, integer shuffle sums), form Sigma, then wave 0
 // alone tridiagonalises and every wave brackets eigenvalues; wave 0 applies
 // the tail rule.  DT > 0: D = DT, and Sigma, the reduction and the pivots
-// live in registers; DT = 0: any D, through LDS.
+// live in registers; DT < 0: D up to -DT, a row of Sigma in each lane's
+// registers; DT = 0: any D, through LDS.
 template <int DT>
 __global__ __launch_bounds__(solve_threads<DT>()) void k_noise_solve(NoiseArgs a,
                                                                      const unsigned long long *__restrict__ acc_all,

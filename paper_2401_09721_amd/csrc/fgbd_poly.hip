@@ -288,7 +288,7 @@ __device__ __forceinline__ void st3(float *__restrict__ x, int64_t i, float a, f
 // PACK: p and dp are formed again from the row's gaps, with the operations and
 // so the bits of k_poly_weights: a step on many points is bound by the bytes of
 // the graph, and 2M points read 112 MB of it so instead of 192 (46 us a step
-// with stored p and dp, 36 so).
+// with stored p and dp, 35 so).
 template <int KT, bool PACK>
 __global__ __launch_bounds__(kBlock) void k_poly_step(int32_t n, int32_t k_rt, int k, int ncoef,
                                                       const int32_t *__restrict__ col,
