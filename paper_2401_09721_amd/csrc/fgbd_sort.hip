@@ -701,9 +701,9 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_downsweep(SortArgs a, con
 // bits and then the position in the range.  The bins are short (on the frames
 // measured an item shares its bin with 5 to 12 others on average, at most
 // about 230), lanes with neighbouring slots read the same keys, and nothing
-// has to be matched across lanes: 19 M vector instructions per launch on the
+// has to be matched across lanes: 20 M vector instructions per launch on the
 // 1M frame against 32 M for three 8-bit LSD passes in LDS whose stable ranks
-// came from 8 ballots per item and pass; 90 -> 61 us there, 410 -> 250 us on
+// came from 8 ballots per item and pass; 90 -> 64 us there, 410 -> 243 us on
 // 8 clouds of 4.4M points, 81 -> 51 us on 421k points in 16 directions.
 // Where a bin holds more than kMaxBin items, or the codes have few bits, the
 // range takes stable 8-bit passes in LDS instead.
